@@ -50,21 +50,31 @@ constexpr int kWaves = kBlock / 64;
 // counters[] slots (uint64)
 constexpr int C_LIST = 0;       // [0..1] list length per parity
 constexpr int C_DESC = 2;       // [2..3] slice count per parity
-constexpr int C_EPROD = 4;      // product edges examined
 constexpr int C_ERR = 6;        // capacity / validation error flags
 constexpr int C_PAIRBASE = 7;   // global key index where the current group starts
 constexpr int C_COUNT = 8;
 constexpr int C_HASH = 9;
-constexpr int C_ITEMS = 10;     // expansion work tallies (profiling)
-constexpr int C_DESCS = 11;
-constexpr int C_ROWW = 12;
-constexpr int C_WREAD = 13;
-constexpr int C_WUPD = 14;
-constexpr int C_LASTLEVEL = 15; // 1 + highest level index whose finalize appended rows (this group)
-constexpr int C_FROWS = 16;     // finalize tallies (profiling): rows finalized,
-constexpr int C_FWORDS = 17;    //   their non-zero Next words,
-constexpr int C_FANS = 18;      //   and those of rows of final states
-constexpr int C_NCOUNTERS = 19;
+constexpr int C_LASTLEVEL = 10; // 1 + highest level index whose finalize appended rows (this group)
+constexpr int C_TALLY = 11;     // [kTallies] the work tallies below, summed over the level kernels' blocks
+
+// Work tallies of the level kernels.  Every block keeps its own copy (blocks of one launch write
+// disjoint lines, launches follow each other on the stream), and k_tally_sum adds the copies up once
+// per call.  One atomic per wave to shared counters cost more than it looked: the 20,000 or more
+// same-line atomics of a launch complete one after another.  Without them: a 2,500-source slice of
+// R-MAT 18 with keys 6.10 -> 3.97 ms, all pairs of R-MAT 18 116.8 -> 111.3 ms (k_expand 1.28 -> 1.22
+// ms a launch), 65,536 sources of R-MAT 23 499 -> 488 ms.
+constexpr int T_EPROD = 0;      // product edges examined
+constexpr int T_ITEMS = 1;      // expansion (profiling)
+constexpr int T_DESCS = 2;
+constexpr int T_WREAD = 3;
+constexpr int T_WUPD = 4;
+constexpr int T_FROWS = 5;      // finalize (profiling): rows finalized,
+constexpr int T_FWORDS = 6;     //   their non-zero Next words,
+constexpr int T_FANS = 7;       //   and those of rows of final states
+constexpr int kTallies = 8;
+constexpr int kTallyStride = 16;            // words per block: one 128-byte line
+constexpr unsigned kMaxLevelBlocks = 4096;  // upper bound of a level kernel's grid
+constexpr int C_NCOUNTERS = C_TALLY + kTallies;
 
 constexpr uint64_t ERR_LIST = 1, ERR_DESC = 2, ERR_SOURCES = 4;
 
@@ -97,6 +107,7 @@ struct Args {
     Desc* desc0;
     Desc* desc1;
     unsigned long long* counters;
+    unsigned long long* tally;   // [kMaxLevelBlocks][kTallyStride]
     const uint64_t* target;   // optional [V / 64] bitmap: only result vertices with their bit set count
     uint32_t V, L, Q, H;
     uint32_t seen_or;         // visit scheme: 0 = two reads, 1 = seen OR (see the expansion)
@@ -250,6 +261,42 @@ __device__ __forceinline__ void expand_segments(const Args& a, const uint32_t* s
     }
 }
 
+// Add each wave's N tallies to the block's copy, words [first, first + N).  Every thread of the block
+// calls it once, at the end of the kernel.
+template <int N>
+__device__ __forceinline__ void add_tallies(const Args& a, int first, const uint64_t (&t)[N]) {
+    __shared__ uint64_t s_part[kWaves][N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const uint64_t x = rpqd::wave_sum_u64(t[i]);
+        if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6][i] = x;
+    }
+    __syncthreads();
+    if (threadIdx.x < N) {
+        uint64_t x = 0;
+        for (int w = 0; w < kWaves; ++w) x += s_part[w][threadIdx.x];
+        if (x) a.tally[(uint64_t)blockIdx.x * kTallyStride + first + threadIdx.x] += x;
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_tally_sum(const unsigned long long* __restrict__ tally,
+                                                    unsigned long long* __restrict__ counters) {
+    __shared__ uint64_t s_part[16][kTallies];
+    uint64_t t[kTallies] = {};
+    for (unsigned b = threadIdx.x; b < kMaxLevelBlocks; b += 1024)
+        for (int i = 0; i < kTallies; ++i) t[i] += tally[(uint64_t)b * kTallyStride + i];
+    for (int i = 0; i < kTallies; ++i) {
+        const uint64_t x = rpqd::wave_sum_u64(t[i]);
+        if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6][i] = x;
+    }
+    __syncthreads();
+    if (threadIdx.x < kTallies) {
+        uint64_t x = 0;
+        for (int w = 0; w < 16; ++w) x += s_part[w][threadIdx.x];
+        counters[C_TALLY + threadIdx.x] = x;
+    }
+}
+
 template <int K, bool SEEN>
 __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
     __shared__ uint32_t s_delta[RPQ_MAX_STATES * RPQ_MAX_LABELS];
@@ -310,17 +357,8 @@ __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
         t_segs += __popcll(__ballot(have)) * (lane == 0);
         expand_segments<K, SEEN>(a, s_delta, rows, have, ent, slot, q, v, m, beg, len, t_items, t_wread, t_wupd);
     }
-    t_items = rpqd::wave_sum_u64(t_items);
-    t_segs = rpqd::wave_sum_u64(t_segs);
-    t_wread = rpqd::wave_sum_u64(t_wread);
-    t_wupd = rpqd::wave_sum_u64(t_wupd);
-    if (lane == 0 && t_items) {
-        atomicAdd(&a.counters[C_ITEMS], (unsigned long long)t_items);
-        atomicAdd(&a.counters[C_DESCS], (unsigned long long)t_segs);
-        atomicAdd(&a.counters[C_ROWW], (unsigned long long)(t_segs * K));
-        atomicAdd(&a.counters[C_WREAD], (unsigned long long)t_wread);
-        atomicAdd(&a.counters[C_WUPD], (unsigned long long)t_wupd);
-    }
+    const uint64_t t[4] = {t_items, t_segs, t_wread, t_wupd};
+    add_tallies<4>(a, T_ITEMS, t);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -508,15 +546,9 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
             }
         }
     }
-    eprod = rpqd::wave_sum_u64(eprod);
-    t_words = rpqd::wave_sum_u64(t_words);
-    t_ans = rpqd::wave_sum_u64(t_ans);
-    if (lane == 0 && eprod) atomicAdd(&a.counters[C_EPROD], (unsigned long long)eprod);
-    if (lane == 0 && t_rows) {
-        atomicAdd(&a.counters[C_FROWS], (unsigned long long)t_rows);
-        atomicAdd(&a.counters[C_FWORDS], (unsigned long long)t_words);
-        atomicAdd(&a.counters[C_FANS], (unsigned long long)t_ans);
-    }
+    const uint64_t t_e[1] = {eprod}, t_f[3] = {t_rows, t_words, t_ans};
+    add_tallies<1>(a, T_EPROD, t_e);
+    add_tallies<3>(a, T_FROWS, t_f);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -735,7 +767,7 @@ struct Layout {
     uint32_t seen_or;   // visit scheme of the expansion (1 = seen OR, 0 = two reads)
     uint64_t max_len;   // deepest level finalized: the length bound, or no bound (UINT64_MAX)
     uint64_t list_cap, desc_cap;
-    uint64_t off_counters, off_nfa, off_vis, off_next, off_touch, off_ans, off_ans2, off_ids[2], off_rows[2],
+    uint64_t off_counters, off_tally, off_nfa, off_vis, off_next, off_touch, off_ans, off_ans2, off_ids[2], off_rows[2],
         off_desc[2], off_acc, off_partial, off_srcbase, total;
 };
 
@@ -876,6 +908,7 @@ int make_layout(const rpq_graph* g, const DevNfa& dn, uint64_t n_sources, uint32
         return o2;
     };
     x.off_counters = take(C_NCOUNTERS * 8);
+    x.off_tally = take((uint64_t)kMaxLevelBlocks * kTallyStride * 8);
     x.off_nfa = take(sizeof(DevNfa));
     x.off_vis = take(G * bitmap_bytes);
     x.off_next = take(G * bitmap_bytes);
@@ -916,6 +949,7 @@ Args make_args(const rpq_graph* g, uint32_t flags, const Layout& x, char* ws) {
     a.desc0 = reinterpret_cast<Desc*>(ws + x.off_desc[0]);
     a.desc1 = reinterpret_cast<Desc*>(ws + x.off_desc[1]);
     a.counters = reinterpret_cast<unsigned long long*>(ws + x.off_counters);
+    a.tally = reinterpret_cast<unsigned long long*>(ws + x.off_tally);
     a.target = nullptr;
     a.V = x.V;
     a.L = x.L;
@@ -936,7 +970,7 @@ unsigned resident_grid(const void* kernel) {
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, 0) != hipSuccess || n_cu <= 0 ||
         per_cu <= 0)
         return 2048;
-    return (unsigned)(n_cu * per_cu);
+    return std::min((unsigned)(n_cu * per_cu), kMaxLevelBlocks);
 }
 
 template <int K>
@@ -1466,6 +1500,7 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
     }
     RPQ_HIP(hipMemcpyAsync(ws + x.off_nfa, &dn, sizeof dn, hipMemcpyHostToDevice, stream));
     RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.counters), C_NCOUNTERS, 0, stream));
+    RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.tally), (uint64_t)kMaxLevelBlocks * kTallyStride, 0, stream));
     RPQ_TRY(rpq::fill_u64(a.next, (uint64_t)x.G * x.Q * x.V * x.K, 0, stream));
     RPQ_TRY(rpq::fill_u64(a.touch, ((uint64_t)x.G * x.Q * x.V + 63) / 64, 0, stream));
     if (sources) {
@@ -1603,34 +1638,37 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
         RPQ_HIP(hipEventRecord(side.leveled, xs));
         RPQ_HIP(hipStreamWaitEvent(stream, side.leveled, 0));
     }
+    hipLaunchKernelGGL(k_tally_sum, dim3(1), dim3(1024), 0, stream, a.tally, a.counters);
+    RPQ_LAUNCH_CHECK();
     RPQ_HIP(hipMemcpyAsync(stage, a.counters, C_NCOUNTERS * 8, hipMemcpyDeviceToHost, stream));
     RPQ_HIP(hipStreamSynchronize(stream));
+    const uint64_t* const tally = stage + C_TALLY;
     if (!noalloc) {
         Profiler& pr = profiler();
         std::lock_guard<std::mutex> lk(pr.mu);
         if (pr.on) {
             pr.resolve(true);   // both streams are drained here
-            pr.acc.finalize_rows += stage[C_FROWS];
-            pr.acc.finalize_row_words += stage[C_FROWS] * x.K;
-            pr.acc.finalize_words += stage[C_FWORDS];
+            pr.acc.finalize_rows += tally[T_FROWS];
+            pr.acc.finalize_row_words += tally[T_FROWS] * x.K;
+            pr.acc.finalize_words += tally[T_FWORDS];
             // 8-byte accesses of finalize to Vis: a read of every row word (seen OR), or a read and
             // a write of every non-zero word (two reads)
-            pr.acc.finalize_vis_words += x.seen_or ? stage[C_FROWS] * x.K : 2 * stage[C_FWORDS];
+            pr.acc.finalize_vis_words += x.seen_or ? tally[T_FROWS] * x.K : 2 * tally[T_FWORDS];
             // beyond the method's bytes: the Next word read beside each visited word (two reads);
             // seen OR makes the method's accesses only
-            pr.acc.expand_extra_words += x.seen_or ? 0 : stage[C_WREAD];
-            pr.acc.finalize_ans_words += stage[C_FANS];
-            pr.acc.edge_items += stage[C_ITEMS];
-            pr.acc.descriptors += stage[C_DESCS];
-            pr.acc.row_words += stage[C_ROWW];
-            pr.acc.word_reads += stage[C_WREAD];
-            pr.acc.word_updates += stage[C_WUPD];
+            pr.acc.expand_extra_words += x.seen_or ? 0 : tally[T_WREAD];
+            pr.acc.finalize_ans_words += tally[T_FANS];
+            pr.acc.edge_items += tally[T_ITEMS];
+            pr.acc.descriptors += tally[T_DESCS];
+            pr.acc.row_words += tally[T_DESCS] * x.K;
+            pr.acc.word_reads += tally[T_WREAD];
+            pr.acc.word_updates += tally[T_WUPD];
         }
     }
     res->count = stage[C_COUNT];
     res->hash = stage[C_HASH];
     if (ps) res->written = st.delivered;
-    res->product_edges = stage[C_EPROD];
+    res->product_edges = tally[T_EPROD];
     res->levels = levels_total;
     res->max_depth = max_depth;
     if (want_pairs) {
