@@ -500,6 +500,8 @@ def rpq_eval(g: Graph, nfa: Nfa, sources=None, flags: int = 0, opts=None, pairs=
     _check(lib.rpq_eval_workspace_size(g.handle, ctypes.byref(nfa), n, flags,
                                        ctypes.byref(o) if o is not None else None, ctypes.byref(need)))
     ws_bytes = int(need.value)
+    if flags & RPQ_SPARSE:   # room for a search that reaches far, without a second call
+        ws_bytes = max(ws_bytes, 64 << 20)
     for _ in range(16):
         ws = workspace if workspace is not None else g.workspace(ws_bytes)
         res = _Result()

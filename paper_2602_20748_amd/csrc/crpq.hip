@@ -12,12 +12,14 @@
 //
 // Atom evaluation, from the smaller of its two domains (backwards over the in-CSR with the
 // reversed automaton when that is the destination's):
-//   edge scan  the language holds only one-label words: a CSR scan of the source domain
+//   edge scan  the language holds only one-label words: a CSR scan of the source domain, its edges
+//              split evenly over the waves
 //   dense      up to 65,536 sources: the bit-parallel traversal of rpq_eval, with result
 //              vertices filtered by the destination domain at extraction
 //   sparse     more sources: a per-source breadth-first search over (source, state, vertex)
-//              triples with a device hash set as the visited set, for atoms whose sources
-//              are many but reach little (a reply chain from millions of messages)
+//              triples with a device hash set (or, for few sources, a bitmap) as the visited set,
+//              for atoms whose sources are many but reach little (a reply chain from millions of
+//              messages)
 //
 // Join: variables are bound one at a time (a vertex-at-a-time join).  For each partial row
 // the candidates of the new variable z come from the shortest of the sorted lists that the
@@ -50,14 +52,51 @@ inline unsigned grid_for(uint64_t threads, unsigned cap = 65535) {
 // ------------------------------------------------------------------------------------------------
 // device helpers
 // ------------------------------------------------------------------------------------------------
-// Wave-aggregated append: lanes with keep get consecutive positions from *counter (one atomic
-// per wave).  Every lane of the wave must call it.
-__device__ __forceinline__ uint64_t wave_append(bool keep, unsigned long long* counter) {
-    const uint64_t m = __ballot(keep);
-    unsigned long long base = 0;
-    if (__lane_id() == 0 && m) base = atomicAdd(counter, (unsigned long long)__popcll(m));
-    base = __shfl(base, 0, 64);
-    return base + (uint64_t)__popcll(m & rpqd::lanemask_lt());
+// Appends of a wave to a global list, gathered in LDS first.  A returning atomic on one counter
+// completes about every 70 ns whatever issues it, so an append per 64 items bound these kernels by
+// their counter (a single-source search of R-MAT 22: 84 ms); a full stage costs one atomic per
+// kStage - 64 entries or more.  Every lane of the wave must call push and flush.
+constexpr uint32_t kStage = 512;
+
+struct WaveStage {
+    uint64_t* buf;      // [kStage], this wave's own
+    uint32_t n;         // entries held (wave-uniform)
+    uint32_t most;      // flushed when it holds more than this, at most kStage - 64
+    bool over = false;  // an entry found no room in the list
+
+    __device__ __forceinline__ void flush(unsigned long long* counter, uint64_t* out, uint64_t cap) {
+        if (n == 0) return;
+        unsigned long long base = 0;
+        if (__lane_id() == 0) base = atomicAdd(counter, (unsigned long long)n);
+        base = __shfl(base, 0, 64);
+        for (uint32_t i = __lane_id(); i < n; i += 64)
+            if (base + i < cap) out[base + i] = buf[i];
+        over |= base + n > cap;
+        n = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    __device__ __forceinline__ void push(bool keep, uint64_t x, unsigned long long* counter, uint64_t* out,
+                                         uint64_t cap) {
+        const uint64_t m = __ballot(keep);
+        if (m == 0) return;
+        if (keep) buf[n + __popcll(m & rpqd::lanemask_lt())] = x;
+        n += (uint32_t)__popcll(m);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (n > most) flush(counter, out, cap);
+    }
+};
+
+// Sum over the block added to *dst by one atomic (every thread calls it once per use of `part`).
+__device__ __forceinline__ void block_add(uint64_t x, uint64_t* part, unsigned long long* dst) {
+    x = rpqd::wave_sum_u64(x);
+    if (__lane_id() == 0) part[threadIdx.x >> 6] = x;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t t = 0;
+        for (int w = 0; w < kWaves; ++w) t += part[w];
+        if (t) atomicAdd(dst, (unsigned long long)t);
+    }
+    __syncthreads();
 }
 
 // Last lane c whose exclusive prefix is <= item (the lane owning item).
@@ -121,11 +160,21 @@ __global__ void k_bits_from_list(uint64_t* __restrict__ tmp, const uint32_t* __r
     }
 }
 
+// Endpoint bits of sorted keys.  Many keys share an endpoint (a tag of a million messages), and ORs of
+// one word complete one after another: a run of equal high halves ORs once, and a bit that is already
+// set, or that another lane of the wave is setting, is not ORed again (the information-propagation query
+// on four million messages: 2.8 -> 0.12 ms a launch).
 __global__ void k_bits_from_keys(uint64_t* __restrict__ tmp, const uint64_t* __restrict__ keys, uint64_t n,
                                  int hi) {
     for (uint64_t i = gthread(); i < n; i += gstride()) {
-        const uint64_t v = hi ? (keys[i] >> 32) : (keys[i] & 0xFFFFFFFFull);
-        atomicOr(reinterpret_cast<unsigned long long*>(&tmp[v >> 6]), 1ull << (v & 63));
+        const uint64_t k = keys[i];
+        const uint32_t v = hi ? (uint32_t)(k >> 32) : (uint32_t)k;
+        if (hi && i > 0 && (uint32_t)(keys[i - 1] >> 32) == v) continue;
+        const uint64_t same = __ballot(v == (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
+        if (((same >> __lane_id()) & 1) && (same & rpqd::lanemask_lt())) continue;
+        unsigned long long* w = reinterpret_cast<unsigned long long*>(&tmp[v >> 6]);
+        const unsigned long long bit = 1ull << (v & 63);
+        if (!(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)) atomicOr(w, bit);
     }
 }
 
@@ -226,49 +275,70 @@ __global__ __launch_bounds__(kBlock) void k_tile_write(const uint64_t* __restric
 
 // ------------------------------------------------------------------------------------------------
 // edge scan: every (s, l, t) with s in the source list, l in the atom's label set and t in the
-// destination domain; keys s << 32 | t (or t << 32 | s when scanning in-edges)
+// destination domain, as keys s << 32 | t in the order of (s, l, t).  The edges of all sources are one
+// item space (prefix of the sources' degrees), cut into tiles of kScanTile items, a wave each: one source
+// with a million edges (a tag) is then as many tiles as a million sources with one.  A first pass counts
+// each tile's keys, a second writes them at the tile's prefix; neither uses an atomic.  A wave per 64
+// sources, appending through one counter, took 14 ms a pass on a tag of a million messages; the query of
+// information propagation on 400,000 persons and four million messages went 85 -> 7.1 ms with this and
+// the endpoint bits above.  Bound now by the random reads of rows and destination bits.
 // ------------------------------------------------------------------------------------------------
+constexpr uint32_t kScanTile = 512;
+
+__global__ __launch_bounds__(kBlock) void k_scan_degrees(const uint32_t* __restrict__ row_ptr,
+                                                         const uint64_t* __restrict__ lmask, uint32_t L, uint64_t lang,
+                                                         const uint32_t* __restrict__ srcs, uint64_t n_src,
+                                                         uint64_t* __restrict__ deg) {
+    for (uint64_t i = gthread(); i < n_src; i += gstride()) {
+        const uint32_t s = srcs[i];
+        uint64_t mm = lmask[s] & lang, d = 0;
+        while (mm) {
+            const uint64_t r = (uint64_t)s * L + (uint32_t)(__ffsll((long long)mm) - 1);
+            mm &= mm - 1;
+            d += row_ptr[r + 1] - row_ptr[r];
+        }
+        deg[i] = d;
+    }
+}
+
+// last index r in [lo, hi] with offs[r] <= item, given offs[lo] <= item
+__device__ __forceinline__ uint64_t owner_of(const uint64_t* offs, uint64_t lo, uint64_t hi, uint64_t item) {
+    while (lo < hi) {
+        const uint64_t mid = (lo + hi + 1) >> 1;
+        if (offs[mid] <= item) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+template <bool WRITE>
 __global__ __launch_bounds__(kBlock) void k_edge_scan(const uint32_t* __restrict__ row_ptr,
                                                       const uint32_t* __restrict__ dst,
                                                       const uint64_t* __restrict__ lmask, uint32_t L, uint64_t lang,
                                                       const uint32_t* __restrict__ srcs, uint64_t n_src,
-                                                      const uint64_t* __restrict__ target, int swap,
-                                                      uint64_t* __restrict__ out, unsigned long long* __restrict__ cnt,
-                                                      uint64_t cap) {
+                                                      const uint64_t* __restrict__ offs, uint64_t total,
+                                                      const uint64_t* __restrict__ target,
+                                                      uint64_t* __restrict__ tiles, uint64_t* __restrict__ out) {
     const int lane = __lane_id();
-    for (uint64_t b = gwave_base(); b < n_src; b += gstride()) {
-        const uint64_t i = b + lane;
-        uint32_t s = 0;
-        uint64_t m = 0, deg = 0;
-        if (i < n_src) {
-            s = srcs[i];
-            m = lmask[s] & lang;
-            uint64_t mm = m;
-            while (mm) {
-                const uint32_t l = (uint32_t)(__ffsll((long long)mm) - 1);
-                mm &= mm - 1;
-                const uint64_t r = (uint64_t)s * L + l;
-                deg += row_ptr[r + 1] - row_ptr[r];
-            }
-        }
-        const uint64_t incl = rpqd::wave_incl_scan_u64(deg);
-        const uint64_t excl = incl - deg;
-        const uint64_t total = __shfl(incl, 63, 64);
-        for (uint64_t base = 0; base < total; base += 64) {
+    const uint64_t n_tiles = (total + kScanTile - 1) / kScanTile;
+    for (uint64_t tile = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); tile < n_tiles;
+         tile += (uint64_t)gridDim.x * kWaves) {
+        const uint64_t t0 = tile * kScanTile, t1 = min(total, t0 + kScanTile);
+        const uint64_t first = owner_of(offs, 0, n_src - 1, t0);
+        const uint64_t last = owner_of(offs, first, n_src - 1, t1 - 1);
+        uint64_t pos = WRITE ? tiles[tile] : 0;
+        for (uint64_t base = t0; base < t1; base += 64) {
             const uint64_t item = base + lane;
-            const int c = wave_owner(excl, item);
-            const uint32_t cs = __shfl(s, c, 64);
-            const uint64_t cm = __shfl(m, c, 64);
-            const uint64_t cx = __shfl(excl, c, 64);
             bool keep = false;
-            uint32_t t = 0;
-            if (item < total) {
-                uint64_t off = item - cx;
-                uint64_t mm = cm;
+            uint32_t s = 0, t = 0;
+            if (item < t1) {
+                const uint64_t i = owner_of(offs, first, last, item);
+                s = srcs[i];
+                uint64_t off = item - offs[i];
+                uint64_t mm = lmask[s] & lang;
                 while (mm) {
-                    const uint32_t l = (uint32_t)(__ffsll((long long)mm) - 1);
+                    const uint64_t r = (uint64_t)s * L + (uint32_t)(__ffsll((long long)mm) - 1);
                     mm &= mm - 1;
-                    const uint64_t r = (uint64_t)cs * L + l;
                     const uint32_t b0 = row_ptr[r], d = row_ptr[r + 1] - b0;
                     if (off < d) {
                         t = dst[b0 + off];
@@ -278,20 +348,49 @@ __global__ __launch_bounds__(kBlock) void k_edge_scan(const uint32_t* __restrict
                 }
                 keep = bit_of(target, t);
             }
-            const uint64_t pos = wave_append(keep, cnt);
-            if (keep && pos < cap) out[pos] = swap ? (((uint64_t)t << 32) | cs) : (((uint64_t)cs << 32) | t);
+            const uint64_t m = __ballot(keep);
+            if (WRITE && keep) out[pos + __popcll(m & rpqd::lanemask_lt())] = ((uint64_t)s << 32) | t;
+            pos += (uint64_t)__popcll(m);
         }
+        if (!WRITE && lane == 0) tiles[tile] = pos;
     }
 }
 
 // ------------------------------------------------------------------------------------------------
-// sparse multi-source search: visited set = device hash set of (source index, state, vertex)
+// sparse multi-source search.  Visited set of (source index, state, vertex):
+//   hash set  64-bit keys, open addressing: memory follows what the sources reach
+//   bitmap    one bit per triple: for few sources it is smaller than the smallest useful hash set (a
+//             source over 4 states of 4M vertices: 2 MB), stays in cache, cannot overflow, and yields
+//             its result keys in order without a sort
+// Found triples go to one list in the order found; a level's frontier is a stretch [beg, end) of it.
+// Entries of more than kLight edges are cut into slices of kSlice edges, a wave each: a hub's edges
+// walked by one wave, and one counter update per 64 items, made a level of b.(a|c)* from one vertex of
+// R-MAT 22 5.7 ms and the search 78 ms; it takes 7.8 ms now, bound by the random accesses to the bitmap.
 // ------------------------------------------------------------------------------------------------
+constexpr uint32_t kLight = 32;
+constexpr uint32_t kSlice = 256;
+
 struct SNfa {
     uint32_t Q, L, init, final;
     uint64_t qlab[RPQ_MAX_STATES];
     uint32_t delta[RPQ_MAX_STATES * RPQ_MAX_LABELS];   // compact [q * L + l]
 };
+
+struct SSlice {
+    uint64_t key;
+    uint32_t beg, len;   // edges [beg, beg + len) of the entry's edges over the labels its state follows
+};
+
+// search counters
+constexpr int S_LEN = 0;      // entries of the list
+constexpr int S_PAIRS = 1;    // result pairs (hash set)
+constexpr int S_FLAGS = 2;    // kFlag*
+constexpr int S_EPROD = 3;    // product edges
+constexpr int S_SLICES = 4;   // [2] slices of the level, by level parity
+constexpr int S_BEG = 6;      // the frontier: list entries [beg, end)
+constexpr int S_END = 7;
+constexpr int S_LEVELS = 8;   // non-empty frontiers so far
+constexpr int kCounters = 16;
 
 struct SArgs {
     const uint32_t* row_ptr;
@@ -301,31 +400,37 @@ struct SArgs {
     const uint32_t* srcs;        // source vertices (ascending), index = source id in keys
     uint64_t n_src;
     const uint64_t* target;      // destination domain bitmap, or null (every vertex)
-    unsigned long long* table;   // hash set, kEmpty = free
+    unsigned long long* table;   // hash set, kEmpty = free; or null
     uint64_t mask;               // table size - 1
-    const uint64_t* front_in;
-    uint64_t n_in;
-    uint64_t* front_out;
-    uint64_t front_cap;
-    uint64_t* pairs;
-    uint64_t pair_cap;
-    unsigned long long* ctr;     // [0] next frontier length, [1] pairs, [2] error flags, [3] product edges
-    uint64_t ins_limit;          // new entries this launch may add before the table counts as full
+    unsigned long long* bits;    // bitmap [n_src][Q][vw]; or null
+    uint64_t vw;                 // 64-bit words of V bits
+    uint64_t* list;
+    uint64_t list_cap;           // most triples the search may find (hash set: load 1/2)
+    SSlice* slices;
+    uint64_t slice_cap;
+    unsigned long long* ctr;     // S_*
     uint32_t V;
 };
 
-// Flags in ctr[2]: an insert ran out of probes, or the table passed its load limit.  Either one
-// ends the run (the host retries with a larger table), so the waves of the launch stop early
-// instead of probing an overfull table.
+// Flags in ctr[S_FLAGS]: an insert ran out of probes, or more triples were found than fit.  Either one
+// ends the run (the host retries with more room), so the waves of the launch stop early instead of
+// probing an overfull table.
 constexpr unsigned long long kFlagProbe = 1, kFlagFull = 2;
 
 __device__ __forceinline__ bool run_over(const SArgs& a) {
-    const unsigned long long f = __hip_atomic_load(&a.ctr[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long f = __hip_atomic_load(&a.ctr[S_FLAGS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return __ballot(f != 0) != 0;
 }
 
-// true if key was not in the set (and is now)
-__device__ __forceinline__ bool set_insert(const SArgs& a, uint64_t key) {
+// true if (source si, state q, vertex v) was not in the visited set (and is now)
+__device__ __forceinline__ bool set_insert(const SArgs& a, uint64_t si, uint32_t q, uint32_t Q, uint32_t v) {
+    if (a.bits) {
+        unsigned long long* w = &a.bits[(si * Q + q) * a.vw + (v >> 6)];
+        const unsigned long long bit = 1ull << (v & 63);
+        // a stale copy of the word can only let through an OR that finds the bit set
+        return !(*w & bit) && !(atomicOr(w, bit) & bit);
+    }
+    const uint64_t key = (si << 32) | ((uint64_t)q * a.V + v);
     uint64_t h = rpqd::mix64(key) & a.mask;
     for (uint32_t p = 0; p < kMaxProbe; ++p) {
         const unsigned long long cur = a.table[h];
@@ -337,47 +442,107 @@ __device__ __forceinline__ bool set_insert(const SArgs& a, uint64_t key) {
         }
         h = (h + 1) & a.mask;
     }
-    atomicOr(&a.ctr[2], kFlagProbe);
+    atomicOr(&a.ctr[S_FLAGS], kFlagProbe);
     return false;
 }
 
+// Appends of found triples.  Stages hold back what the load limit of a hash set should see, so theirs
+// are short enough that all the waves of a launch together hold at most half the limit.
+__device__ __forceinline__ WaveStage found_stage(const SArgs& a, uint64_t (&stage)[kWaves][kStage]) {
+    const uint32_t most = a.bits ? kStage - 64 : (uint32_t)min<uint64_t>(kStage - 64, a.list_cap >> 14);
+    return WaveStage{stage[threadIdx.x >> 6], 0, most};
+}
+
+__device__ __forceinline__ void push_found(const SArgs& a, WaveStage& st, bool keep, uint64_t key) {
+    st.push(keep, key, &a.ctr[S_LEN], a.list, a.list_cap);
+    if (st.over && __lane_id() == 0) atomicOr(&a.ctr[S_FLAGS], kFlagFull);
+    st.over = false;
+}
+
 __global__ __launch_bounds__(kBlock) void k_sparse_seed(SArgs a) {
+    __shared__ uint64_t s_stage[kWaves][kStage];
+    WaveStage st = found_stage(a, s_stage);
     const int lane = __lane_id();
-    const uint32_t init = a.nfa->init, fin = a.nfa->final;
+    const uint32_t init = a.nfa->init, Q = a.nfa->Q;
     for (uint64_t b = gwave_base(); b < a.n_src; b += gstride()) {
         const uint64_t si = b + lane;
         const bool ok = si < a.n_src;
         const uint32_t s = ok ? a.srcs[si] : 0;
-        for (uint32_t q = 0; q < a.nfa->Q; ++q) {
+        for (uint32_t q = 0; q < Q; ++q) {
             if (!((init >> q) & 1)) continue;
-            const uint64_t key = (si << 32) | ((uint64_t)q * a.V + s);
-            const bool ins = ok && set_insert(a, key);
-            const uint64_t pos = wave_append(ins, &a.ctr[0]);
-            if (ins && pos < a.front_cap) a.front_out[pos] = key;
-            if (ins && pos >= a.ins_limit) atomicOr(&a.ctr[2], kFlagFull);
-            const bool emit = ins && ((fin >> q) & 1) && (!a.target || bit_of(a.target, s));
-            const uint64_t pp = wave_append(emit, &a.ctr[1]);
-            if (emit && pp < a.pair_cap) a.pairs[pp] = ((uint64_t)s << 32) | s;
+            const bool ins = ok && set_insert(a, si, q, Q, s);
+            push_found(a, st, ins, (si << 32) | ((uint64_t)q * a.V + s));
         }
+    }
+    st.flush(&a.ctr[S_LEN], a.list, a.list_cap);
+}
+
+// between two levels: what the last one found is the next frontier
+__global__ void k_sparse_mark(SArgs a) {
+    const unsigned long long len = a.ctr[S_LEN], end = a.ctr[S_END];
+    if (len > a.list_cap) a.ctr[S_FLAGS] |= kFlagFull;
+    a.ctr[S_BEG] = end;
+    a.ctr[S_END] = min(len, (unsigned long long)a.list_cap);
+    if (len > end) ++a.ctr[S_LEVELS];
+}
+
+// 64 edges, one per lane (w, with the successor states of its label; 0 = none): one successor state
+// per round, every lane takes part in every append
+__device__ __forceinline__ void visit_edges(const SArgs& a, WaveStage& st, uint64_t si, uint32_t w, uint32_t succ,
+                                            uint32_t Q) {
+    while (__ballot(succ != 0)) {
+        bool ins = false;
+        uint32_t q2 = 0;
+        if (succ) {
+            q2 = __ffs(succ) - 1;
+            succ &= succ - 1;
+            ins = set_insert(a, si, q2, Q, w);
+        }
+        push_found(a, st, ins, (si << 32) | ((uint64_t)q2 * a.V + w));
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_sparse_level(SArgs a) {
+// edge `off` of vertex v over the labels of m: its target, and the successor states of its label
+__device__ __forceinline__ void edge_at(const SArgs& a, const uint32_t* s_delta, uint32_t L, uint32_t q, uint32_t v,
+                                        uint64_t m, uint64_t off, uint32_t* w, uint32_t* succ) {
+    while (m) {
+        const uint32_t l = (uint32_t)(__ffsll((long long)m) - 1);
+        m &= m - 1;
+        const uint64_t r = (uint64_t)v * L + l;
+        const uint32_t b0 = a.row_ptr[r], d = a.row_ptr[r + 1] - b0;
+        if (off < d) {
+            *w = a.dst[b0 + off];
+            *succ = s_delta[q * L + l];
+            return;
+        }
+        off -= d;
+    }
+}
+
+// Light entries of the frontier are expanded, heavy ones become slices for k_sparse_slices.
+__global__ __launch_bounds__(kBlock) void k_sparse_level(SArgs a, int parity) {
     __shared__ uint32_t s_delta[RPQ_MAX_STATES * RPQ_MAX_LABELS];
     __shared__ uint64_t s_qlab[RPQ_MAX_STATES];
-    const uint32_t Q = a.nfa->Q, L = a.nfa->L, fin = a.nfa->final;
+    __shared__ uint64_t s_stage[kWaves][kStage];
+    __shared__ uint64_t s_part[kWaves];
+    const uint64_t beg = a.ctr[S_BEG], end = a.ctr[S_END];
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr[S_SLICES + (parity ^ 1)] = 0;   // read by no kernel in flight
+    if (beg >= end) return;
+    const uint32_t Q = a.nfa->Q, L = a.nfa->L;
     for (uint32_t i = threadIdx.x; i < Q * L; i += kBlock) s_delta[i] = a.nfa->delta[i];
     for (uint32_t i = threadIdx.x; i < Q; i += kBlock) s_qlab[i] = a.nfa->qlab[i];
     __syncthreads();
+    WaveStage st = found_stage(a, s_stage);
     const int lane = __lane_id();
     const uint32_t V = a.V;
-    for (uint64_t b = gwave_base(); b < a.n_in; b += gstride()) {
-        if (run_over(a)) return;
+    uint64_t eprod = 0;
+    for (uint64_t b = beg + gwave_base(); b < end; b += gstride()) {
+        if (run_over(a)) break;
         const uint64_t e = b + lane;
-        uint64_t key = 0, m = 0, deg = 0, eprod = 0;
+        uint64_t key = 0, m = 0, deg = 0;
         uint32_t q = 0, v = 0;
-        if (e < a.n_in) {
-            key = a.front_in[e];
+        if (e < end) {
+            key = a.list[e];
             const uint32_t lo = (uint32_t)(key & 0xFFFFFFFFull);
             q = lo / V;
             v = lo - q * V;
@@ -392,13 +557,31 @@ __global__ __launch_bounds__(kBlock) void k_sparse_level(SArgs a) {
                 eprod += (uint64_t)d * (uint32_t)__popc(s_delta[q * L + l]);
             }
         }
-        eprod = rpqd::wave_sum_u64(eprod);
-        if (lane == 0 && eprod) atomicAdd(&a.ctr[3], (unsigned long long)eprod);
+        // heavy entries leave as slices; where the buffer has no room for the wave's, the wave walks
+        // them itself, and what it reserved inside the buffer is written empty
+        const uint64_t ns = deg > kLight ? (deg + kSlice - 1) / kSlice : 0;
+        const uint64_t ns_incl = rpqd::wave_incl_scan_u64(ns);
+        const uint64_t ns_tot = __shfl(ns_incl, 63, 64);
+        if (ns_tot) {
+            unsigned long long base = 0;
+            if (lane == 0) base = atomicAdd(&a.ctr[S_SLICES + parity], (unsigned long long)ns_tot);
+            base = __shfl(base, 0, 64);
+            const bool room = base + ns_tot <= a.slice_cap;
+            const uint64_t p0 = base + ns_incl - ns;
+            for (uint64_t i = 0; i < ns && p0 + i < a.slice_cap; ++i) {
+                SSlice sl;
+                sl.key = key;
+                sl.beg = (uint32_t)(i * kSlice);
+                sl.len = room ? (uint32_t)min<uint64_t>(kSlice, deg - i * kSlice) : 0;
+                a.slices[p0 + i] = sl;
+            }
+            if (room && ns) deg = 0;
+        }
         const uint64_t incl = rpqd::wave_incl_scan_u64(deg);
         const uint64_t excl = incl - deg;
         const uint64_t total = __shfl(incl, 63, 64);
         for (uint64_t base = 0; base < total; base += 64) {
-            if (base && run_over(a)) return;
+            if (base && run_over(a)) break;
             const uint64_t item = base + lane;
             const int c = wave_owner(excl, item);
             const uint64_t ckey = __shfl(key, c, 64);
@@ -407,41 +590,124 @@ __global__ __launch_bounds__(kBlock) void k_sparse_level(SArgs a) {
             const uint64_t cm = __shfl(m, c, 64);
             const uint64_t cx = __shfl(excl, c, 64);
             uint32_t w = 0, succ = 0;
-            if (item < total) {
-                uint64_t off = item - cx;
-                uint64_t mm = cm;
-                while (mm) {
-                    const uint32_t l = (uint32_t)(__ffsll((long long)mm) - 1);
-                    mm &= mm - 1;
-                    const uint64_t r = (uint64_t)cv * L + l;
-                    const uint32_t b0 = a.row_ptr[r], d = a.row_ptr[r + 1] - b0;
-                    if (off < d) {
-                        w = a.dst[b0 + off];
-                        succ = s_delta[cq * L + l];
-                        break;
-                    }
-                    off -= d;
-                }
-            }
-            const uint64_t si = ckey >> 32;
-            // one successor state per round; every lane takes part in every append
-            while (__ballot(succ != 0)) {
-                bool ins = false;
-                uint32_t q2 = 0;
-                if (succ) {
-                    q2 = __ffs(succ) - 1;
-                    succ &= succ - 1;
-                    ins = set_insert(a, (si << 32) | ((uint64_t)q2 * V + w));
-                }
-                const uint64_t pos = wave_append(ins, &a.ctr[0]);
-                if (ins && pos < a.front_cap) a.front_out[pos] = (si << 32) | ((uint64_t)q2 * V + w);
-                if (ins && pos >= a.ins_limit) atomicOr(&a.ctr[2], kFlagFull);
-                const bool emit = ins && ((fin >> q2) & 1) && (!a.target || bit_of(a.target, w));
-                const uint64_t pp = wave_append(emit, &a.ctr[1]);
-                if (emit && pp < a.pair_cap) a.pairs[pp] = ((uint64_t)a.srcs[si] << 32) | w;
-            }
+            if (item < total) edge_at(a, s_delta, L, cq, cv, cm, item - cx, &w, &succ);
+            visit_edges(a, st, ckey >> 32, w, succ, Q);
         }
     }
+    st.flush(&a.ctr[S_LEN], a.list, a.list_cap);
+    block_add(eprod, s_part, &a.ctr[S_EPROD]);
+}
+
+// One wave per slice.
+__global__ __launch_bounds__(kBlock) void k_sparse_slices(SArgs a, int parity) {
+    __shared__ uint32_t s_delta[RPQ_MAX_STATES * RPQ_MAX_LABELS];
+    __shared__ uint64_t s_qlab[RPQ_MAX_STATES];
+    __shared__ uint64_t s_stage[kWaves][kStage];
+    const uint64_t n = min((uint64_t)a.ctr[S_SLICES + parity], a.slice_cap);
+    if (n == 0) return;
+    const uint32_t Q = a.nfa->Q, L = a.nfa->L;
+    for (uint32_t i = threadIdx.x; i < Q * L; i += kBlock) s_delta[i] = a.nfa->delta[i];
+    for (uint32_t i = threadIdx.x; i < Q; i += kBlock) s_qlab[i] = a.nfa->qlab[i];
+    __syncthreads();
+    WaveStage st = found_stage(a, s_stage);
+    const int lane = __lane_id();
+    for (uint64_t i = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); i < n; i += (uint64_t)gridDim.x * kWaves) {
+        if (run_over(a)) break;
+        const SSlice sl = a.slices[i];
+        const uint32_t lo = (uint32_t)(sl.key & 0xFFFFFFFFull);
+        const uint32_t q = lo / a.V, v = lo - q * a.V;
+        const uint64_t m = a.lmask[v] & s_qlab[q];
+        for (uint32_t base = 0; base < sl.len; base += 64) {
+            uint32_t w = 0, succ = 0;
+            if (base + lane < sl.len) edge_at(a, s_delta, L, q, v, m, (uint64_t)sl.beg + base + lane, &w, &succ);
+            visit_edges(a, st, sl.key >> 32, w, succ, Q);
+        }
+    }
+    st.flush(&a.ctr[S_LEN], a.list, a.list_cap);
+}
+
+// hash set: the result pairs of the triples found, in no particular order
+__global__ __launch_bounds__(kBlock) void k_sparse_pairs(SArgs a, uint64_t n, uint64_t* __restrict__ pairs) {
+    __shared__ uint64_t s_stage[kWaves][kStage];
+    WaveStage st{s_stage[threadIdx.x >> 6], 0, kStage - 64};
+    const uint32_t fin = a.nfa->final, V = a.V;
+    for (uint64_t b = gwave_base(); b < n; b += gstride()) {
+        const uint64_t i = b + __lane_id();
+        uint64_t pair = 0;
+        bool emit = false;
+        if (i < n) {
+            const uint64_t key = a.list[i];
+            const uint32_t lo = (uint32_t)key, q = lo / V, v = lo - q * V;
+            emit = ((fin >> q) & 1) && (!a.target || bit_of(a.target, v));
+            pair = ((uint64_t)a.srcs[key >> 32] << 32) | v;
+        }
+        st.push(emit, pair, &a.ctr[S_PAIRS], pairs, n);
+    }
+    st.flush(&a.ctr[S_PAIRS], pairs, n);
+}
+
+// Bitmap: the result keys in order.  A block takes kBitTile words of one source's answer bits (the OR of
+// its final states' bits); a first pass counts them per block, a second writes keys [off, off + cap) of
+// the whole sequence and sums checksums (per_source: [n_src][2], or null).
+constexpr uint32_t kBitTile = 256;
+
+__device__ __forceinline__ uint64_t answer_word(const SArgs& a, uint32_t fin, uint32_t Q, uint64_t si, uint64_t w) {
+    uint64_t x = 0;
+    for (uint32_t f = fin; f; f &= f - 1) x |= a.bits[(si * Q + (__ffs(f) - 1)) * a.vw + w];
+    return a.target ? x & a.target[w] : x;
+}
+
+__global__ __launch_bounds__(kBlock) void k_bits_count(SArgs a, uint64_t n_tiles, uint64_t* __restrict__ counts) {
+    __shared__ uint64_t s_part[kWaves];
+    const uint32_t fin = a.nfa->final, Q = a.nfa->Q;
+    for (uint64_t t = blockIdx.x; t < a.n_src * n_tiles; t += gridDim.x) {
+        const uint64_t si = t / n_tiles, w = (t - si * n_tiles) * kBitTile + threadIdx.x;
+        const uint64_t c = rpqd::wave_sum_u64(w < a.vw ? (uint64_t)__popcll(answer_word(a, fin, Q, si, w)) : 0);
+        if (__lane_id() == 0) s_part[threadIdx.x >> 6] = c;
+        __syncthreads();
+        if (threadIdx.x == 0) counts[t] = s_part[0] + s_part[1] + s_part[2] + s_part[3];
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_bits_keys(SArgs a, uint64_t n_tiles, const uint64_t* __restrict__ offs,
+                                                      uint64_t* __restrict__ out, uint64_t off, uint64_t cap,
+                                                      unsigned long long* __restrict__ per_source,
+                                                      unsigned long long* __restrict__ hash) {
+    __shared__ uint64_t s_part[kWaves];
+    const uint32_t fin = a.nfa->final, Q = a.nfa->Q;
+    const int lane = __lane_id(), wv = threadIdx.x >> 6;
+    uint64_t h_all = 0;
+    for (uint64_t t = blockIdx.x; t < a.n_src * n_tiles; t += gridDim.x) {
+        const uint64_t si = t / n_tiles, w = (t - si * n_tiles) * kBitTile + threadIdx.x;
+        const uint64_t key0 = (uint64_t)a.srcs[si] << 32;
+        const uint64_t word = w < a.vw ? answer_word(a, fin, Q, si, w) : 0;
+        const uint64_t c = (uint64_t)__popcll(word);
+        const uint64_t incl = rpqd::wave_incl_scan_u64(c);
+        if (lane == 63) s_part[wv] = incl;
+        __syncthreads();
+        uint64_t pos = offs[t] + incl - c;
+        for (int i = 0; i < wv; ++i) pos += s_part[i];
+        const uint64_t n_tile = s_part[0] + s_part[1] + s_part[2] + s_part[3];
+        __syncthreads();
+        uint64_t h = 0;
+        for (uint64_t any = __ballot(word != 0); any; any &= any - 1) {
+            const int j = __ffsll((long long)any) - 1;
+            const uint64_t wj = __shfl(word, j, 64), pj = __shfl(pos, j, 64);
+            if ((wj >> lane) & 1) {
+                const uint64_t key = key0 | ((w - lane + j) * 64 + lane);
+                const uint64_t p = pj + __popcll(wj & rpqd::lanemask_lt());
+                if (p >= off && p - off < cap) out[p - off] = key;
+                h += rpqd::mix64(key);
+            }
+        }
+        h_all += h;
+        if (per_source && n_tile) {   // n_tile is the same in every thread
+            if (threadIdx.x == 0) atomicAdd(&per_source[2 * si], (unsigned long long)n_tile);
+            block_add(h, s_part, &per_source[2 * si + 1]);
+        }
+    }
+    if (hash) block_add(h_all, s_part, hash);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -497,9 +763,31 @@ __global__ __launch_bounds__(kBlock) void k_step_ranges(StepArgs a) {
     }
 }
 
+// Rows that pass are gathered per wave in LDS and written kStage - 64 or more at a time (one counter
+// update each, see WaveStage); when only counted, each block adds its totals once.
 __global__ __launch_bounds__(kBlock) void k_step_expand(StepArgs a) {
+    __shared__ uint64_t s_row[kWaves][kStage];
+    __shared__ uint32_t s_z[kWaves][kStage];
+    __shared__ uint64_t s_part[kWaves];
+    uint64_t* const st_row = s_row[threadIdx.x >> 6];
+    uint32_t* const st_z = s_z[threadIdx.x >> 6];
+    uint32_t st_n = 0;
     const int lane = __lane_id();
     uint64_t cnt = 0, hsum = 0;
+    auto flush = [&]() {
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(a.out_cnt, (unsigned long long)st_n);
+        base = __shfl(base, 0, 64);
+        for (uint32_t i = lane; i < st_n; i += 64) {
+            const uint64_t pos = base + i;
+            if (pos >= a.cap) continue;
+            const uint64_t r = st_row[i];
+            for (uint32_t c = 0; c < a.n_cols; ++c) a.out_cols[c][pos] = a.in_cols[c][r];
+            a.out_cols[a.n_cols][pos] = st_z[i];
+        }
+        st_n = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
     for (uint64_t b = gwave_base(); b < a.total; b += gstride()) {
         const uint64_t item = b + lane;
         bool keep = false;
@@ -545,20 +833,22 @@ __global__ __launch_bounds__(kBlock) void k_step_expand(StepArgs a) {
                 hsum += m;
             }
         } else {
-            const uint64_t pos = wave_append(keep, a.out_cnt);
-            if (keep && pos < a.cap) {
-                for (uint32_t c = 0; c < a.n_cols; ++c) a.out_cols[c][pos] = a.in_cols[c][r];
-                a.out_cols[a.n_cols][pos] = z;
+            const uint64_t m = __ballot(keep);
+            if (keep) {
+                const uint32_t at = st_n + (uint32_t)__popcll(m & rpqd::lanemask_lt());
+                st_row[at] = r;
+                st_z[at] = z;
             }
+            st_n += (uint32_t)__popcll(m);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (st_n > kStage - 64) flush();
         }
     }
     if (a.reduce) {
-        cnt = rpqd::wave_sum_u64(cnt);
-        hsum = rpqd::wave_sum_u64(hsum);
-        if (lane == 0 && cnt) {
-            atomicAdd(&a.acc[0], (unsigned long long)cnt);
-            atomicAdd(&a.acc[1], (unsigned long long)hsum);
-        }
+        block_add(cnt, s_part, &a.acc[0]);
+        block_add(hsum, s_part, &a.acc[1]);
+    } else if (st_n) {
+        flush();
     }
 }
 
@@ -572,14 +862,14 @@ struct OutArgs {
 };
 
 __global__ __launch_bounds__(kBlock) void k_rows_hash(OutArgs a, unsigned long long* __restrict__ acc) {
+    __shared__ uint64_t s_part[kWaves];
     uint64_t h = 0;
     for (uint64_t r = gthread(); r < a.n_rows; r += gstride()) {
         uint64_t m = 0;
         for (uint32_t j = 0; j < a.n_free; ++j) m = j == 0 ? rpqd::mix64(a.cols[j][r]) : rpqd::mix64(m ^ a.cols[j][r]);
         h += m;
     }
-    h = rpqd::wave_sum_u64(h);
-    if (__lane_id() == 0 && h) atomicAdd(&acc[1], (unsigned long long)h);
+    block_add(h, s_part, &acc[1]);
 }
 
 __global__ void k_iota(uint32_t* __restrict__ p, uint64_t n) {
@@ -637,7 +927,7 @@ struct Ctx {
     hipStream_t s;
     Arena ar;
     uint64_t* stage;                 // pinned host staging (graph-owned)
-    unsigned long long* dctr;        // device counters [8]
+    unsigned long long* dctr;        // device counters [kCounters]
     uint64_t n_words;
 };
 
@@ -657,7 +947,7 @@ int read_counters(Ctx& c, int n) {
     return RPQ_OK;
 }
 
-int zero_counters(Ctx& c) { return rpq::fill_u64(reinterpret_cast<uint64_t*>(c.dctr), 8, 0, c.s); }
+int zero_counters(Ctx& c) { return rpq::fill_u64(reinterpret_cast<uint64_t*>(c.dctr), kCounters, 0, c.s); }
 
 int popcount_bits(Ctx& c, const uint64_t* bits, uint64_t* count) {
     const uint64_t mark = c.ar.top;
@@ -800,19 +1090,41 @@ void to_snfa(const rpq_nfa& n, uint32_t L, SNfa* d) {
 // of the traversal direction.  *keys is allocated in the arena; *sorted tells whether the
 // keys come out sorted and distinct.
 int eval_edge_scan(Ctx& c, const rpq::Csr& csr, uint64_t lang, const uint32_t* srcs, uint64_t n_src,
-                   const uint64_t* target, uint64_t** keys, uint64_t* n) {
-    // count first (capacity 0), then write
-    RPQ_TRY(zero_counters(c));
-    hipLaunchKernelGGL(k_edge_scan, dim3(grid_for(n_src, 16384)), dim3(kBlock), 0, c.s, csr.row_ptr, csr.dst,
-                       csr.lmask, c.g->L, lang, srcs, n_src, target, 0, nullptr, c.dctr, (uint64_t)0);
+                   const uint64_t* target, uint64_t** keys, uint64_t* n, bool* sorted) {
+    uint64_t* offs;
+    CRPQ_TAKE(offs, uint64_t, n_src + 1);
+    uint64_t* stmp;
+    CRPQ_TAKE(stmp, uint64_t, rpq::scan_temp_elems(n_src));
+    hipLaunchKernelGGL(k_scan_degrees, dim3(grid_for(n_src, 16384)), dim3(kBlock), 0, c.s, csr.row_ptr, csr.lmask,
+                       c.g->L, lang, srcs, n_src, offs);
     RPQ_LAUNCH_CHECK();
-    RPQ_TRY(read_counters(c, 1));
+    RPQ_TRY(rpq::exclusive_scan_u64(offs, offs, n_src, stmp, offs + n_src, c.s));
+    RPQ_HIP(hipMemcpyAsync(c.stage, offs + n_src, 8, hipMemcpyDeviceToHost, c.s));
+    RPQ_HIP(hipStreamSynchronize(c.s));
+    const uint64_t total = c.stage[0];
+    // one label: (s, t) ascending and distinct, as the CSR holds them
+    *sorted = (lang & (lang - 1)) == 0;
+    *n = 0;
+    CRPQ_TAKE(*keys, uint64_t, 1);
+    if (!n_src || !total) return RPQ_OK;
+    const uint64_t n_tiles = (total + kScanTile - 1) / kScanTile;
+    uint64_t *tiles, *ttmp;
+    CRPQ_TAKE(tiles, uint64_t, n_tiles + 1);
+    CRPQ_TAKE(ttmp, uint64_t, rpq::scan_temp_elems(n_tiles));
+    const unsigned grid = grid_for(n_tiles * 64, 16384);
+    hipLaunchKernelGGL(k_edge_scan<false>, dim3(grid), dim3(kBlock), 0, c.s, csr.row_ptr, csr.dst, csr.lmask, c.g->L,
+                       lang, srcs, n_src, offs, total, target, tiles, nullptr);
+    RPQ_LAUNCH_CHECK();
+    RPQ_TRY(rpq::exclusive_scan_u64(tiles, tiles, n_tiles, ttmp, tiles + n_tiles, c.s));
+    RPQ_HIP(hipMemcpyAsync(c.stage, tiles + n_tiles, 8, hipMemcpyDeviceToHost, c.s));
+    RPQ_HIP(hipStreamSynchronize(c.s));
     const uint64_t m = c.stage[0];
     CRPQ_TAKE(*keys, uint64_t, m);
-    RPQ_TRY(zero_counters(c));
-    hipLaunchKernelGGL(k_edge_scan, dim3(grid_for(n_src, 16384)), dim3(kBlock), 0, c.s, csr.row_ptr, csr.dst,
-                       csr.lmask, c.g->L, lang, srcs, n_src, target, 0, *keys, c.dctr, m);
-    RPQ_LAUNCH_CHECK();
+    if (m) {
+        hipLaunchKernelGGL(k_edge_scan<true>, dim3(grid), dim3(kBlock), 0, c.s, csr.row_ptr, csr.dst, csr.lmask,
+                           c.g->L, lang, srcs, n_src, offs, total, target, tiles, *keys);
+        RPQ_LAUNCH_CHECK();
+    }
     *n = m;
     return RPQ_OK;
 }
@@ -945,29 +1257,44 @@ int batch_atoms(Ctx& c, const crpq_atom* atoms, uint32_t n_atoms, uint32_t flags
     return RPQ_OK;
 }
 
-// One run of the sparse search with a hash set of T slots; returns RPQ_ENOMEM (without setting
-// the error) when T was too small.
+// Bytes of the bitmap visited set, and the most triples there are.
+uint64_t bitmap_bytes(const Ctx& c, uint64_t n_src, uint32_t Q) { return n_src * Q * c.n_words * 8; }
+uint64_t all_triples(const Ctx& c, uint64_t n_src, uint32_t Q) { return n_src * Q * (uint64_t)c.g->V; }
+
+// A bitmap where it is no larger than the hash set of T slots that would be filled instead; the two
+// cost the same to clear, and a bitmap insert touches one word where a hash insert walks a chain.
+bool use_bitmap(const Ctx& c, uint64_t n_src, uint32_t Q, uint64_t T) {
+    return n_src <= T && bitmap_bytes(c, n_src, Q) <= 8 * T;
+}
+
+// Levels between two looks of the host at the search.
+constexpr int kSparseLevels = 3;
+
+// One run of the sparse search: with a hash set of T slots (load at most 1/2), or with a bitmap and room
+// for T / 2 triples.  Everything stays in the arena above `mark`; returns RPQ_ENOMEM (without setting the
+// error) when T was too small.
 int sparse_run(Ctx& c, const rpq_nfa& nfa, const rpq::Csr& csr, const uint32_t* srcs, uint64_t n_src,
-               const uint64_t* target, uint64_t T, uint64_t** keys, uint64_t* n, uint64_t* eprod = nullptr,
-               uint64_t* levels = nullptr, uint64_t max_len = ~0ull) {
+               const uint64_t* target, bool bitmap, uint64_t T, SArgs* out, uint64_t* found, uint64_t* eprod,
+               uint64_t* levels, uint64_t max_len = ~0ull) {
     SNfa h;
     to_snfa(nfa, c.g->L, &h);
-    const uint64_t out_mark = c.ar.top;
-    uint64_t* pairs;
-    CRPQ_TAKE(pairs, uint64_t, T / 2);
-    const uint64_t mark = c.ar.top;
-    SNfa* dn;
-    CRPQ_TAKE(dn, SNfa, 1);
-    unsigned long long* table;
-    CRPQ_TAKE(table, unsigned long long, T);
-    uint64_t *fa, *fb;
-    CRPQ_TAKE(fa, uint64_t, T / 2);
-    CRPQ_TAKE(fb, uint64_t, T / 2);
-    RPQ_HIP(hipMemcpyAsync(dn, &h, sizeof h, hipMemcpyHostToDevice, c.s));
-    RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(table), T, kEmpty, c.s));
-    RPQ_TRY(zero_counters(c));
+    const uint64_t cap = bitmap ? std::min(T / 2, all_triples(c, n_src, nfa.n_states)) : T / 2;
     SArgs a;
     std::memset(&a, 0, sizeof a);
+    SNfa* dn;
+    CRPQ_TAKE(a.list, uint64_t, cap);
+    CRPQ_TAKE(dn, SNfa, 1);
+    if (bitmap) {
+        CRPQ_TAKE(a.bits, unsigned long long, bitmap_bytes(c, n_src, nfa.n_states) / 8);
+        RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.bits), bitmap_bytes(c, n_src, nfa.n_states) / 8, 0, c.s));
+    } else {
+        CRPQ_TAKE(a.table, unsigned long long, T);
+        RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.table), T, kEmpty, c.s));
+    }
+    a.slice_cap = cap / 8 + 64;
+    CRPQ_TAKE(a.slices, SSlice, a.slice_cap);
+    RPQ_HIP(hipMemcpyAsync(dn, &h, sizeof h, hipMemcpyHostToDevice, c.s));
+    RPQ_TRY(zero_counters(c));
     a.row_ptr = csr.row_ptr;
     a.dst = csr.dst;
     a.lmask = csr.lmask;
@@ -975,69 +1302,78 @@ int sparse_run(Ctx& c, const rpq_nfa& nfa, const rpq::Csr& csr, const uint32_t* 
     a.srcs = srcs;
     a.n_src = n_src;
     a.target = target;
-    a.table = table;
     a.mask = T - 1;
-    a.front_out = fa;
-    a.front_cap = T / 2;
-    a.pairs = pairs;
-    a.pair_cap = T / 2;
+    a.vw = c.n_words;
+    a.list_cap = cap;
     a.ctr = c.dctr;
-    a.ins_limit = T / 2;
     a.V = c.g->V;
-    hipLaunchKernelGGL(k_sparse_seed, dim3(grid_for(n_src, 16384)), dim3(kBlock), 0, c.s, a);
+    hipLaunchKernelGGL(k_sparse_seed, dim3(grid_for(n_src, 2048)), dim3(kBlock), 0, c.s, a);
     RPQ_LAUNCH_CHECK();
-    RPQ_TRY(read_counters(c, 3));
-    uint64_t n_front = c.stage[0], inserted = n_front;
-    uint64_t* cur = fa;
-    uint64_t* nxt = fb;
-    bool over = c.stage[2] || n_front > T / 2;
-    uint64_t n_levels = n_front ? 1 : 0;
+    hipLaunchKernelGGL(k_sparse_mark, dim3(1), dim3(1), 0, c.s, a);
+    RPQ_LAUNCH_CHECK();
     // a first-reach distance in the product graph is below Q * V
     const uint64_t level_bound = (uint64_t)nfa.n_states * c.g->V + 2;
     // level l expands depth l; a length bound k leaves depth k recorded but unexpanded
-    for (uint64_t level = 0; !over && n_front > 0 && level < max_len; ++level) {
+    for (uint64_t level = 0;;) {
+        for (int i = 0; i < kSparseLevels && level < max_len; ++i, ++level) {
+            hipLaunchKernelGGL(k_sparse_level, dim3(2048), dim3(kBlock), 0, c.s, a, (int)(level & 1));
+            RPQ_LAUNCH_CHECK();
+            hipLaunchKernelGGL(k_sparse_slices, dim3(2048), dim3(kBlock), 0, c.s, a, (int)(level & 1));
+            RPQ_LAUNCH_CHECK();
+            hipLaunchKernelGGL(k_sparse_mark, dim3(1), dim3(1), 0, c.s, a);
+            RPQ_LAUNCH_CHECK();
+        }
+        RPQ_TRY(read_counters(c, S_LEVELS + 1));
+        if (c.stage[S_FLAGS]) return RPQ_ENOMEM;
+        if (c.stage[S_BEG] >= c.stage[S_END] || level >= max_len) break;
         if (level > level_bound) {
             rpq::set_error("sparse search found no fixpoint");
             return RPQ_EDEVICE;
         }
-        RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(c.dctr), 1, 0, c.s));
-        a.front_in = cur;
-        a.n_in = n_front;
-        a.front_out = nxt;
-        a.ins_limit = T / 2 - inserted;   // inserted <= T / 2 here, or the loop would have ended
-        hipLaunchKernelGGL(k_sparse_level, dim3(grid_for(n_front, 16384)), dim3(kBlock), 0, c.s, a);
-        RPQ_LAUNCH_CHECK();
-        RPQ_TRY(read_counters(c, 3));
-        n_front = c.stage[0];
-        inserted += n_front;
-        over = c.stage[2] || n_front > T / 2 || inserted > T / 2;
-        if (n_front) ++n_levels;
-        std::swap(cur, nxt);
     }
-    RPQ_TRY(read_counters(c, 4));
-    if (over || c.stage[1] > T / 2) {
-        c.ar.top = out_mark;
-        return RPQ_ENOMEM;
-    }
-    (void)mark;
-    const uint64_t np = c.stage[1];
-    if (eprod) *eprod = c.stage[3];
-    if (levels) *levels = n_levels;
-    c.ar.top = out_mark + align256(std::max<uint64_t>(1, np) * 8);   // keep the pairs, drop the search state
-    *keys = pairs;
-    *n = np;
+    *found = c.stage[S_LEN];
+    if (eprod) *eprod = c.stage[S_EPROD];
+    if (levels) *levels = c.stage[S_LEVELS];
+    *out = a;
+    return RPQ_OK;
+}
+
+// Bitmap: counts per tile of answer words and their prefix (in the arena), and the number of keys.
+int bitmap_count(Ctx& c, const SArgs& a, uint64_t** offs, uint64_t* n_tiles, uint64_t* total) {
+    *n_tiles = (a.vw + kBitTile - 1) / kBitTile;
+    const uint64_t n = a.n_src * *n_tiles;
+    CRPQ_TAKE(*offs, uint64_t, n + 1);
+    uint64_t* tmp;
+    CRPQ_TAKE(tmp, uint64_t, rpq::scan_temp_elems(n));
+    hipLaunchKernelGGL(k_bits_count, dim3((unsigned)std::min<uint64_t>(n, 8192)), dim3(kBlock), 0, c.s, a, *n_tiles,
+                       *offs);
+    RPQ_LAUNCH_CHECK();
+    RPQ_TRY(rpq::exclusive_scan_u64(*offs, *offs, n, tmp, *offs + n, c.s));
+    RPQ_HIP(hipMemcpyAsync(c.stage, *offs + n, 8, hipMemcpyDeviceToHost, c.s));
+    RPQ_HIP(hipStreamSynchronize(c.s));
+    *total = c.stage[0];
+    return RPQ_OK;
+}
+
+int bitmap_keys(Ctx& c, const SArgs& a, const uint64_t* offs, uint64_t n_tiles, uint64_t* out, uint64_t off,
+                uint64_t cap, uint64_t* per_source, unsigned long long* hash) {
+    hipLaunchKernelGGL(k_bits_keys, dim3((unsigned)std::min<uint64_t>(a.n_src * n_tiles, 4096)), dim3(kBlock), 0, c.s,
+                       a, n_tiles, offs, out, off, cap, reinterpret_cast<unsigned long long*>(per_source), hash);
+    RPQ_LAUNCH_CHECK();
     return RPQ_OK;
 }
 
 // t_cap: largest table to try (0 = no limit); past it the search returns RPQ_EOVERFLOW without
 // setting an error, and the caller evaluates the atom bit-parallel instead.
 int eval_sparse(Ctx& c, const rpq_nfa& nfa_fwd, bool reverse, const uint32_t* srcs, uint64_t n_src,
-                const uint64_t* target, uint64_t t_cap, uint64_t** keys, uint64_t* n) {
+                const uint64_t* target, uint64_t t_cap, uint64_t** keys, uint64_t* n, bool* sorted) {
+    *sorted = false;
     rpq_nfa nfa;
     if (reverse) RPQ_TRY(rpq_nfa_reverse(&nfa_fwd, &nfa));
     else nfa = nfa_fwd;
     const rpq::Csr& csr = reverse ? c.g->in : c.g->out;
-    // table of T slots (load <= 1/2), two frontiers and the pairs of T/2 each: 20 bytes per slot.
+    // table of T slots (load <= 1/2), the list and the pairs of T/2 each, slices: 20 bytes per slot
+    // (a bitmap takes the table's place where it is no larger).
     // Start near 8 states per source and double while the search overflows and the arena allows.
     constexpr uint64_t kSlack = 1ull << 16;
     uint64_t T = 1ull << 16;
@@ -1050,9 +1386,37 @@ int eval_sparse(Ctx& c, const rpq_nfa& nfa_fwd, bool reverse, const uint32_t* sr
             rpq::set_error("workspace exhausted (sparse search with %llu slots)", (unsigned long long)T);
             return RPQ_ENOMEM;
         }
-        const int rc = sparse_run(c, nfa, csr, srcs, n_src, target, T, keys, n);
-        if (rc != RPQ_ENOMEM) return rc;
-        T *= 2;
+        const uint64_t out_mark = c.ar.top;
+        uint64_t* pairs;
+        CRPQ_TAKE(pairs, uint64_t, T / 2);
+        SArgs a;
+        uint64_t found = 0;
+        const bool bitmap = use_bitmap(c, n_src, nfa.n_states, T);
+        const int rc = sparse_run(c, nfa, csr, srcs, n_src, target, bitmap, T, &a, &found, nullptr, nullptr);
+        if (rc == RPQ_ENOMEM) {
+            c.ar.top = out_mark;
+            T *= 2;
+            continue;
+        }
+        RPQ_TRY(rc);
+        uint64_t np = 0;
+        if (bitmap) {
+            uint64_t *offs, n_tiles;
+            RPQ_TRY(bitmap_count(c, a, &offs, &n_tiles, &np));   // at most `found` <= T / 2
+            if (np) RPQ_TRY(bitmap_keys(c, a, offs, n_tiles, pairs, 0, np, nullptr, nullptr));
+            *sorted = true;
+        } else {
+            if (found) {
+                hipLaunchKernelGGL(k_sparse_pairs, dim3(grid_for(found, 2048)), dim3(kBlock), 0, c.s, a, found, pairs);
+                RPQ_LAUNCH_CHECK();
+            }
+            RPQ_TRY(read_counters(c, 2));
+            np = c.stage[S_PAIRS];
+        }
+        c.ar.top = out_mark + align256(std::max<uint64_t>(1, np) * 8);   // keep the pairs, drop the search state
+        *keys = pairs;
+        *n = np;
+        return RPQ_OK;
     }
 }
 
@@ -1062,30 +1426,54 @@ __global__ void k_check_sorted_sources(const uint32_t* __restrict__ s, uint64_t 
         if (s[i] >= V || (i > 0 && s[i - 1] >= s[i])) atomicOr(err, 1ull);
 }
 
-// count, checksum and per-source tallies of sorted distinct keys (s << 32 | v)
+// count, checksum and per-source tallies of sorted distinct keys (s << 32 | v).  Sorted keys come in
+// runs of one source: a wave whose 64 keys share it carries the sums on and adds them once per run.
 __global__ __launch_bounds__(kBlock) void k_key_tallies(const uint64_t* __restrict__ keys, uint64_t n,
                                                         const uint32_t* __restrict__ srcs, uint64_t n_src,
                                                         unsigned long long* __restrict__ per_source,
                                                         unsigned long long* __restrict__ acc) {
-    uint64_t h = 0;
-    for (uint64_t i = gthread(); i < n; i += gstride()) {
-        const uint64_t k = keys[i];
-        const uint64_t m = rpqd::mix64(k);
+    __shared__ uint64_t s_part[kWaves];
+    const int lane = __lane_id();
+    const uint64_t n_waves = (uint64_t)gridDim.x * kWaves;
+    const uint64_t chunk = ((n + n_waves - 1) / n_waves + 63) / 64 * 64;
+    const uint64_t beg = ((uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6)) * chunk;
+    const uint64_t end = min(n, beg + chunk);
+    uint64_t h = 0, run_n = 0, run_h = 0;
+    uint32_t run_s = 0;
+    auto add = [&](uint32_t s, uint64_t cnt, uint64_t hash) {
+        uint64_t lo = 0, hi = n_src;   // position of s in the ascending source list
+        while (lo < hi) {
+            const uint64_t mid = (lo + hi) >> 1;
+            if (srcs[mid] < s) lo = mid + 1;
+            else hi = mid;
+        }
+        atomicAdd(&per_source[2 * lo], (unsigned long long)cnt);
+        atomicAdd(&per_source[2 * lo + 1], (unsigned long long)hash);
+    };
+    auto end_run = [&]() {
+        const uint64_t t = rpqd::wave_sum_u64(run_h);
+        if (run_n && lane == 0) add(run_s, run_n, t);
+        run_n = run_h = 0;
+    };
+    for (uint64_t b = beg; b < end; b += 64) {
+        const uint64_t i = b + lane;
+        const uint64_t k = i < end ? keys[i] : 0;
+        const uint64_t m = i < end ? rpqd::mix64(k) : 0;
         h += m;
         if (per_source) {
-            const uint64_t s = k >> 32;
-            uint64_t lo = 0, hi = n_src;   // position of s in the ascending source list
-            while (lo < hi) {
-                const uint64_t mid = (lo + hi) >> 1;
-                if (srcs[mid] < s) lo = mid + 1;
-                else hi = mid;
+            const uint32_t s = (uint32_t)(k >> 32), s0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s);
+            if (__ballot(i < end && s != s0) == 0) {
+                if (s0 != run_s) end_run();
+                run_s = s0;
+                run_n += min<uint64_t>(64, end - b);
+                run_h += m;
+            } else if (i < end) {
+                add(s, 1, m);
             }
-            atomicAdd(&per_source[2 * lo], 1ull);
-            atomicAdd(&per_source[2 * lo + 1], (unsigned long long)m);
         }
     }
-    h = rpqd::wave_sum_u64(h);
-    if (__lane_id() == 0 && h) atomicAdd(&acc[0], (unsigned long long)h);
+    if (per_source) end_run();
+    block_add(h, s_part, &acc[0]);
 }
 
 // Starting hash-set size: 16 slots per (source, state), at least 2^16, and as large as the free
@@ -1154,7 +1542,7 @@ int sparse_eval(rpq_graph_t g, const rpq_nfa* nfa_in, const uint32_t* sources, u
         return rc;
     };
     auto body = [&]() -> int {
-        CRPQ_TAKE(c.dctr, unsigned long long, 8);
+        CRPQ_TAKE(c.dctr, unsigned long long, kCounters);
         const uint32_t* srcs = sources;
         if (!srcs) {
             uint32_t* all;
@@ -1177,24 +1565,62 @@ int sparse_eval(rpq_graph_t g, const rpq_nfa* nfa_in, const uint32_t* sources, u
         // room for the search and, after it, the sort of up to T/2 pairs (~12 bytes per slot)
         uint64_t T = sparse_start_slots(n_sources, nfa.n_states, c.ar.free_bytes());
         uint64_t* keys = nullptr;
-        uint64_t nk = 0, eprod = 0, levels = 0;
+        uint64_t nk = 0, eprod = 0, levels = 0, found = 0;
+        const uint64_t mark = c.ar.top;
+        SArgs a;
+        bool bitmap = false;
         for (;;) {
             if (T * 20 + (1ull << 16) > c.ar.free_bytes()) {
                 c.ar.need = std::max<uint64_t>(c.ar.need, c.ar.top + T * 20 + (1ull << 16) + (1ull << 20));
                 rpq::set_error("workspace exhausted (sparse search with %llu slots)", (unsigned long long)T);
                 return RPQ_ENOMEM;
             }
+            bitmap = use_bitmap(c, n_sources, nfa.n_states, T);
+            if (!bitmap) CRPQ_TAKE(keys, uint64_t, T / 2);
             const int rc =
-                sparse_run(c, nfa, csr, srcs, n_sources, nullptr, T, &keys, &nk, &eprod, &levels, max_len);
+                sparse_run(c, nfa, csr, srcs, n_sources, nullptr, bitmap, T, &a, &found, &eprod, &levels, max_len);
             if (rc == RPQ_OK) break;
             if (rc != RPQ_ENOMEM) return rc;
+            c.ar.top = mark;
             T *= 2;
         }
+        res->product_edges = eprod;
+        res->levels = levels;
+        res->max_depth = levels ? levels - 1 : 0;
+        if (flags & RPQ_PER_SOURCE) RPQ_TRY(rpq::fill_u64(res->per_source, 2 * n_sources, 0, c.s));
+        if (bitmap) {
+            uint64_t *offs, n_tiles;
+            RPQ_TRY(bitmap_count(c, a, &offs, &n_tiles, &nk));
+            const bool write = (flags & RPQ_PAIRS) && res->pairs;
+            if (nk)
+                RPQ_TRY(bitmap_keys(c, a, offs, n_tiles, res->pairs, res->pair_offset, write ? res->capacity : 0,
+                                    (flags & RPQ_PER_SOURCE) ? res->per_source : nullptr, c.dctr + kCounters - 1));
+            RPQ_TRY(read_counters(c, kCounters));
+            res->count = nk;
+            res->hash = c.stage[kCounters - 1];
+            if (write) {
+                const uint64_t avail = nk > res->pair_offset ? nk - res->pair_offset : 0;
+                res->written = std::min<uint64_t>(avail, res->capacity);
+                if (avail > res->capacity) {
+                    rpq::set_error("result has %llu keys past offset %llu; capacity is %llu",
+                                   (unsigned long long)avail, (unsigned long long)res->pair_offset,
+                                   (unsigned long long)res->capacity);
+                    return RPQ_EOVERFLOW;
+                }
+            }
+            return RPQ_OK;
+        }
+        if (found) {
+            hipLaunchKernelGGL(k_sparse_pairs, dim3(grid_for(found, 2048)), dim3(kBlock), 0, c.s, a, found, keys);
+            RPQ_LAUNCH_CHECK();
+        }
+        RPQ_TRY(read_counters(c, 2));
+        nk = c.stage[S_PAIRS];
+        c.ar.top = mark + align256(std::max<uint64_t>(1, nk) * 8);   // keep the pairs, drop the search state
         RPQ_TRY(sort_unique(c, keys, &nk, false, 0));
         RPQ_TRY(zero_counters(c));
-        if (flags & RPQ_PER_SOURCE) RPQ_TRY(rpq::fill_u64(res->per_source, 2 * n_sources, 0, c.s));
         if (nk) {
-            hipLaunchKernelGGL(k_key_tallies, dim3(grid_for(nk, 16384)), dim3(kBlock), 0, c.s, keys, nk, srcs,
+            hipLaunchKernelGGL(k_key_tallies, dim3(grid_for(nk, 2048)), dim3(kBlock), 0, c.s, keys, nk, srcs,
                                n_sources,
                                (flags & RPQ_PER_SOURCE) ? reinterpret_cast<unsigned long long*>(res->per_source)
                                                         : nullptr,
@@ -1204,9 +1630,6 @@ int sparse_eval(rpq_graph_t g, const rpq_nfa* nfa_in, const uint32_t* sources, u
         RPQ_TRY(read_counters(c, 1));
         res->count = nk;
         res->hash = c.stage[0];
-        res->product_edges = eprod;
-        res->levels = levels;
-        res->max_depth = levels ? levels - 1 : 0;
         if ((flags & RPQ_PAIRS) && res->pairs) {
             const uint64_t avail = nk > res->pair_offset ? nk - res->pair_offset : 0;
             const uint64_t w = std::min<uint64_t>(avail, res->capacity);
@@ -1327,7 +1750,7 @@ int crpq_eval_body(rpq_graph_t g, const crpq_atom* atoms, uint32_t n_atoms, cons
     } while (0)
 
     CRPQ_STEP([&]() -> int {
-        CRPQ_TAKE(c.dctr, unsigned long long, 8);
+        CRPQ_TAKE(c.dctr, unsigned long long, kCounters);
         return RPQ_OK;
     }());
 
@@ -1428,7 +1851,7 @@ int crpq_eval_body(rpq_graph_t g, const crpq_atom* atoms, uint32_t n_atoms, cons
                 nk = pre_n[pick];
                 sorted = true;
             } else if (strategy == CRPQ_STRATEGY_EDGE_SCAN) {
-                RPQ_TRY(eval_edge_scan(c, reverse ? g->in : g->out, lang, srcs, n_src, dom[dv], &keys, &nk));
+                RPQ_TRY(eval_edge_scan(c, reverse ? g->in : g->out, lang, srcs, n_src, dom[dv], &keys, &nk, &sorted));
             } else if (strategy == CRPQ_STRATEGY_DENSE) {
                 RPQ_TRY(eval_dense(c, at.nfa, reverse, srcs, n_src, dom[dv], &keys, &nk));
                 sorted = true;
@@ -1439,7 +1862,7 @@ int crpq_eval_body(rpq_graph_t g, const crpq_atom* atoms, uint32_t n_atoms, cons
                 const uint64_t cap = (flags & CRPQ_FORCE_SPARSE)
                                          ? 0
                                          : std::max<uint64_t>(1ull << 20, 2 * n_src * std::max<uint64_t>(1, g->V / 256));
-                const int rc = eval_sparse(c, at.nfa, reverse, srcs, n_src, dom[dv], cap, &keys, &nk);
+                const int rc = eval_sparse(c, at.nfa, reverse, srcs, n_src, dom[dv], cap, &keys, &nk, &sorted);
                 if (rc == RPQ_EOVERFLOW) {
                     strategy = CRPQ_STRATEGY_DENSE;
                     res->atom_strategy[pick] = strategy | (reverse ? CRPQ_STRATEGY_REVERSED : 0u);
@@ -1617,7 +2040,7 @@ int crpq_eval_body(rpq_graph_t g, const crpq_atom* atoms, uint32_t n_atoms, cons
                 }
             }
             if (a.total) {
-                hipLaunchKernelGGL(k_step_expand, dim3(grid_for(a.total, 65535)), dim3(kBlock), 0, c.s, a);
+                hipLaunchKernelGGL(k_step_expand, dim3(grid_for(a.total, 4096)), dim3(kBlock), 0, c.s, a);
                 RPQ_LAUNCH_CHECK();
             }
             RPQ_TRY(read_counters(c, 4));
@@ -1660,7 +2083,7 @@ int crpq_eval_body(rpq_graph_t g, const crpq_atom* atoms, uint32_t n_atoms, cons
     CRPQ_STEP([&]() -> int {
         RPQ_TRY(zero_counters(c));
         if (n_free) {
-            hipLaunchKernelGGL(k_rows_hash, dim3(grid_for(n_rows, 16384)), dim3(kBlock), 0, c.s, o, c.dctr);
+            hipLaunchKernelGGL(k_rows_hash, dim3(grid_for(n_rows, 2048)), dim3(kBlock), 0, c.s, o, c.dctr);
             RPQ_LAUNCH_CHECK();
         }
         RPQ_TRY(read_counters(c, 2));
@@ -1681,13 +2104,14 @@ int crpq_eval_body(rpq_graph_t g, const crpq_atom* atoms, uint32_t n_atoms, cons
         CRPQ_TAKE(tmp, char, rpq::radix_temp_bytes(n_rows));
         hipLaunchKernelGGL(k_iota, dim3(grid_for(n_rows, 16384)), dim3(kBlock), 0, c.s, perm, n_rows);
         RPQ_LAUNCH_CHECK();
-        const int lo_bits = rpq::bits_for(n_rows - 1), hi_bits = rpq::bits_for(g->V ? g->V - 1 : 0);
+        // the sort is stable and the keys start in order of their low halves: only the high halves are sorted
+        const int hi_bits = rpq::bits_for(g->V ? g->V - 1 : 0);
         for (int j = (int)n_free - 1; j >= 0; --j) {
             hipLaunchKernelGGL(k_sort_keys, dim3(grid_for(n_rows, 16384)), dim3(kBlock), 0, c.s, o.cols[j], perm,
                                n_rows, keys);
             RPQ_LAUNCH_CHECK();
             uint64_t* sorted = nullptr;
-            RPQ_TRY(rpq::radix_sort_u64(keys, alt, n_rows, lo_bits, hi_bits, tmp, c.s, &sorted));
+            RPQ_TRY(rpq::radix_sort_u64(keys, alt, n_rows, 0, hi_bits, tmp, c.s, &sorted));
             hipLaunchKernelGGL(k_perm_apply, dim3(grid_for(n_rows, 16384)), dim3(kBlock), 0, c.s, sorted, perm,
                                n_rows, perm2);
             RPQ_LAUNCH_CHECK();
