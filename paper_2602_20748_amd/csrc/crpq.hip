@@ -1136,12 +1136,17 @@ int eval_dense(Ctx& c, const rpq_nfa& nfa, bool reverse, const uint32_t* srcs, u
     std::memset(&o, 0, sizeof o);
     uint64_t ws = 0;
     RPQ_TRY(rpq_eval_workspace_size(c.g, &nfa, n_src, flags, &o, &ws));
-    // leave at least half of the free workspace for the pairs: fewer units in flight if needed
+    // leave at least half of the free workspace for the pairs: fewer units in flight if needed, then
+    // narrower ones
     const uint64_t avail = c.ar.free_bytes();
     uint32_t conc = 1024;
     while (ws + 4096 > avail / 2 && conc > 1) {
         conc /= 2;
         o.concurrency = conc;
+        RPQ_TRY(rpq_eval_workspace_size(c.g, &nfa, n_src, flags, &o, &ws));
+    }
+    for (uint32_t w = 2048; ws + 4096 > avail / 2 && w >= 64; w /= 2) {
+        o.batch_width = w;
         RPQ_TRY(rpq_eval_workspace_size(c.g, &nfa, n_src, flags, &o, &ws));
     }
     if (ws + 4096 > avail) {

@@ -7,13 +7,14 @@
 // pairs per source keeps every product vertex expanded once per source.
 //
 // Bit-parallel layout.  Sources are taken W = 64*K at a time (a "unit", the
-// counterpart of the paper's start-vertex batch, Section 4.1).  For a unit,
-// every product vertex (q, v) owns a row of K 64-bit words; bit i of word k
-// stands for source 64*k + i.  Per unit:
-//   Vis [Q][V][K]  bits already reached (the per-source visited sets)
-//   Next[Q][V][K]  bits reached in the level being expanded
-//   Touch[Q][V]    1 while (q, v) already sits on the next frontier list
-//   Ans [V][K]     bits of result pairs (s_i, v)
+// counterpart of the paper's start-vertex batch, Section 4.1).  Sources without an edge that an
+// initial state can follow reach nothing: they get no bit, only their zero-length walk is counted.
+// For a unit, every product vertex (q, v) that some label can lead to owns a row of K 64-bit
+// words (see "rows" below); bit i of word k stands for source 64*k + i.  Per unit:
+//   Vis [R][K]  bits already reached (the per-source visited sets)
+//   Next[R][K]  bits reached in the level being expanded (or Vis as of the last level)
+//   Touch[R]    1 while a row already sits on the next frontier list
+// The answer bits of a vertex are the OR of its rows of final states.
 // G units advance together; their rows are tagged by a slot id.
 //
 // One level = three kernels:
@@ -25,13 +26,13 @@
 //             arrive as slices of at most H items (edge-balanced work whatever the degree
 //             skew, with slice memory bounded by 2 * items / H).
 //   compact   the touched rows become the next frontier list (ballot/popcount prefix).
-//   finalize  for each new entry moves Next into a compact frontier row, ORs it into Vis
-//             (and into Ans when q' is final), counts the product edges it will examine,
-//             and cuts entries of more than H items into slices.
+//   finalize  for each new entry moves Next into a compact frontier row, ORs it into Vis,
+//             counts the product edges it will examine, and cuts entries of more than H items
+//             into slices.
 // The fixpoint is reached when a level appends nothing; the host checks the
 // list counter every few levels (no hop bound).
 //
-// Extraction walks Ans: per source its count and checksum, and optionally the
+// Extraction walks the answer bits: per source its count and checksum, and optionally the
 // result keys (s << 32) | v written source-major with ascending v, so the
 // output is sorted and distinct by construction.
 #include "internal.h"
@@ -55,7 +56,8 @@ constexpr int C_PAIRBASE = 7;   // global key index where the current group star
 constexpr int C_COUNT = 8;
 constexpr int C_HASH = 9;
 constexpr int C_LASTLEVEL = 10; // 1 + highest level index whose finalize appended rows (this group)
-constexpr int C_TALLY = 11;     // [kTallies] the work tallies below, summed over the level kernels' blocks
+constexpr int C_ALIVE = 11;     // sources that got a bit
+constexpr int C_TALLY = 12;     // [kTallies] the work tallies below, summed over the level kernels' blocks
 
 // Work tallies of the level kernels.  Every block keeps its own copy (blocks of one launch write
 // disjoint lines, launches follow each other on the stream), and k_tally_sum adds the copies up once
@@ -69,11 +71,11 @@ constexpr int T_DESCS = 2;
 constexpr int T_WREAD = 3;
 constexpr int T_WUPD = 4;
 constexpr int T_FROWS = 5;      // finalize (profiling): rows finalized,
-constexpr int T_FWORDS = 6;     //   their non-zero Next words,
-constexpr int T_FANS = 7;       //   and those of rows of final states
-constexpr int kTallies = 8;
-constexpr int kTallyStride = 16;            // words per block: one 128-byte line
-constexpr unsigned kMaxLevelBlocks = 4096;  // upper bound of a level kernel's grid
+constexpr int T_FWORDS = 6;     //   and their non-zero Next words
+constexpr int kTallies = 7;
+constexpr int kTallyStride = 8;             // words per block
+constexpr unsigned kMaxLevelBlocks = 2048;  // upper bound of a level kernel's grid
+constexpr unsigned kMaxExtractBlocks = 4096;  // and of an extraction that keeps totals per block
 constexpr int C_NCOUNTERS = C_TALLY + kTallies;
 
 constexpr uint64_t ERR_LIST = 1, ERR_DESC = 2, ERR_SOURCES = 4;
@@ -85,9 +87,31 @@ struct Desc {
     uint64_t beg;
 };
 
+// Rows.  A slot has R rows; those of state q are [base[q], base[q + 1]):
+//   ROW_ALL     row base + v for every vertex v
+//   ROW_RANKED  one row for each vertex of a class, the vertices that q's entering labels can lead to
+//               (and the sources, for an initial state): row base + (rank of v in the class)
+//   ROW_SOURCE  q is initial and nothing leads back to it: row base + j for source j of the unit
+// Bitmaps are cleared, and final rows extracted, for every group of units, so rows that no walk can reach
+// cost as much as the others: of R-MAT 23's 8.4M vertices a given label leads to a fifth, and an initial
+// state of 4,096 sources needs 4,096 rows.  A rank costs one 16-byte read of a table that stays in L2
+// (2 MB a class there), so classes are used where the bitmaps are large (kCompactBytes) and the class
+// leaves out at least a quarter of the vertices.
+enum RowKind : uint32_t { ROW_ALL = 0, ROW_RANKED = 1, ROW_SOURCE = 2 };
+
+constexpr uint32_t kNone = 0xFFFFFFFFu;
+
 struct DevNfa {
     uint32_t Q, L, init, final;
+    uint32_t base[RPQ_MAX_STATES + 1];
+    uint32_t kind[RPQ_MAX_STATES];
+    uint32_t rank_at[RPQ_MAX_STATES];   // ROW_RANKED: its class's first word in Args::rank
+    uint64_t list_at[RPQ_MAX_STATES];   //             its class's first vertex in Args::verts
     uint64_t qlab[RPQ_MAX_STATES];                   // labels with a transition out of q
+    // answers: the vertices to look at (every vertex, or a class) and where sources rank (kNone: no
+    // ROW_SOURCE state is final)
+    uint32_t ans_class, ans_rank_at, src_rank_at;
+    uint64_t ans_list_at;
     uint32_t delta[RPQ_MAX_STATES * RPQ_MAX_LABELS]; // compact [q * L + l]
 };
 
@@ -96,20 +120,26 @@ struct Args {
     const uint32_t* dst;
     const uint64_t* lmask;
     const DevNfa* nfa;
+    const ulonglong2* rank;   // per class and 64 vertices: {member bits, members before them}
+    const uint32_t* verts;    // per class: its vertices, ascending
+    const uint32_t* class_n;  // per class: how many
+    const uint32_t* srcs;     // sources that have a bit, ascending, or null: 0, 1, ...
+    const uint32_t* pos;      // their positions in the caller's list, or null: the same
+    uint64_t n_srcs, gbase;   // how many; the first one of the group
     uint64_t* vis;          // visited bits (with seen_or: also those found at the current level)
     uint64_t* next;         // two reads: bits found at this level; seen_or: Vis as of the last finalize
-    uint64_t* touch;        // one bit per (slot, q, v) row: row has bits new at this level
-    uint64_t* ans;
+    uint64_t* touch;        // one bit per row: row has bits new at this level
     uint64_t* rows0;
     uint64_t* rows1;
-    uint32_t* ids0;         // row ids of the frontier lists (row = (slot * Q + q) * V + v)
+    uint32_t* ids0;         // row ids of the frontier lists (row = slot * R + row within the slot)
     uint32_t* ids1;
     Desc* desc0;
     Desc* desc1;
     unsigned long long* counters;
-    unsigned long long* tally;   // [kMaxLevelBlocks][kTallyStride]
+    unsigned long long* tally;    // [kMaxLevelBlocks][kTallyStride]
+    unsigned long long* xtally;   // [kMaxExtractBlocks][2]: count and checksum
     const uint64_t* target;   // optional [V / 64] bitmap: only result vertices with their bit set count
-    uint32_t V, L, Q, H;
+    uint32_t V, L, Q, H, R, W;
     uint32_t seen_or;         // visit scheme: 0 = two reads, 1 = seen OR (see the expansion)
     uint64_t list_cap, desc_cap;
 };
@@ -124,13 +154,57 @@ __device__ __forceinline__ void or_relaxed(uint64_t* p, uint64_t v) {
                                 __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ void load_nfa(const Args& a, uint32_t* s_delta, uint64_t* s_qlab, uint32_t* s_final) {
+// the automaton and the row map in LDS
+struct LdsNfa {
+    uint32_t delta[RPQ_MAX_STATES * RPQ_MAX_LABELS];
+    uint64_t qlab[RPQ_MAX_STATES];
+    uint64_t list_at[RPQ_MAX_STATES];
+    uint32_t base[RPQ_MAX_STATES];
+    uint32_t kind[RPQ_MAX_STATES];
+    uint32_t rank_at[RPQ_MAX_STATES];
+};
+
+__device__ __forceinline__ void load_nfa(const Args& a, LdsNfa& s) {
     const uint32_t QL = a.Q * a.L;
-    for (uint32_t i = threadIdx.x; i < QL; i += kBlock) s_delta[i] = a.nfa->delta[i];
-    if (s_qlab)
-        for (uint32_t i = threadIdx.x; i < a.Q; i += kBlock) s_qlab[i] = a.nfa->qlab[i];
-    if (s_final && threadIdx.x == 0) *s_final = a.nfa->final;
+    for (uint32_t i = threadIdx.x; i < QL; i += kBlock) s.delta[i] = a.nfa->delta[i];
+    if (threadIdx.x < a.Q) {
+        const uint32_t q = threadIdx.x;
+        s.qlab[q] = a.nfa->qlab[q];
+        s.list_at[q] = a.nfa->list_at[q];
+        s.base[q] = a.nfa->base[q];
+        s.kind[q] = a.nfa->kind[q];
+        s.rank_at[q] = a.nfa->rank_at[q];
+    }
     __syncthreads();
+}
+
+__device__ __forceinline__ uint32_t rank_in(const ulonglong2* rank, uint32_t rank_at, uint32_t v) {
+    const ulonglong2 e = rank[rank_at + (v >> 6)];
+    return (uint32_t)e.y + (uint32_t)__popcll(e.x & ((1ull << (v & 63)) - 1));
+}
+
+// row, within its slot, of state q2 (not ROW_SOURCE) at vertex w
+__device__ __forceinline__ uint32_t target_row(const Args& a, const LdsNfa& s, uint32_t q2, uint32_t w) {
+    return s.base[q2] + (s.kind[q2] == ROW_ALL ? w : rank_in(a.rank, s.rank_at[q2], w));
+}
+
+// slot, state and vertex of a row
+__device__ __forceinline__ void row_entry(const Args& a, const LdsNfa& s, uint32_t row, uint32_t* slot, uint32_t* q_out,
+                                          uint32_t* v) {
+    const uint32_t sl = row / a.R, r = row - sl * a.R;
+    uint32_t q = 0;   // the last state whose rows begin at or before r (a state without rows is passed over)
+#pragma unroll
+    for (uint32_t step = RPQ_MAX_STATES / 2; step >= 1; step >>= 1)
+        if (q + step < a.Q && s.base[q + step] <= r) q += step;
+    const uint32_t off = r - s.base[q];
+    *slot = sl;
+    *q_out = q;
+    if (s.kind[q] == ROW_ALL) *v = off;
+    else if (s.kind[q] == ROW_RANKED) *v = a.verts[s.list_at[q] + off];
+    else {
+        const uint64_t gi = a.gbase + (uint64_t)sl * a.W + off;
+        *v = a.srcs ? a.srcs[gi] : (uint32_t)gi;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -171,7 +245,7 @@ __device__ __forceinline__ void keep_in_flight(uint64_t (&x)[N]) {
 }
 
 template <int K, bool SEEN>
-__device__ __forceinline__ void expand_segments(const Args& a, const uint32_t* s_delta, const uint64_t* rows,
+__device__ __forceinline__ void expand_segments(const Args& a, const LdsNfa& s, const uint64_t* rows,
                                                 bool have, uint32_t ent, uint32_t slot, uint32_t q, uint32_t v,
                                                 uint64_t m, uint64_t beg, uint32_t len, uint64_t& t_items,
                                                 uint64_t& t_wread, uint64_t& t_wupd) {
@@ -179,7 +253,6 @@ __device__ __forceinline__ void expand_segments(const Args& a, const uint32_t* s
     const int lane = threadIdx.x & 63;
     const int grp = lane / K, k = lane % K;
     const uint64_t gmask = (K == 64) ? ~0ull : (((1ull << K) - 1) << (grp * K));
-    const uint32_t Q = a.Q, V = a.V;
     if (!have) len = 0;
     const uint32_t incl = rpqd::wave_incl_scan_u32(len);
     const uint32_t excl = incl - len;
@@ -205,8 +278,8 @@ __device__ __forceinline__ void expand_segments(const Args& a, const uint32_t* s
         uint32_t my_row = 0;
         if (item < total) {
             uint32_t w = 0, q2 = 0;
-            rpqd::decode_item(a.row_ptr, a.dst, a.L, s_delta, c_v, c_q, c_m, c_beg + (item - c_ex), &w, &q2);
-            my_row = (c_slot * Q + q2) * V + w;
+            rpqd::decode_item(a.row_ptr, a.dst, a.L, s.delta, c_v, c_q, c_m, c_beg + (item - c_ex), &w, &q2);
+            my_row = c_slot * a.R + target_row(a, s, q2, w);
         }
         const uint32_t n_here = min(64u, total - base);
         // word phase
@@ -280,37 +353,41 @@ __device__ __forceinline__ void add_tallies(const Args& a, int first, const uint
 }
 
 __global__ __launch_bounds__(1024) void k_tally_sum(const unsigned long long* __restrict__ tally,
+                                                    const unsigned long long* __restrict__ xtally,
                                                     unsigned long long* __restrict__ counters) {
-    __shared__ uint64_t s_part[16][kTallies];
-    uint64_t t[kTallies] = {};
+    constexpr int N = kTallies + 2;
+    __shared__ uint64_t s_part[16][N];
+    uint64_t t[N] = {};
     for (unsigned b = threadIdx.x; b < kMaxLevelBlocks; b += 1024)
         for (int i = 0; i < kTallies; ++i) t[i] += tally[(uint64_t)b * kTallyStride + i];
-    for (int i = 0; i < kTallies; ++i) {
+    for (unsigned b = threadIdx.x; b < kMaxExtractBlocks; b += 1024)
+        for (int i = 0; i < 2; ++i) t[kTallies + i] += xtally[2 * (uint64_t)b + i];
+    for (int i = 0; i < N; ++i) {
         const uint64_t x = rpqd::wave_sum_u64(t[i]);
         if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6][i] = x;
     }
     __syncthreads();
-    if (threadIdx.x < kTallies) {
+    if (threadIdx.x < N) {
         uint64_t x = 0;
         for (int w = 0; w < 16; ++w) x += s_part[w][threadIdx.x];
-        counters[C_TALLY + threadIdx.x] = x;
+        if (threadIdx.x < kTallies) counters[C_TALLY + threadIdx.x] = x;
+        else counters[threadIdx.x == kTallies ? C_COUNT : C_HASH] += x;
     }
 }
 
 template <int K, bool SEEN>
 __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
-    __shared__ uint32_t s_delta[RPQ_MAX_STATES * RPQ_MAX_LABELS];
-    __shared__ uint64_t s_qlab[RPQ_MAX_STATES];
-    load_nfa(a, s_delta, s_qlab, nullptr);
+    __shared__ LdsNfa s_nfa;
     const uint64_t n_list = min((uint64_t)a.counters[C_LIST + p], a.list_cap);
     const uint64_t n_desc = min((uint64_t)a.counters[C_DESC + p], a.desc_cap);
     if (n_list == 0) return;
+    load_nfa(a, s_nfa);
     const int lane = threadIdx.x & 63;
     const uint64_t n_waves = (uint64_t)gridDim.x * kWaves;
     const uint64_t wave = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
     const uint64_t* rows = rows_of(a, p);
     const uint32_t* ids = ids_of(a, p);
-    const uint32_t QV = a.Q * a.V, V = a.V, H = a.H;
+    const uint32_t H = a.H;
     uint64_t t_items = 0, t_segs = 0, t_wread = 0, t_wupd = 0;
     // light entries, straight from the frontier list
     const uint64_t n_lb = (n_list + 63) / 64;
@@ -320,18 +397,14 @@ __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
         uint32_t slot = 0, q = 0, v = 0, len = 0;
         uint64_t m = 0;
         if (e < n_list) {
-            const uint32_t row = ids[e];
-            slot = row / QV;
-            const uint32_t rem = row - slot * QV;
-            q = rem / V;
-            v = rem - q * V;
-            m = a.lmask[v] & s_qlab[q];
-            const uint64_t work = m ? rpqd::entry_work(a.row_ptr, a.L, s_delta, v, q, m) : 0;
+            row_entry(a, s_nfa, ids[e], &slot, &q, &v);
+            m = a.lmask[v] & s_nfa.qlab[q];
+            const uint64_t work = m ? rpqd::entry_work(a.row_ptr, a.L, s_nfa.delta, v, q, m) : 0;
             have = work != 0 && work <= H;
             len = have ? (uint32_t)work : 0;
         }
         t_segs += __popcll(__ballot(have)) * (lane == 0);
-        expand_segments<K, SEEN>(a, s_delta, rows, have, (uint32_t)e, slot, q, v, m, 0, len, t_items, t_wread, t_wupd);
+        expand_segments<K, SEEN>(a, s_nfa, rows, have, (uint32_t)e, slot, q, v, m, 0, len, t_items, t_wread, t_wupd);
     }
     // heavy entries, as slices
     const Desc* desc = desc_of(a, p);
@@ -346,16 +419,12 @@ __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
             ent = d.entry;
             beg = d.beg;
             len = d.len;
-            const uint32_t row = ids[ent];
-            slot = row / QV;
-            const uint32_t rem = row - slot * QV;
-            q = rem / V;
-            v = rem - q * V;
-            m = a.lmask[v] & s_qlab[q];
+            row_entry(a, s_nfa, ids[ent], &slot, &q, &v);
+            m = a.lmask[v] & s_nfa.qlab[q];
             have = true;
         }
         t_segs += __popcll(__ballot(have)) * (lane == 0);
-        expand_segments<K, SEEN>(a, s_delta, rows, have, ent, slot, q, v, m, beg, len, t_items, t_wread, t_wupd);
+        expand_segments<K, SEEN>(a, s_nfa, rows, have, ent, slot, q, v, m, beg, len, t_items, t_wread, t_wupd);
     }
     const uint64_t t[4] = {t_items, t_segs, t_wread, t_wupd};
     add_tallies<4>(a, T_ITEMS, t);
@@ -407,8 +476,8 @@ __global__ __launch_bounds__(kBlock) void k_compact(Args a, int p, uint64_t n_ro
 // ------------------------------------------------------------------------------------------------
 // finalize.  Per batch of 64 new frontier rows:
 //   word phase  groups of K lanes take a row each (lane k, word k): Next moves into the compact
-//               frontier row, Vis and (for final states) Ans take the new bits, and the group
-//               counts the new source bits of the row;
+//               frontier row, Vis takes the new bits, and the group counts the new source bits of
+//               the row;
 //   row phase   lane i takes row i: counts the items of its item space (the product edges each of
 //               its new source bits will examine); the slices of rows with more than H items are
 //               written by the whole wave.  With count_work == 0 (the last depth of a
@@ -417,47 +486,38 @@ __global__ __launch_bounds__(kBlock) void k_compact(Args a, int p, uint64_t n_ro
 template <int K>
 __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_work) {
     constexpr int GS = 64 / K;
-    __shared__ uint32_t s_delta[RPQ_MAX_STATES * RPQ_MAX_LABELS];
-    __shared__ uint64_t s_qlab[RPQ_MAX_STATES];
-    __shared__ uint32_t s_final;
-    load_nfa(a, s_delta, s_qlab, &s_final);
+    __shared__ LdsNfa s_nfa;
     const int np = p ^ 1;
     const uint64_t n = min((uint64_t)a.counters[C_LIST + np], a.list_cap);
     if (n == 0) return;
+    load_nfa(a, s_nfa);
     const int lane = threadIdx.x & 63;
     const int grp = lane / K, k = lane % K;
     const uint32_t* ids = ids_of(a, np);
     uint64_t* rows = rows_of(a, np);
     Desc* dout = desc_of(a, np);
     unsigned long long* dcnt = &a.counters[C_DESC + np];
-    const uint32_t H = a.H, V = a.V;
-    const uint32_t QV = a.Q * a.V;
-    const uint32_t fin = s_final;
-    uint64_t eprod = 0, t_rows = 0, t_words = 0, t_ans = 0;
+    const uint32_t H = a.H;
+    uint64_t eprod = 0, t_rows = 0, t_words = 0;
     const uint64_t n_waves = (uint64_t)gridDim.x * kWaves;
     const uint64_t wave = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
     for (uint64_t e0 = wave * 64; e0 < n; e0 += n_waves * 64) {
         const uint64_t e = e0 + lane;
         const bool active = e < n;
         const uint32_t my_row = active ? ids[e] : 0;
-        const uint32_t slot = my_row / QV;
-        const uint32_t rem = my_row - slot * QV;
-        const uint32_t q = rem / V;
-        const uint32_t v = rem - q * V;
-        // Ans row of a final-state entry, else none
-        const uint32_t my_ans = ((fin >> q) & 1) ? slot * V + v : 0xFFFFFFFFu;
+        uint32_t slot = 0, q = 0, v = 0;
+        if (active) row_entry(a, s_nfa, my_row, &slot, &q, &v);
         const uint32_t n_here = (uint32_t)min<uint64_t>(64, n - e0);
         t_rows += n_here * (lane == 0);
         uint32_t my_pc = 0;
         // word phase
         for (uint32_t j = 0; j < n_here; j += GS * kUnroll) {
-            uint32_t r[kUnroll], an[kUnroll];
+            uint32_t r[kUnroll];
             uint64_t nk[kUnroll], ov[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const uint32_t idx = j + u * GS + grp;
                 r[u] = __shfl(my_row, idx & 63, 64);
-                an[u] = __shfl(my_ans, idx & 63, 64);
                 nk[u] = ov[u] = 0;
                 if (idx < n_here) {
                     if (a.seen_or) {
@@ -486,10 +546,6 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
                         // launch).  With seen OR the expansion has already set these bits.
                         if (!a.seen_or) a.vis[(uint64_t)r[u] * K + k] |= nk[u];
                         ++t_words;
-                        if (an[u] != 0xFFFFFFFFu) {
-                            or_relaxed(&a.ans[(uint64_t)an[u] * K + k], nk[u]);
-                            ++t_ans;
-                        }
                         pc = (uint32_t)__popcll(nk[u]);
                     }
                 }
@@ -506,8 +562,8 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
         // product edges, no slices.
         uint64_t work = 0;
         if (active && count_work) {
-            const uint64_t m = a.lmask[v] & s_qlab[q];
-            work = m ? rpqd::entry_work(a.row_ptr, a.L, s_delta, v, q, m) : 0;
+            const uint64_t m = a.lmask[v] & s_nfa.qlab[q];
+            work = m ? rpqd::entry_work(a.row_ptr, a.L, s_nfa.delta, v, q, m) : 0;
             eprod += (uint64_t)my_pc * work;
         }
         const uint64_t ndesc = work > H ? (work + H - 1) / H : 0;
@@ -546,195 +602,508 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
             }
         }
     }
-    const uint64_t t_e[1] = {eprod}, t_f[3] = {t_rows, t_words, t_ans};
+    const uint64_t t_e[1] = {eprod}, t_f[2] = {t_rows, t_words};
     add_tallies<1>(a, T_EPROD, t_e);
-    add_tallies<3>(a, T_FROWS, t_f);
+    add_tallies<2>(a, T_FROWS, t_f);
+}
+
+// ------------------------------------------------------------------------------------------------
+// sources: validity, which of them get a bit, and the results of those that do not
+// ------------------------------------------------------------------------------------------------
+constexpr uint32_t kSrcTile = 2048;   // sources per block
+
+struct SrcArgs {
+    const uint32_t* sources;   // the caller's list, or null: 0, 1, ...
+    uint64_t n;
+    const uint64_t* lmask;
+    uint64_t init_labels;      // labels that an initial state can follow
+    uint32_t V;
+    uint32_t compact;          // sources without such a label get no bit
+    uint32_t eps;              // the empty word is in the language: (s, s) is a result
+    const uint64_t* target;
+    uint64_t* per_source;      // [n][2] or null
+    unsigned long long* bits;  // [V / 64], zero on entry: sources with a bit, or null if no class needs them
+    uint32_t* tile_n;          // sources with a bit per tile
+    uint32_t* out_srcs;        // compact: their list and positions
+    uint32_t* out_pos;
+    unsigned long long* counters;
+};
+
+__device__ __forceinline__ bool has_bit(const SrcArgs& a, uint32_t s) {
+    return s < a.V && (!a.compact || (a.lmask[s] & a.init_labels));
+}
+
+__global__ __launch_bounds__(kBlock) void k_src_count(SrcArgs a) {
+    __shared__ uint64_t s_part[kWaves][3];
+    const int lane = threadIdx.x & 63;
+    uint64_t kept = 0, dead = 0, hash = 0;
+    for (uint32_t r = 0; r < kSrcTile; r += kBlock) {
+        const uint64_t i = (uint64_t)blockIdx.x * kSrcTile + r + threadIdx.x;
+        bool alive = false;
+        uint32_t s = 0;
+        if (i < a.n) {
+            s = a.sources ? a.sources[i] : (uint32_t)i;
+            if (a.sources && (s >= a.V || (i > 0 && a.sources[i - 1] >= s)))
+                atomicOr(&a.counters[C_ERR], (unsigned long long)ERR_SOURCES);
+            alive = has_bit(a, s);
+            if (!alive && s < a.V) {
+                const bool self = a.eps && (!a.target || ((a.target[s >> 6] >> (s & 63)) & 1));
+                const uint64_t h = self ? rpqd::mix64(((uint64_t)s << 32) | s) : 0;
+                dead += self;
+                hash += h;
+                if (a.per_source) {
+                    a.per_source[2 * i] = self;
+                    a.per_source[2 * i + 1] = h;
+                }
+            }
+        }
+        const uint64_t m = __ballot(alive);
+        kept += (uint64_t)__popcll(m) * (lane == 0);
+        if (a.bits && m) {
+            // every vertex is a source: the wave's 64 are one word of the bitmap
+            if (!a.sources) {
+                if (lane == 0) a.bits[i >> 6] = m;
+            } else if (alive) {
+                atomicOr(&a.bits[s >> 6], 1ull << (s & 63));
+            }
+        }
+    }
+    kept = rpqd::wave_sum_u64(kept);
+    dead = rpqd::wave_sum_u64(dead);
+    hash = rpqd::wave_sum_u64(hash);
+    if (lane == 0) {
+        s_part[threadIdx.x >> 6][0] = kept;
+        s_part[threadIdx.x >> 6][1] = dead;
+        s_part[threadIdx.x >> 6][2] = hash;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        uint64_t t = 0;
+        for (int w = 0; w < kWaves; ++w) t += s_part[w][threadIdx.x];
+        if (threadIdx.x == 0) a.tile_n[blockIdx.x] = (uint32_t)t;
+        else if (t) atomicAdd(&a.counters[threadIdx.x == 1 ? C_COUNT : C_HASH], (unsigned long long)t);
+    }
+}
+
+// sum of n words over the block, in every thread
+__device__ __forceinline__ uint64_t block_sum_of(const uint32_t* x, uint64_t n) {
+    __shared__ uint64_t s_sum[kWaves];
+    uint64_t t = 0;
+    for (uint64_t i = threadIdx.x; i < n; i += kBlock) t += x[i];
+    t = rpqd::wave_sum_u64(t);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = t;
+    __syncthreads();
+    t = 0;
+    for (int w = 0; w < kWaves; ++w) t += s_sum[w];
+    __syncthreads();
+    return t;
+}
+
+__global__ __launch_bounds__(kBlock) void k_src_write(SrcArgs a) {
+    __shared__ uint32_t s_n[kWaves];
+    uint64_t at = block_sum_of(a.tile_n, blockIdx.x);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) a.counters[C_ALIVE] = at + a.tile_n[blockIdx.x];
+    for (uint32_t r = 0; r < kSrcTile; r += kBlock) {
+        const uint64_t i = (uint64_t)blockIdx.x * kSrcTile + r + threadIdx.x;
+        uint32_t s = 0;
+        bool alive = false;
+        if (i < a.n) {
+            s = a.sources ? a.sources[i] : (uint32_t)i;
+            alive = has_bit(a, s);
+        }
+        const uint64_t m = __ballot(alive);
+        if ((threadIdx.x & 63) == 0) s_n[threadIdx.x >> 6] = (uint32_t)__popcll(m);
+        __syncthreads();
+        uint32_t before = 0, all = 0;
+        for (int w = 0; w < kWaves; ++w) {
+            before += w < (int)(threadIdx.x >> 6) ? s_n[w] : 0;
+            all += s_n[w];
+        }
+        if (alive) {
+            const uint64_t j = at + before + __popcll(m & rpqd::lanemask_lt());
+            a.out_srcs[j] = s;
+            a.out_pos[j] = (uint32_t)i;
+        }
+        at += all;
+        __syncthreads();
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// classes: the vertices a set of labels can lead to (and, if asked, the sources), as a rank table and
+// an ascending list.  One wave per 64 words of vertex bits; a first pass counts, a second sums the counts
+// before it and writes.
+// ------------------------------------------------------------------------------------------------
+constexpr int kMaxClasses = RPQ_MAX_STATES + 2;
+
+struct ClassArgs {
+    uint64_t labels[kMaxClasses];
+    uint64_t list_at[kMaxClasses];
+    uint64_t src;                 // bit c: class c holds the sources too
+    const uint64_t* entered;      // [L][n_words]
+    const unsigned long long* src_bits;
+    uint64_t n_words;
+    uint32_t n_tiles;             // of 64 words
+    uint32_t* tile_n;             // [classes][n_tiles]
+    ulonglong2* rank;             // [classes][n_words]
+    uint32_t* verts;
+    uint32_t* class_n;            // [classes]
+};
+
+__device__ __forceinline__ uint64_t class_word(const ClassArgs& a, uint32_t c, uint64_t w) {
+    uint64_t x = (a.src >> c) & 1 ? a.src_bits[w] : 0;
+    for (uint64_t m = a.labels[c]; m; m &= m - 1) x |= a.entered[(uint64_t)(__ffsll((long long)m) - 1) * a.n_words + w];
+    return x;
+}
+
+__global__ __launch_bounds__(kBlock) void k_class_count(ClassArgs a) {
+    const uint32_t c = blockIdx.y, tile = blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (tile >= a.n_tiles) return;
+    const uint64_t w = (uint64_t)tile * 64 + (threadIdx.x & 63);
+    const uint64_t t = rpqd::wave_sum_u64(w < a.n_words ? (uint64_t)__popcll(class_word(a, c, w)) : 0);
+    if ((threadIdx.x & 63) == 0) a.tile_n[(uint64_t)c * a.n_tiles + tile] = (uint32_t)t;
+}
+
+__global__ __launch_bounds__(kBlock) void k_class_write(ClassArgs a) {
+    const uint32_t c = blockIdx.y, tile0 = blockIdx.x * kWaves, tile = tile0 + (threadIdx.x >> 6);
+    const uint32_t* tn = a.tile_n + (uint64_t)c * a.n_tiles;
+    uint64_t at = block_sum_of(tn, tile0);
+    for (uint32_t t = tile0; t < tile && t < a.n_tiles; ++t) at += tn[t];
+    if (tile >= a.n_tiles) return;
+    const int lane = threadIdx.x & 63;
+    const uint64_t w = (uint64_t)tile * 64 + lane;
+    const uint64_t x = w < a.n_words ? class_word(a, c, w) : 0;
+    const uint32_t n = (uint32_t)__popcll(x);
+    const uint32_t incl = rpqd::wave_incl_scan_u32(n);
+    const uint64_t before = at + incl - n;
+    if (w < a.n_words) a.rank[(uint64_t)c * a.n_words + w] = make_ulonglong2(x, before);
+    if (tile == a.n_tiles - 1 && lane == 63) a.class_n[c] = (uint32_t)(at + incl);
+    uint32_t* verts = a.verts + a.list_at[c];
+    for (int j = 0; j < 64; ++j) {
+        const uint64_t xj = __shfl(x, j, 64), bj = __shfl(before, j, 64);
+        if ((xj >> lane) & 1) verts[bj + __popcll(xj & rpqd::lanemask_lt())] = (uint32_t)((w - lane + j) * 64 + lane);
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
 // seeding: (q0, s_i) for every initial state q0 and every source of the group
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void k_seed(Args a, const uint32_t* __restrict__ sources,
-                                                 uint64_t n_sources, uint64_t group_base, uint32_t G,
-                                                 uint32_t W, uint32_t K) {
+__global__ __launch_bounds__(kBlock) void k_seed(Args a, uint32_t G, uint32_t K) {
     const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= (uint64_t)G * W) return;
-    const uint64_t gi = group_base + i;
-    if (gi >= n_sources) return;
-    const uint32_t slot = (uint32_t)(i / W), j = (uint32_t)(i % W);
-    const uint32_t s = sources ? sources[gi] : (uint32_t)gi;
+    if (i == 0) {
+        // a new group: no list or slice is left (a length-bounded group ends with a frontier), no level ran
+        a.counters[C_LIST] = a.counters[C_LIST + 1] = a.counters[C_DESC] = a.counters[C_DESC + 1] = 0;
+        a.counters[C_LASTLEVEL] = 0;
+    }
+    if (i >= (uint64_t)G * a.W) return;
+    const uint64_t gi = a.gbase + i;
+    if (gi >= a.n_srcs) return;
+    const uint32_t slot = (uint32_t)(i / a.W), j = (uint32_t)(i % a.W);
+    const uint32_t s = a.srcs ? a.srcs[gi] : (uint32_t)gi;
     const uint32_t k = j >> 6;
     const uint64_t bit = 1ull << (j & 63);
     uint32_t init = a.nfa->init;
     while (init) {
         const uint32_t q = __ffs(init) - 1;
         init &= init - 1;
-        const uint64_t row = ((uint64_t)slot * a.Q + q) * a.V + s;
-        if (a.seen_or)
-            or_relaxed(&a.vis[row * K + k], bit);
-        else
-            or_relaxed(&a.next[row * K + k], bit);
+        const uint32_t kind = a.nfa->kind[q];
+        const uint32_t off = kind == ROW_SOURCE ? j : kind == ROW_ALL ? s : rank_in(a.rank, a.nfa->rank_at[q], s);
+        const uint64_t row = (uint64_t)slot * a.R + a.nfa->base[q] + off;
+        or_relaxed(&(a.seen_or ? a.vis : a.next)[row * K + k], bit);
         or_relaxed(&a.touch[row >> 6], 1ull << (row & 63));
-    }
-}
-
-__global__ void k_check_sources(const uint32_t* __restrict__ s, uint64_t n, uint32_t V,
-                                unsigned long long* __restrict__ counters) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const uint32_t x = s[i];
-        if (x >= V || (i > 0 && s[i - 1] >= x)) atomicOr(&counters[C_ERR], (unsigned long long)ERR_SOURCES);
     }
 }
 
 // ------------------------------------------------------------------------------------------------
 // extraction
 // ------------------------------------------------------------------------------------------------
-// Answer words each lane loads per 64-vertex group: four adjacent words (two 16-byte loads) where K
-// allows.  Neighbouring lanes read rows one row (K words) apart, so every lane makes its own memory
-// request; loading four words per request instead of one cuts the requests per byte fourfold,
-// which is what bounds this kernel when most answer words are zero.
+// Answer words each lane loads per vertex: four adjacent words (two 16-byte loads) where K allows.
+// Neighbouring lanes read rows one row (K words) apart, so every lane makes its own memory request;
+// loading four words per request instead of one cuts the requests per byte fourfold.
 template <int K>
 constexpr int kExtractWords() { return K >= 4 ? 4 : (K >= 2 ? 2 : 1); }
 
-// One wave per (slot, block of kExtractWords consecutive words, vertex chunk); for word k of the
-// block, lane i owns source 64k + i of the slot and walks the non-zero vertex words in ascending
-// vertex order.
-template <int K, bool WRITE>
-__global__ __launch_bounds__(kBlock) void k_extract(Args a, const uint32_t* __restrict__ sources,
-                                                    uint64_t n_sources, uint64_t group_base, uint32_t G,
-                                                    uint32_t W, uint32_t nchunks, uint32_t chunk_v,
-                                                    unsigned long long* __restrict__ acc,
-                                                    uint32_t* __restrict__ partial,
-                                                    const uint64_t* __restrict__ srcbase,
-                                                    uint64_t* __restrict__ pairs, uint64_t pair_off,
-                                                    uint64_t capacity) {
+enum ExtractMode { X_TOTALS = 0, X_TALLIES = 1, X_KEYS = 2 };
+
+struct ExtractArgs {
+    uint32_t G, nchunks, chunk;    // units; chunks of answer vertices
+    unsigned long long* acc;       // [G * W][2] count and checksum (tallies)
+    uint32_t* partial;             // [G * W][nchunks] keys per chunk (tallies), their prefixes (keys), or null
+    const uint64_t* srcbase;       // [G * W] first key of each source (keys)
+    uint64_t* pairs;
+    uint64_t off, cap;             // keys [off, off + cap) are written
+};
+
+__device__ __forceinline__ uint64_t wave_or_u64(uint64_t v) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v |= __shfl_xor(v, o, 64);
+    return v;
+}
+
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+
+// The checksum of key s << 32 | v, mix64, with what depends on the source alone taken out of the loop
+// over v.  Vertex ids are below 2^31, so v plus the constant's low half never carries: the first sum is
+// {s + hi, v + lo}, and after the first shift the high half is the source's own.
+struct MixSource {
+    uint32_t a;    // what the source's half adds to the low half by the first shift
+    uint64_t b;    // its high half's part of the first product
+};
+
+__device__ __forceinline__ MixSource mix_source(uint32_t s) {
+    const uint32_t z = s + 0x9e3779b9u;
+    MixSource m;
+    m.a = z << 2;
+    m.b = (uint64_t)((z ^ (z >> 30)) * 0x1ce4e5b9u) << 32;
+    return m;
+}
+
+__device__ __forceinline__ uint64_t mix_pair(const MixSource& m, uint32_t v) {
+    const uint32_t z = v + 0x7f4a7c15u;
+    const uint32_t t = (z ^ (z >> 30)) ^ m.a;
+    uint64_t y = (uint64_t)t * 0x1ce4e5b9u + m.b;
+    y += (uint64_t)(t * 0xbf58476du) << 32;
+    y = (y ^ (y >> 27)) * 0x94d049bb133111ebull;
+    return y ^ (y >> 31);
+}
+
+// One wave per (slot, block of kExtractWords consecutive words, chunk of answer vertices).  Lane i loads
+// answer vertex i's words: the OR of its rows of final states.  A word block of 64 vertices x 64 sources
+// is then walked by rows or by columns, whichever is shorter for what it holds:
+//   rows     for each vertex with a bit, lane i is source i: checksums are one lane-constant mix per pair,
+//            keys go to 64 streams;
+//   columns  for each source with a bit, lane i is vertex i: a source's keys are written as one run,
+//            and a few sources do not cost a pass per vertex (one source of R-MAT 18: 216 -> 10 us).
+// The totals of a call that asks for neither keys nor per-source results need no accumulator per source.
+template <int K, int MODE>
+__global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
     constexpr int KP = kExtractWords<K>();
     constexpr int NKP = K / KP;
     const int lane = threadIdx.x & 63;
     const uint64_t n_waves = (uint64_t)gridDim.x * kWaves;
-    const uint64_t total = (uint64_t)G * NKP * nchunks;
-    const uint32_t V = a.V;
+    const uint64_t total = (uint64_t)x.G * NKP * x.nchunks;
+    const DevNfa& nfa = *a.nfa;
+    const bool all = nfa.ans_class == kNone;
+    const uint32_t n_ans = all ? a.V : a.class_n[nfa.ans_class];
+    const uint32_t finals = nfa.final, W = a.W;
+    uint64_t tot_c = 0, tot_h = 0;
     for (uint64_t wv = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); wv < total; wv += n_waves) {
-        const uint32_t chunk = (uint32_t)(wv % nchunks);
-        const uint32_t kp = (uint32_t)((wv / nchunks) % NKP);
-        const uint32_t slot = (uint32_t)(wv / ((uint64_t)nchunks * NKP));
-        const uint32_t vbeg = chunk * chunk_v;
-        const uint32_t vend = min(V, vbeg + chunk_v);
-        bool valid[KP];
-        uint64_t skey[KP], cnt[KP], h[KP], cursor[KP];
-        bool in_window = !WRITE;
+        const uint32_t chunk = (uint32_t)(wv % x.nchunks);
+        const uint32_t kp = (uint32_t)((wv / x.nchunks) % NKP);
+        const uint32_t slot = (uint32_t)(wv / ((uint64_t)x.nchunks * NKP));
+        const uint32_t ibeg = min(n_ans, chunk * x.chunk);
+        const uint32_t iend = min(n_ans, ibeg + x.chunk);
+        const uint64_t* vis = a.vis + (uint64_t)slot * a.R * K + (uint64_t)kp * KP;
+        uint32_t src[KP];
+        uint64_t cnt[KP], h[KP], cursor[KP];
+        MixSource ms[KP];
+        bool in_window = MODE != X_KEYS;
 #pragma unroll
         for (int u = 0; u < KP; ++u) {
             const uint64_t si = (uint64_t)slot * W + (uint64_t)(kp * KP + u) * 64 + lane;
-            const uint64_t gi = group_base + si;
-            valid[u] = gi < n_sources;
-            skey[u] = (valid[u] ? (sources ? (uint64_t)sources[gi] : gi) : 0) << 32;
+            const uint64_t gi = a.gbase + si;
+            const bool valid = gi < a.n_srcs;
+            src[u] = valid ? (a.srcs ? a.srcs[gi] : (uint32_t)gi) : 0;
+            ms[u] = mix_source(src[u]);
             cnt[u] = h[u] = cursor[u] = 0;
-            if (WRITE && valid[u]) {
-                // this source's keys in this vertex chunk are [cursor, end): partial holds the
-                // source's chunk prefixes, acc its total
-                const uint32_t* pp = partial + si * nchunks;
-                cursor[u] = srcbase[si] + pp[chunk];
-                const uint64_t end = srcbase[si] + (chunk + 1 < nchunks ? (uint64_t)pp[chunk + 1] : acc[2 * si]);
-                in_window |= end > pair_off && cursor[u] < pair_off + capacity;
+            if (MODE == X_KEYS && valid) {
+                // this source's keys in this chunk are [cursor, end): partial holds the source's chunk
+                // prefixes, acc its total
+                const uint32_t* pp = x.partial + si * x.nchunks;
+                cursor[u] = x.srcbase[si] + pp[chunk];
+                const uint64_t end =
+                    x.srcbase[si] + (chunk + 1 < x.nchunks ? (uint64_t)pp[chunk + 1] : x.acc[2 * si]);
+                in_window |= end > cursor[u] && end > x.off && cursor[u] < x.off + x.cap;
             }
         }
         // a wave none of whose keys fall in the output window has nothing to write
-        if (WRITE && __ballot(in_window) == 0) continue;
-        for (uint32_t v0 = vbeg; v0 < vend; v0 += 64) {
-            const uint32_t vv = v0 + lane;
+        if (MODE == X_KEYS && __ballot(in_window) == 0) continue;
+        for (uint32_t i0 = ibeg; i0 < iend; i0 += 64) {
+            const uint32_t i = i0 + lane;
+            uint32_t v = 0;
             uint64_t word[KP];
-            if (vv < vend) {
-                const uint64_t* p = a.ans + ((uint64_t)slot * V + vv) * K + (uint64_t)kp * KP;
-                if constexpr (KP >= 2) {
 #pragma unroll
-                    for (int u = 0; u < KP; u += 2) {
-                        const ulonglong2 w2 = *reinterpret_cast<const ulonglong2*>(p + u);
-                        word[u] = w2.x;
-                        word[u + 1] = w2.y;
+            for (int u = 0; u < KP; ++u) word[u] = 0;
+            if (i < iend) {
+                v = all ? i : a.verts[nfa.ans_list_at + i];
+                for (uint32_t f = finals; f; f &= f - 1) {
+                    const uint32_t q = __ffs(f) - 1;
+                    uint32_t r = kNone;
+                    if (nfa.kind[q] == ROW_ALL) {
+                        r = v;
+                    } else if (nfa.kind[q] == ROW_RANKED) {
+                        if (!all && nfa.rank_at[q] == nfa.ans_rank_at) {
+                            r = i;
+                        } else {
+                            const ulonglong2 e = a.rank[nfa.rank_at[q] + (v >> 6)];
+                            if ((e.x >> (v & 63)) & 1)
+                                r = (uint32_t)e.y + (uint32_t)__popcll(e.x & ((1ull << (v & 63)) - 1));
+                        }
                     }
-                } else {
-                    word[0] = p[0];
+                    if (r == kNone || nfa.base[q] == nfa.base[q + 1]) continue;
+                    const uint64_t* p = vis + (uint64_t)(nfa.base[q] + r) * K;
+                    if constexpr (KP >= 2) {
+#pragma unroll
+                        for (int u = 0; u < KP; u += 2) {
+                            const ulonglong2 w2 = *reinterpret_cast<const ulonglong2*>(p + u);
+                            word[u] |= w2.x;
+                            word[u + 1] |= w2.y;
+                        }
+                    } else {
+                        word[0] |= p[0];
+                    }
                 }
-            } else {
+                if (nfa.src_rank_at != kNone) {
+                    // the empty word: v itself, if it is a source of this unit and of this word block
+                    const ulonglong2 e = a.rank[nfa.src_rank_at + (v >> 6)];
+                    if ((e.x >> (v & 63)) & 1) {
+                        const uint64_t j = (uint64_t)e.y + __popcll(e.x & ((1ull << (v & 63)) - 1)) - a.gbase -
+                                           (uint64_t)slot * W - (uint64_t)kp * KP * 64;
 #pragma unroll
-                for (int u = 0; u < KP; ++u) word[u] = 0;
-            }
-            if (a.target && vv < vend && !((a.target[vv >> 6] >> (vv & 63)) & 1)) {
+                        for (int u = 0; u < KP; ++u)
+                            if (j >> 6 == (uint64_t)u) word[u] |= 1ull << (j & 63);
+                    }
+                }
+                if (a.target && !((a.target[v >> 6] >> (v & 63)) & 1)) {
 #pragma unroll
-                for (int u = 0; u < KP; ++u) word[u] = 0;
+                    for (int u = 0; u < KP; ++u) word[u] = 0;
+                }
             }
 #pragma unroll
             for (int u = 0; u < KP; ++u) {
                 uint64_t any = __ballot(word[u] != 0);
-                while (any) {
-                    const int jj = __ffsll((long long)any) - 1;
-                    any &= any - 1;
-                    const uint64_t wj = __shfl(word[u], jj, 64);
-                    if (valid[u] && ((wj >> lane) & 1)) {
-                        const uint64_t key = skey[u] | (uint64_t)(v0 + jj);
-                        if (WRITE) {
-                            if (cursor[u] >= pair_off && cursor[u] - pair_off < capacity)
-                                pairs[cursor[u] - pair_off] = key;
-                            ++cursor[u];
+                if (any == 0) continue;
+                uint64_t cols = wave_or_u64(word[u]);
+                const uint32_t nr = (uint32_t)__popcll(any), nc = (uint32_t)__popcll(cols);
+                if (MODE == X_KEYS ? nc < 2 * nr : MODE == X_TALLIES ? 5 * nc < 2 * nr : 3 * nc < 2 * nr) {
+                    while (cols) {
+                        const int c = __ffsll((long long)cols) - 1;
+                        cols &= cols - 1;
+                        const bool bit = (word[u] >> c) & 1;
+                        const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)src[u], c);
+                        if constexpr (MODE == X_KEYS) {
+                            const uint64_t m = __ballot(bit);
+                            const uint64_t cur = readlane_u64(cursor[u], c);
+                            const uint64_t at = cur + __popcll(m & rpqd::lanemask_lt());
+                            if (bit && at >= x.off && at - x.off < x.cap) x.pairs[at - x.off] = ((uint64_t)s << 32) | v;
+                            if (lane == c) cursor[u] = cur + __popcll(m);
                         } else {
-                            ++cnt[u];
-                            h[u] += rpqd::mix64(key);
+                            const uint64_t hv = bit ? rpqd::mix64(((uint64_t)s << 32) | v) : 0;
+                            if constexpr (MODE == X_TOTALS) {
+                                cnt[u] += bit;
+                                h[u] += hv;
+                            } else {
+                                const uint64_t hs = rpqd::wave_sum_u64(hv);
+                                const uint64_t m = __ballot(bit);
+                                if (lane == c) {
+                                    cnt[u] += (uint64_t)__popcll(m);
+                                    h[u] += hs;
+                                }
+                            }
+                        }
+                    }
+                } else {
+                    while (any) {
+                        const int j = __ffsll((long long)any) - 1;
+                        any &= any - 1;
+                        const uint64_t wj = readlane_u64(word[u], j);
+                        const uint32_t vj = (uint32_t)__builtin_amdgcn_readlane((int)v, j);
+                        if ((wj >> lane) & 1) {
+                            if constexpr (MODE == X_KEYS) {
+                                if (cursor[u] >= x.off && cursor[u] - x.off < x.cap)
+                                    x.pairs[cursor[u] - x.off] = ((uint64_t)src[u] << 32) | vj;
+                                ++cursor[u];
+                            } else {
+                                ++cnt[u];
+                                h[u] += mix_pair(ms[u], vj);
+                            }
                         }
                     }
                 }
             }
         }
-        if (!WRITE) {
+        if constexpr (MODE == X_TOTALS) {
 #pragma unroll
             for (int u = 0; u < KP; ++u) {
-                if (!valid[u]) continue;
+                tot_c += cnt[u];
+                tot_h += h[u];
+            }
+        }
+        if constexpr (MODE == X_TALLIES) {
+#pragma unroll
+            for (int u = 0; u < KP; ++u) {
                 const uint64_t si = (uint64_t)slot * W + (uint64_t)(kp * KP + u) * 64 + lane;
-                if (partial) partial[si * nchunks + chunk] = (uint32_t)cnt[u];
+                if (a.gbase + si >= a.n_srcs) continue;
+                if (x.partial) x.partial[si * x.nchunks + chunk] = (uint32_t)cnt[u];
                 if (cnt[u]) {
-                    atomicAdd(&acc[2 * si], (unsigned long long)cnt[u]);
-                    atomicAdd(&acc[2 * si + 1], (unsigned long long)h[u]);
+                    atomicAdd(&x.acc[2 * si], (unsigned long long)cnt[u]);
+                    atomicAdd(&x.acc[2 * si + 1], (unsigned long long)h[u]);
                 }
             }
         }
     }
+    if constexpr (MODE == X_TOTALS) {
+        __shared__ uint64_t s_part[kWaves][2];
+        tot_c = rpqd::wave_sum_u64(tot_c);
+        tot_h = rpqd::wave_sum_u64(tot_h);
+        if (lane == 0) {
+            s_part[threadIdx.x >> 6][0] = tot_c;
+            s_part[threadIdx.x >> 6][1] = tot_h;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            uint64_t t = 0;
+            for (int w = 0; w < kWaves; ++w) t += s_part[w][threadIdx.x];
+            a.xtally[2 * (uint64_t)blockIdx.x + threadIdx.x] += t;
+        }
+    }
 }
 
-// One block: per-source results of the group, chunk prefixes, source offsets, totals.
-__global__ __launch_bounds__(1024) void k_group_finish(unsigned long long* __restrict__ counters,
-                                                       const unsigned long long* __restrict__ acc,
-                                                       uint32_t* __restrict__ partial, uint64_t* __restrict__ srcbase,
-                                                       uint64_t* __restrict__ per_source, uint64_t n_sources,
-                                                       uint64_t group_base, uint64_t n_group, uint32_t nchunks) {
+// Exclusive chunk prefixes of each source's keys; one wave per source.
+__global__ __launch_bounds__(kBlock) void k_chunk_prefix(uint32_t* __restrict__ partial, uint64_t n, uint32_t nchunks) {
+    const int lane = threadIdx.x & 63;
+    for (uint64_t i = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); i < n; i += (uint64_t)gridDim.x * kWaves) {
+        uint32_t* pp = partial + i * nchunks;
+        uint32_t run = 0;
+        for (uint32_t c0 = 0; c0 < nchunks; c0 += 64) {
+            const uint32_t c = c0 + lane;
+            const uint32_t t = c < nchunks ? pp[c] : 0;
+            const uint32_t incl = rpqd::wave_incl_scan_u32(t);
+            if (c < nchunks) pp[c] = run + incl - t;
+            run += __shfl(incl, 63, 64);
+        }
+    }
+}
+
+// Per-source results of the group and its totals; with SCAN (one block) also the sources' first keys.
+template <bool SCAN>
+__global__ __launch_bounds__(1024) void k_group_finish(Args a, const unsigned long long* __restrict__ acc,
+                                                       uint64_t* __restrict__ srcbase,
+                                                       uint64_t* __restrict__ per_source, uint64_t n_group) {
     __shared__ uint64_t s_w[16];
+    __shared__ uint64_t s_h[16];
     __shared__ uint64_t s_carry;
     const int t = threadIdx.x;
     const int lane = t & 63, wv = t >> 6;
-    if (t == 0) s_carry = counters[C_PAIRBASE];
+    if (SCAN && t == 0) s_carry = a.counters[C_PAIRBASE];
     uint64_t csum = 0, hsum = 0;
     __syncthreads();
-    for (uint64_t b0 = 0; b0 < n_group; b0 += 1024) {
-        const uint64_t i = b0 + t;
-        const bool valid = i < n_group && group_base + i < n_sources;
+    for (uint64_t b0 = (uint64_t)blockIdx.x * 1024; b0 < n_group; b0 += (uint64_t)gridDim.x * 1024) {
+        const uint64_t i = b0 + t, gi = a.gbase + i;
+        const bool valid = i < n_group && gi < a.n_srcs;
         const uint64_t c = valid ? acc[2 * i] : 0;
         const uint64_t h = valid ? acc[2 * i + 1] : 0;
         csum += c;
         hsum += h;
         if (valid && per_source) {
-            per_source[2 * (group_base + i)] = c;
-            per_source[2 * (group_base + i) + 1] = h;
+            const uint64_t at = a.pos ? a.pos[gi] : gi;
+            per_source[2 * at] = c;
+            per_source[2 * at + 1] = h;
         }
-        if (srcbase) {
-            if (valid) {
-                uint32_t run = 0;
-                uint32_t* pp = partial + i * nchunks;
-                for (uint32_t ch = 0; ch < nchunks; ++ch) {
-                    const uint32_t x = pp[ch];
-                    pp[ch] = run;
-                    run += x;
-                }
-            }
+        if (SCAN) {
             const uint64_t incl = rpqd::wave_incl_scan_u64(c);
             if (lane == 63) s_w[wv] = incl;
             __syncthreads();
@@ -752,23 +1121,56 @@ __global__ __launch_bounds__(1024) void k_group_finish(unsigned long long* __res
     }
     csum = rpqd::wave_sum_u64(csum);
     hsum = rpqd::wave_sum_u64(hsum);
+    __syncthreads();
     if (lane == 0) {
-        atomicAdd(&counters[C_COUNT], (unsigned long long)csum);
-        atomicAdd(&counters[C_HASH], (unsigned long long)hsum);
+        s_w[wv] = csum;
+        s_h[wv] = hsum;
     }
-    if (srcbase && t == 0) counters[C_PAIRBASE] = s_carry;
+    __syncthreads();
+    if (t == 0) {
+        csum = hsum = 0;
+        for (int w = 0; w < 16; ++w) {
+            csum += s_w[w];
+            hsum += s_h[w];
+        }
+        atomicAdd(&a.counters[C_COUNT], (unsigned long long)csum);
+        atomicAdd(&a.counters[C_HASH], (unsigned long long)hsum);
+        if (SCAN) a.counters[C_PAIRBASE] = s_carry;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------------
+// What a call's rows look like, from the automaton, the direction's entered labels and the number of
+// sources: fixed before the sources are looked at.
+struct Plan {
+    DevNfa dn;                  // base[] is set with the unit width
+    const rpq::Csr* csr;
+    uint64_t rows[RPQ_MAX_STATES];   // upper bound of a state's rows (ROW_SOURCE: the unit width instead)
+    uint32_t n_classes;
+    uint64_t labels[kMaxClasses];
+    uint64_t bound[kMaxClasses];     // upper bound of a class's vertices
+    uint64_t list_at[kMaxClasses];
+    uint64_t src;                    // bit c: class c holds the sources
+    uint64_t verts;                  // vertices over all classes
+    uint64_t ans_bound;              // answer vertices
+    uint64_t init_labels;
+    bool eps, compact_src;
+    uint64_t n_words, desc_items;    // words of V bits; items of a level and unit, at most
+};
+
 struct Layout {
-    uint32_t K, W, G, Q, L, V, H, nchunks, chunk_v, sync_every;
+    uint32_t K, W, G, Q, L, V, H, R, nchunks, chunk, sync_every;
     uint32_t seen_or;   // visit scheme of the expansion (1 = seen OR, 0 = two reads)
     uint64_t max_len;   // deepest level finalized: the length bound, or no bound (UINT64_MAX)
     uint64_t list_cap, desc_cap;
-    uint64_t off_counters, off_tally, off_nfa, off_vis, off_next, off_touch, off_ans, off_ans2, off_ids[2], off_rows[2],
-        off_desc[2], off_acc, off_partial, off_srcbase, total;
+    // fixed by the plan and the number of sources
+    uint64_t off_counters, off_tally, off_xtally, off_src_bits, zero_words, off_nfa, off_tile_n, off_srcs, off_pos,
+        off_rank, off_verts, off_class_n, off_class_tile_n;
+    // by the unit width and units in flight
+    uint64_t off_vis, off_next, off_vis2, off_touch, off_ids[2], off_rows[2], off_desc[2], off_acc, off_partial,
+        off_srcbase, total;
 };
 
 uint64_t align256(uint64_t x) { return (x + 255) & ~255ull; }
@@ -819,41 +1221,155 @@ void to_dev_nfa(const rpq_nfa* nfa, uint32_t L, DevNfa* d) {
         }
 }
 
-// Default shape: about 64K sources in flight, in units of up to 2048 sources below 2^22
-// vertices and 4096 from there (measured: R-MAT scale 18 all-pairs, where throughput rises with
-// the sources advanced per level up to ~64K and 2048-wide units beat 1024 and 4096; R-MAT
-// scale 23 from 65,536 sources, where 4096-wide units beat 2048 by 5% and 1024 lost 6%), entries
-// of more than 16 items cut into slices (16 beat 32, 64, 128 and 256; raised on graphs where the
-// slice buffers would outgrow a quarter of the bitmaps).  Units in flight are sized for 64 GB of
-// the 288 GB device, and a unit of the default width may take up to 96 GB alone (at scale 23 one
-// 4096-wide unit per group, 3.45 s per step, beat two per group within 96 GB, 3.57 s).
+// Default shape: about 64K sources with a bit in flight, in units of up to 2048 sources below 2^22
+// vertices and 4096 from there (R-MAT scale 18 all pairs: 51.3 ms at 2048, 59.6 at 1024, 50.5 at 4096;
+// R-MAT scale 23, 65,536 sources: 152.7 ms at 4096, 154.7 at 2048, 172.8 at 1024), entries of more than
+// 16 items cut into slices (16 beat 32, 64, 128 and 256; raised on graphs where the slice buffers would
+// outgrow a quarter of the bitmaps).  Units in flight are sized for 64 GB of the 288 GB device, and a
+// unit of the default width may take up to 96 GB alone.
 constexpr uint64_t kTargetInFlight = 65536;
 constexpr uint64_t kWorkspaceBudget = 64ull << 30;
 constexpr uint64_t kUnitBudget = 96ull << 30;
 constexpr uint32_t kDefaultChunk = 16;
+// Bitmaps of all vertices below this size are not worth the classes' launches: they are cleared in the
+// same 10 us.
+constexpr uint64_t kCompactBytes = 64ull << 20;
+// Sources up to one word of bits run in one unit either way.
+constexpr uint64_t kCompactSources = 64;
 
 uint32_t max_default_width(uint32_t V) { return V >= (1u << 22) ? 4096 : 2048; }
 
-uint64_t unit_bytes(uint64_t QV, uint32_t W) {
+uint64_t unit_bytes(uint64_t rows, uint32_t W) {
     // Vis + Next + two frontier lists of rows + row ids
-    return QV * (W / 8) * 4 + QV * 8;
+    return rows * (W / 8) * 4 + rows * 8;
 }
 
-uint32_t default_width(uint64_t n_sources, uint64_t QV, uint32_t V) {
+uint32_t add_class(Plan* p, uint64_t labels, bool src, uint64_t bound) {
+    for (uint32_t c = 0; c < p->n_classes; ++c)
+        if (p->labels[c] == labels && (((p->src >> c) & 1) != 0) == src) return c;
+    const uint32_t c = p->n_classes++;
+    p->labels[c] = labels;
+    p->bound[c] = bound;
+    p->list_at[c] = p->verts;
+    p->verts += bound;
+    if (src) p->src |= 1ull << c;
+    return c;
+}
+
+void make_plan(const rpq_graph* g, const rpq::Csr& csr, const rpq_nfa* nfa, uint64_t n_sources, bool keys, Plan* p) {
+    std::memset(p, 0, sizeof *p);
+    to_dev_nfa(nfa, g->L, &p->dn);
+    DevNfa& d = p->dn;
+    p->csr = &csr;
+    p->n_words = ((uint64_t)g->V + 63) / 64;
+    p->eps = (d.init & d.final) != 0;
+    // A source without a bit may have its zero-length walk as a key, which only extraction could put in
+    // its place among the others' keys: with keys and the empty word every source gets a bit.
+    p->compact_src = n_sources > kCompactSources && !(keys && p->eps);
+    for (uint32_t q = 0; q < d.Q; ++q)
+        if ((d.init >> q) & 1) p->init_labels |= d.qlab[q];
+    uint64_t entering[RPQ_MAX_STATES] = {};
+    for (uint32_t q = 0; q < d.Q; ++q) {
+        uint32_t max_succ = 0;
+        for (uint32_t l = 0; l < g->L; ++l) {
+            const uint32_t to = d.delta[q * g->L + l];
+            max_succ = std::max(max_succ, (uint32_t)__builtin_popcount(to));
+            for (uint32_t t = to; t; t &= t - 1) entering[__builtin_ctz(t)] |= 1ull << l;
+        }
+        p->desc_items += (uint64_t)max_succ * g->E;   // the in-CSR holds the same distinct edges
+    }
+    const uint64_t in_flight = std::min<uint64_t>(kTargetInFlight, (n_sources + 63) / 64 * 64);
+    const bool compact = (uint64_t)d.Q * g->V * (in_flight / 8) * 2 > kCompactBytes;
+    auto bound_of = [&](uint64_t labels, bool src) {
+        uint64_t n = src ? n_sources : 0;
+        for (uint64_t m = labels; m; m &= m - 1) n += csr.n_entered[__builtin_ctzll(m)];
+        return std::min<uint64_t>(n, g->V);
+    };
+    auto worth = [&](uint64_t bound) { return bound <= (uint64_t)g->V * 3 / 4; };
+    bool ans_all = !compact, ans_src = false;
+    uint64_t ans_labels = 0;
+    for (uint32_t q = 0; q < d.Q; ++q) {
+        const bool init = (d.init >> q) & 1, fin = (d.final >> q) & 1;
+        const uint64_t bound = bound_of(entering[q], init);
+        d.kind[q] = ROW_ALL;
+        p->rows[q] = g->V;
+        if (!entering[q] && !init) {
+            p->rows[q] = 0;   // nothing leads here
+            continue;
+        }
+        if (compact && !entering[q]) {
+            d.kind[q] = ROW_SOURCE;
+            p->rows[q] = 0;
+        } else if (compact && worth(bound)) {
+            const uint32_t c = add_class(p, entering[q], init, bound);
+            d.kind[q] = ROW_RANKED;
+            d.rank_at[q] = (uint32_t)(c * p->n_words);
+            d.list_at[q] = p->list_at[c];
+            p->rows[q] = bound;
+        }
+        if (fin) {
+            ans_labels |= entering[q];
+            ans_src |= init;
+            ans_all |= d.kind[q] == ROW_ALL;
+        }
+    }
+    d.src_rank_at = kNone;
+    for (uint32_t q = 0; q < d.Q; ++q)
+        if (((d.final >> q) & 1) && d.kind[q] == ROW_SOURCE)
+            d.src_rank_at = (uint32_t)(add_class(p, 0, true, std::min<uint64_t>(n_sources, g->V)) * p->n_words);
+    d.ans_class = d.ans_rank_at = kNone;
+    p->ans_bound = g->V;
+    if (!ans_all && worth(bound_of(ans_labels, ans_src))) {
+        p->ans_bound = bound_of(ans_labels, ans_src);
+        d.ans_class = add_class(p, ans_labels, ans_src, p->ans_bound);
+        d.ans_rank_at = (uint32_t)(d.ans_class * p->n_words);
+        d.ans_list_at = p->list_at[d.ans_class];
+    }
+}
+
+// Slot rows at unit width W, and where each state's begin.
+uint64_t place_rows(const Plan& p, uint32_t W, uint32_t* base) {
+    uint64_t r = 0;
+    for (uint32_t q = 0; q < p.dn.Q; ++q) {
+        if (base) base[q] = (uint32_t)r;
+        r += p.dn.kind[q] == ROW_SOURCE ? W : p.rows[q];
+    }
+    if (base) base[p.dn.Q] = (uint32_t)r;
+    return r;
+}
+
+// Width of a unit for n_bits sources.  Wide rows turn one visit of an edge into work for more sources, so
+// one unit takes as many as it may, up to a quarter of its words unused rather than a second unit
+// (R-MAT 22, 1,130 of a slice's 4,096 sources with a bit: 54.5 ms at 64, 14.1 at 512, 10.7 at 2048).
+// Below 512 sources a row still gets 64 bytes of its own: at 8 bytes a row, ORs to neighbouring rows from
+// different dies meet in one line (R-MAT 18, 40 sources: 1.28 ms at 64, 0.78 at 512, 1.53 at 2048, where
+// the unused words cost), as long as a unit stays small.  On graphs of up to 2^13 vertices a level is one
+// wave's work per unit, and more, narrower units are the faster way (1,000 vertices, all pairs: 1.04 ms at
+// 64, 1.53 at 1024).
+constexpr uint64_t kPadBudget = 4ull << 30;
+
+uint32_t default_width(const Plan& p, uint64_t n_bits, uint32_t V) {
     uint32_t W = 64;
-    while (W < max_default_width(V) && (uint64_t)W * 2 <= std::max<uint64_t>(64, n_sources / 8)) W *= 2;
-    while (W > 64 && unit_bytes(QV, W) > kUnitBudget) W /= 2;
+    if (V <= (1u << 13)) {
+        while (W < 512 && (uint64_t)W * 2 <= std::max<uint64_t>(64, n_bits / 8)) W *= 2;
+    } else {
+        W = 512;
+        while (W < max_default_width(V) && (uint64_t)W * 4 < n_bits * 3) W *= 2;
+        while (W > 64 && W / 2 >= n_bits && unit_bytes(place_rows(p, W, nullptr), W) > kPadBudget) W /= 2;
+    }
+    while (W > 64 && unit_bytes(place_rows(p, W, nullptr), W) > kUnitBudget) W /= 2;
     return W;
 }
 
-int make_layout(const rpq_graph* g, const DevNfa& dn, uint64_t n_sources, uint32_t flags,
-                const rpq_eval_opts* o, bool single_ans, Layout* Lo) {
+// n_sources: the caller's; n_bits: those that get a bit (at most n_sources), which decides the shape.
+int make_layout(const rpq_graph* g, const Plan& p, uint64_t n_sources, uint64_t n_bits, uint32_t flags,
+                const rpq_eval_opts* o, bool noalloc, Layout* Lo) {
     Layout x;
     std::memset(&x, 0, sizeof x);
-    x.Q = dn.Q;
+    x.Q = p.dn.Q;
     x.L = g->L;
     x.V = g->V;
-    x.W = (o && o->batch_width) ? o->batch_width : default_width(n_sources, (uint64_t)dn.Q * g->V, g->V);
+    x.W = (o && o->batch_width) ? o->batch_width : default_width(p, n_bits, g->V);
     if (x.W != 64 && x.W != 128 && x.W != 256 && x.W != 512 && x.W != 1024 && x.W != 2048 && x.W != 4096) {
         rpq::set_error("batch_width must be 64, 128, 256, 512, 1024, 2048 or 4096");
         return RPQ_EINVAL;
@@ -870,37 +1386,36 @@ int make_layout(const rpq_graph* g, const DevNfa& dn, uint64_t n_sources, uint32
     const bool auto_chunk = !(o && o->chunk_edges);
     x.sync_every = (o && o->sync_every) ? o->sync_every : 4;
     x.max_len = (flags & RPQ_LENGTH_BOUND) ? (uint64_t)o->max_length : ~0ull;
-    const uint64_t units = std::max<uint64_t>(1, (n_sources + x.W - 1) / x.W);
-    const uint64_t QV = (uint64_t)x.Q * x.V;
-    const uint64_t bitmap_bytes = QV * x.K * 8;
+    const uint64_t units = std::max<uint64_t>(1, (n_bits + x.W - 1) / x.W);
+    const uint64_t R = std::max<uint64_t>(1, place_rows(p, x.W, nullptr));
+    const uint64_t bitmap_bytes = R * x.K * 8;
     // slices of one level and unit: entries with work > H take ceil(work / H) <= 2 work / H
-    // each, and the work of all entries of state q is at most E * max |delta(q, l)|
-    uint64_t items = 0;
-    for (uint32_t q = 0; q < x.Q; ++q) {
-        uint32_t max_succ = 0;
-        for (uint32_t l = 0; l < x.L; ++l) max_succ = std::max(max_succ, (uint32_t)__builtin_popcount(dn.delta[q * x.L + l]));
-        items += (uint64_t)max_succ * g->E;   // the in-CSR holds the same distinct edges
-    }
-    // default slice size: the smallest (fastest) that keeps a unit's two slice buffers within a
+    // each, and the work of all entries of state q is at most E * max |delta(q, l)|.
+    // Default slice size: the smallest (fastest) that keeps a unit's two slice buffers within a
     // quarter of its bitmaps
-    while (auto_chunk && x.H < 256 && 2 * (2 * items / x.H + 2) * sizeof(Desc) > unit_bytes(QV, x.W) / 4) x.H *= 2;
-    const uint64_t desc_per_unit = 2 * items / x.H + 2;
+    while (auto_chunk && x.H < 256 && 2 * (2 * p.desc_items / x.H + 2) * sizeof(Desc) > unit_bytes(R, x.W) / 4)
+        x.H *= 2;
+    const uint64_t desc_per_unit = 2 * p.desc_items / x.H + 2;
     uint64_t G = (o && o->concurrency) ? o->concurrency : 0;
     if (!G) {
         G = std::max<uint64_t>(1, kTargetInFlight / x.W);
-        const uint64_t per_unit = unit_bytes(QV, x.W) + 2 * desc_per_unit * sizeof(Desc);
+        const uint64_t per_unit = unit_bytes(R, x.W) + 2 * desc_per_unit * sizeof(Desc);
         G = std::min<uint64_t>(G, std::max<uint64_t>(1, kWorkspaceBudget / per_unit));
     }
     G = std::min<uint64_t>(G, units);
     x.G = (uint32_t)G;
-    x.list_cap = G * QV;
+    x.list_cap = G * R;
     if (x.list_cap >= 0xFFFFFFFFull) {
         rpq::set_error("concurrency * states * vertices must stay below 2^32; lower concurrency");
         return RPQ_EUNSUPPORTED;
     }
+    x.R = (uint32_t)R;
     x.desc_cap = G * desc_per_unit;
-    x.chunk_v = 4096;
-    x.nchunks = (uint32_t)((x.V + x.chunk_v - 1) / x.chunk_v);
+    // answer vertices per extraction wave: 4096, fewer while that leaves the device idle
+    const uint64_t ans = std::max<uint64_t>(1, p.ans_bound);
+    x.chunk = 4096;
+    while (x.chunk > 256 && G * ((x.K + 3) / 4) * ((ans + x.chunk - 1) / x.chunk) < 8192) x.chunk /= 2;
+    x.nchunks = (uint32_t)((ans + x.chunk - 1) / x.chunk);
     uint64_t off = 0;
     auto take = [&](uint64_t bytes) {
         const uint64_t o2 = off;
@@ -909,18 +1424,28 @@ int make_layout(const rpq_graph* g, const DevNfa& dn, uint64_t n_sources, uint32
     };
     x.off_counters = take(C_NCOUNTERS * 8);
     x.off_tally = take((uint64_t)kMaxLevelBlocks * kTallyStride * 8);
+    x.off_xtally = take((uint64_t)kMaxExtractBlocks * 2 * 8);
+    x.off_src_bits = take(p.src ? p.n_words * 8 : 0);
+    x.zero_words = off / 8;   // everything up to here starts at zero
     x.off_nfa = take(sizeof(DevNfa));
+    x.off_tile_n = take((n_sources + kSrcTile - 1) / kSrcTile * 4);
+    x.off_srcs = take(p.compact_src ? n_sources * 4 : 0);
+    x.off_pos = take(p.compact_src ? n_sources * 4 : 0);
+    x.off_rank = take(p.n_classes * p.n_words * 16);
+    x.off_verts = take(p.verts * 4);
+    x.off_class_n = take(p.n_classes * 4);
+    x.off_class_tile_n = take(p.n_classes * ((p.n_words + 63) / 64) * 4);
+    // With more than one group the visited bitmap is double-buffered: a group's answers are extracted
+    // from it on a second stream while the next group's levels fill the other one.  Vis, Next, Vis2 in
+    // this order: either Vis and Next are cleared with one fill.
     x.off_vis = take(G * bitmap_bytes);
     x.off_next = take(G * bitmap_bytes);
-    x.off_touch = take((G * QV + 63) / 64 * 8);
-    x.off_ans = take(G * (uint64_t)x.V * x.K * 8);
-    // a second Ans bitmap when there is more than one group: a group's extraction then runs on a
-    // second stream while the next group's levels fill the other bitmap
-    x.off_ans2 = units > G && !single_ans ? take(G * (uint64_t)x.V * x.K * 8) : x.off_ans;
-    for (int p = 0; p < 2; ++p) {
-        x.off_ids[p] = take(x.list_cap * 4);
-        x.off_rows[p] = take(x.list_cap * x.K * 8);
-        x.off_desc[p] = take(x.desc_cap * sizeof(Desc));
+    x.off_vis2 = units > G && !noalloc ? take(G * bitmap_bytes) : x.off_vis;
+    x.off_touch = take((G * R + 63) / 64 * 8);
+    for (int i = 0; i < 2; ++i) {
+        x.off_ids[i] = take(x.list_cap * 4);
+        x.off_rows[i] = take(x.list_cap * x.K * 8);
+        x.off_desc[i] = take(x.desc_cap * sizeof(Desc));
     }
     x.off_acc = take(G * x.W * 16);
     const bool want_pairs = (flags & RPQ_PAIRS) != 0;
@@ -931,17 +1456,19 @@ int make_layout(const rpq_graph* g, const DevNfa& dn, uint64_t n_sources, uint32
     return RPQ_OK;
 }
 
-Args make_args(const rpq_graph* g, uint32_t flags, const Layout& x, char* ws) {
-    const rpq::Csr& csr = (flags & RPQ_REVERSE) ? g->in : g->out;
+Args make_args(const rpq_graph* g, const Plan& p, const Layout& x, char* ws) {
     Args a;
-    a.row_ptr = csr.row_ptr;
-    a.dst = csr.dst;
-    a.lmask = csr.lmask;
+    std::memset(&a, 0, sizeof a);
+    a.row_ptr = p.csr->row_ptr;
+    a.dst = p.csr->dst;
+    a.lmask = p.csr->lmask;
     a.nfa = reinterpret_cast<const DevNfa*>(ws + x.off_nfa);
+    a.rank = reinterpret_cast<const ulonglong2*>(ws + x.off_rank);
+    a.verts = reinterpret_cast<const uint32_t*>(ws + x.off_verts);
+    a.class_n = reinterpret_cast<const uint32_t*>(ws + x.off_class_n);
     a.vis = reinterpret_cast<uint64_t*>(ws + x.off_vis);
     a.next = reinterpret_cast<uint64_t*>(ws + x.off_next);
     a.touch = reinterpret_cast<uint64_t*>(ws + x.off_touch);
-    a.ans = reinterpret_cast<uint64_t*>(ws + x.off_ans);
     a.ids0 = reinterpret_cast<uint32_t*>(ws + x.off_ids[0]);
     a.ids1 = reinterpret_cast<uint32_t*>(ws + x.off_ids[1]);
     a.rows0 = reinterpret_cast<uint64_t*>(ws + x.off_rows[0]);
@@ -950,11 +1477,13 @@ Args make_args(const rpq_graph* g, uint32_t flags, const Layout& x, char* ws) {
     a.desc1 = reinterpret_cast<Desc*>(ws + x.off_desc[1]);
     a.counters = reinterpret_cast<unsigned long long*>(ws + x.off_counters);
     a.tally = reinterpret_cast<unsigned long long*>(ws + x.off_tally);
-    a.target = nullptr;
+    a.xtally = reinterpret_cast<unsigned long long*>(ws + x.off_xtally);
     a.V = x.V;
     a.L = x.L;
     a.Q = x.Q;
     a.H = x.H;
+    a.R = x.R;
+    a.W = x.W;
     a.seen_or = x.seen_or;
     a.list_cap = x.list_cap;
     a.desc_cap = x.desc_cap;
@@ -1141,18 +1670,13 @@ struct SideStream {
 };
 
 template <int K>
-int launch_extract(const Args& a, bool write, const uint32_t* sources, uint64_t n_sources, uint64_t group_base,
-                   uint32_t G, uint32_t W, uint32_t nchunks, uint32_t chunk_v, unsigned long long* acc,
-                   uint32_t* partial, const uint64_t* srcbase, uint64_t* pairs, uint64_t off, uint64_t cap,
-                   hipStream_t s) {
-    const uint64_t waves = (uint64_t)G * (K / kExtractWords<K>()) * nchunks;
-    const unsigned grid = (unsigned)std::min<uint64_t>((waves + kWaves - 1) / kWaves, 16384);
-    if (write)
-        hipLaunchKernelGGL((k_extract<K, true>), dim3(grid), dim3(kBlock), 0, s, a, sources, n_sources, group_base, G,
-                           W, nchunks, chunk_v, acc, partial, srcbase, pairs, off, cap);
-    else
-        hipLaunchKernelGGL((k_extract<K, false>), dim3(grid), dim3(kBlock), 0, s, a, sources, n_sources, group_base,
-                           G, W, nchunks, chunk_v, acc, partial, srcbase, pairs, off, cap);
+int launch_extract(const Args& a, int mode, const ExtractArgs& e, hipStream_t s) {
+    const uint64_t waves = (uint64_t)e.G * (K / kExtractWords<K>()) * e.nchunks;
+    const uint64_t blocks = (waves + kWaves - 1) / kWaves;
+    const dim3 grid((unsigned)std::min<uint64_t>(blocks, mode == X_TOTALS ? kMaxExtractBlocks : 16384));
+    if (mode == X_KEYS) hipLaunchKernelGGL((k_extract<K, X_KEYS>), grid, dim3(kBlock), 0, s, a, e);
+    else if (mode == X_TALLIES) hipLaunchKernelGGL((k_extract<K, X_TALLIES>), grid, dim3(kBlock), 0, s, a, e);
+    else hipLaunchKernelGGL((k_extract<K, X_TOTALS>), grid, dim3(kBlock), 0, s, a, e);
     RPQ_LAUNCH_CHECK();
     return RPQ_OK;
 }
@@ -1195,12 +1719,8 @@ struct PairStreamer {
     uint64_t next_key = 0, end_key = 0;
     hipEvent_t group_done = nullptr;   // recorded on xs after the group's last window
     Args ga;
-    const uint32_t* sources = nullptr;
-    uint64_t n_sources = 0, gbase = 0;
-    uint32_t G_eff = 0, K = 0, W = 0, nchunks = 0, chunk_v = 0;
-    unsigned long long* acc = nullptr;
-    uint32_t* partial = nullptr;
-    const uint64_t* srcbase = nullptr;
+    ExtractArgs ge;
+    uint32_t K = 0;
     // windows issued and not yet delivered: a ring of two, oldest at head
     int win_buf[2] = {0, 0};
     uint64_t win_n[2] = {0, 0};
@@ -1236,27 +1756,16 @@ struct PairStreamer {
 
     // The keys of a group whose count pass and per-source offsets are enqueued on xs; `done` is
     // recorded on xs once its last window is issued.
-    int start_group(const Args& a, hipEvent_t done, const uint32_t* src, uint64_t n_src, uint64_t base, uint32_t G,
-                    uint32_t K_, uint32_t W_, uint32_t nch, uint32_t chv, unsigned long long* acc_,
-                    uint32_t* partial_, const uint64_t* srcbase_, const unsigned long long* pairbase) {
-        RPQ_HIP(hipMemcpyAsync(gend, pairbase, 8, hipMemcpyDeviceToHost, xs));
+    int start_group(const Args& a, const ExtractArgs& e, uint32_t K_, hipEvent_t done) {
+        RPQ_HIP(hipMemcpyAsync(gend, a.counters + C_PAIRBASE, 8, hipMemcpyDeviceToHost, xs));
         RPQ_HIP(hipEventRecord(counted, xs));
         pending = true;
         end_known = false;
         next_key = end_key;   // this group's keys follow the previous group's
         group_done = done;
         ga = a;
-        sources = src;
-        n_sources = n_src;
-        gbase = base;
-        G_eff = G;
+        ge = e;
         K = K_;
-        W = W_;
-        nchunks = nch;
-        chunk_v = chv;
-        acc = acc_;
-        partial = partial_;
-        srcbase = srcbase_;
         return RPQ_OK;
     }
 
@@ -1299,8 +1808,10 @@ struct PairStreamer {
         next_buf ^= 1;
         const uint64_t n = std::min<uint64_t>(ps->chunk_keys, end_key - next_key);
         uint64_t* dev = ps->device_chunks + (uint64_t)b * ps->chunk_keys;
-        RPQ_DISPATCH_K(K, RPQ_TRY(launch_extract<KK>(ga, true, sources, n_sources, gbase, G_eff, W, nchunks, chunk_v,
-                                                     acc, partial, srcbase, dev, next_key, n, xs)));
+        ge.pairs = dev;
+        ge.off = next_key;
+        ge.cap = n;
+        RPQ_DISPATCH_K(K, RPQ_TRY(launch_extract<KK>(ga, X_KEYS, ge, xs)));
         RPQ_HIP(hipEventRecord(ext_done[b], xs));
         RPQ_HIP(hipStreamWaitEvent(cs, ext_done[b], 0));
         RPQ_HIP(hipMemcpyAsync(ps->host_chunks + (uint64_t)b * ps->chunk_keys, dev, n * 8, hipMemcpyDeviceToHost, cs));
@@ -1354,7 +1865,7 @@ struct PairStreamer {
 };
 
 int prepare(rpq_graph_t g, const rpq_nfa* nfa_in, uint64_t n_sources, uint32_t flags, const rpq_eval_opts* opts,
-            rpq_nfa* eff, DevNfa* dn, Layout* lay, bool single_ans = false) {
+            Plan* plan, Layout* lay, bool noalloc = false) {
     if (!g) {
         rpq::set_error("graph is NULL");
         return RPQ_EINVAL;
@@ -1376,10 +1887,11 @@ int prepare(rpq_graph_t g, const rpq_nfa* nfa_in, uint64_t n_sources, uint32_t f
         rpq::set_error("RPQ_REVERSE needs a graph built with RPQ_BUILD_IN_CSR");
         return RPQ_EUNSUPPORTED;
     }
-    if (flags & RPQ_REVERSE) RPQ_TRY(rpq_nfa_reverse(nfa_in, eff));
-    else *eff = *nfa_in;
-    to_dev_nfa(eff, g->L, dn);
-    return make_layout(g, *dn, n_sources, flags, opts, single_ans, lay);
+    rpq_nfa rev;
+    if (flags & RPQ_REVERSE) RPQ_TRY(rpq_nfa_reverse(nfa_in, &rev));
+    make_plan(g, (flags & RPQ_REVERSE) ? g->in : g->out, (flags & RPQ_REVERSE) ? &rev : nfa_in, n_sources,
+              (flags & RPQ_PAIRS) != 0, plan);
+    return make_layout(g, *plan, n_sources, n_sources, flags, opts, noalloc, lay);
 }
 
 }  // namespace
@@ -1395,10 +1907,9 @@ int rpq_eval_workspace_size(rpq_graph_t g, const rpq_nfa* nfa, uint64_t n_source
     }
     if (g && (flags & RPQ_ALL_SOURCES) && n_sources == 0) n_sources = g->V;
     if (flags & RPQ_SPARSE) return rpq::sparse_workspace_size(g, nfa, n_sources, flags, bytes);
-    rpq_nfa eff;
-    DevNfa dn;
+    Plan plan;
     Layout lay;
-    RPQ_TRY(prepare(g, nfa, n_sources, flags, opts, &eff, &dn, &lay));
+    RPQ_TRY(prepare(g, nfa, n_sources, flags, opts, &plan, &lay));
     *bytes = lay.total;
     return RPQ_OK;
 }
@@ -1421,7 +1932,7 @@ namespace {
 
 // The plain evaluation.  With noalloc the call creates nothing: counters are read into a
 // pageable stack buffer instead of the thread's pinned staging buffer, extraction stays on the
-// caller's stream (the layout then holds a single answer bitmap), and no profiling events are
+// caller's stream (the layout then holds a single visited bitmap), and no profiling events are
 // recorded.
 int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64_t n_sources, uint32_t flags,
               const rpq_eval_opts* opts, const uint64_t* target, void* workspace, uint64_t workspace_bytes,
@@ -1469,12 +1980,11 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
         const uint64_t max_len = (flags & RPQ_LENGTH_BOUND) ? (uint64_t)opts->max_length : ~0ull;
         return rpq::sparse_eval(g, nfa, sources, n_sources, flags, max_len, workspace, workspace_bytes, res, stream);
     }
-    rpq_nfa eff;
-    DevNfa dn;
+    Plan plan;
     Layout x;
     // streamed keys need the per-source offsets of the pairs layout
     if (ps) flags |= RPQ_PAIRS;
-    RPQ_TRY(prepare(g, nfa, n_sources, flags, opts, &eff, &dn, &x, noalloc));
+    RPQ_TRY(prepare(g, nfa, n_sources, flags, opts, &plan, &x, noalloc));
     if (!workspace || workspace_bytes < x.total) {
         rpq::set_error("workspace of %llu bytes is smaller than the %llu bytes needed",
                        (unsigned long long)workspace_bytes, (unsigned long long)x.total);
@@ -1490,22 +2000,56 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
     if (n_sources == 0) return RPQ_OK;
 
     char* ws = reinterpret_cast<char*>(workspace);
-    Args a = make_args(g, flags, x, ws);
-    a.target = target;
+    Args a = make_args(g, plan, x, ws);
     uint64_t local_stage[C_NCOUNTERS];
     uint64_t* stage = noalloc ? local_stage : rpq::host_stage();
     if (!stage) {
         rpq::set_error("pinned host staging memory is unavailable");
         return RPQ_EDEVICE;
     }
-    RPQ_HIP(hipMemcpyAsync(ws + x.off_nfa, &dn, sizeof dn, hipMemcpyHostToDevice, stream));
-    RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.counters), C_NCOUNTERS, 0, stream));
-    RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.tally), (uint64_t)kMaxLevelBlocks * kTallyStride, 0, stream));
-    RPQ_TRY(rpq::fill_u64(a.next, (uint64_t)x.G * x.Q * x.V * x.K, 0, stream));
-    RPQ_TRY(rpq::fill_u64(a.touch, ((uint64_t)x.G * x.Q * x.V + 63) / 64, 0, stream));
-    if (sources) {
-        hipLaunchKernelGGL(k_check_sources, dim3((unsigned)std::min<uint64_t>((n_sources + 255) / 256, 4096)),
-                           dim3(256), 0, stream, sources, n_sources, x.V, a.counters);
+    // 1. the sources (validity, which of them get a bit) and the classes
+    RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(ws), x.zero_words, 0, stream));
+    SrcArgs sa;
+    std::memset(&sa, 0, sizeof sa);
+    sa.sources = sources;
+    sa.n = n_sources;
+    sa.lmask = plan.csr->lmask;
+    sa.init_labels = plan.init_labels;
+    sa.V = x.V;
+    sa.compact = plan.compact_src ? 1 : 0;
+    sa.eps = plan.eps ? 1 : 0;
+    sa.target = target;
+    sa.per_source = (flags & RPQ_PER_SOURCE) ? res->per_source : nullptr;
+    sa.bits = plan.src ? reinterpret_cast<unsigned long long*>(ws + x.off_src_bits) : nullptr;
+    sa.tile_n = reinterpret_cast<uint32_t*>(ws + x.off_tile_n);
+    sa.out_srcs = reinterpret_cast<uint32_t*>(ws + x.off_srcs);
+    sa.out_pos = reinterpret_cast<uint32_t*>(ws + x.off_pos);
+    sa.counters = a.counters;
+    const dim3 src_grid((unsigned)((n_sources + kSrcTile - 1) / kSrcTile));
+    hipLaunchKernelGGL(k_src_count, src_grid, dim3(kBlock), 0, stream, sa);
+    RPQ_LAUNCH_CHECK();
+    if (plan.compact_src) {
+        hipLaunchKernelGGL(k_src_write, src_grid, dim3(kBlock), 0, stream, sa);
+        RPQ_LAUNCH_CHECK();
+    }
+    if (plan.n_classes) {
+        ClassArgs ca;
+        std::memset(&ca, 0, sizeof ca);
+        std::memcpy(ca.labels, plan.labels, sizeof ca.labels);
+        std::memcpy(ca.list_at, plan.list_at, sizeof ca.list_at);
+        ca.src = plan.src;
+        ca.entered = plan.csr->entered;
+        ca.src_bits = sa.bits;
+        ca.n_words = plan.n_words;
+        ca.n_tiles = (uint32_t)((plan.n_words + 63) / 64);
+        ca.tile_n = reinterpret_cast<uint32_t*>(ws + x.off_class_tile_n);
+        ca.rank = reinterpret_cast<ulonglong2*>(ws + x.off_rank);
+        ca.verts = reinterpret_cast<uint32_t*>(ws + x.off_verts);
+        ca.class_n = reinterpret_cast<uint32_t*>(ws + x.off_class_n);
+        const dim3 cgrid((ca.n_tiles + kWaves - 1) / kWaves, plan.n_classes);
+        hipLaunchKernelGGL(k_class_count, cgrid, dim3(kBlock), 0, stream, ca);
+        RPQ_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_class_write, cgrid, dim3(kBlock), 0, stream, ca);
         RPQ_LAUNCH_CHECK();
     }
     RPQ_HIP(hipMemcpyAsync(stage, a.counters, C_NCOUNTERS * 8, hipMemcpyDeviceToHost, stream));
@@ -1515,18 +2059,46 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
         return RPQ_EINVAL;
     }
 
+    // 2. the shape for the sources that have a bit (the planned one where that needs more room)
+    const uint64_t n_bits = plan.compact_src ? stage[C_ALIVE] : n_sources;
+    if (n_bits < n_sources) {
+        Layout y;
+        RPQ_TRY(make_layout(g, plan, n_sources, n_bits, flags, opts, noalloc, &y));
+        if (y.total <= workspace_bytes) x = y;
+        a = make_args(g, plan, x, ws);
+    }
+    place_rows(plan, x.W, plan.dn.base);
+    RPQ_HIP(hipMemcpyAsync(ws + x.off_nfa, &plan.dn, sizeof plan.dn, hipMemcpyHostToDevice, stream));
+    a.target = target;
+    a.srcs = plan.compact_src ? sa.out_srcs : sources;
+    a.pos = plan.compact_src ? sa.out_pos : nullptr;
+    a.n_srcs = n_bits;
+    const uint64_t bitmap_words = (uint64_t)x.R * x.K;   // of one unit
+    RPQ_TRY(rpq::fill_u64(a.touch, ((uint64_t)x.G * x.R + 63) / 64, 0, stream));
+    if (!x.seen_or) RPQ_TRY(rpq::fill_u64(a.next, x.G * bitmap_words, 0, stream));
+
     const uint64_t per_group = (uint64_t)x.G * x.W;
-    const uint64_t n_groups = (n_sources + per_group - 1) / per_group;
-    unsigned long long* acc = reinterpret_cast<unsigned long long*>(ws + x.off_acc);
-    uint32_t* partial = want_pairs || ps ? reinterpret_cast<uint32_t*>(ws + x.off_partial) : nullptr;
+    const uint64_t n_groups = (n_bits + per_group - 1) / per_group;
+    const bool tallies = want_pairs || ps || (flags & RPQ_PER_SOURCE);
+    ExtractArgs ea;
+    std::memset(&ea, 0, sizeof ea);
+    ea.nchunks = x.nchunks;
+    ea.chunk = x.chunk;
+    ea.acc = reinterpret_cast<unsigned long long*>(ws + x.off_acc);
+    ea.partial = want_pairs || ps ? reinterpret_cast<uint32_t*>(ws + x.off_partial) : nullptr;
     uint64_t* srcbase = want_pairs || ps ? reinterpret_cast<uint64_t*>(ws + x.off_srcbase) : nullptr;
-    uint64_t levels_total = 0, max_depth = 0;
+    ea.srcbase = srcbase;
+    uint64_t final_rows = 0;
+    for (uint32_t q = 0; q < x.Q; ++q)
+        if ((plan.dn.final >> q) & 1) final_rows += plan.rows[q];
+    // sources without a bit still have their zero-length level
+    uint64_t levels_total = n_bits ? 0 : 1, max_depth = 0;
     // Extraction of group g runs on a second stream (xs) while the levels of group g + 1 run on
-    // `stream` into the other Ans bitmap: the level kernels are bound by memory, extraction by its
+    // `stream` into the other visited bitmap: the level kernels are bound by memory, extraction by its
     // instruction stream.  Events order each bitmap's reuse and the final join.
-    uint64_t* const ans_buf[2] = {reinterpret_cast<uint64_t*>(ws + x.off_ans),
-                                  reinterpret_cast<uint64_t*>(ws + x.off_ans2)};
-    const bool overlap = n_groups > 1 && x.off_ans2 != x.off_ans && !noalloc;
+    uint64_t* const vis_buf[2] = {reinterpret_cast<uint64_t*>(ws + x.off_vis),
+                                  reinterpret_cast<uint64_t*>(ws + x.off_vis2)};
+    const bool overlap = n_groups > 1 && x.off_vis2 != x.off_vis && !noalloc;
     SideStream side(overlap);
     hipStream_t xs = side.stream ? side.stream : stream;
     // streamed keys: windows of group g are extracted on xs while group g + 1's levels run; the
@@ -1535,22 +2107,26 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
     if (ps) RPQ_TRY(st.init(ps, xs, stage + 64, &res->written));
     for (uint64_t grp = 0; grp < n_groups; ++grp) {
         const uint64_t gbase = grp * per_group;
-        const uint64_t n_here = std::min<uint64_t>(per_group, n_sources - gbase);
+        const uint64_t n_here = std::min<uint64_t>(per_group, n_bits - gbase);
         const uint32_t G_eff = (uint32_t)((n_here + x.W - 1) / x.W);
         const int buf = side.stream ? (int)(grp & 1) : 0;
-        a.ans = ans_buf[buf];
+        a.gbase = gbase;
+        a.vis = vis_buf[buf];
+        ea.G = G_eff;
         // the bitmap's previous group must be extracted before it is cleared for this one
         if (side.stream && grp >= 2) RPQ_HIP(hipStreamWaitEvent(stream, side.extracted[buf], 0));
-        RPQ_TRY(rpq::fill_u64(a.vis, (uint64_t)G_eff * x.Q * x.V * x.K, 0, stream));
-        if (x.seen_or) RPQ_TRY(rpq::fill_u64(a.next, (uint64_t)G_eff * x.Q * x.V * x.K, 0, stream));
-        RPQ_TRY(rpq::fill_u64(a.ans, (uint64_t)G_eff * x.V * x.K, 0, stream));
+        if (x.seen_or && G_eff == x.G) {   // Vis and Next lie side by side
+            const uint64_t* lo = std::min(a.vis, a.next);
+            const uint64_t span = (uint64_t)(std::max(a.vis, a.next) - lo) + x.G * bitmap_words;
+            RPQ_TRY(rpq::fill_u64(const_cast<uint64_t*>(lo), span, 0, stream));
+        } else {
+            RPQ_TRY(rpq::fill_u64(a.vis, G_eff * bitmap_words, 0, stream));
+            if (x.seen_or) RPQ_TRY(rpq::fill_u64(a.next, G_eff * bitmap_words, 0, stream));
+        }
         hipLaunchKernelGGL(k_seed, dim3((unsigned)(((uint64_t)G_eff * x.W + kBlock - 1) / kBlock)), dim3(kBlock), 0,
-                           stream, a, sources, n_sources, gbase, G_eff, x.W, x.K);
+                           stream, a, G_eff, x.K);
         RPQ_LAUNCH_CHECK();
-        const uint64_t n_rows = (uint64_t)G_eff * x.Q * x.V;
-        RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.counters) + C_LASTLEVEL, 1, 0, stream));
-        // list and slice counts start at zero (a length-bounded group ends with a frontier left)
-        RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.counters) + C_LIST, 4, 0, stream));
+        const uint64_t n_rows = (uint64_t)G_eff * x.R;
         RPQ_DISPATCH_K(x.K, RPQ_TRY(launch_finalize<KK>(a, 0, n_rows, 0, x.max_len > 0, stream)));
         uint64_t level = 1;
         int p = 1;
@@ -1596,37 +2172,48 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
         // the previous group's windows read acc, partial and srcbase: all of them go on xs before
         // this group's count pass overwrites those arrays
         if (ps) RPQ_TRY(st.pump(true));
-        RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(acc), (uint64_t)G_eff * x.W * 2, 0, xs));
-        // profiling: the count pass timed on its own stream; it reads every answer word of the group
+        if (tallies)
+            RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(ea.acc), (uint64_t)G_eff * x.W * 2, 0, xs));
+        // profiling: the count pass timed on its own stream; it reads every final row of the group
         hipEvent_t xe0 = nullptr, xe1 = nullptr;
         if (!noalloc && profiler().on) {
             Profiler& pr = profiler();
             std::lock_guard<std::mutex> lk(pr.mu);
             xe0 = pr.get();
             xe1 = pr.get();
-            pr.acc.extract_words += (uint64_t)G_eff * x.V * x.K;
+            pr.acc.extract_words += (uint64_t)G_eff * final_rows * x.K;
         }
         if (xe0) RPQ_HIP(hipEventRecord(xe0, xs));
-        RPQ_DISPATCH_K(x.K, RPQ_TRY(launch_extract<KK>(a, false, sources, n_sources, gbase, G_eff, x.W, x.nchunks,
-                                                       x.chunk_v, acc, partial, nullptr, nullptr, 0, 0, xs)));
+        RPQ_DISPATCH_K(x.K, RPQ_TRY(launch_extract<KK>(a, tallies ? X_TALLIES : X_TOTALS, ea, xs)));
         if (xe0 && xe1) {
             RPQ_HIP(hipEventRecord(xe1, xs));
             Profiler& pr = profiler();
             std::lock_guard<std::mutex> lk(pr.mu);
             pr.pend_extract.emplace_back(xe0, xe1);
         }
-        hipLaunchKernelGGL(k_group_finish, dim3(1), dim3(1024), 0, xs, a.counters, acc, partial, srcbase,
-                           (flags & RPQ_PER_SOURCE) ? res->per_source : nullptr, n_sources, gbase,
-                           (uint64_t)G_eff * x.W, x.nchunks);
-        RPQ_LAUNCH_CHECK();
+        if (tallies) {
+            const uint64_t n = (uint64_t)G_eff * x.W;
+            uint64_t* per_source = (flags & RPQ_PER_SOURCE) ? res->per_source : nullptr;
+            if (srcbase) {
+                hipLaunchKernelGGL(k_chunk_prefix, dim3((unsigned)std::min<uint64_t>((n + kWaves - 1) / kWaves, 8192)),
+                                   dim3(kBlock), 0, xs, ea.partial, n, x.nchunks);
+                RPQ_LAUNCH_CHECK();
+                hipLaunchKernelGGL((k_group_finish<true>), dim3(1), dim3(1024), 0, xs, a, ea.acc, srcbase, per_source,
+                                   n);
+            } else {
+                hipLaunchKernelGGL((k_group_finish<false>), dim3((unsigned)((n + 1023) / 1024)), dim3(1024), 0, xs, a,
+                                   ea.acc, srcbase, per_source, n);
+            }
+            RPQ_LAUNCH_CHECK();
+        }
         if (want_pairs) {
-            RPQ_DISPATCH_K(x.K, RPQ_TRY(launch_extract<KK>(a, true, sources, n_sources, gbase, G_eff, x.W, x.nchunks,
-                                                           x.chunk_v, acc, partial, srcbase, res->pairs,
-                                                           res->pair_offset, res->capacity, xs)));
+            ea.pairs = res->pairs;
+            ea.off = res->pair_offset;
+            ea.cap = res->capacity;
+            RPQ_DISPATCH_K(x.K, RPQ_TRY(launch_extract<KK>(a, X_KEYS, ea, xs)));
         }
         if (ps) {
-            RPQ_TRY(st.start_group(a, side.stream ? side.extracted[buf] : nullptr, sources, n_sources, gbase, G_eff,
-                                   x.K, x.W, x.nchunks, x.chunk_v, acc, partial, srcbase, a.counters + C_PAIRBASE));
+            RPQ_TRY(st.start_group(a, ea, x.K, side.stream ? side.extracted[buf] : nullptr));
             RPQ_TRY(st.pump(false));
         } else if (side.stream) {
             RPQ_HIP(hipEventRecord(side.extracted[buf], xs));
@@ -1638,7 +2225,7 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
         RPQ_HIP(hipEventRecord(side.leveled, xs));
         RPQ_HIP(hipStreamWaitEvent(stream, side.leveled, 0));
     }
-    hipLaunchKernelGGL(k_tally_sum, dim3(1), dim3(1024), 0, stream, a.tally, a.counters);
+    hipLaunchKernelGGL(k_tally_sum, dim3(1), dim3(1024), 0, stream, a.tally, a.xtally, a.counters);
     RPQ_LAUNCH_CHECK();
     RPQ_HIP(hipMemcpyAsync(stage, a.counters, C_NCOUNTERS * 8, hipMemcpyDeviceToHost, stream));
     RPQ_HIP(hipStreamSynchronize(stream));
@@ -1657,7 +2244,6 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
             // beyond the method's bytes: the Next word read beside each visited word (two reads);
             // seen OR makes the method's accesses only
             pr.acc.expand_extra_words += x.seen_or ? 0 : tally[T_WREAD];
-            pr.acc.finalize_ans_words += tally[T_FANS];
             pr.acc.edge_items += tally[T_ITEMS];
             pr.acc.descriptors += tally[T_DESCS];
             pr.acc.row_words += tally[T_DESCS] * x.K;
@@ -1749,11 +2335,10 @@ int rpq_eval_noalloc(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources,
     // scratch (fewer units in flight first, then narrower units)
     rpq_eval_opts o{};
     if (opts) o = *opts;
-    rpq_nfa eff;
-    DevNfa dn;
+    Plan plan;
     Layout lay;
     for (;;) {
-        RPQ_TRY(prepare(g, nfa, n, flags, &o, &eff, &dn, &lay, true));
+        RPQ_TRY(prepare(g, nfa, n, flags, &o, &plan, &lay, true));
         if (lay.total <= kScratchBytes) break;
         if (!(opts && opts->concurrency) && lay.G > 1) {
             o.batch_width = lay.W;

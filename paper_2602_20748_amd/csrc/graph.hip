@@ -99,6 +99,47 @@ __global__ void k_label_mask(const uint32_t* __restrict__ row_ptr, uint32_t V, u
     if ((threadIdx.x & 63) == 0 && local) atomicAdd(nonempty, (unsigned long long)local);
 }
 
+// entered bits of a direction, from its keys (row << 32 | neighbour).  Hubs are entered by many edges: a
+// bit that is already set is not ORed again.
+__global__ void k_entered(const uint64_t* __restrict__ ukeys, uint64_t m, uint32_t L, uint64_t n_words,
+                          unsigned long long* __restrict__ entered) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
+        const uint64_t k = ukeys[i];
+        const uint32_t v = (uint32_t)k;
+        unsigned long long* w = &entered[(uint64_t)((uint32_t)(k >> 32) % L) * n_words + (v >> 6)];
+        const unsigned long long bit = 1ull << (v & 63);
+        if (!(*w & bit)) atomicOr(w, bit);
+    }
+}
+
+// the same from the other direction's label masks: v is entered by the labels it leaves by there
+__global__ void k_entered_from_masks(const uint64_t* __restrict__ lmask, uint32_t V, uint32_t L, uint64_t n_words,
+                                     uint64_t* __restrict__ entered) {
+    const int lane = threadIdx.x & 63;
+    const uint64_t stride = (uint64_t)gridDim.x * (blockDim.x / 64);
+    for (uint64_t w = (uint64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6); w < n_words; w += stride) {
+        const uint64_t v = w * 64 + lane;
+        const uint64_t m = v < V ? lmask[v] : 0;
+        for (uint32_t l = 0; l < L; ++l) {
+            const uint64_t b = __ballot((m >> l) & 1);
+            if (lane == 0) entered[(uint64_t)l * n_words + w] = b;
+        }
+    }
+}
+
+// counts[l] += bits of entered[l]; one block row (gridDim.y) per label
+__global__ void k_entered_counts(const uint64_t* __restrict__ entered, uint64_t n_words,
+                                 unsigned long long* __restrict__ counts) {
+    uint64_t c = 0;
+    const uint64_t* e = entered + (uint64_t)blockIdx.y * n_words;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_words;
+         i += (uint64_t)gridDim.x * blockDim.x)
+        c += __popcll(e[i]);
+    c = rpqd::wave_sum_u64(c);
+    if ((threadIdx.x & 63) == 0 && c) atomicAdd(&counts[blockIdx.y], (unsigned long long)c);
+}
+
 struct DevBuf {
     void* p = nullptr;
     ~DevBuf() {
@@ -116,10 +157,12 @@ int dev_alloc(void** p, uint64_t bytes) {
     return RPQ_OK;
 }
 
-// Build one CSR direction.  a/b: row-side and neighbour-side endpoint arrays.
+// Build one CSR direction (more: the other one follows).  a/b: row-side and neighbour-side endpoint arrays.
+// other: the direction built before this one (its label masks then give this one's entered bits, and
+// this one's give its), or null.
 int build_csr(const uint32_t* a, const uint8_t* lab, const uint32_t* b, uint64_t n_edges, uint32_t V,
-              uint32_t L, rpq::Csr* out, uint64_t* E_out, uint64_t* per_label, uint64_t* stage,
-              hipStream_t s) {
+              uint32_t L, rpq::Csr* out, rpq::Csr* other, bool more, uint64_t* E_out, uint64_t* per_label,
+              uint64_t* stage, hipStream_t s) {
     using namespace rpq;
     const uint64_t R = (uint64_t)V * L;
     const uint64_t ne = n_edges ? n_edges : 1;
@@ -128,10 +171,12 @@ int build_csr(const uint32_t* a, const uint8_t* lab, const uint32_t* b, uint64_t
     RPQ_TRY(dev_alloc(&alt.p, ne * 8));
     RPQ_TRY(dev_alloc(&flag.p, (ne + scan_temp_elems(ne) + 1) * 8));
     RPQ_TRY(dev_alloc(&sort_tmp.p, radix_temp_bytes(ne)));
-    RPQ_TRY(dev_alloc(&ctr.p, (4 + RPQ_MAX_LABELS) * 8));
+    constexpr uint64_t kCtr = 4 + 3 * RPQ_MAX_LABELS;
+    RPQ_TRY(dev_alloc(&ctr.p, kCtr * 8));
     unsigned long long* c = reinterpret_cast<unsigned long long*>(ctr.p);   // [0] err [1] total [2] nonempty
     unsigned long long* pl = c + 4;
-    RPQ_TRY(fill_u64(reinterpret_cast<uint64_t*>(c), 4 + RPQ_MAX_LABELS, 0, s));
+    unsigned long long* ent = pl + RPQ_MAX_LABELS;   // [2][RPQ_MAX_LABELS]: entered counts, this and other
+    RPQ_TRY(fill_u64(reinterpret_cast<uint64_t*>(c), kCtr, 0, s));
     uint64_t* k = reinterpret_cast<uint64_t*>(keys.p);
     if (n_edges) {
         hipLaunchKernelGGL(k_make_keys, dim3(grid_for(n_edges)), dim3(kThreads), 0, s, a, lab, b, n_edges, V, L,
@@ -147,7 +192,7 @@ int build_csr(const uint32_t* a, const uint8_t* lab, const uint32_t* b, uint64_t
     uint64_t* sorted = k;
     RPQ_TRY(radix_sort_u64(k, reinterpret_cast<uint64_t*>(alt.p), n_edges, bits_for(V ? V - 1 : 0),
                            bits_for(R ? R - 1 : 0), sort_tmp.p, s, &sorted));
-    uint64_t* other = sorted == k ? reinterpret_cast<uint64_t*>(alt.p) : k;
+    uint64_t* uniq = sorted == k ? reinterpret_cast<uint64_t*>(alt.p) : k;
     uint64_t* fl = reinterpret_cast<uint64_t*>(flag.p);
     uint64_t E = 0;
     if (n_edges) {
@@ -167,17 +212,40 @@ int build_csr(const uint32_t* a, const uint8_t* lab, const uint32_t* b, uint64_t
     RPQ_TRY(dev_alloc(reinterpret_cast<void**>(&out->lmask), (uint64_t)V * 8));
     if (n_edges) {
         hipLaunchKernelGGL(k_compact, dim3(grid_for(n_edges, 8192)), dim3(kThreads), 0, s, sorted, fl, n_edges,
-                           other, out->dst, L, pl);
+                           uniq, out->dst, L, pl);
         RPQ_LAUNCH_CHECK();
     }
-    hipLaunchKernelGGL(k_row_ptr, dim3(grid_for(R + 1)), dim3(kThreads), 0, s, other, E, R, out->row_ptr);
+    hipLaunchKernelGGL(k_row_ptr, dim3(grid_for(R + 1)), dim3(kThreads), 0, s, uniq, E, R, out->row_ptr);
     RPQ_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_label_mask, dim3(grid_for(V, 8192)), dim3(kThreads), 0, s, out->row_ptr, V, L,
                        out->lmask, c + 2);
     RPQ_LAUNCH_CHECK();
-    RPQ_HIP(hipMemcpyAsync(stage, c, (4 + RPQ_MAX_LABELS) * 8, hipMemcpyDeviceToHost, s));
+    // entered bits: for both directions from the other's masks once both are there, else from the edges
+    const uint64_t n_words = ((uint64_t)V + 63) / 64;
+    const dim3 cgrid(grid_for(n_words, 32), L);
+    for (int i = 0; i < 2; ++i) {
+        rpq::Csr* t = i == 0 ? out : other;
+        if (!t || (i == 0 && more)) continue;
+        RPQ_TRY(dev_alloc(reinterpret_cast<void**>(&t->entered), L * n_words * 8));
+        if (other) {
+            hipLaunchKernelGGL(k_entered_from_masks, dim3(grid_for(n_words * 64, 4096)), dim3(kThreads), 0, s,
+                               i == 0 ? other->lmask : out->lmask, V, L, n_words, t->entered);
+        } else {
+            RPQ_TRY(fill_u64(t->entered, L * n_words, 0, s));
+            hipLaunchKernelGGL(k_entered, dim3(grid_for(E, 8192)), dim3(kThreads), 0, s, uniq, E, L, n_words, reinterpret_cast<unsigned long long*>(t->entered));
+        }
+        RPQ_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_entered_counts, cgrid, dim3(kThreads), 0, s, t->entered, n_words,
+                           ent + i * RPQ_MAX_LABELS);
+        RPQ_LAUNCH_CHECK();
+    }
+    RPQ_HIP(hipMemcpyAsync(stage, c, kCtr * 8, hipMemcpyDeviceToHost, s));
     RPQ_HIP(hipStreamSynchronize(s));
     out->nonempty_rows = stage[2];
+    for (uint32_t l = 0; l < L; ++l) {
+        out->n_entered[l] = stage[4 + RPQ_MAX_LABELS + l];
+        if (other) other->n_entered[l] = stage[4 + 2 * RPQ_MAX_LABELS + l];
+    }
     if (per_label)
         for (uint32_t l = 0; l < L; ++l) per_label[l] = stage[4 + l];
     *E_out = E;
@@ -188,6 +256,7 @@ void free_csr(rpq::Csr* c) {
     if (c->row_ptr) (void)hipFree(c->row_ptr);
     if (c->dst) (void)hipFree(c->dst);
     if (c->lmask) (void)hipFree(c->lmask);
+    if (c->entered) (void)hipFree(c->entered);
     *c = rpq::Csr();
 }
 
@@ -247,11 +316,13 @@ int rpq_graph_create(const uint32_t* src, const uint8_t* label, const uint32_t* 
         free_graph(g);
         return RPQ_EDEVICE;
     }
-    int rc = build_csr(src, label, dst, n_edges, n_vertices, n_labels, &g->out, &g->E, g->per_label, g->h_stage,
-                       stream);
-    if (rc == RPQ_OK && (flags & RPQ_BUILD_IN_CSR)) {
+    const bool both = (flags & RPQ_BUILD_IN_CSR) != 0;
+    int rc = build_csr(src, label, dst, n_edges, n_vertices, n_labels, &g->out, nullptr, both, &g->E, g->per_label,
+                       g->h_stage, stream);
+    if (rc == RPQ_OK && both) {
         uint64_t e_in = 0;
-        rc = build_csr(dst, label, src, n_edges, n_vertices, n_labels, &g->in, &e_in, nullptr, g->h_stage, stream);
+        rc = build_csr(dst, label, src, n_edges, n_vertices, n_labels, &g->in, &g->out, false, &e_in, nullptr,
+                       g->h_stage, stream);
         g->has_in = rc == RPQ_OK;
     }
     if (rc == RPQ_OK && vertex_label) {
@@ -271,7 +342,8 @@ int rpq_graph_create(const uint32_t* src, const uint8_t* label, const uint32_t* 
         return rc;
     }
     const uint64_t R = (uint64_t)n_vertices * n_labels;
-    g->device_bytes = (R + 1) * 4 + g->E * 4 + (uint64_t)n_vertices * 8;
+    g->device_bytes = (R + 1) * 4 + g->E * 4 + (uint64_t)n_vertices * 8 +
+                      n_labels * (((uint64_t)n_vertices + 63) / 64) * 8;
     if (g->has_in) g->device_bytes *= 2;
     if (g->vlabel) g->device_bytes += n_vertices;
     *out = g;

@@ -35,11 +35,14 @@ void clear_error();
 
 // One direction of the label-partitioned CSR.  Row r = v * n_labels + l holds
 // the neighbours of v over label l in dst[row_ptr[r] .. row_ptr[r + 1]),
-// ascending.  lmask[v] has bit l set when row (v, l) is non-empty.
+// ascending.  lmask[v] has bit l set when row (v, l) is non-empty; bit v of entered[l] is set when some
+// row (u, l) of this direction holds v, so that a search knows which vertices a label can lead to.
 struct Csr {
     uint32_t* row_ptr = nullptr;   // [V * L + 1]
     uint32_t* dst = nullptr;       // [E]
     uint64_t* lmask = nullptr;     // [V]
+    uint64_t* entered = nullptr;   // [L][(V + 63) / 64]
+    uint64_t n_entered[RPQ_MAX_LABELS] = {};   // vertices label l can lead to
     uint64_t nonempty_rows = 0;
 };
 
