@@ -26,6 +26,8 @@
 //             arrive as slices of at most H items (edge-balanced work whatever the degree
 //             skew, with slice memory bounded by 2 * items / H).
 //   compact   the touched rows become the next frontier list (ballot/popcount prefix).
+//             Items whose target row is full -- it holds every source that still had a bit in the
+//             last frontier but one -- are dropped before the row is read.
 //   finalize  for each new entry moves Next into a compact frontier row, ORs it into Vis,
 //             counts the product edges it will examine, and cuts entries of more than H items
 //             into slices.
@@ -123,12 +125,15 @@ struct Args {
     const ulonglong2* rank;   // per class and 64 vertices: {member bits, members before them}
     const uint32_t* verts;    // per class: its vertices, ascending
     const uint32_t* class_n;  // per class: how many
-    const uint32_t* srcs;     // sources that have a bit, ascending, or null: 0, 1, ...
+    const uint32_t* srcs;     // sources that have a bit, in bit order, or null: 0, 1, ...
     const uint32_t* pos;      // their positions in the caller's list, or null: the same
+    const uint32_t* bit_of;   // bit, within its group, of each in ascending order, or null: the same order
     uint64_t n_srcs, gbase;   // how many; the first one of the group
     uint64_t* vis;          // visited bits (with seen_or: also those found at the current level)
     uint64_t* next;         // two reads: bits found at this level; seen_or: Vis as of the last finalize
     uint64_t* touch;        // one bit per row: row has bits new at this level
+    uint64_t* full;         // one bit per row: no source still searching can add to it (seen_or)
+    uint64_t* active;       // [2][G][K] by list parity: sources with a bit in that frontier, or more
     uint64_t* rows0;
     uint64_t* rows1;
     uint32_t* ids0;         // row ids of the frontier lists (row = slot * R + row within the slot)
@@ -139,6 +144,7 @@ struct Args {
     unsigned long long* tally;    // [kMaxLevelBlocks][kTallyStride]
     unsigned long long* xtally;   // [kMaxExtractBlocks][2]: count and checksum
     const uint64_t* target;   // optional [V / 64] bitmap: only result vertices with their bit set count
+    uint64_t n_active;        // G * K
     uint32_t V, L, Q, H, R, W;
     uint32_t seen_or;         // visit scheme: 0 = two reads, 1 = seen OR (see the expansion)
     uint64_t list_cap, desc_cap;
@@ -276,12 +282,23 @@ __device__ __forceinline__ void expand_segments(const Args& a, const LdsNfa& s, 
         const uint64_t c_beg = __shfl(beg, c, 64);
         const uint32_t c_ex = __shfl(excl, c, 64);
         uint32_t my_row = 0;
+        bool live = false;
         if (item < total) {
             uint32_t w = 0, q2 = 0;
             rpqd::decode_item(a.row_ptr, a.dst, a.L, s.delta, c_v, c_q, c_m, c_beg + (item - c_ex), &w, &q2);
             my_row = c_slot * a.R + target_row(a, s, q2, w);
+            live = !SEEN || !((a.full[my_row >> 6] >> (my_row & 63)) & 1);
         }
-        const uint32_t n_here = min(64u, total - base);
+        // live items to the front, so that the word phase sees no others
+        const uint64_t lm = __ballot(live);
+        const uint32_t n_here = (uint32_t)__popcll(lm);
+        uint32_t my_ent = c_ent;
+        if (n_here != min(64u, total - base)) {
+            const uint32_t before = (uint32_t)__popcll(lm & rpqd::lanemask_lt());
+            const int to = (int)(live ? before : n_here + lane - before) * 4;
+            my_row = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)my_row);
+            my_ent = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)c_ent);
+        }
         // word phase
         for (uint32_t j = 0; j < n_here; j += GS * kUnroll) {
             uint32_t r[kUnroll];
@@ -290,7 +307,7 @@ __device__ __forceinline__ void expand_segments(const Args& a, const LdsNfa& s, 
             for (int u = 0; u < kUnroll; ++u) {
                 const uint32_t idx = j + u * GS + grp;
                 r[u] = __shfl(my_row, idx & 63, 64);
-                const uint32_t e = __shfl(c_ent, idx & 63, 64);
+                const uint32_t e = __shfl(my_ent, idx & 63, 64);
                 f[u] = idx < n_here ? rows[(uint64_t)e * K + k] : 0;
             }
             if constexpr (SEEN) {
@@ -442,6 +459,9 @@ __global__ __launch_bounds__(kBlock) void k_compact(Args a, int p, uint64_t n_ro
         a.counters[C_LIST + p] = 0;
         a.counters[C_DESC + p] = 0;
     }
+    // the finalize that follows collects its frontier's sources there
+    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < a.n_active; i += (uint64_t)gridDim.x * kBlock)
+        a.active[np * a.n_active + i] = 0;
     const int lane = threadIdx.x & 63;
     const uint64_t n_waves = (uint64_t)gridDim.x * kWaves;
     const uint64_t wave = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
@@ -474,7 +494,10 @@ __global__ __launch_bounds__(kBlock) void k_compact(Args a, int p, uint64_t n_ro
 }
 
 // ------------------------------------------------------------------------------------------------
-// finalize.  Per batch of 64 new frontier rows:
+// finalize.  (Seen OR) a row is full when it holds every source of its unit that had a bit in the previous
+// frontier: a source without one has ended its search, so nothing can be added to the row any more.  The
+// set only shrinks from level to level and a row only grows, so a full row stays full.  Per batch of 64 new
+// frontier rows:
 //   word phase  groups of K lanes take a row each (lane k, word k): Next moves into the compact
 //               frontier row, Vis takes the new bits, and the group counts the new source bits of
 //               the row;
@@ -499,6 +522,17 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
     unsigned long long* dcnt = &a.counters[C_DESC + np];
     const uint32_t H = a.H;
     uint64_t eprod = 0, t_rows = 0, t_words = 0;
+    const uint64_t gmask = (K == 64) ? ~0ull : (((1ull << (K & 63)) - 1) << (grp * K));
+    const uint64_t* was_active = a.active + p * a.n_active;
+    unsigned long long* now_active = reinterpret_cast<unsigned long long*>(a.active + np * a.n_active);
+    // this lane's word of its unit's sources with a bit in the new frontier
+    uint64_t seen_k = 0;
+    uint32_t seen_slot = kNone;
+    auto put_active = [&]() {
+        if (seen_slot == kNone || !seen_k) return;
+        unsigned long long* w = &now_active[(uint64_t)seen_slot * K + k];
+        if (seen_k & ~*w) atomicOr(w, (unsigned long long)seen_k);   // a stale copy only costs an OR
+    };
     const uint64_t n_waves = (uint64_t)gridDim.x * kWaves;
     const uint64_t wave = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
     for (uint64_t e0 = wave * 64; e0 < n; e0 += n_waves * 64) {
@@ -512,12 +546,14 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
         uint32_t my_pc = 0;
         // word phase
         for (uint32_t j = 0; j < n_here; j += GS * kUnroll) {
-            uint32_t r[kUnroll];
+            uint32_t r[kUnroll], sl[kUnroll];
             uint64_t nk[kUnroll], ov[kUnroll];
+            bool full[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const uint32_t idx = j + u * GS + grp;
                 r[u] = __shfl(my_row, idx & 63, 64);
+                sl[u] = __shfl(slot, idx & 63, 64);
                 nk[u] = ov[u] = 0;
                 if (idx < n_here) {
                     if (a.seen_or) {
@@ -530,7 +566,23 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
             }
             if (a.seen_or) {
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) nk[u] &= ~ov[u];
+                for (int u = 0; u < kUnroll; ++u) {
+                    const uint32_t idx = j + u * GS + grp;
+                    full[u] = idx < n_here && (was_active[(uint64_t)sl[u] * K + k] & ~nk[u]) == 0;
+                    nk[u] &= ~ov[u];
+                    if (idx < n_here) {
+                        if (sl[u] != seen_slot) {
+                            put_active();
+                            seen_slot = sl[u];
+                            seen_k = 0;
+                        }
+                        seen_k |= nk[u];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u)
+                    if ((__ballot(full[u]) & gmask) == gmask && k == 0)
+                        or_relaxed(&a.full[r[u] >> 6], 1ull << (r[u] & 63));
             }
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
@@ -602,6 +654,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
             }
         }
     }
+    put_active();
     const uint64_t t_e[1] = {eprod}, t_f[2] = {t_rows, t_words};
     add_tallies<1>(a, T_EPROD, t_e);
     add_tallies<2>(a, T_FROWS, t_f);
@@ -730,6 +783,67 @@ __global__ __launch_bounds__(kBlock) void k_src_write(SrcArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
+// bit order.  A word of a row is expanded once for every level at which one of its 64 sources arrives, so
+// sources that arrive together belong into one word.  Two sources with an edge to the same hub are at most
+// two levels apart at every vertex, and mostly not apart at all; so a group's sources are ordered by the
+// largest degree among (up to kScoreEdges of) their first neighbours, and within it by that neighbour.
+// One counting pass over kScores buckets; the order within a bucket is of no consequence.
+// ------------------------------------------------------------------------------------------------
+constexpr uint32_t kScoreEdges = 16;
+constexpr uint32_t kScores = 1u << 16;   // 5 bits of degree, 8 of the neighbour, 3 that spread a hub's counter
+
+struct OrderArgs {
+    const uint32_t* row_ptr;
+    const uint32_t* dst;
+    const uint64_t* lmask;
+    uint64_t init_labels;
+    uint32_t L;
+    uint64_t n, gbase;           // the group
+    const uint32_t* in_srcs;     // ascending
+    const uint32_t* in_pos;
+    uint64_t* hist;              // [kScores]: zero, then counts, then their prefixes
+    uint32_t* score;             // [n]
+    uint32_t* rank;              // [n]
+    uint32_t* srcs;
+    uint32_t* pos;
+    uint32_t* bit_of;
+};
+
+__global__ __launch_bounds__(kBlock) void k_order_score(OrderArgs a) {
+    const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= a.n) return;
+    const uint32_t s = a.in_srcs[a.gbase + i];
+    uint32_t best = 0, hub = 0;
+    for (uint64_t m = a.lmask[s] & a.init_labels; m; m &= m - 1) {
+        const uint64_t r = (uint64_t)s * a.L + (uint32_t)(__ffsll((long long)m) - 1);
+        const uint32_t b = a.row_ptr[r], d = a.row_ptr[r + 1] - b;
+        const uint32_t n = min(d, kScoreEdges);
+        for (uint32_t t = 0; t < n; ++t) {
+            const uint32_t w = a.dst[b + (uint32_t)((uint64_t)d * t / n)];
+            const uint64_t rw = (uint64_t)w * a.L;
+            const uint32_t deg = a.row_ptr[rw + a.L] - a.row_ptr[rw];
+            if (deg > best || (deg == best && w > hub)) {
+                best = deg;
+                hub = w;
+            }
+        }
+    }
+    const uint32_t bits = best ? 32 - __clz(best) : 0;
+    const uint32_t score = ((31 - min(bits, 31u)) << 11) | (((hub * 0x9E3779B1u) >> 24) << 3) | (threadIdx.x & 7);
+    a.score[i] = score;
+    a.rank[i] = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&a.hist[score]), 1ull);
+}
+
+__global__ __launch_bounds__(kBlock) void k_order_place(OrderArgs a) {
+    const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= a.n) return;
+    const uint32_t bit = (uint32_t)a.hist[a.score[i]] + a.rank[i];
+    a.srcs[a.gbase + bit] = a.in_srcs[a.gbase + i];
+    a.pos[a.gbase + bit] = a.in_pos[a.gbase + i];
+    a.bit_of[a.gbase + i] = bit;
+}
+
+// ------------------------------------------------------------------------------------------------
 // classes: the vertices a set of labels can lead to (and, if asked, the sources), as a rank table and
 // an ascending list.  One wave per 64 words of vertex bits; a first pass counts, a second sums the counts
 // before it and writes.
@@ -797,6 +911,11 @@ __global__ __launch_bounds__(kBlock) void k_seed(Args a, uint32_t G, uint32_t K)
     }
     if (i >= (uint64_t)G * a.W) return;
     const uint64_t gi = a.gbase + i;
+    // before the first frontier every source of the unit counts as searching
+    if ((i & 63) == 0) {
+        const uint64_t n = gi < a.n_srcs ? a.n_srcs - gi : 0;
+        a.active[i >> 6] = n >= 64 ? ~0ull : (1ull << n) - 1;
+    }
     if (gi >= a.n_srcs) return;
     const uint32_t slot = (uint32_t)(i / a.W), j = (uint32_t)(i % a.W);
     const uint32_t s = a.srcs ? a.srcs[gi] : (uint32_t)gi;
@@ -959,9 +1078,10 @@ __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
                 if (nfa.src_rank_at != kNone) {
                     // the empty word: v itself, if it is a source of this unit and of this word block
                     const ulonglong2 e = a.rank[nfa.src_rank_at + (v >> 6)];
-                    if ((e.x >> (v & 63)) & 1) {
-                        const uint64_t j = (uint64_t)e.y + __popcll(e.x & ((1ull << (v & 63)) - 1)) - a.gbase -
-                                           (uint64_t)slot * W - (uint64_t)kp * KP * 64;
+                    const uint64_t order = (uint64_t)e.y + __popcll(e.x & ((1ull << (v & 63)) - 1));
+                    if (((e.x >> (v & 63)) & 1) && order >= a.gbase && order - a.gbase < (uint64_t)x.G * W) {
+                        const uint64_t bit = a.bit_of ? a.bit_of[order] : order - a.gbase;
+                        const uint64_t j = bit - (uint64_t)slot * W - (uint64_t)kp * KP * 64;
 #pragma unroll
                         for (int u = 0; u < KP; ++u)
                             if (j >> 6 == (uint64_t)u) word[u] |= 1ull << (j & 63);
@@ -1092,14 +1212,16 @@ __global__ __launch_bounds__(1024) void k_group_finish(Args a, const unsigned lo
     uint64_t csum = 0, hsum = 0;
     __syncthreads();
     for (uint64_t b0 = (uint64_t)blockIdx.x * 1024; b0 < n_group; b0 += (uint64_t)gridDim.x * 1024) {
-        const uint64_t i = b0 + t, gi = a.gbase + i;
-        const bool valid = i < n_group && gi < a.n_srcs;
-        const uint64_t c = valid ? acc[2 * i] : 0;
-        const uint64_t h = valid ? acc[2 * i + 1] : 0;
+        // in ascending order of the sources; j is the source's bit
+        const uint64_t i = b0 + t;
+        const bool valid = i < n_group && a.gbase + i < a.n_srcs;
+        const uint64_t j = valid && a.bit_of ? a.bit_of[a.gbase + i] : i;
+        const uint64_t c = valid ? acc[2 * j] : 0;
+        const uint64_t h = valid ? acc[2 * j + 1] : 0;
         csum += c;
         hsum += h;
         if (valid && per_source) {
-            const uint64_t at = a.pos ? a.pos[gi] : gi;
+            const uint64_t at = a.pos ? a.pos[a.gbase + j] : a.gbase + j;
             per_source[2 * at] = c;
             per_source[2 * at + 1] = h;
         }
@@ -1109,7 +1231,7 @@ __global__ __launch_bounds__(1024) void k_group_finish(Args a, const unsigned lo
             __syncthreads();
             uint64_t pre = s_carry;
             for (int w = 0; w < wv; ++w) pre += s_w[w];
-            if (valid) srcbase[i] = pre + incl - c;
+            if (valid) srcbase[j] = pre + incl - c;
             __syncthreads();
             if (t == 0) {
                 uint64_t tot = 0;
@@ -1162,14 +1284,15 @@ struct Plan {
 
 struct Layout {
     uint32_t K, W, G, Q, L, V, H, R, nchunks, chunk, sync_every;
+    bool order;         // sources are ordered within their group
     uint32_t seen_or;   // visit scheme of the expansion (1 = seen OR, 0 = two reads)
     uint64_t max_len;   // deepest level finalized: the length bound, or no bound (UINT64_MAX)
     uint64_t list_cap, desc_cap;
     // fixed by the plan and the number of sources
     uint64_t off_counters, off_tally, off_xtally, off_src_bits, zero_words, off_nfa, off_tile_n, off_srcs, off_pos,
-        off_rank, off_verts, off_class_n, off_class_tile_n;
+        off_srcs2, off_pos2, off_bit_of, off_hist, off_score, off_rank, off_verts, off_class_n, off_class_tile_n;
     // by the unit width and units in flight
-    uint64_t off_vis, off_next, off_vis2, off_touch, off_ids[2], off_rows[2], off_desc[2], off_acc, off_partial,
+    uint64_t off_vis, off_next, off_vis2, off_touch, off_full, off_active, off_ids[2], off_rows[2], off_desc[2], off_acc, off_partial,
         off_srcbase, total;
 };
 
@@ -1234,8 +1357,10 @@ constexpr uint32_t kDefaultChunk = 16;
 // Bitmaps of all vertices below this size are not worth the classes' launches: they are cleared in the
 // same 10 us.
 constexpr uint64_t kCompactBytes = 64ull << 20;
-// Sources up to one word of bits run in one unit either way.
+// Sources up to one word of bits run in one unit either way; up to eight words their order is not worth
+// its launches.
 constexpr uint64_t kCompactSources = 64;
+constexpr uint64_t kOrderSources = 512;
 
 uint32_t max_default_width(uint32_t V) { return V >= (1u << 22) ? 4096 : 2048; }
 
@@ -1431,6 +1556,14 @@ int make_layout(const rpq_graph* g, const Plan& p, uint64_t n_sources, uint64_t 
     x.off_tile_n = take((n_sources + kSrcTile - 1) / kSrcTile * 4);
     x.off_srcs = take(p.compact_src ? n_sources * 4 : 0);
     x.off_pos = take(p.compact_src ? n_sources * 4 : 0);
+    // the ordered copies, and what ordering a group takes
+    x.order = p.compact_src && n_sources > kOrderSources && !noalloc;
+    const uint64_t n_order = x.order ? n_sources : 0;
+    x.off_srcs2 = take(n_order * 4);
+    x.off_pos2 = take(n_order * 4);
+    x.off_bit_of = take(n_order * 4);
+    x.off_hist = take(x.order ? (kScores + rpq::scan_temp_elems(kScores)) * 8 : 0);
+    x.off_score = take(n_order * 8);
     x.off_rank = take(p.n_classes * p.n_words * 16);
     x.off_verts = take(p.verts * 4);
     x.off_class_n = take(p.n_classes * 4);
@@ -1442,6 +1575,8 @@ int make_layout(const rpq_graph* g, const Plan& p, uint64_t n_sources, uint64_t 
     x.off_next = take(G * bitmap_bytes);
     x.off_vis2 = units > G && !noalloc ? take(G * bitmap_bytes) : x.off_vis;
     x.off_touch = take((G * R + 63) / 64 * 8);
+    x.off_full = take((G * R + 63) / 64 * 8);
+    x.off_active = take(2 * G * x.K * 8);
     for (int i = 0; i < 2; ++i) {
         x.off_ids[i] = take(x.list_cap * 4);
         x.off_rows[i] = take(x.list_cap * x.K * 8);
@@ -1469,6 +1604,9 @@ Args make_args(const rpq_graph* g, const Plan& p, const Layout& x, char* ws) {
     a.vis = reinterpret_cast<uint64_t*>(ws + x.off_vis);
     a.next = reinterpret_cast<uint64_t*>(ws + x.off_next);
     a.touch = reinterpret_cast<uint64_t*>(ws + x.off_touch);
+    a.full = reinterpret_cast<uint64_t*>(ws + x.off_full);
+    a.active = reinterpret_cast<uint64_t*>(ws + x.off_active);
+    a.n_active = (uint64_t)x.G * x.K;
     a.ids0 = reinterpret_cast<uint32_t*>(ws + x.off_ids[0]);
     a.ids1 = reinterpret_cast<uint32_t*>(ws + x.off_ids[1]);
     a.rows0 = reinterpret_cast<uint64_t*>(ws + x.off_rows[0]);
@@ -2070,8 +2208,25 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
     place_rows(plan, x.W, plan.dn.base);
     RPQ_HIP(hipMemcpyAsync(ws + x.off_nfa, &plan.dn, sizeof plan.dn, hipMemcpyHostToDevice, stream));
     a.target = target;
-    a.srcs = plan.compact_src ? sa.out_srcs : sources;
-    a.pos = plan.compact_src ? sa.out_pos : nullptr;
+    const bool order = x.order && n_bits > kOrderSources;
+    OrderArgs oa;
+    std::memset(&oa, 0, sizeof oa);
+    oa.row_ptr = a.row_ptr;
+    oa.dst = a.dst;
+    oa.lmask = a.lmask;
+    oa.init_labels = plan.init_labels;
+    oa.L = x.L;
+    oa.in_srcs = sa.out_srcs;
+    oa.in_pos = sa.out_pos;
+    oa.srcs = reinterpret_cast<uint32_t*>(ws + x.off_srcs2);
+    oa.pos = reinterpret_cast<uint32_t*>(ws + x.off_pos2);
+    oa.bit_of = reinterpret_cast<uint32_t*>(ws + x.off_bit_of);
+    oa.hist = reinterpret_cast<uint64_t*>(ws + x.off_hist);
+    oa.score = reinterpret_cast<uint32_t*>(ws + x.off_score);
+    oa.rank = oa.score + n_sources;
+    a.srcs = order ? oa.srcs : plan.compact_src ? sa.out_srcs : sources;
+    a.pos = order ? oa.pos : plan.compact_src ? sa.out_pos : nullptr;
+    a.bit_of = order ? oa.bit_of : nullptr;
     a.n_srcs = n_bits;
     const uint64_t bitmap_words = (uint64_t)x.R * x.K;   // of one unit
     RPQ_TRY(rpq::fill_u64(a.touch, ((uint64_t)x.G * x.R + 63) / 64, 0, stream));
@@ -2113,6 +2268,17 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
         a.gbase = gbase;
         a.vis = vis_buf[buf];
         ea.G = G_eff;
+        if (order) {
+            oa.gbase = gbase;
+            oa.n = n_here;
+            const dim3 og((unsigned)((n_here + kBlock - 1) / kBlock));
+            RPQ_TRY(rpq::fill_u64(oa.hist, kScores, 0, stream));
+            hipLaunchKernelGGL(k_order_score, og, dim3(kBlock), 0, stream, oa);
+            RPQ_LAUNCH_CHECK();
+            RPQ_TRY(rpq::exclusive_scan_u64(oa.hist, oa.hist, kScores, oa.hist + kScores, nullptr, stream));
+            hipLaunchKernelGGL(k_order_place, og, dim3(kBlock), 0, stream, oa);
+            RPQ_LAUNCH_CHECK();
+        }
         // the bitmap's previous group must be extracted before it is cleared for this one
         if (side.stream && grp >= 2) RPQ_HIP(hipStreamWaitEvent(stream, side.extracted[buf], 0));
         if (x.seen_or && G_eff == x.G) {   // Vis and Next lie side by side
@@ -2123,6 +2289,7 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
             RPQ_TRY(rpq::fill_u64(a.vis, G_eff * bitmap_words, 0, stream));
             if (x.seen_or) RPQ_TRY(rpq::fill_u64(a.next, G_eff * bitmap_words, 0, stream));
         }
+        RPQ_TRY(rpq::fill_u64(a.full, (G_eff * (uint64_t)x.R + 63) / 64, 0, stream));
         hipLaunchKernelGGL(k_seed, dim3((unsigned)(((uint64_t)G_eff * x.W + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                            stream, a, G_eff, x.K);
         RPQ_LAUNCH_CHECK();
