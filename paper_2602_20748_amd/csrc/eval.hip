@@ -132,7 +132,7 @@ struct Args {
     uint64_t* vis;          // visited bits (with seen_or: also those found at the current level)
     uint64_t* next;         // two reads: bits found at this level; seen_or: Vis as of the last finalize
     uint64_t* touch;        // one bit per row: row has bits new at this level
-    uint64_t* full;         // one bit per row: no source still searching can add to it (seen_or)
+    uint8_t* full;          // per row: no source still searching can add to it
     uint64_t* active;       // [2][G][K] by list parity: sources with a bit in that frontier, or more
     uint64_t* rows0;
     uint64_t* rows1;
@@ -287,7 +287,7 @@ __device__ __forceinline__ void expand_segments(const Args& a, const LdsNfa& s, 
             uint32_t w = 0, q2 = 0;
             rpqd::decode_item(a.row_ptr, a.dst, a.L, s.delta, c_v, c_q, c_m, c_beg + (item - c_ex), &w, &q2);
             my_row = c_slot * a.R + target_row(a, s, q2, w);
-            live = !SEEN || !((a.full[my_row >> 6] >> (my_row & 63)) & 1);
+            live = !SEEN || !a.full[my_row];
         }
         // live items to the front, so that the word phase sees no others
         const uint64_t lm = __ballot(live);
@@ -392,6 +392,15 @@ __global__ __launch_bounds__(1024) void k_tally_sum(const unsigned long long* __
     }
 }
 
+// Entries a wave takes at a time: 64, fewer while that leaves waves without any.  A wave walks its entries'
+// items 64 at a time, each step a chain of dependent reads; one source of R-MAT 18 has levels of 80,000
+// entries, which at 64 are a quarter of the resident waves and 16 steps each.
+__device__ __forceinline__ uint32_t batch_of(uint64_t n, uint64_t n_waves) {
+    uint32_t b = 64;
+    while (b > 4 && n <= n_waves * (b / 2)) b /= 2;
+    return b;
+}
+
 template <int K, bool SEEN>
 __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
     __shared__ LdsNfa s_nfa;
@@ -407,13 +416,13 @@ __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
     const uint32_t H = a.H;
     uint64_t t_items = 0, t_segs = 0, t_wread = 0, t_wupd = 0;
     // light entries, straight from the frontier list
-    const uint64_t n_lb = (n_list + 63) / 64;
-    for (uint64_t b = wave; b < n_lb; b += n_waves) {
-        const uint64_t e = b * 64 + lane;
+    const uint32_t lb = batch_of(n_list, n_waves);
+    for (uint64_t b = wave; b * lb < n_list; b += n_waves) {
+        const uint64_t e = b * lb + lane;
         bool have = false;
         uint32_t slot = 0, q = 0, v = 0, len = 0;
         uint64_t m = 0;
-        if (e < n_list) {
+        if ((uint32_t)lane < lb && e < n_list) {
             row_entry(a, s_nfa, ids[e], &slot, &q, &v);
             m = a.lmask[v] & s_nfa.qlab[q];
             const uint64_t work = m ? rpqd::entry_work(a.row_ptr, a.L, s_nfa.delta, v, q, m) : 0;
@@ -425,13 +434,13 @@ __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
     }
     // heavy entries, as slices
     const Desc* desc = desc_of(a, p);
-    const uint64_t n_db = (n_desc + 63) / 64;
-    for (uint64_t b = wave; b < n_db; b += n_waves) {
-        const uint64_t di = b * 64 + lane;
+    const uint32_t db = batch_of(n_desc, n_waves);
+    for (uint64_t b = wave; b * db < n_desc; b += n_waves) {
+        const uint64_t di = b * db + lane;
         bool have = false;
         uint32_t ent = 0, slot = 0, q = 0, v = 0, len = 0;
         uint64_t m = 0, beg = 0;
-        if (di < n_desc) {
+        if ((uint32_t)lane < db && di < n_desc) {
             const Desc d = desc[di];
             ent = d.entry;
             beg = d.beg;
@@ -495,7 +504,7 @@ __global__ __launch_bounds__(kBlock) void k_compact(Args a, int p, uint64_t n_ro
 
 // ------------------------------------------------------------------------------------------------
 // finalize.  (Seen OR) a row is full when it holds every source of its unit that had a bit in the previous
-// frontier: a source without one has ended its search, so nothing can be added to the row any more.  The
+// frontier: a source without one has ended its search, so nothing can be added to the row any more.  That
 // set only shrinks from level to level and a row only grows, so a full row stays full.  Per batch of 64 new
 // frontier rows:
 //   word phase  groups of K lanes take a row each (lane k, word k): Next moves into the compact
@@ -506,7 +515,9 @@ __global__ __launch_bounds__(kBlock) void k_compact(Args a, int p, uint64_t n_ro
 //               written by the whole wave.  With count_work == 0 (the last depth of a
 //               length-bounded search) the rows are recorded but not prepared for expansion.
 // ------------------------------------------------------------------------------------------------
-template <int K>
+constexpr uint64_t kTrackWords = 1ull << 20;
+
+template <int K, bool SEEN>
 __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_work) {
     constexpr int GS = 64 / K;
     __shared__ LdsNfa s_nfa;
@@ -525,38 +536,56 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
     const uint64_t gmask = (K == 64) ? ~0ull : (((1ull << (K & 63)) - 1) << (grp * K));
     const uint64_t* was_active = a.active + p * a.n_active;
     unsigned long long* now_active = reinterpret_cast<unsigned long long*>(a.active + np * a.n_active);
-    // this lane's word of its unit's sources with a bit in the new frontier
-    uint64_t seen_k = 0;
-    uint32_t seen_slot = kNone;
-    auto put_active = [&]() {
-        if (seen_slot == kNone || !seen_k) return;
-        unsigned long long* w = &now_active[(uint64_t)seen_slot * K + k];
-        if (seen_k & ~*w) atomicOr(w, (unsigned long long)seen_k);   // a stale copy only costs an OR
+    // sources with a bit in the new frontier: word k of slot acc_slot, collected while the wave's rows
+    // share a slot.  A stale copy of the word only costs an OR that is not needed.  A short list keeps the
+    // previous frontier's sources, which hold its own: every wave's OR of a few words would be most of its
+    // time (one source of R-MAT 18: 14 us a launch).
+    const bool track = SEEN && n * K >= kTrackWords;
+    if (SEEN && !track && blockIdx.x == 0)
+        for (uint64_t i = threadIdx.x; i < a.n_active; i += kBlock) now_active[i] = was_active[i];
+    uint64_t acc_k = 0;
+    uint32_t acc_slot = kNone;
+    auto put_active = [&](uint32_t sl, uint64_t x) {
+        unsigned long long* w = &now_active[(uint64_t)sl * K + k];
+        if (x & ~*w) atomicOr(w, (unsigned long long)x);
+    };
+    auto flush_active = [&]() {
+        if (acc_slot == kNone) return;
+#pragma unroll
+        for (int o = K; o < 64; o <<= 1) acc_k |= __shfl_xor(acc_k, o, 64);
+        if (lane < K) put_active(acc_slot, acc_k);
+        acc_k = 0;
     };
     const uint64_t n_waves = (uint64_t)gridDim.x * kWaves;
     const uint64_t wave = (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
-    for (uint64_t e0 = wave * 64; e0 < n; e0 += n_waves * 64) {
+    const uint32_t fb = batch_of(n, n_waves);
+    for (uint64_t e0 = wave * fb; e0 < n; e0 += n_waves * fb) {
         const uint64_t e = e0 + lane;
-        const bool active = e < n;
+        const bool active = (uint32_t)lane < fb && e < n;
         const uint32_t my_row = active ? ids[e] : 0;
         uint32_t slot = 0, q = 0, v = 0;
         if (active) row_entry(a, s_nfa, my_row, &slot, &q, &v);
-        const uint32_t n_here = (uint32_t)min<uint64_t>(64, n - e0);
+        const uint32_t n_here = (uint32_t)min<uint64_t>(fb, n - e0);
         t_rows += n_here * (lane == 0);
+        const uint32_t slot0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot);
+        const bool one_slot = __ballot(active && slot != slot0) == 0;
+        if (SEEN && track && (!one_slot || slot0 != acc_slot)) {
+            flush_active();
+            acc_slot = one_slot ? slot0 : kNone;
+        }
         uint32_t my_pc = 0;
         // word phase
         for (uint32_t j = 0; j < n_here; j += GS * kUnroll) {
             uint32_t r[kUnroll], sl[kUnroll];
             uint64_t nk[kUnroll], ov[kUnroll];
-            bool full[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const uint32_t idx = j + u * GS + grp;
                 r[u] = __shfl(my_row, idx & 63, 64);
-                sl[u] = __shfl(slot, idx & 63, 64);
+                sl[u] = one_slot ? slot0 : __shfl(slot, idx & 63, 64);
                 nk[u] = ov[u] = 0;
                 if (idx < n_here) {
-                    if (a.seen_or) {
+                    if constexpr (SEEN) {
                         ov[u] = a.next[(uint64_t)r[u] * K + k];
                         nk[u] = a.vis[(uint64_t)r[u] * K + k];
                     } else {
@@ -564,25 +593,17 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
                     }
                 }
             }
-            if (a.seen_or) {
+            if constexpr (SEEN) {
 #pragma unroll
                 for (int u = 0; u < kUnroll; ++u) {
                     const uint32_t idx = j + u * GS + grp;
-                    full[u] = idx < n_here && (was_active[(uint64_t)sl[u] * K + k] & ~nk[u]) == 0;
+                    const bool ok = idx < n_here && (was_active[(uint64_t)sl[u] * K + k] & ~nk[u]) == 0;
                     nk[u] &= ~ov[u];
-                    if (idx < n_here) {
-                        if (sl[u] != seen_slot) {
-                            put_active();
-                            seen_slot = sl[u];
-                            seen_k = 0;
-                        }
-                        seen_k |= nk[u];
-                    }
+                    if (one_slot) acc_k |= nk[u];
+                    else if (track && idx < n_here && nk[u]) put_active(sl[u], nk[u]);
+                    // the row is on the list once: nothing else writes its byte
+                    if ((__ballot(ok) & gmask) == gmask && k == 0) a.full[r[u]] = 1;
                 }
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u)
-                    if ((__ballot(full[u]) & gmask) == gmask && k == 0)
-                        or_relaxed(&a.full[r[u] >> 6], 1ull << (r[u] & 63));
             }
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
@@ -592,11 +613,11 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
                     rows[(e0 + idx) * K + k] = nk[u];
                     if (nk[u]) {
                         // seen OR: the snapshot catches up with Vis.  Two reads: Next is cleared.
-                        a.next[(uint64_t)r[u] * K + k] = a.seen_or ? (ov[u] | nk[u]) : 0;
+                        a.next[(uint64_t)r[u] * K + k] = SEEN ? (ov[u] | nk[u]) : 0;
                         // a row is on the list once, and nothing else writes its Vis word in this
                         // kernel: a plain read-modify-write (an atomic OR cost 0.82 vs 0.69 ms a
                         // launch).  With seen OR the expansion has already set these bits.
-                        if (!a.seen_or) a.vis[(uint64_t)r[u] * K + k] |= nk[u];
+                        if (!SEEN) a.vis[(uint64_t)r[u] * K + k] |= nk[u];
                         ++t_words;
                         pc = (uint32_t)__popcll(nk[u]);
                     }
@@ -654,7 +675,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
             }
         }
     }
-    put_active();
+    flush_active();
     const uint64_t t_e[1] = {eprod}, t_f[2] = {t_rows, t_words};
     add_tallies<1>(a, T_EPROD, t_e);
     add_tallies<2>(a, T_FROWS, t_f);
@@ -1017,7 +1038,8 @@ __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
         const uint32_t iend = min(n_ans, ibeg + x.chunk);
         const uint64_t* vis = a.vis + (uint64_t)slot * a.R * K + (uint64_t)kp * KP;
         uint32_t src[KP];
-        uint64_t cnt[KP], h[KP], cursor[KP];
+        uint32_t cnt[KP];   // at most the chunk's vertices
+        uint64_t h[KP], cursor[KP];
         MixSource ms[KP];
         bool in_window = MODE != X_KEYS;
 #pragma unroll
@@ -1027,7 +1049,8 @@ __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
             const bool valid = gi < a.n_srcs;
             src[u] = valid ? (a.srcs ? a.srcs[gi] : (uint32_t)gi) : 0;
             ms[u] = mix_source(src[u]);
-            cnt[u] = h[u] = cursor[u] = 0;
+            cnt[u] = 0;
+            h[u] = cursor[u] = 0;
             if (MODE == X_KEYS && valid) {
                 // this source's keys in this chunk are [cursor, end): partial holds the source's chunk
                 // prefixes, acc its total
@@ -1119,29 +1142,33 @@ __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
                                 const uint64_t hs = rpqd::wave_sum_u64(hv);
                                 const uint64_t m = __ballot(bit);
                                 if (lane == c) {
-                                    cnt[u] += (uint64_t)__popcll(m);
+                                    cnt[u] += (uint32_t)__popcll(m);
                                     h[u] += hs;
                                 }
                             }
                         }
                     }
                 } else {
+                    uint32_t row_bits = 0;   // wave-uniform
                     while (any) {
                         const int j = __ffsll((long long)any) - 1;
                         any &= any - 1;
                         const uint64_t wj = readlane_u64(word[u], j);
                         const uint32_t vj = (uint32_t)__builtin_amdgcn_readlane((int)v, j);
-                        if ((wj >> lane) & 1) {
+                        // the word itself is the mask of the lanes whose source reaches the vertex
+                        if constexpr (MODE == X_TOTALS) row_bits += (uint32_t)__popcll(wj);
+                        if (__builtin_amdgcn_inverse_ballot_w64(wj)) {
                             if constexpr (MODE == X_KEYS) {
                                 if (cursor[u] >= x.off && cursor[u] - x.off < x.cap)
                                     x.pairs[cursor[u] - x.off] = ((uint64_t)src[u] << 32) | vj;
                                 ++cursor[u];
                             } else {
-                                ++cnt[u];
+                                if constexpr (MODE == X_TALLIES) ++cnt[u];
                                 h[u] += mix_pair(ms[u], vj);
                             }
                         }
                     }
+                    if constexpr (MODE == X_TOTALS) tot_c += lane == 0 ? row_bits : 0;
                 }
             }
         }
@@ -1157,7 +1184,7 @@ __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
             for (int u = 0; u < KP; ++u) {
                 const uint64_t si = (uint64_t)slot * W + (uint64_t)(kp * KP + u) * 64 + lane;
                 if (a.gbase + si >= a.n_srcs) continue;
-                if (x.partial) x.partial[si * x.nchunks + chunk] = (uint32_t)cnt[u];
+                if (x.partial) x.partial[si * x.nchunks + chunk] = cnt[u];
                 if (cnt[u]) {
                     atomicAdd(&x.acc[2 * si], (unsigned long long)cnt[u]);
                     atomicAdd(&x.acc[2 * si + 1], (unsigned long long)h[u]);
@@ -1575,7 +1602,7 @@ int make_layout(const rpq_graph* g, const Plan& p, uint64_t n_sources, uint64_t 
     x.off_next = take(G * bitmap_bytes);
     x.off_vis2 = units > G && !noalloc ? take(G * bitmap_bytes) : x.off_vis;
     x.off_touch = take((G * R + 63) / 64 * 8);
-    x.off_full = take((G * R + 63) / 64 * 8);
+    x.off_full = take((G * R + 7) / 8 * 8);
     x.off_active = take(2 * G * x.K * 8);
     for (int i = 0; i < 2; ++i) {
         x.off_ids[i] = take(x.list_cap * 4);
@@ -1604,7 +1631,7 @@ Args make_args(const rpq_graph* g, const Plan& p, const Layout& x, char* ws) {
     a.vis = reinterpret_cast<uint64_t*>(ws + x.off_vis);
     a.next = reinterpret_cast<uint64_t*>(ws + x.off_next);
     a.touch = reinterpret_cast<uint64_t*>(ws + x.off_touch);
-    a.full = reinterpret_cast<uint64_t*>(ws + x.off_full);
+    a.full = reinterpret_cast<uint8_t*>(ws + x.off_full);
     a.active = reinterpret_cast<uint64_t*>(ws + x.off_active);
     a.n_active = (uint64_t)x.G * x.K;
     a.ids0 = reinterpret_cast<uint32_t*>(ws + x.off_ids[0]);
@@ -1642,12 +1669,13 @@ unsigned resident_grid(const void* kernel) {
 
 template <int K>
 struct LevelGrids {
-    unsigned expand, expand_seen, compact, finalize;
+    unsigned expand, expand_seen, compact, finalize, finalize_seen;
     static const LevelGrids& get() {
         static const LevelGrids g{resident_grid(reinterpret_cast<const void*>(&k_expand<K, false>)),
                                   resident_grid(reinterpret_cast<const void*>(&k_expand<K, true>)),
                                   resident_grid(reinterpret_cast<const void*>(&k_compact)),
-                                  resident_grid(reinterpret_cast<const void*>(&k_finalize<K>))};
+                                  resident_grid(reinterpret_cast<const void*>(&k_finalize<K, false>)),
+                                  resident_grid(reinterpret_cast<const void*>(&k_finalize<K, true>))};
         return g;
     }
 };
@@ -1739,7 +1767,12 @@ int launch_level(const Args& a, int p, uint64_t n_rows, uint32_t level, int coun
     if (e1) RPQ_HIP(hipEventRecord(e1, s));
     hipLaunchKernelGGL(k_compact, dim3(LevelGrids<K>::get().compact), dim3(kBlock), 0, s, a, p, n_rows, level);
     RPQ_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_finalize<K>, dim3(LevelGrids<K>::get().finalize), dim3(kBlock), 0, s, a, p, count_work);
+    if (a.seen_or)
+        hipLaunchKernelGGL((k_finalize<K, true>), dim3(LevelGrids<K>::get().finalize_seen), dim3(kBlock), 0, s, a, p,
+                           count_work);
+    else
+        hipLaunchKernelGGL((k_finalize<K, false>), dim3(LevelGrids<K>::get().finalize), dim3(kBlock), 0, s, a, p,
+                           count_work);
     RPQ_LAUNCH_CHECK();
     if (e2) RPQ_HIP(hipEventRecord(e2, s));
     if (on && e0 && e1 && e2) {
@@ -1760,7 +1793,12 @@ template <int K>
 int launch_finalize(const Args& a, int p, uint64_t n_rows, uint32_t level, int count_work, hipStream_t s) {
     hipLaunchKernelGGL(k_compact, dim3(LevelGrids<K>::get().compact), dim3(kBlock), 0, s, a, p, n_rows, level);
     RPQ_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_finalize<K>, dim3(LevelGrids<K>::get().finalize), dim3(kBlock), 0, s, a, p, count_work);
+    if (a.seen_or)
+        hipLaunchKernelGGL((k_finalize<K, true>), dim3(LevelGrids<K>::get().finalize_seen), dim3(kBlock), 0, s, a, p,
+                           count_work);
+    else
+        hipLaunchKernelGGL((k_finalize<K, false>), dim3(LevelGrids<K>::get().finalize), dim3(kBlock), 0, s, a, p,
+                           count_work);
     RPQ_LAUNCH_CHECK();
     return RPQ_OK;
 }
@@ -2289,7 +2327,7 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
             RPQ_TRY(rpq::fill_u64(a.vis, G_eff * bitmap_words, 0, stream));
             if (x.seen_or) RPQ_TRY(rpq::fill_u64(a.next, G_eff * bitmap_words, 0, stream));
         }
-        RPQ_TRY(rpq::fill_u64(a.full, (G_eff * (uint64_t)x.R + 63) / 64, 0, stream));
+        RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.full), (G_eff * (uint64_t)x.R + 7) / 8, 0, stream));
         hipLaunchKernelGGL(k_seed, dim3((unsigned)(((uint64_t)G_eff * x.W + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                            stream, a, G_eff, x.K);
         RPQ_LAUNCH_CHECK();
