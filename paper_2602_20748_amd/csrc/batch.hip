@@ -59,7 +59,9 @@ struct BNfa {
 };
 
 struct BQuery {
-    const uint32_t* sources;   // device, ascending; null = implicit ids [0, n)
+    const uint32_t* sources;   // device, indexed by a unit's src_off; null = implicit ids [0, n).  Closed
+                               // form: the sources with a bit, of all queries (k_batch_sources)
+    const uint32_t* pos;       // their positions in the caller's list, or null: the same
     uint64_t n_sources;
     uint64_t* per_source;      // device [n][2] or null
     uint64_t* pairs;           // device output or null
@@ -80,6 +82,17 @@ struct BQueryOut {
 struct BUnit {
     uint32_t query, n;
     uint64_t src_off;
+};
+
+// Closed form: kSegment consecutive sources of one query.  k_batch_sources lists the ones with a bit and
+// cuts them into units, at most the n_units planned for the segment.
+struct BSeg {
+    const uint32_t* given;     // the caller's list, or null
+    uint64_t off;              // position of the first one in it
+    uint64_t out;              // where the segment's list starts
+    uint32_t query, n, first_unit, n_units;
+    uint32_t compact;          // sources that can leave nowhere get no bit
+    uint32_t keys;             // keys are wanted: the list stays in ascending order
 };
 
 struct BSlot {
@@ -109,11 +122,12 @@ struct BArgs {
     const BNfa* nfas;
     const BQuery* queries;
     BQueryOut* qout;
-    const BUnit* units;
+    BUnit* units;
+    const uint32_t* order;   // closed form: the units that hold sources, in queue order; null: all of them
     BSlot* slots;
     BCtl* ctl;
     uint64_t* vis;
-    uint64_t* next;
+    uint64_t* next;          // two reads: bits found at this level; seen_or: Vis as of the last finalize
     uint64_t* touch;
     uint64_t* ever;          // [G][slot_stride bits]: row touched at some level of the slot's unit
     uint64_t* ans;
@@ -133,6 +147,7 @@ struct BArgs {
     uint64_t* unit_total;    // [n_units] keys per unit
     uint64_t* unit_start;    // [n_units] staging index (query-relative) of each unit's keys
     uint32_t V, L, Qmax, H, G, W, nchunks, n_units, n_queries, n_blocks;
+    uint32_t W_cut;          // closed form: sources a unit holds at most (W: the bits of its rows)
     uint64_t slot_stride, summ_words, list_cap, desc_cap, timeout, deadline;
     uint64_t log_cap;        // first-visit log entries per slot
     // open form (a resident engine fed between launches): the unit queue is a ring of unit_mask + 1
@@ -179,6 +194,11 @@ __device__ __forceinline__ uint64_t gwave(const BArgs& a) {
     return (uint64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
 }
 __device__ __forceinline__ uint64_t gwaves(const BArgs& a) { return (uint64_t)a.n_blocks * kWaves; }
+
+// Slots that ever take a unit: in the closed form no more than there are units, and only these were cleared.
+__device__ __forceinline__ uint32_t slots_used(const BArgs& a) {
+    return a.order ? (uint32_t)min((unsigned long long)a.G, ld(&a.ctl->units_tail)) : a.G;
+}
 
 // ------------------------------------------------------------------------------------------------
 // expand: the level expansion of the plain form with per-slot automata.  Segments (entry, first
@@ -258,10 +278,7 @@ __device__ __forceinline__ void expand_segments(const BArgs& a, const uint64_t* 
 #pragma unroll
                 for (int u = 0; u < kUnroll; ++u) {
                     nb[u] = f[u] & ~sw[u];
-                    if (nb[u]) {
-                        or_relaxed(a.vis + (uint64_t)r[u] * K + k, nb[u]);
-                        or_relaxed(a.next + (uint64_t)r[u] * K + k, nb[u]);
-                    }
+                    if (nb[u]) or_relaxed(a.vis + (uint64_t)r[u] * K + k, nb[u]);
                 }
             } else {
                 // visited and Next words together (as in the plain form)
@@ -288,6 +305,13 @@ __device__ __forceinline__ void expand_segments(const BArgs& a, const uint64_t* 
     }
 }
 
+// Entries a wave takes at a time (as in the plain form): fewer than 64 while that leaves waves without any.
+__device__ __forceinline__ uint32_t batch_of(uint64_t n, uint64_t n_waves) {
+    uint32_t b = 64;
+    while (b > 4 && n <= n_waves * (b / 2)) b /= 2;
+    return b;
+}
+
 template <int K, bool SEEN>
 __device__ void phase_expand(const BArgs& a, int p, uint64_t& t_items, uint64_t& t_descs, uint64_t& t_wread,
                              uint64_t& t_wupd) {
@@ -299,14 +323,14 @@ __device__ void phase_expand(const BArgs& a, int p, uint64_t& t_items, uint64_t&
     const uint64_t* rows = p ? a.rows1 : a.rows0;
     const Desc* desc = p ? a.desc1 : a.desc0;
     const uint32_t H = a.H;
-    const uint64_t n_lb = (n_list + 63) / 64;
-    for (uint64_t b = gwave(a); b < n_lb; b += gwaves(a)) {
-        const uint64_t e = b * 64 + lane;
+    const uint32_t lb = batch_of(n_list, gwaves(a));
+    for (uint64_t b = gwave(a); b * lb < n_list; b += gwaves(a)) {
+        const uint64_t e = b * lb + lane;
         bool have = false;
         uint32_t slot = 0, q = 0, v = 0, len = 0;
         uint64_t m = 0;
         const BNfa* nfa = a.nfas;
-        if (e < n_list) {
+        if ((uint32_t)lane < lb && e < n_list) {
             entry_of(a, xld(ids + e), &slot, &q, &v, &nfa);
             m = a.lmask[v] & nfa->qlab[q];
             const uint64_t work = m ? rpqd::entry_work(a.row_ptr, a.L, nfa->delta, v, q, m) : 0;
@@ -317,14 +341,14 @@ __device__ void phase_expand(const BArgs& a, int p, uint64_t& t_items, uint64_t&
         if (lane == 0) t_descs += __popcll(hb);
         expand_segments<K, SEEN>(a, rows, have, (uint32_t)e, slot, q, v, m, nfa->delta, 0, len, t_items, t_wread, t_wupd);
     }
-    const uint64_t n_db = (n_desc + 63) / 64;
-    for (uint64_t b = gwave(a); b < n_db; b += gwaves(a)) {
-        const uint64_t di = b * 64 + lane;
+    const uint32_t db = batch_of(n_desc, gwaves(a));
+    for (uint64_t b = gwave(a); b * db < n_desc; b += gwaves(a)) {
+        const uint64_t di = b * db + lane;
         bool have = false;
         uint32_t ent = 0, slot = 0, q = 0, v = 0, len = 0;
         uint64_t m = 0, beg = 0;
         const BNfa* nfa = a.nfas;
-        if (di < n_desc) {
+        if ((uint32_t)lane < db && di < n_desc) {
             const uint32_t* dw = reinterpret_cast<const uint32_t*>(desc + di);
             ent = xld(dw + 0);
             len = xld(dw + 1);
@@ -349,7 +373,7 @@ __device__ void phase_compact(const BArgs& a, int p, uint32_t iter) {
         st64(&a.ctl->desc_cnt[p], 0);
     }
     const int lane = threadIdx.x & 63;
-    const uint64_t n_words = (uint64_t)a.G * a.slot_stride / 64;
+    const uint64_t n_words = (uint64_t)slots_used(a) * a.slot_stride / 64;
     const uint64_t words_per_slot = a.slot_stride / 64;
     uint32_t* ids = np ? a.ids1 : a.ids0;
     for (uint64_t w0 = gwave(a) * 64; w0 < n_words; w0 += gwaves(a) * 64) {
@@ -481,6 +505,7 @@ __device__ void phase_retire_extract(const BArgs& a, const uint32_t* list, uint3
         const uint64_t sw_i = (uint64_t)slot * a.summ_words + vbeg / 64 + lane;
         const uint64_t sw = (vbeg / 64 + lane < a.summ_words) ? xld(a.summ + sw_i) : 0;
         uint64_t cnt = 0, h = 0, cursor = 0;
+        const rpqd::MixSource ms = rpqd::mix_source((uint32_t)s);
         const uint64_t pidx = ((uint64_t)slot * a.W + j) * a.nchunks + chunk;
         if (WRITE && valid) cursor = a.srcbase[(uint64_t)slot * a.W + j] + a.partial[pidx];
         // per 64-vertex group with a non-empty summary word: one load per lane (lane = vertex),
@@ -497,16 +522,16 @@ __device__ void phase_retire_extract(const BArgs& a, const uint32_t* list, uint3
             while (nz) {
                 const int jj = __ffsll((long long)nz) - 1;
                 nz &= nz - 1;
-                const uint64_t word = __shfl(mine, jj, 64);
+                const uint64_t word = rpqd::readlane_u64(mine, jj);
                 const uint32_t v = vg + (uint32_t)jj;
-                if (valid && ((word >> lane) & 1)) {
-                    const uint64_t key = (s << 32) | v;
+                // bits are sources of the unit only, so the word is the mask of the lanes that take it
+                if (__builtin_amdgcn_inverse_ballot_w64(word)) {
                     if (WRITE) {
-                        if (cursor < Qy.capacity) Qy.stage[cursor] = key;
+                        if (cursor < Qy.capacity) Qy.stage[cursor] = (s << 32) | v;
                         ++cursor;
                     } else {
                         ++cnt;
-                        h += rpqd::mix64(key);
+                        h += rpqd::mix_pair(ms, v);
                     }
                 }
             }
@@ -514,8 +539,9 @@ __device__ void phase_retire_extract(const BArgs& a, const uint32_t* list, uint3
         if (!WRITE) {
             if (Qy.pairs && valid) a.partial[pidx] = (uint32_t)cnt;
             if (Qy.per_source && valid && cnt) {
-                atomicAdd((unsigned long long*)&Qy.per_source[2 * sidx], (unsigned long long)cnt);
-                atomicAdd((unsigned long long*)&Qy.per_source[2 * sidx + 1], (unsigned long long)h);
+                const uint64_t at = Qy.pos ? (uint64_t)Qy.pos[sidx] : sidx;
+                atomicAdd((unsigned long long*)&Qy.per_source[2 * at], (unsigned long long)cnt);
+                atomicAdd((unsigned long long*)&Qy.per_source[2 * at + 1], (unsigned long long)h);
             }
             const uint64_t wc = rpqd::wave_sum_u64(cnt), wh = rpqd::wave_sum_u64(h);
             if (lane == 0 && wc) {
@@ -595,16 +621,23 @@ __device__ void phase_retire_clear(const BArgs& a, const uint32_t* list, uint32_
         if (n > a.log_cap) {
             // the log overflowed: clear every row of the slot
             uint64_t* vs = a.vis + (uint64_t)slot * a.slot_stride * K;
+            uint64_t* os = a.next + (uint64_t)slot * a.slot_stride * K;
             const uint64_t words = a.slot_stride * K;
-            for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < words; i += (uint64_t)a.n_blocks * kBlock)
+            for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < words; i += (uint64_t)a.n_blocks * kBlock) {
                 vs[i] = 0;
+                if (a.seen_or) os[i] = 0;
+            }
             continue;
         }
         const uint32_t* log = a.logs + (uint64_t)slot * a.log_cap;
         for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (uint64_t)a.n_blocks * kBlock) {
-            uint64_t* vs = a.vis + ((uint64_t)slot * a.slot_stride + xld(log + i)) * K;
+            const uint64_t at = ((uint64_t)slot * a.slot_stride + xld(log + i)) * K;
 #pragma unroll
-            for (int k = 0; k < K; ++k) vs[k] = 0;
+            for (int k = 0; k < K; ++k) a.vis[at + k] = 0;
+            if (a.seen_or) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) a.next[at + k] = 0;
+            }
         }
     }
     // Ans rows flagged in the summary, then the summary itself
@@ -638,12 +671,13 @@ __device__ void phase_assign(const BArgs& a, uint32_t iter) {
         s_idle = 0;
         s_started = 0;
         const unsigned long long head = ld(&a.ctl->queue_head);
-        const unsigned long long tail = a.open_form ? ld(&a.ctl->units_tail) : (unsigned long long)a.n_units;
+        const unsigned long long tail = ld(&a.ctl->units_tail);
         s_head = head;
         s_avail = tail > head ? tail - head : 0;
     }
     __syncthreads();
     const unsigned long long head = s_head, avail = s_avail;
+    const uint32_t n_slots = slots_used(a);
     for (uint32_t s = threadIdx.x; s < a.G; s += kBlock) {
         uint32_t st = ld32(&a.slots[s].state);
         const bool drained = st == S_DRAIN && ld32(&a.slots[s].end_iter) != iter;
@@ -659,12 +693,12 @@ __device__ void phase_assign(const BArgs& a, uint32_t iter) {
             st32(&a.slots[s].state, S_IDLE);
             st = S_IDLE;
         }
-        if (st == S_IDLE) {
+        if (st == S_IDLE && s < n_slots) {
             // idle slots take the next units in queue order; the head moves by exactly the units
             // taken, so a unit published later is never skipped
             const uint32_t rank = atomicAdd(&s_idle, 1u);
             if (rank < avail) {
-                const unsigned long long u = head + rank;
+                const unsigned long long u = a.order ? a.order[head + rank] : head + rank;
                 st32(&a.slots[s].unit, (uint32_t)u);
                 st32(&a.slots[s].query, a.units[u & a.unit_mask].query);
                 st32(&a.slots[s].alive, iter);
@@ -720,8 +754,7 @@ __device__ void phase_seed(const BArgs& a, int p, uint32_t iter) {
                 const uint32_t q = __ffs(init) - 1;
                 init &= init - 1;
                 row = (uint64_t)slot * a.slot_stride + (uint64_t)q * a.V + s;
-                or_relaxed(&a.next[row * K + (j >> 6)], 1ull << (j & 63));
-                if (a.seen_or) or_relaxed(&a.vis[row * K + (j >> 6)], 1ull << (j & 63));
+                or_relaxed(&(a.seen_or ? a.vis : a.next)[row * K + (j >> 6)], 1ull << (j & 63));
                 or_relaxed(&a.ever[row >> 6], 1ull << (row & 63));
             }
             const uint64_t m = __ballot(take);
@@ -753,7 +786,7 @@ __device__ void phase_seed(const BArgs& a, int p, uint32_t iter) {
 // logged earlier, by the compaction (and the seeding) that put the rows on the list.
 // Word phase: groups of K lanes per row; row phase: lane per row (as in the plain form).
 // ------------------------------------------------------------------------------------------------
-template <int K>
+template <int K, bool SEEN>
 __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t_frows, uint64_t& t_fwords) {
     constexpr int GS = 64 / K;
     const int np = p ^ 1;
@@ -767,9 +800,10 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
     unsigned long long* dcnt = &a.ctl->desc_cnt[np];
     const uint32_t H = a.H, L = a.L, V = a.V;
     const uint32_t stride = (uint32_t)a.slot_stride;
-    for (uint64_t e0 = gwave(a) * 64; e0 < n; e0 += gwaves(a) * 64) {
+    const uint32_t fb = batch_of(n, gwaves(a));
+    for (uint64_t e0 = gwave(a) * fb; e0 < n; e0 += gwaves(a) * fb) {
         const uint64_t e = e0 + lane;
-        const bool active = e < n;
+        const bool active = (uint32_t)lane < fb && e < n;
         uint32_t row32 = 0, slot = 0, lrow = 0, q = 0, v = 0, qid = 0;
         uint64_t eprod = 0, work = 0;
         const BNfa* nfa = a.nfas;
@@ -788,7 +822,7 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
             if ((nfa->final >> q) & 1) my_ans = slot * V + v;
             stop = iter - ld32(&a.slots[slot].start_iter) >= a.queries[qid].max_len;
         }
-        const uint32_t n_here = (uint32_t)min<uint64_t>(64, n - e0);
+        const uint32_t n_here = (uint32_t)min<uint64_t>(fb, n - e0);
         // the entry's work (its item count) and slices come first: a wave that finds no room for
         // its slices changes nothing and leaves its rows for the next iteration
         if (active) {
@@ -825,15 +859,18 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
         uint32_t my_pc = 0;   // new source bits of this lane's row
         for (uint32_t j = 0; j < n_here; j += GS * kUnroll) {
             uint32_t r[kUnroll], an[kUnroll], sp[kUnroll];
-            uint64_t nk[kUnroll];
+            uint64_t nk[kUnroll], ov[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const uint32_t idx = j + u * GS + grp;
                 r[u] = __shfl(row32, idx & 63, 64);
                 an[u] = __shfl(my_ans, idx & 63, 64);
                 sp[u] = __shfl((uint32_t)stop, idx & 63, 64);
-                nk[u] = idx < n_here ? xld(a.next + (uint64_t)r[u] * K + k) : 0;
+                ov[u] = idx < n_here ? xld(a.next + (uint64_t)r[u] * K + k) : 0;
+                if (SEEN) nk[u] = idx < n_here ? xld(a.vis + (uint64_t)r[u] * K + k) : 0;
             }
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) nk[u] = SEEN ? nk[u] & ~ov[u] : ov[u];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const uint32_t idx = j + u * GS + grp;
@@ -841,10 +878,9 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
                 if (idx < n_here) {
                     rows[(e0 + idx) * K + k] = sp[u] ? 0 : nk[u];
                     if (nk[u]) {
-                        a.next[(uint64_t)r[u] * K + k] = 0;
-                        // the row is on the list once and nothing else writes its Vis word in this
-                        // phase (with seen OR the expansion has set these bits)
-                        if (!a.seen_or) a.vis[(uint64_t)r[u] * K + k] |= nk[u];
+                        // the row is on the list once and nothing else writes its words in this phase
+                        a.next[(uint64_t)r[u] * K + k] = SEEN ? ov[u] | nk[u] : 0;
+                        if (!SEEN) a.vis[(uint64_t)r[u] * K + k] |= nk[u];
                         pc = (uint32_t)__popcll(nk[u]);
                         ++t_fwords;
                         if (an[u] != 0xFFFFFFFFu) or_relaxed(a.ans + (uint64_t)an[u] * K + k, nk[u]);
@@ -971,7 +1007,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_batch(BArgs a) {
             phase_seed<K>(a, p, iter);
             BAR(6);
         }
-        phase_finalize<K>(a, p, iter, t_frows, t_fwords);
+        phase_finalize<K, SEEN>(a, p, iter, t_frows, t_fwords);
         BAR(7);
         p ^= 1;
         if (blockIdx.x == 0 && threadIdx.x == 0) st64(&a.ctl->iterations, iter);
@@ -999,6 +1035,176 @@ __global__ __launch_bounds__(kBlock, 4) void k_batch(BArgs a) {
     }
 }
 #undef BAR
+
+// ------------------------------------------------------------------------------------------------
+// closed form, before the persistent kernel: the sources that get a bit
+// ------------------------------------------------------------------------------------------------
+constexpr uint32_t kSegment = 4096;    // a multiple of every unit width
+constexpr uint32_t kScores = 1024;     // 5 bits of degree, 5 of the neighbour
+constexpr uint32_t kScoreEdges = 16;
+
+// One block per segment.  As in the plain form, sources without an edge that an initial state can follow
+// get no bit (their zero-length walk is counted here), and the others are ordered by their largest
+// neighbour, so that sources that arrive together share a word.
+__global__ __launch_bounds__(kBlock) void k_batch_sources(BArgs a, const BSeg* __restrict__ segs, uint32_t* out_srcs,
+                                                          uint32_t* out_pos) {
+    __shared__ uint32_t s_src[kSegment];
+    __shared__ uint16_t s_at[kSegment], s_score[kSegment];
+    __shared__ uint32_t s_hist[kScores];
+    __shared__ uint32_t s_w[kWaves];
+    const BSeg g = segs[blockIdx.x];
+    const BQuery& Qy = a.queries[g.query];
+    const BNfa& nfa = a.nfas[g.query];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint64_t labels = 0;
+    for (uint32_t f = nfa.init; f; f &= f - 1) labels |= nfa.qlab[__ffs(f) - 1];
+    const bool eps = (nfa.init & nfa.final) != 0;
+    uint32_t n = 0;   // listed so far (the same in every thread)
+    uint64_t dead = 0, hash = 0;
+    for (uint32_t r = 0; r < g.n; r += kBlock) {
+        const uint32_t i = r + threadIdx.x;
+        const uint64_t at = g.off + i;
+        uint32_t s = 0;
+        bool alive = false;
+        if (i < g.n) {
+            s = g.given ? g.given[at] : (uint32_t)at;
+            alive = !g.compact || (a.lmask[s] & labels);
+            if (!alive && eps && (!Qy.target || ((Qy.target[s >> 6] >> (s & 63)) & 1))) {
+                const uint64_t h = rpqd::mix64(((uint64_t)s << 32) | s);
+                ++dead;
+                hash += h;
+                if (Qy.per_source) {
+                    Qy.per_source[2 * at] = 1;
+                    Qy.per_source[2 * at + 1] = h;
+                }
+            }
+        }
+        const uint64_t m = __ballot(alive);
+        if (lane == 0) s_w[wv] = (uint32_t)__popcll(m);
+        __syncthreads();
+        uint32_t before = n;
+        for (int w = 0; w < kWaves; ++w) {
+            before += w < wv ? s_w[w] : 0;
+            n += s_w[w];
+        }
+        if (alive) {
+            const uint32_t j = before + (uint32_t)__popcll(m & rpqd::lanemask_lt());
+            s_src[j] = s;
+            s_at[j] = (uint16_t)i;
+        }
+        __syncthreads();
+    }
+    dead = rpqd::wave_sum_u64(dead);
+    hash = rpqd::wave_sum_u64(hash);
+    if (lane == 0 && dead) {
+        atomicAdd(&a.qout[g.query].count, (unsigned long long)dead);
+        atomicAdd(&a.qout[g.query].hash, (unsigned long long)hash);
+    }
+    const bool order = !g.keys && n > 64;
+    if (order) {
+        for (uint32_t i = threadIdx.x; i < kScores; i += kBlock) s_hist[i] = 0;
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
+            const uint32_t s = s_src[i];
+            uint32_t best = 0, hub = 0;
+            for (uint64_t m = a.lmask[s] & labels; m; m &= m - 1) {
+                const uint64_t row = (uint64_t)s * a.L + (uint32_t)(__ffsll((long long)m) - 1);
+                const uint32_t b = a.row_ptr[row], d = a.row_ptr[row + 1] - b;
+                const uint32_t ne = min(d, kScoreEdges);
+                for (uint32_t t = 0; t < ne; ++t) {
+                    const uint32_t w = a.dst[b + (uint32_t)((uint64_t)d * t / ne)];
+                    const uint64_t rw = (uint64_t)w * a.L;
+                    const uint32_t deg = a.row_ptr[rw + a.L] - a.row_ptr[rw];
+                    if (deg > best || (deg == best && w > hub)) {
+                        best = deg;
+                        hub = w;
+                    }
+                }
+            }
+            const uint32_t bits = best ? 32 - __clz(best) : 0;
+            const uint32_t score = ((31 - min(bits, 31u)) << 5) | ((hub * 0x9E3779B1u) >> 27);
+            s_score[i] = (uint16_t)score;
+            atomicAdd(&s_hist[score], 1u);
+        }
+        __syncthreads();
+        // exclusive prefix of the buckets, four a thread
+        uint32_t h4[kScores / kBlock], t = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < kScores / kBlock; ++j) {
+            h4[j] = s_hist[threadIdx.x * (kScores / kBlock) + j];
+            t += h4[j];
+        }
+        const uint32_t incl = rpqd::wave_incl_scan_u32(t);
+        if (lane == 63) s_w[wv] = incl;
+        __syncthreads();
+        uint32_t run = incl - t;
+        for (int w = 0; w < wv; ++w) run += s_w[w];
+#pragma unroll
+        for (uint32_t j = 0; j < kScores / kBlock; ++j) {
+            s_hist[threadIdx.x * (kScores / kBlock) + j] = run;
+            run += h4[j];
+        }
+        __syncthreads();
+    }
+    for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
+        const uint32_t bit = order ? atomicAdd(&s_hist[s_score[i]], 1u) : i;
+        out_srcs[g.out + bit] = s_src[i];
+        out_pos[g.out + bit] = (uint32_t)(g.off + s_at[i]);
+    }
+    for (uint32_t u = threadIdx.x; u < g.n_units; u += kBlock) {
+        BUnit x;
+        x.query = g.query;
+        x.n = n > u * a.W_cut ? min(a.W_cut, n - u * a.W_cut) : 0;
+        x.src_off = g.out + (uint64_t)u * a.W_cut;
+        a.units[g.first_unit + u] = x;
+    }
+}
+
+// One block: the queue of units that hold sources.  A unit left without any still counts one level.
+__global__ __launch_bounds__(kBlock) void k_batch_queue(BArgs a, uint32_t* __restrict__ order) {
+    __shared__ uint32_t s_w[kWaves];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint32_t n = 0;
+    for (uint32_t u0 = 0; u0 < a.n_units; u0 += kBlock) {
+        const uint32_t u = u0 + threadIdx.x;
+        const bool live = u < a.n_units && a.units[u].n != 0;
+        if (u < a.n_units && !live) {
+            const uint32_t q = a.units[u].query;
+            atomicMax(&a.qout[q].max_depth, 1ull);
+            atomicAdd(&a.qout[q].levels, 1ull);
+            atomicAdd(&a.qout[q].units_done, 1ull);
+        }
+        const uint64_t m = __ballot(live);
+        if (lane == 0) s_w[wv] = (uint32_t)__popcll(m);
+        __syncthreads();
+        uint32_t before = n;
+        for (int w = 0; w < kWaves; ++w) {
+            before += w < wv ? s_w[w] : 0;
+            n += s_w[w];
+        }
+        if (live) order[before + __popcll(m & rpqd::lanemask_lt())] = u;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) a.ctl->units_tail = n;
+}
+
+// Clears what the slots in use start from.
+__global__ __launch_bounds__(kBlock) void k_batch_clear(BArgs a, uint32_t K) {
+    const uint64_t G = slots_used(a);
+    const ulonglong2 zero = make_ulonglong2(0, 0);
+    auto clear = [&](uint64_t* p, uint64_t words) {   // 256-byte aligned arrays
+        ulonglong2* p2 = reinterpret_cast<ulonglong2*>(p);
+        for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < words / 2; i += (uint64_t)gridDim.x * kBlock)
+            p2[i] = zero;
+        if ((words & 1) && blockIdx.x == 0 && threadIdx.x == 0) p[words - 1] = 0;
+    };
+    clear(a.vis, G * a.slot_stride * K);
+    clear(a.next, G * a.slot_stride * K);
+    clear(a.touch, G * a.slot_stride / 64);
+    clear(a.ever, G * a.slot_stride / 64);
+    clear(a.ans, G * a.V * K);
+    clear(a.summ, G * a.summ_words);
+}
 
 __global__ void k_check_sources(const uint32_t* __restrict__ src, uint64_t n, uint32_t V,
                                 unsigned long long* __restrict__ bad) {
@@ -1042,8 +1248,10 @@ struct HostQuery {
 };
 
 struct Layout {
-    uint32_t K, W, G, Qmax, H, nchunks, n_units;
+    uint32_t K, W, G, Qmax, H, nchunks, n_units;   // units hold at most W sources, rows K words
     uint32_t seen_or;   // visit scheme of the expansion (1 = seen OR, 0 = two reads)
+    uint64_t n_segs, n_srcs;   // closed form: source segments, sources of all queries
+    uint64_t off_segs, off_srcs, off_pos, off_order;
     uint64_t slot_stride, summ_words, list_cap, desc_cap, log_cap, stage_keys;
     uint64_t off_ctl, off_nfas, off_queries, off_qout, off_units, off_slots, off_vis, off_next, off_touch, off_ever,
         off_ans,
@@ -1061,6 +1269,7 @@ struct rpq_batch {
     rpq_batch_opts opts{};
     std::vector<HostQuery> queries;
     std::vector<BUnit> units;
+    std::vector<BSeg> segs;
     bool frozen = false;
     Layout lay{};
     // graph capture
@@ -1069,7 +1278,7 @@ struct rpq_batch {
     void* ws_captured = nullptr;
     hipStream_t cap_stream = nullptr;
     unsigned n_blocks = 0;
-    BQueryOut* h_out = nullptr;      // pinned copy of the per-query outputs
+    std::vector<BQueryOut> out;      // the queries' outputs of the last run
     BCtl* h_ctl = nullptr;
     double last_ms = 0;
     uint32_t unit_limit = 0;         // autotuning: run only the first units of the queue (0 = all)
@@ -1148,8 +1357,12 @@ void place(const rpq_graph* g, uint32_t nq, uint64_t n_unit_entries, Layout* x) 
     x->off_logs = take(G * x->log_cap * 4);
     x->off_retiring = take(G * 4);
     x->off_drain = take(2 * G * 4);
-    x->off_partial = take(G * x->W * (uint64_t)x->nchunks * 4);
-    x->off_srcbase = take(G * x->W * 8);
+    x->off_partial = take(G * x->K * 64 * (uint64_t)x->nchunks * 4);
+    x->off_srcbase = take(G * x->K * 64 * 8);
+    x->off_segs = take(x->n_segs * sizeof(BSeg));
+    x->off_srcs = take(x->n_srcs * 4);
+    x->off_pos = take(x->n_srcs * 4);
+    x->off_order = take(x->n_segs ? nu * 4 : 0);
     x->off_stage = take(std::max<uint64_t>(1, x->stage_keys) * 8);
     x->off_utotal = take(nu * 8);
     x->off_ustart = take(nu * 8);
@@ -1171,7 +1384,6 @@ int plan(rpq_batch* b) {
         rpq::set_error("batch_width must be 64 .. 4096, a power of two");
         return RPQ_EINVAL;
     }
-    x.K = x.W / 64;
     x.H = b->opts.chunk_edges ? b->opts.chunk_edges : 16;
     if (x.H > 65535) {
         rpq::set_error("chunk_edges must be <= 65535");
@@ -1181,22 +1393,45 @@ int plan(rpq_batch* b) {
         rpq::set_error("visit must be 0, RPQ_VISIT_TWO_READS or RPQ_VISIT_SEEN_OR");
         return RPQ_EINVAL;
     }
-    x.seen_or = b->opts.visit ? b->opts.visit == RPQ_VISIT_SEEN_OR : g->V >= kSeenOrFrom;
+    x.seen_or = b->opts.visit ? b->opts.visit == RPQ_VISIT_SEEN_OR : 1u;
     x.Qmax = 1;
     for (auto& q : b->queries) x.Qmax = std::max(x.Qmax, q.nfa.n_states);
-    // units
+    // segments of the queries' sources, and units cut from them
     b->units.clear();
-    uint32_t qi = 0;
+    b->segs.clear();
+    uint32_t qi = 0, widest = 1;
     for (auto& q : b->queries) {
-        for (uint64_t off = 0; off < q.n_sources; off += x.W) {
-            BUnit u;
-            u.query = qi;
-            u.n = (uint32_t)std::min<uint64_t>(x.W, q.n_sources - off);
-            u.src_off = off;
-            b->units.push_back(u);
+        for (uint64_t off = 0; off < q.n_sources; off += kSegment) {
+            BSeg sg;
+            std::memset(&sg, 0, sizeof sg);
+            sg.given = q.sources;
+            sg.off = off;
+            sg.out = x.n_srcs + off;
+            sg.query = qi;
+            sg.n = (uint32_t)std::min<uint64_t>(kSegment, q.n_sources - off);
+            sg.first_unit = (uint32_t)b->units.size();
+            // with keys, a source without a bit could not put its zero-length walk among them
+            sg.compact = !(q.pairs && (q.nfa.initial_mask & q.nfa.final_mask));
+            sg.keys = q.pairs != nullptr;
+            for (uint32_t at = 0; at < sg.n; at += x.W) {
+                BUnit u;
+                u.query = qi;
+                u.n = std::min(x.W, sg.n - at);
+                u.src_off = off + at;
+                b->units.push_back(u);
+                widest = std::max(widest, u.n);
+            }
+            sg.n_units = (uint32_t)b->units.size() - sg.first_unit;
+            b->segs.push_back(sg);
         }
+        x.n_srcs += q.n_sources;
         ++qi;
     }
+    x.n_segs = b->segs.size();
+    // rows hold as many words as the widest unit needs (two at least, as in the plain form)
+    x.K = 2;
+    while (x.K * 64 < widest) x.K *= 2;
+    x.K = std::min(x.K, x.W / 64);
     x.n_units = (uint32_t)b->units.size();
     uint32_t max_succ = 1;
     for (auto& q : b->queries)
@@ -1216,7 +1451,7 @@ int plan(rpq_batch* b) {
     uint64_t G = b->opts.slots;
     if (!G) {
         const uint64_t budget = 64ull << 30;
-        G = std::max<uint64_t>(1, std::min<uint64_t>(std::max<uint64_t>(1, 65536 / x.W), budget / per_slot));
+        G = std::max<uint64_t>(1, std::min<uint64_t>(65536 / (64 * x.K), budget / per_slot));
     }
     G = std::min<uint64_t>(G, std::max<uint32_t>(1, x.n_units));
     G = std::min<uint64_t>(G, 1024);
@@ -1246,7 +1481,8 @@ BArgs args_for(const rpq_graph* g, const Layout& x, char* ws, unsigned n_blocks,
     a.nfas = reinterpret_cast<const BNfa*>(ws + x.off_nfas);
     a.queries = reinterpret_cast<const BQuery*>(ws + x.off_queries);
     a.qout = reinterpret_cast<BQueryOut*>(ws + x.off_qout);
-    a.units = reinterpret_cast<const BUnit*>(ws + x.off_units);
+    a.units = reinterpret_cast<BUnit*>(ws + x.off_units);
+    a.order = x.n_segs ? reinterpret_cast<const uint32_t*>(ws + x.off_order) : nullptr;
     a.slots = reinterpret_cast<BSlot*>(ws + x.off_slots);
     a.ctl = reinterpret_cast<BCtl*>(ws + x.off_ctl);
     a.vis = reinterpret_cast<uint64_t*>(ws + x.off_vis);
@@ -1274,7 +1510,8 @@ BArgs args_for(const rpq_graph* g, const Layout& x, char* ws, unsigned n_blocks,
     a.Qmax = x.Qmax;
     a.H = x.H;
     a.G = x.G;
-    a.W = x.W;
+    a.W = x.K * 64;
+    a.W_cut = x.W;
     a.nchunks = x.nchunks;
     a.n_units = n_units;
     a.n_queries = n_queries;
@@ -1354,15 +1591,21 @@ int enqueue_run(rpq_batch* b, char* ws, hipStream_t s) {
     RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(ws + x.off_qout), sizeof(BQueryOut) / 8 * b->queries.size(),
                           0, s));
     RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(ws + x.off_slots), sizeof(BSlot) / 8 * x.G, 0, s));
-    RPQ_TRY(rpq::fill_u64(a.vis, (uint64_t)x.G * x.slot_stride * x.K, 0, s));
-    RPQ_TRY(rpq::fill_u64(a.next, (uint64_t)x.G * x.slot_stride * x.K, 0, s));
-    RPQ_TRY(rpq::fill_u64(a.touch, (uint64_t)x.G * x.slot_stride / 64, 0, s));
-    RPQ_TRY(rpq::fill_u64(a.ever, (uint64_t)x.G * x.slot_stride / 64, 0, s));
-    RPQ_TRY(rpq::fill_u64(a.ans, (uint64_t)x.G * b->g->V * x.K, 0, s));
-    RPQ_TRY(rpq::fill_u64(a.summ, (uint64_t)x.G * x.summ_words, 0, s));
     RPQ_TRY(rpq::fill_u64(a.unit_total, std::max<uint32_t>(1, x.n_units), 0, s));
     for (auto& q : b->queries)
         if (q.per_source) RPQ_TRY(rpq::fill_u64(q.per_source, q.n_sources * 2, 0, s));
+    if (!x.n_segs) return RPQ_OK;   // no query has a source
+    {
+        hipLaunchKernelGGL(k_batch_sources, dim3((unsigned)x.n_segs), dim3(kBlock), 0, s, a,
+                           reinterpret_cast<const BSeg*>(ws + x.off_segs), reinterpret_cast<uint32_t*>(ws + x.off_srcs),
+                           reinterpret_cast<uint32_t*>(ws + x.off_pos));
+        RPQ_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_batch_queue, dim3(1), dim3(kBlock), 0, s, a,
+                           reinterpret_cast<uint32_t*>(ws + x.off_order));
+        RPQ_LAUNCH_CHECK();
+        hipLaunchKernelGGL(k_batch_clear, dim3(4096), dim3(kBlock), 0, s, a, x.K);
+        RPQ_LAUNCH_CHECK();
+    }
     hipLaunchKernelGGL((k_batch<K, SEEN>), dim3(nb), dim3(kBlock), 0, s, a);
     RPQ_LAUNCH_CHECK();
     bool any_pairs = false;
@@ -1409,7 +1652,6 @@ int rpq_batch_destroy(rpq_batch_t b) {
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
-    if (b->h_out) (void)hipHostFree(b->h_out);
     if (b->h_ctl) (void)hipHostFree(b->h_ctl);
     delete b;
     return RPQ_OK;
@@ -1531,7 +1773,7 @@ int rpq_batch_workspace_size(rpq_batch_t b, uint64_t* bytes) {
         *bytes = 256;
         return RPQ_OK;
     }
-    RPQ_TRY(plan(b));
+    if (!b->frozen) RPQ_TRY(plan(b));   // a batch that ran keeps its plan
     *bytes = b->lay.total;
     return RPQ_OK;
 }
@@ -1583,7 +1825,8 @@ int rpq_batch_run(rpq_batch_t b, void* workspace, uint64_t workspace_bytes, hipS
             to_bnfa(h.nfa, b->g->L, &nf[i]);
             BQuery& d = qs[i];
             std::memset(&d, 0, sizeof d);
-            d.sources = h.sources;
+            d.sources = reinterpret_cast<const uint32_t*>(ws + x.off_srcs);
+            d.pos = reinterpret_cast<const uint32_t*>(ws + x.off_pos);
             d.n_sources = h.n_sources;
             d.per_source = h.per_source;
             d.pairs = h.pairs;
@@ -1599,8 +1842,8 @@ int rpq_batch_run(rpq_batch_t b, void* workspace, uint64_t workspace_bytes, hipS
         }
         RPQ_HIP(hipMemcpy(ws + x.off_nfas, nf.data(), sizeof(BNfa) * nq, hipMemcpyHostToDevice));
         RPQ_HIP(hipMemcpy(ws + x.off_queries, qs.data(), sizeof(BQuery) * nq, hipMemcpyHostToDevice));
-        if (!b->units.empty())
-            RPQ_HIP(hipMemcpy(ws + x.off_units, b->units.data(), sizeof(BUnit) * b->units.size(),
+        if (!b->segs.empty())
+            RPQ_HIP(hipMemcpy(ws + x.off_segs, b->segs.data(), sizeof(BSeg) * b->segs.size(),
                               hipMemcpyHostToDevice));
         if (b->exec) {
             (void)hipGraphExecDestroy(b->exec);
@@ -1641,6 +1884,8 @@ int rpq_batch_run(rpq_batch_t b, void* workspace, uint64_t workspace_bytes, hipS
     (void)hipEventDestroy(e1);
     b->last_ms = ms;
     RPQ_HIP(hipMemcpy(b->h_ctl, ws + x.off_ctl, sizeof(BCtl), hipMemcpyDeviceToHost));
+    b->out.resize(nq);
+    RPQ_HIP(hipMemcpy(b->out.data(), ws + x.off_qout, sizeof(BQueryOut) * nq, hipMemcpyDeviceToHost));
     // block 0 stamps the constant clock (100 MHz) when it enters and leaves the persistent kernel
     if (b->h_ctl->t_end > b->h_ctl->t_begin) b->last_kernel_ms = (b->h_ctl->t_end - b->h_ctl->t_begin) / 1.0e5;
     if (b->h_ctl->gs.abort) {
@@ -1658,13 +1903,11 @@ int rpq_batch_run(rpq_batch_t b, void* workspace, uint64_t workspace_bytes, hipS
 
 int rpq_batch_result(rpq_batch_t b, uint32_t query_id, rpq_result* out) {
     rpq::clear_error();
-    if (!b || !out || query_id >= b->queries.size() || !b->frozen || !b->ws_captured) {
+    if (!b || !out || query_id >= b->queries.size() || !b->frozen || !b->ws_captured || b->out.size() <= query_id) {
         rpq::set_error("invalid batch, query id, or batch has not run");
         return RPQ_EINVAL;
     }
-    BQueryOut o;
-    const char* ws = reinterpret_cast<const char*>(b->ws_captured);
-    RPQ_HIP(hipMemcpy(&o, ws + b->lay.off_qout + sizeof(BQueryOut) * query_id, sizeof o, hipMemcpyDeviceToHost));
+    const BQueryOut& o = b->out[query_id];
     const HostQuery& h = b->queries[query_id];
     std::memset(out, 0, sizeof *out);
     out->pairs = h.pairs;

@@ -980,43 +980,14 @@ __device__ __forceinline__ uint64_t wave_or_u64(uint64_t v) {
     return v;
 }
 
-__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
-    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
-           (uint32_t)__builtin_amdgcn_readlane((int)v, l);
-}
-
-// The checksum of key s << 32 | v, mix64, with what depends on the source alone taken out of the loop
-// over v.  Vertex ids are below 2^31, so v plus the constant's low half never carries: the first sum is
-// {s + hi, v + lo}, and after the first shift the high half is the source's own.
-struct MixSource {
-    uint32_t a;    // what the source's half adds to the low half by the first shift
-    uint64_t b;    // its high half's part of the first product
-};
-
-__device__ __forceinline__ MixSource mix_source(uint32_t s) {
-    const uint32_t z = s + 0x9e3779b9u;
-    MixSource m;
-    m.a = z << 2;
-    m.b = (uint64_t)((z ^ (z >> 30)) * 0x1ce4e5b9u) << 32;
-    return m;
-}
-
-__device__ __forceinline__ uint64_t mix_pair(const MixSource& m, uint32_t v) {
-    const uint32_t z = v + 0x7f4a7c15u;
-    const uint32_t t = (z ^ (z >> 30)) ^ m.a;
-    uint64_t y = (uint64_t)t * 0x1ce4e5b9u + m.b;
-    y += (uint64_t)(t * 0xbf58476du) << 32;
-    y = (y ^ (y >> 27)) * 0x94d049bb133111ebull;
-    return y ^ (y >> 31);
-}
-
 // One wave per (slot, block of kExtractWords consecutive words, chunk of answer vertices).  Lane i loads
 // answer vertex i's words: the OR of its rows of final states.  A word block of 64 vertices x 64 sources
-// is then walked by rows or by columns, whichever is shorter for what it holds:
+// is then walked by rows or by columns, whichever takes fewer steps for what it holds:
 //   rows     for each vertex with a bit, lane i is source i: checksums are one lane-constant mix per pair,
-//            keys go to 64 streams;
-//   columns  for each source with a bit, lane i is vertex i: a source's keys are written as one run,
-//            and a few sources do not cost a pass per vertex (one source of R-MAT 18: 216 -> 10 us).
+//            bound by its five multiplications where the block is dense (41 G pairs in 30.6 ms);
+//   columns  for each source with a bit, lane i is vertex i: a source's keys are written as one run (64
+//            streams of single keys wrote 4.6 times the bytes: 87 M keys 1.10 -> 0.45 ms), and a few
+//            sources do not cost a step per vertex.
 // The totals of a call that asks for neither keys nor per-source results need no accumulator per source.
 template <int K, int MODE>
 __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
@@ -1040,7 +1011,7 @@ __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
         uint32_t src[KP];
         uint32_t cnt[KP];   // at most the chunk's vertices
         uint64_t h[KP], cursor[KP];
-        MixSource ms[KP];
+        rpqd::MixSource ms[KP];
         bool in_window = MODE != X_KEYS;
 #pragma unroll
         for (int u = 0; u < KP; ++u) {
@@ -1048,7 +1019,7 @@ __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
             const uint64_t gi = a.gbase + si;
             const bool valid = gi < a.n_srcs;
             src[u] = valid ? (a.srcs ? a.srcs[gi] : (uint32_t)gi) : 0;
-            ms[u] = mix_source(src[u]);
+            ms[u] = rpqd::mix_source(src[u]);
             cnt[u] = 0;
             h[u] = cursor[u] = 0;
             if (MODE == X_KEYS && valid) {
@@ -1121,7 +1092,7 @@ __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
                 if (any == 0) continue;
                 uint64_t cols = wave_or_u64(word[u]);
                 const uint32_t nr = (uint32_t)__popcll(any), nc = (uint32_t)__popcll(cols);
-                if (MODE == X_KEYS ? nc < 2 * nr : MODE == X_TALLIES ? 5 * nc < 2 * nr : 3 * nc < 2 * nr) {
+                if (MODE == X_KEYS ? nc < 8 * nr : MODE == X_TALLIES ? 5 * nc < 2 * nr : 3 * nc < 2 * nr) {
                     while (cols) {
                         const int c = __ffsll((long long)cols) - 1;
                         cols &= cols - 1;
@@ -1129,7 +1100,7 @@ __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
                         const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)src[u], c);
                         if constexpr (MODE == X_KEYS) {
                             const uint64_t m = __ballot(bit);
-                            const uint64_t cur = readlane_u64(cursor[u], c);
+                            const uint64_t cur = rpqd::readlane_u64(cursor[u], c);
                             const uint64_t at = cur + __popcll(m & rpqd::lanemask_lt());
                             if (bit && at >= x.off && at - x.off < x.cap) x.pairs[at - x.off] = ((uint64_t)s << 32) | v;
                             if (lane == c) cursor[u] = cur + __popcll(m);
@@ -1153,7 +1124,7 @@ __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
                     while (any) {
                         const int j = __ffsll((long long)any) - 1;
                         any &= any - 1;
-                        const uint64_t wj = readlane_u64(word[u], j);
+                        const uint64_t wj = rpqd::readlane_u64(word[u], j);
                         const uint32_t vj = (uint32_t)__builtin_amdgcn_readlane((int)v, j);
                         // the word itself is the mask of the lanes whose source reaches the vertex
                         if constexpr (MODE == X_TOTALS) row_bits += (uint32_t)__popcll(wj);
@@ -1164,7 +1135,7 @@ __global__ __launch_bounds__(kBlock) void k_extract(Args a, ExtractArgs x) {
                                 ++cursor[u];
                             } else {
                                 if constexpr (MODE == X_TALLIES) ++cnt[u];
-                                h[u] += mix_pair(ms[u], vj);
+                                h[u] += rpqd::mix_pair(ms[u], vj);
                             }
                         }
                     }
@@ -1491,24 +1462,16 @@ uint64_t place_rows(const Plan& p, uint32_t W, uint32_t* base) {
 }
 
 // Width of a unit for n_bits sources.  Wide rows turn one visit of an edge into work for more sources, so
-// one unit takes as many as it may, up to a quarter of its words unused rather than a second unit
-// (R-MAT 22, 1,130 of a slice's 4,096 sources with a bit: 54.5 ms at 64, 14.1 at 512, 10.7 at 2048).
-// Below 512 sources a row still gets 64 bytes of its own: at 8 bytes a row, ORs to neighbouring rows from
-// different dies meet in one line (R-MAT 18, 40 sources: 1.28 ms at 64, 0.78 at 512, 1.53 at 2048, where
-// the unused words cost), as long as a unit stays small.  On graphs of up to 2^13 vertices a level is one
-// wave's work per unit, and more, narrower units are the faster way (1,000 vertices, all pairs: 1.04 ms at
-// 64, 1.53 at 1024).
-constexpr uint64_t kPadBudget = 4ull << 30;
-
+// one unit takes them all where it can: a second unit visits every edge again (R-MAT 22, about 300 sources
+// with a bit: 11.5 ms at 64, 5.4 at 256, 4.0 at 512), and words that no source uses are still read and
+// written (6.7 at 2048).  From 512 on, up to a quarter of a unit's sources rather go to a second unit.  A
+// row has at least two words: at one, ORs to neighbouring rows from different dies meet in one line more
+// often (R-MAT 18, about 30 sources: 0.57 ms at 64 and 0.56 at 128, 0.64 at 512).  On up to 2^13 vertices
+// a level is too short for wide units to fill the device (1,000 vertices, all pairs: 1.05 ms at 128, 1.29
+// at 1024).
 uint32_t default_width(const Plan& p, uint64_t n_bits, uint32_t V) {
-    uint32_t W = 64;
-    if (V <= (1u << 13)) {
-        while (W < 512 && (uint64_t)W * 2 <= std::max<uint64_t>(64, n_bits / 8)) W *= 2;
-    } else {
-        W = 512;
-        while (W < max_default_width(V) && (uint64_t)W * 4 < n_bits * 3) W *= 2;
-        while (W > 64 && W / 2 >= n_bits && unit_bytes(place_rows(p, W, nullptr), W) > kPadBudget) W /= 2;
-    }
+    uint32_t W = 128;
+    while (V > (1u << 13) && W < max_default_width(V) && (W < 512 ? W < n_bits : (uint64_t)W * 4 < n_bits * 3)) W *= 2;
     while (W > 64 && unit_bytes(place_rows(p, W, nullptr), W) > kUnitBudget) W /= 2;
     return W;
 }

@@ -169,6 +169,36 @@ __device__ __forceinline__ uint64_t mix64(uint64_t x) {
     return z ^ (z >> 31);
 }
 
+// The checksum of key s << 32 | v, mix64, with what depends on the source alone taken out of the loop
+// over v.  Vertex ids are below 2^31, so v plus the constant's low half never carries: the first sum is
+// {s + hi, v + lo}, and after the first shift the high half is the source's own.
+struct MixSource {
+    uint32_t a;    // what the source's half adds to the low half by the first shift
+    uint64_t b;    // its high half's part of the first product
+};
+
+__device__ __forceinline__ MixSource mix_source(uint32_t s) {
+    const uint32_t z = s + 0x9e3779b9u;
+    MixSource m;
+    m.a = z << 2;
+    m.b = (uint64_t)((z ^ (z >> 30)) * 0x1ce4e5b9u) << 32;
+    return m;
+}
+
+__device__ __forceinline__ uint64_t mix_pair(const MixSource& m, uint32_t v) {
+    const uint32_t z = v + 0x7f4a7c15u;
+    const uint32_t t = (z ^ (z >> 30)) ^ m.a;
+    uint64_t y = (uint64_t)t * 0x1ce4e5b9u + m.b;
+    y += (uint64_t)(t * 0xbf58476du) << 32;
+    y = (y ^ (y >> 27)) * 0x94d049bb133111ebull;
+    return y ^ (y >> 31);
+}
+
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+
 __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
     const int l = __lane_id();
 #pragma unroll
