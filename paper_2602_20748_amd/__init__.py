@@ -500,8 +500,14 @@ def rpq_eval(g: Graph, nfa: Nfa, sources=None, flags: int = 0, opts=None, pairs=
     _check(lib.rpq_eval_workspace_size(g.handle, ctypes.byref(nfa), n, flags,
                                        ctypes.byref(o) if o is not None else None, ctypes.byref(need)))
     ws_bytes = int(need.value)
-    if flags & RPQ_SPARSE:   # room for a search that reaches far, without a second call
+    if flags & RPQ_SPARSE:
+        # room for a search that reaches far, without a second call; for few sources, room for the
+        # bit-parallel search that takes it over
         ws_bytes = max(ws_bytes, 64 << 20)
+        if n <= 512 and lib.rpq_eval_workspace_size(g.handle, ctypes.byref(nfa), n, flags & ~RPQ_SPARSE,
+                                                    ctypes.byref(o) if o is not None else None,
+                                                    ctypes.byref(need)) == RPQ_OK and need.value <= 1 << 30:
+            ws_bytes = max(ws_bytes, int(need.value))
     for _ in range(16):
         ws = workspace if workspace is not None else g.workspace(ws_bytes)
         res = _Result()

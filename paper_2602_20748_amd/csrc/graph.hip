@@ -7,10 +7,15 @@
 // per-vertex label bitmask lets the traversal skip labels with no edges.
 //
 // Steps (all on the device): pack (row, neighbour) into a uint64 key, stable
-// radix sort, drop repeated keys (the edge relation is a set), then derive
-// row pointers by binary search over the sorted keys and the label masks
-// from non-empty rows.  The in-edge CSR is the same construction with source
-// and destination swapped.
+// radix sort, drop repeated keys (the edge relation is a set) and mark where
+// each row starts, then fill the row pointers between the marks and derive the
+// label masks from non-empty rows.  The in-edge CSR is the same construction
+// with source and destination swapped.
+//
+// One scratch allocation serves both directions and each direction's arrays
+// are one allocation: releasing several large allocations one after another
+// takes the runtime 5 ms each (16M edges both ways: 46 ms a call with twenty of
+// them, of which the kernels were 4).  The host waits once per direction.
 #include "internal.h"
 
 #include <cstring>
@@ -41,71 +46,196 @@ __global__ void k_make_keys(const uint32_t* __restrict__ a, const uint8_t* __res
     }
 }
 
-__global__ void k_mark_first(const uint64_t* __restrict__ keys, uint64_t n, uint64_t* __restrict__ flag) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        flag[i] = (i == 0 || keys[i] != keys[i - 1]) ? 1 : 0;
-}
+// Distinct keys: a block takes kTile sorted keys; a first pass counts those that differ from their
+// predecessor, a second writes them at the prefix of the counts and marks the start of each row.
+constexpr uint32_t kTile = 2048;
 
-__global__ void k_compact(const uint64_t* __restrict__ keys, const uint64_t* __restrict__ pos, uint64_t n,
-                          uint64_t* __restrict__ ukeys, uint32_t* __restrict__ dst, uint32_t L,
-                          unsigned long long* __restrict__ per_label) {
-    __shared__ unsigned long long cnt[RPQ_MAX_LABELS];
-    for (int i = threadIdx.x; i < RPQ_MAX_LABELS; i += blockDim.x) cnt[i] = 0;
+__global__ __launch_bounds__(kThreads) void k_uniq_count(const uint64_t* __restrict__ keys, uint64_t n,
+                                                         uint64_t* __restrict__ counts) {
+    __shared__ uint32_t s_w[kThreads / 64];
+    uint32_t c = 0;
+    for (uint32_t j = threadIdx.x; j < kTile; j += kThreads) {
+        const uint64_t i = (uint64_t)blockIdx.x * kTile + j;
+        if (i < n && (i == 0 || keys[i] != keys[i - 1])) ++c;
+    }
+    c = (uint32_t)rpqd::wave_sum_u64(c);
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = c;
     __syncthreads();
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const uint64_t k = keys[i];
-        if (i == 0 || k != keys[i - 1]) {
-            const uint64_t p = pos[i];
-            ukeys[p] = k;
-            dst[p] = (uint32_t)k;
-            atomicAdd(&cnt[(uint32_t)(k >> 32) % L], 1ull);
-        }
+    if (threadIdx.x == 0) {
+        uint32_t t = 0;
+        for (int w = 0; w < kThreads / 64; ++w) t += s_w[w];
+        counts[blockIdx.x] = t;
     }
+}
+
+__global__ __launch_bounds__(kThreads) void k_uniq_write(const uint64_t* __restrict__ keys, uint64_t n,
+                                                         const uint64_t* __restrict__ offs,
+                                                         uint32_t* __restrict__ dst, uint32_t* __restrict__ start) {
+    __shared__ uint32_t s_w[kThreads / 64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint64_t at = offs[blockIdx.x];
+    for (uint32_t j = threadIdx.x; j < kTile; j += kThreads) {
+        const uint64_t i = (uint64_t)blockIdx.x * kTile + j;
+        uint64_t k = 0, before = 0;
+        bool first = false;
+        if (i < n) {
+            k = keys[i];
+            before = i ? keys[i - 1] : ~k;
+            first = k != before;
+        }
+        const uint64_t m = __ballot(first);
+        if (lane == 0) s_w[wv] = (uint32_t)__popcll(m);
+        __syncthreads();
+        uint64_t pos = at + __popcll(m & rpqd::lanemask_lt());
+        for (int w = 0; w < kThreads / 64; ++w) {
+            pos += w < wv ? s_w[w] : 0;
+            at += s_w[w];
+        }
+        if (first) {
+            dst[pos] = (uint32_t)k;
+            if ((k >> 32) != (before >> 32)) start[k >> 32] = (uint32_t)pos;
+        }
+        __syncthreads();
+    }
+}
+
+// Row pointers from the marked starts (kNoRow: an empty row, which begins where the next one does).  A
+// block takes kRows rows; what follows its last row comes from a suffix minimum over the blocks.
+constexpr uint32_t kRows = 2048;
+constexpr uint32_t kNoRow = 0xFFFFFFFFu;
+
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v = min(v, (uint32_t)__shfl_xor(v, o, 64));
+    return v;
+}
+
+__global__ __launch_bounds__(kThreads) void k_row_min(const uint32_t* __restrict__ start, uint64_t R,
+                                                      uint32_t* __restrict__ mins) {
+    __shared__ uint32_t s_w[kThreads / 64];
+    uint32_t m = kNoRow;
+    for (uint32_t j = threadIdx.x; j < kRows; j += kThreads) {
+        const uint64_t r = (uint64_t)blockIdx.x * kRows + j;
+        if (r < R) m = min(m, start[r]);
+    }
+    m = wave_min_u32(m);
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = m;
     __syncthreads();
-    for (int i = threadIdx.x; i < (int)L; i += blockDim.x)
-        if (cnt[i]) atomicAdd(&per_label[i], cnt[i]);
+    if (threadIdx.x == 0) {
+        for (int w = 0; w < kThreads / 64; ++w) m = min(m, s_w[w]);
+        mins[blockIdx.x] = m;
+    }
 }
 
-// row_ptr[r] = first index whose row id (upper key word) is >= r, r in [0, R]
-__global__ void k_row_ptr(const uint64_t* __restrict__ ukeys, uint64_t m, uint64_t R,
-                          uint32_t* __restrict__ row_ptr) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; r <= R; r += stride) {
-        uint64_t lo = 0, hi = m;
-        while (lo < hi) {
-            const uint64_t mid = (lo + hi) >> 1;
-            if ((ukeys[mid] >> 32) < r) lo = mid + 1;
-            else hi = mid;
+// mins[b] = minimum over blocks after b, or the number of edges (one block, from the last entry down)
+__global__ __launch_bounds__(1024) void k_row_after(uint32_t* __restrict__ mins, uint64_t nb,
+                                                    const unsigned long long* __restrict__ n_edges) {
+    __shared__ uint32_t s_w[16];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint32_t carry = (uint32_t)*n_edges;
+    for (uint64_t top = nb; top > 0; top = top > 1024 ? top - 1024 : 0) {
+        // thread t holds entry top - 1 - t: later blocks are lower threads
+        const bool ok = threadIdx.x < top;
+        const uint32_t x = ok ? mins[top - 1 - threadIdx.x] : kNoRow;
+        uint32_t incl = x;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl = min(incl, y);
         }
-        row_ptr[r] = (uint32_t)lo;
+        if (lane == 63) s_w[wv] = incl;
+        __syncthreads();
+        uint32_t before = carry, all = carry;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wv) before = min(before, s_w[w]);
+            all = min(all, s_w[w]);
+        }
+        const uint32_t up = __shfl_up(incl, 1, 64);
+        if (ok) mins[top - 1 - threadIdx.x] = lane ? min(before, up) : before;
+        carry = all;
+        __syncthreads();
     }
 }
 
-__global__ void k_label_mask(const uint32_t* __restrict__ row_ptr, uint32_t V, uint32_t L,
-                             uint64_t* __restrict__ lmask, unsigned long long* __restrict__ nonempty) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    uint64_t local = 0;
-    for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < V; v += stride) {
-        uint64_t m = 0;
-        const uint32_t* r = row_ptr + v * L;
-        for (uint32_t l = 0; l < L; ++l)
-            if (r[l + 1] > r[l]) m |= 1ull << l;
-        lmask[v] = m;
-        local += __popcll(m);
+// In place: start becomes row_ptr[0 .. R].  Rows are v * L + l, so a row's label is its remainder.
+__global__ __launch_bounds__(kThreads) void k_row_fill(uint32_t* __restrict__ row_ptr, uint64_t R, uint32_t L,
+                                                       const uint32_t* __restrict__ after,
+                                                       const unsigned long long* __restrict__ n_edges,
+                                                       unsigned long long* __restrict__ per_label,
+                                                       unsigned long long* __restrict__ nonempty) {
+    constexpr uint32_t kEach = kRows / kThreads;   // consecutive rows of a thread
+    __shared__ uint32_t s_w[kThreads / 64];
+    __shared__ uint32_t s_lab[RPQ_MAX_LABELS];
+    __shared__ uint32_t s_rows;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (uint32_t i = threadIdx.x; i < L; i += kThreads) s_lab[i] = 0;
+    if (threadIdx.x == 0) s_rows = 0;
+    const uint64_t r0 = (uint64_t)blockIdx.x * kRows + (uint64_t)threadIdx.x * kEach;
+    uint32_t x[kEach], lo = kNoRow;
+#pragma unroll
+    for (uint32_t j = 0; j < kEach; ++j) {
+        x[j] = r0 + j < R ? row_ptr[r0 + j] : kNoRow;
+        lo = min(lo, x[j]);
     }
-    local = rpqd::wave_sum_u64(local);
-    if ((threadIdx.x & 63) == 0 && local) atomicAdd(nonempty, (unsigned long long)local);
+    // minimum over the threads after this one
+    uint32_t incl = lo;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_down(incl, o, 64);
+        if (lane + o < 64) incl = min(incl, y);
+    }
+    if (lane == 0) s_w[wv] = incl;
+    __syncthreads();
+    uint32_t next = after[blockIdx.x];
+    for (int w = wv + 1; w < kThreads / 64; ++w) next = min(next, s_w[w]);
+    const uint32_t later = __shfl_down(incl, 1, 64);
+    if (lane < 63) next = min(next, later);
+    uint32_t rows = 0;
+    for (int j = kEach - 1; j >= 0; --j) {
+        if (r0 + j >= R) continue;
+        if (x[j] != kNoRow) {
+            atomicAdd(&s_lab[(uint32_t)((r0 + j) % L)], next - x[j]);
+            next = x[j];
+            ++rows;
+        }
+        row_ptr[r0 + j] = next;
+    }
+    rows = (uint32_t)rpqd::wave_sum_u64(rows);
+    if (lane == 0 && rows) atomicAdd(&s_rows, rows);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) row_ptr[R] = (uint32_t)*n_edges;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < L; i += kThreads)
+        if (s_lab[i]) atomicAdd(&per_label[i], (unsigned long long)s_lab[i]);
+    if (threadIdx.x == 0 && s_rows) atomicAdd(nonempty, (unsigned long long)s_rows);
+}
+
+// Label masks: a wave takes 64 vertices, whose rows are one stretch of row pointers, and reads them 64 at a
+// time (a thread per vertex read them L apart: 207 us for a million vertices of 8 labels).
+__global__ __launch_bounds__(kThreads) void k_label_mask(const uint32_t* __restrict__ row_ptr, uint32_t V, uint32_t L,
+                                                         uint64_t* __restrict__ lmask) {
+    __shared__ unsigned long long s_m[kThreads / 64][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint64_t stride = (uint64_t)gridDim.x * (kThreads / 64);
+    for (uint64_t w = (uint64_t)blockIdx.x * (kThreads / 64) + wv; w * 64 < V; w += stride) {
+        s_m[wv][lane] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const uint64_t r0 = w * 64 * L;
+        const uint32_t n = (uint32_t)min((uint64_t)64, V - w * 64) * L;
+        for (uint32_t i = lane; i < n; i += 64)
+            if (row_ptr[r0 + i + 1] > row_ptr[r0 + i]) atomicOr(&s_m[wv][i / L], 1ull << (i % L));
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (w * 64 + lane < V) lmask[w * 64 + lane] = s_m[wv][lane];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
 }
 
 // entered bits of a direction, from its keys (row << 32 | neighbour).  Hubs are entered by many edges: a
 // bit that is already set is not ORed again.
-__global__ void k_entered(const uint64_t* __restrict__ ukeys, uint64_t m, uint32_t L, uint64_t n_words,
+__global__ void k_entered(const uint64_t* __restrict__ keys, uint64_t m, uint32_t L, uint64_t n_words,
                           unsigned long long* __restrict__ entered) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
-        const uint64_t k = ukeys[i];
+        const uint64_t k = keys[i];
         const uint32_t v = (uint32_t)k;
         unsigned long long* w = &entered[(uint64_t)((uint32_t)(k >> 32) % L) * n_words + (v >> 6)];
         const unsigned long long bit = 1ull << (v & 63);
@@ -157,115 +287,134 @@ int dev_alloc(void** p, uint64_t bytes) {
     return RPQ_OK;
 }
 
+// Scratch of a build: the keys and their sorting, shared by the two directions.
+struct Scratch {
+    DevBuf mem;
+    uint64_t *keys, *alt, *counts, *scan;
+    uint32_t* mins;
+    void* sort;
+    unsigned long long* ctr;   // [kCtr]
+
+    static constexpr uint64_t kCtr = 4 + 3 * RPQ_MAX_LABELS;
+
+    int alloc(uint64_t n_edges, uint64_t R) {
+        const uint64_t tiles = (n_edges + kTile - 1) / kTile + 1;
+        uint64_t off = 0;
+        auto take = [&](uint64_t bytes) {
+            const uint64_t o = off;
+            off += (bytes + 255) / 256 * 256;
+            return o;
+        };
+        const uint64_t o_keys = take(n_edges * 8), o_alt = take(n_edges * 8), o_counts = take(tiles * 8),
+                       o_scan = take((rpq::scan_temp_elems(tiles) + 1) * 8),
+                       o_mins = take(((R + kRows - 1) / kRows) * 4), o_sort = take(rpq::radix_temp_bytes(n_edges)),
+                       o_ctr = take(kCtr * 8);
+        RPQ_TRY(dev_alloc(&mem.p, off));
+        char* b = reinterpret_cast<char*>(mem.p);
+        keys = reinterpret_cast<uint64_t*>(b + o_keys);
+        alt = reinterpret_cast<uint64_t*>(b + o_alt);
+        counts = reinterpret_cast<uint64_t*>(b + o_counts);
+        scan = reinterpret_cast<uint64_t*>(b + o_scan);
+        mins = reinterpret_cast<uint32_t*>(b + o_mins);
+        sort = b + o_sort;
+        ctr = reinterpret_cast<unsigned long long*>(b + o_ctr);
+        return RPQ_OK;
+    }
+};
+
 // Build one CSR direction (more: the other one follows).  a/b: row-side and neighbour-side endpoint arrays.
 // other: the direction built before this one (its label masks then give this one's entered bits, and
 // this one's give its), or null.
 int build_csr(const uint32_t* a, const uint8_t* lab, const uint32_t* b, uint64_t n_edges, uint32_t V,
-              uint32_t L, rpq::Csr* out, rpq::Csr* other, bool more, uint64_t* E_out, uint64_t* per_label,
-              uint64_t* stage, hipStream_t s) {
+              uint32_t L, Scratch& sc, rpq::Csr* out, rpq::Csr* other, bool more, uint64_t* E_out,
+              uint64_t* per_label, uint64_t* stage, hipStream_t s) {
     using namespace rpq;
     const uint64_t R = (uint64_t)V * L;
-    const uint64_t ne = n_edges ? n_edges : 1;
-    DevBuf keys, alt, flag, sort_tmp, ctr, uk;
-    RPQ_TRY(dev_alloc(&keys.p, ne * 8));
-    RPQ_TRY(dev_alloc(&alt.p, ne * 8));
-    RPQ_TRY(dev_alloc(&flag.p, (ne + scan_temp_elems(ne) + 1) * 8));
-    RPQ_TRY(dev_alloc(&sort_tmp.p, radix_temp_bytes(ne)));
-    constexpr uint64_t kCtr = 4 + 3 * RPQ_MAX_LABELS;
-    RPQ_TRY(dev_alloc(&ctr.p, kCtr * 8));
-    unsigned long long* c = reinterpret_cast<unsigned long long*>(ctr.p);   // [0] err [1] total [2] nonempty
+    const uint64_t n_words = ((uint64_t)V + 63) / 64;
+    auto up = [](uint64_t x) { return (x + 255) / 256 * 256; };
+    const uint64_t o_dst = up((R + 1) * 4), o_mask = o_dst + up(n_edges * 4 + 4), o_ent = o_mask + up((uint64_t)V * 8);
+    RPQ_TRY(dev_alloc(&out->mem, o_ent + L * n_words * 8));
+    char* mem = reinterpret_cast<char*>(out->mem);
+    out->row_ptr = reinterpret_cast<uint32_t*>(mem);
+    out->dst = reinterpret_cast<uint32_t*>(mem + o_dst);
+    out->lmask = reinterpret_cast<uint64_t*>(mem + o_mask);
+    out->entered = reinterpret_cast<uint64_t*>(mem + o_ent);
+    unsigned long long* c = sc.ctr;   // [0] err [1] distinct edges [2] nonempty rows
     unsigned long long* pl = c + 4;
     unsigned long long* ent = pl + RPQ_MAX_LABELS;   // [2][RPQ_MAX_LABELS]: entered counts, this and other
-    RPQ_TRY(fill_u64(reinterpret_cast<uint64_t*>(c), kCtr, 0, s));
-    uint64_t* k = reinterpret_cast<uint64_t*>(keys.p);
+    RPQ_TRY(fill_u64(reinterpret_cast<uint64_t*>(c), Scratch::kCtr, 0, s));
+    RPQ_TRY(fill_u32(out->row_ptr, R + 1, kNoRow, s));
+    uint64_t* sorted = sc.keys;
     if (n_edges) {
+        // an edge outside the graph becomes key 0 here and an error below
         hipLaunchKernelGGL(k_make_keys, dim3(grid_for(n_edges)), dim3(kThreads), 0, s, a, lab, b, n_edges, V, L,
-                           k, c);
+                           sc.keys, c);
+        RPQ_LAUNCH_CHECK();
+        RPQ_TRY(radix_sort_u64(sc.keys, sc.alt, n_edges, bits_for(V ? V - 1 : 0), bits_for(R ? R - 1 : 0), sc.sort, s,
+                               &sorted));
+        const uint64_t tiles = (n_edges + kTile - 1) / kTile;
+        hipLaunchKernelGGL(k_uniq_count, dim3((unsigned)tiles), dim3(kThreads), 0, s, sorted, n_edges, sc.counts);
+        RPQ_LAUNCH_CHECK();
+        RPQ_TRY(exclusive_scan_u64(sc.counts, sc.counts, tiles, sc.scan, reinterpret_cast<uint64_t*>(c + 1), s));
+        hipLaunchKernelGGL(k_uniq_write, dim3((unsigned)tiles), dim3(kThreads), 0, s, sorted, n_edges, sc.counts,
+                           out->dst, out->row_ptr);
         RPQ_LAUNCH_CHECK();
     }
-    RPQ_HIP(hipMemcpyAsync(stage, c, 8, hipMemcpyDeviceToHost, s));
-    RPQ_HIP(hipStreamSynchronize(s));
-    if (stage[0]) {
-        set_error("edge list holds a vertex id >= n_vertices or a label id >= n_labels");
-        return RPQ_EINVAL;
-    }
-    uint64_t* sorted = k;
-    RPQ_TRY(radix_sort_u64(k, reinterpret_cast<uint64_t*>(alt.p), n_edges, bits_for(V ? V - 1 : 0),
-                           bits_for(R ? R - 1 : 0), sort_tmp.p, s, &sorted));
-    uint64_t* uniq = sorted == k ? reinterpret_cast<uint64_t*>(alt.p) : k;
-    uint64_t* fl = reinterpret_cast<uint64_t*>(flag.p);
-    uint64_t E = 0;
-    if (n_edges) {
-        hipLaunchKernelGGL(k_mark_first, dim3(grid_for(n_edges)), dim3(kThreads), 0, s, sorted, n_edges, fl);
-        RPQ_LAUNCH_CHECK();
-        RPQ_TRY(exclusive_scan_u64(fl, fl, n_edges, fl + ne + 1, reinterpret_cast<uint64_t*>(c + 1), s));
-        RPQ_HIP(hipMemcpyAsync(stage, c + 1, 8, hipMemcpyDeviceToHost, s));
-        RPQ_HIP(hipStreamSynchronize(s));
-        E = stage[0];
-    }
-    if (E >= 0xFFFFFFFFull) {
-        set_error("more than 2^32-1 distinct edges");
-        return RPQ_EUNSUPPORTED;
-    }
-    RPQ_TRY(dev_alloc(reinterpret_cast<void**>(&out->dst), (E ? E : 1) * 4));
-    RPQ_TRY(dev_alloc(reinterpret_cast<void**>(&out->row_ptr), (R + 1) * 4));
-    RPQ_TRY(dev_alloc(reinterpret_cast<void**>(&out->lmask), (uint64_t)V * 8));
-    if (n_edges) {
-        hipLaunchKernelGGL(k_compact, dim3(grid_for(n_edges, 8192)), dim3(kThreads), 0, s, sorted, fl, n_edges,
-                           uniq, out->dst, L, pl);
-        RPQ_LAUNCH_CHECK();
-    }
-    hipLaunchKernelGGL(k_row_ptr, dim3(grid_for(R + 1)), dim3(kThreads), 0, s, uniq, E, R, out->row_ptr);
+    const uint64_t rblocks = (R + kRows - 1) / kRows;
+    hipLaunchKernelGGL(k_row_min, dim3((unsigned)rblocks), dim3(kThreads), 0, s, out->row_ptr, R, sc.mins);
     RPQ_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_label_mask, dim3(grid_for(V, 8192)), dim3(kThreads), 0, s, out->row_ptr, V, L,
-                       out->lmask, c + 2);
+    hipLaunchKernelGGL(k_row_after, dim3(1), dim3(1024), 0, s, sc.mins, rblocks, c + 1);
+    RPQ_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_row_fill, dim3((unsigned)rblocks), dim3(kThreads), 0, s, out->row_ptr, R, L, sc.mins, c + 1,
+                       pl, c + 2);
+    RPQ_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_label_mask, dim3(grid_for(n_words * 64, 4096)), dim3(kThreads), 0, s, out->row_ptr, V, L,
+                       out->lmask);
     RPQ_LAUNCH_CHECK();
     // entered bits: for both directions from the other's masks once both are there, else from the edges
-    const uint64_t n_words = ((uint64_t)V + 63) / 64;
     const dim3 cgrid(grid_for(n_words, 32), L);
     for (int i = 0; i < 2; ++i) {
         rpq::Csr* t = i == 0 ? out : other;
         if (!t || (i == 0 && more)) continue;
-        RPQ_TRY(dev_alloc(reinterpret_cast<void**>(&t->entered), L * n_words * 8));
         if (other) {
             hipLaunchKernelGGL(k_entered_from_masks, dim3(grid_for(n_words * 64, 4096)), dim3(kThreads), 0, s,
                                i == 0 ? other->lmask : out->lmask, V, L, n_words, t->entered);
         } else {
             RPQ_TRY(fill_u64(t->entered, L * n_words, 0, s));
-            hipLaunchKernelGGL(k_entered, dim3(grid_for(E, 8192)), dim3(kThreads), 0, s, uniq, E, L, n_words, reinterpret_cast<unsigned long long*>(t->entered));
+            hipLaunchKernelGGL(k_entered, dim3(grid_for(n_edges, 8192)), dim3(kThreads), 0, s, sorted, n_edges, L,
+                               n_words, reinterpret_cast<unsigned long long*>(t->entered));
         }
         RPQ_LAUNCH_CHECK();
         hipLaunchKernelGGL(k_entered_counts, cgrid, dim3(kThreads), 0, s, t->entered, n_words,
                            ent + i * RPQ_MAX_LABELS);
         RPQ_LAUNCH_CHECK();
     }
-    RPQ_HIP(hipMemcpyAsync(stage, c, kCtr * 8, hipMemcpyDeviceToHost, s));
+    RPQ_HIP(hipMemcpyAsync(stage, c, Scratch::kCtr * 8, hipMemcpyDeviceToHost, s));
     RPQ_HIP(hipStreamSynchronize(s));
+    if (stage[0]) {
+        set_error("edge list holds a vertex id >= n_vertices or a label id >= n_labels");
+        return RPQ_EINVAL;
+    }
+    if (stage[1] >= 0xFFFFFFFFull) {
+        set_error("more than 2^32-1 distinct edges");
+        return RPQ_EUNSUPPORTED;
+    }
     out->nonempty_rows = stage[2];
+    if (per_label)
+        for (uint32_t l = 0; l < L; ++l) per_label[l] = stage[4 + l];
     for (uint32_t l = 0; l < L; ++l) {
         out->n_entered[l] = stage[4 + RPQ_MAX_LABELS + l];
         if (other) other->n_entered[l] = stage[4 + 2 * RPQ_MAX_LABELS + l];
     }
-    if (per_label)
-        for (uint32_t l = 0; l < L; ++l) per_label[l] = stage[4 + l];
-    *E_out = E;
+    *E_out = stage[1];
     return RPQ_OK;
-}
-
-void free_csr(rpq::Csr* c) {
-    if (c->row_ptr) (void)hipFree(c->row_ptr);
-    if (c->dst) (void)hipFree(c->dst);
-    if (c->lmask) (void)hipFree(c->lmask);
-    if (c->entered) (void)hipFree(c->entered);
-    *c = rpq::Csr();
 }
 
 void free_graph(rpq_graph* g) {
     if (!g) return;
-    free_csr(&g->out);
-    free_csr(&g->in);
+    if (g->out.mem) (void)hipFree(g->out.mem);
+    if (g->in.mem) (void)hipFree(g->in.mem);
     if (g->vlabel) (void)hipFree(g->vlabel);
-    if (g->h_stage) (void)hipHostFree(g->h_stage);
     delete g;
 }
 
@@ -310,19 +459,22 @@ int rpq_graph_create(const uint32_t* src, const uint8_t* label, const uint32_t* 
     g->V = n_vertices;
     g->L = n_labels;
     g->E_in = n_edges;
-    if (hipGetDevice(&g->device) != hipSuccess || hipHostMalloc(reinterpret_cast<void**>(&g->h_stage), 4096) !=
-                                                      hipSuccess) {
+    uint64_t* stage = rpq::host_stage();
+    if (hipGetDevice(&g->device) != hipSuccess || !stage) {
         rpq::set_error("HIP device or pinned staging unavailable");
         free_graph(g);
         return RPQ_EDEVICE;
     }
     const bool both = (flags & RPQ_BUILD_IN_CSR) != 0;
-    int rc = build_csr(src, label, dst, n_edges, n_vertices, n_labels, &g->out, nullptr, both, &g->E, g->per_label,
-                       g->h_stage, stream);
+    Scratch sc;
+    int rc = sc.alloc(n_edges, (uint64_t)n_vertices * n_labels);
+    if (rc == RPQ_OK)
+        rc = build_csr(src, label, dst, n_edges, n_vertices, n_labels, sc, &g->out, nullptr, both, &g->E,
+                       g->per_label, stage, stream);
     if (rc == RPQ_OK && both) {
         uint64_t e_in = 0;
-        rc = build_csr(dst, label, src, n_edges, n_vertices, n_labels, &g->in, &g->out, false, &e_in, nullptr,
-                       g->h_stage, stream);
+        rc = build_csr(dst, label, src, n_edges, n_vertices, n_labels, sc, &g->in, &g->out, false, &e_in, nullptr,
+                       stage, stream);
         g->has_in = rc == RPQ_OK;
     }
     if (rc == RPQ_OK && vertex_label) {

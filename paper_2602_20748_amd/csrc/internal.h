@@ -38,6 +38,7 @@ void clear_error();
 // ascending.  lmask[v] has bit l set when row (v, l) is non-empty; bit v of entered[l] is set when some
 // row (u, l) of this direction holds v, so that a search knows which vertices a label can lead to.
 struct Csr {
+    void* mem = nullptr;           // the one allocation that holds the arrays
     uint32_t* row_ptr = nullptr;   // [V * L + 1]
     uint32_t* dst = nullptr;       // [E]
     uint64_t* lmask = nullptr;     // [V]
@@ -57,7 +58,6 @@ struct rpq_graph {
     uint8_t* vlabel = nullptr;          // [V] or null
     uint64_t device_bytes = 0;
     int device = 0;
-    uint64_t* h_stage = nullptr;        // pinned host staging for small device->host reads
 };
 
 namespace rpq {
