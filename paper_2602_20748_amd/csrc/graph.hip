@@ -12,13 +12,13 @@
 // label masks from non-empty rows.  The in-edge CSR is the same construction
 // with source and destination swapped.
 //
-// One scratch allocation serves both directions and each direction's arrays
-// are one allocation: releasing several large allocations one after another
-// takes the runtime 5 ms each (16M edges both ways: 46 ms a call with twenty of
-// them, of which the kernels were 4).  The host waits once per direction.
+// One scratch allocation serves both directions, each direction's arrays are
+// one allocation, and released blocks are kept for the next graph (Blocks).
+// The host waits once per direction.
 #include "internal.h"
 
 #include <cstring>
+#include <mutex>
 #include <new>
 
 namespace {
@@ -270,26 +270,106 @@ __global__ void k_entered_counts(const uint64_t* __restrict__ entered, uint64_t 
     if ((threadIdx.x & 63) == 0 && c) atomicAdd(&counts[blockIdx.y], (unsigned long long)c);
 }
 
-struct DevBuf {
-    void* p = nullptr;
-    ~DevBuf() {
-        if (p) (void)hipFree(p);
+// Device memory of graphs and their builds.  The runtime takes 0.25 ms to release a block, and 15 ms and more
+// each while it is still clearing much other memory released shortly before: a build of 16M edges both ways
+// then took 45 ms, of which its kernels were 2, and takes 2.3 ms with its blocks kept.  So up to kKept bytes in
+// kSlots released blocks wait for the next build.  A block comes here only when no work uses it any more, so
+// any stream may take it; it goes back to the runtime when a newer block needs its room, when two builds in a
+// row had no use for it, or when an allocation here fails.
+class Blocks {
+public:
+    static constexpr uint64_t kKept = 1ull << 30;
+    static constexpr int kSlots = 16;
+
+    int take(uint64_t bytes, rpq::Block* out) {
+        bytes = bytes ? bytes : 8;
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        std::lock_guard<std::mutex> lk(mu_);
+        int best = -1;   // the smallest that fits and is at most twice as large
+        for (int i = 0; i < n_; ++i) {
+            const rpq::Block& b = kept_[i].b;
+            if (b.device == dev && b.bytes >= bytes && b.bytes / 2 <= bytes &&
+                (best < 0 || b.bytes < kept_[best].b.bytes))
+                best = i;
+        }
+        if (best >= 0) {
+            *out = kept_[best].b;
+            drop(best);
+            return RPQ_OK;
+        }
+        hipError_t e = hipMalloc(&out->p, bytes);
+        if (e == hipErrorOutOfMemory && n_) {
+            (void)hipGetLastError();
+            while (n_) release(0);
+            e = hipMalloc(&out->p, bytes);
+        }
+        if (e != hipSuccess) {
+            *out = rpq::Block();
+            rpq::set_error("hipMalloc(%llu) failed: %s", (unsigned long long)bytes, hipGetErrorString(e));
+            return e == hipErrorOutOfMemory ? RPQ_ENOMEM : RPQ_EDEVICE;
+        }
+        out->bytes = bytes;
+        out->device = dev;
+        return RPQ_OK;
     }
+    // idle: the caller has waited for everything on the current device that used the block
+    void give(rpq::Block* b, bool idle) {
+        if (!b->p) return;
+        int dev = -1;
+        (void)hipGetDevice(&dev);
+        std::lock_guard<std::mutex> lk(mu_);
+        if (idle && b->device == dev && b->bytes <= kKept) {
+            while (n_ == kSlots || total_ + b->bytes > kKept) release(0);   // oldest first
+            kept_[n_++] = {*b, builds_};
+            total_ += b->bytes;
+        } else {
+            (void)hipFree(b->p);
+        }
+        *b = rpq::Block();
+    }
+    void build_begins() {
+        std::lock_guard<std::mutex> lk(mu_);
+        ++builds_;
+        for (int i = n_; i-- > 0;)
+            if (builds_ - kept_[i].since > 2) release(i);
+    }
+
+private:
+    struct Kept {
+        rpq::Block b;
+        uint64_t since;   // builds begun when it came
+    };
+    void drop(int i) {
+        total_ -= kept_[i].b.bytes;
+        for (--n_; i < n_; ++i) kept_[i] = kept_[i + 1];
+    }
+    void release(int i) {
+        (void)hipFree(kept_[i].b.p);
+        drop(i);
+    }
+    std::mutex mu_;
+    Kept kept_[kSlots];
+    int n_ = 0;
+    uint64_t total_ = 0, builds_ = 0;
 };
 
-int dev_alloc(void** p, uint64_t bytes) {
-    hipError_t e = hipMalloc(p, bytes ? bytes : 8);
-    if (e != hipSuccess) {
-        *p = nullptr;
-        rpq::set_error("hipMalloc(%llu) failed: %s", (unsigned long long)bytes, hipGetErrorString(e));
-        return e == hipErrorOutOfMemory ? RPQ_ENOMEM : RPQ_EDEVICE;
-    }
-    return RPQ_OK;
+Blocks& blocks() {
+    static Blocks* b = new Blocks();   // outlives every graph; what it still holds goes with the process
+    return *b;
 }
 
 // Scratch of a build: the keys and their sorting, shared by the two directions.
 struct Scratch {
-    DevBuf mem;
+    rpq::Block mem;
+    hipStream_t stream;
+    explicit Scratch(hipStream_t s) : stream(s) {}
+    ~Scratch() {
+        const bool idle = hipStreamSynchronize(stream) == hipSuccess;   // a failed build may leave work queued
+        blocks().give(&mem, idle);
+    }
+    Scratch(const Scratch&) = delete;
+    Scratch& operator=(const Scratch&) = delete;
     uint64_t *keys, *alt, *counts, *scan;
     uint32_t* mins;
     void* sort;
@@ -309,7 +389,7 @@ struct Scratch {
                        o_scan = take((rpq::scan_temp_elems(tiles) + 1) * 8),
                        o_mins = take(((R + kRows - 1) / kRows) * 4), o_sort = take(rpq::radix_temp_bytes(n_edges)),
                        o_ctr = take(kCtr * 8);
-        RPQ_TRY(dev_alloc(&mem.p, off));
+        RPQ_TRY(blocks().take(off, &mem));
         char* b = reinterpret_cast<char*>(mem.p);
         keys = reinterpret_cast<uint64_t*>(b + o_keys);
         alt = reinterpret_cast<uint64_t*>(b + o_alt);
@@ -333,8 +413,8 @@ int build_csr(const uint32_t* a, const uint8_t* lab, const uint32_t* b, uint64_t
     const uint64_t n_words = ((uint64_t)V + 63) / 64;
     auto up = [](uint64_t x) { return (x + 255) / 256 * 256; };
     const uint64_t o_dst = up((R + 1) * 4), o_mask = o_dst + up(n_edges * 4 + 4), o_ent = o_mask + up((uint64_t)V * 8);
-    RPQ_TRY(dev_alloc(&out->mem, o_ent + L * n_words * 8));
-    char* mem = reinterpret_cast<char*>(out->mem);
+    RPQ_TRY(blocks().take(o_ent + L * n_words * 8, &out->mem));
+    char* mem = reinterpret_cast<char*>(out->mem.p);
     out->row_ptr = reinterpret_cast<uint32_t*>(mem);
     out->dst = reinterpret_cast<uint32_t*>(mem + o_dst);
     out->lmask = reinterpret_cast<uint64_t*>(mem + o_mask);
@@ -412,9 +492,10 @@ int build_csr(const uint32_t* a, const uint8_t* lab, const uint32_t* b, uint64_t
 
 void free_graph(rpq_graph* g) {
     if (!g) return;
-    if (g->out.mem) (void)hipFree(g->out.mem);
-    if (g->in.mem) (void)hipFree(g->in.mem);
-    if (g->vlabel) (void)hipFree(g->vlabel);
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
+    blocks().give(&g->out.mem, idle);
+    blocks().give(&g->in.mem, idle);
+    blocks().give(&g->vlabels, idle);
     delete g;
 }
 
@@ -466,7 +547,8 @@ int rpq_graph_create(const uint32_t* src, const uint8_t* label, const uint32_t* 
         return RPQ_EDEVICE;
     }
     const bool both = (flags & RPQ_BUILD_IN_CSR) != 0;
-    Scratch sc;
+    blocks().build_begins();
+    Scratch sc(stream);
     int rc = sc.alloc(n_edges, (uint64_t)n_vertices * n_labels);
     if (rc == RPQ_OK)
         rc = build_csr(src, label, dst, n_edges, n_vertices, n_labels, sc, &g->out, nullptr, both, &g->E,
@@ -478,10 +560,9 @@ int rpq_graph_create(const uint32_t* src, const uint8_t* label, const uint32_t* 
         g->has_in = rc == RPQ_OK;
     }
     if (rc == RPQ_OK && vertex_label) {
-        void* p = nullptr;
-        rc = dev_alloc(&p, n_vertices);
+        rc = blocks().take(n_vertices, &g->vlabels);
         if (rc == RPQ_OK) {
-            g->vlabel = reinterpret_cast<uint8_t*>(p);
+            g->vlabel = reinterpret_cast<uint8_t*>(g->vlabels.p);
             if (hipMemcpyAsync(g->vlabel, vertex_label, n_vertices, hipMemcpyDeviceToDevice, stream) != hipSuccess ||
                 hipStreamSynchronize(stream) != hipSuccess) {
                 rpq::set_error("copying vertex labels failed");
@@ -504,7 +585,6 @@ int rpq_graph_create(const uint32_t* src, const uint8_t* label, const uint32_t* 
 
 int rpq_graph_destroy(rpq_graph_t g) {
     if (!g) return RPQ_OK;
-    (void)hipDeviceSynchronize();
     free_graph(g);
     return RPQ_OK;
 }

@@ -33,12 +33,18 @@ void clear_error();
 
 #define RPQ_LAUNCH_CHECK() RPQ_HIP(hipGetLastError())
 
+struct Block {   // a device allocation
+    void* p = nullptr;
+    uint64_t bytes = 0;
+    int device = 0;
+};
+
 // One direction of the label-partitioned CSR.  Row r = v * n_labels + l holds
 // the neighbours of v over label l in dst[row_ptr[r] .. row_ptr[r + 1]),
 // ascending.  lmask[v] has bit l set when row (v, l) is non-empty; bit v of entered[l] is set when some
 // row (u, l) of this direction holds v, so that a search knows which vertices a label can lead to.
 struct Csr {
-    void* mem = nullptr;           // the one allocation that holds the arrays
+    Block mem;                     // the one allocation that holds the arrays
     uint32_t* row_ptr = nullptr;   // [V * L + 1]
     uint32_t* dst = nullptr;       // [E]
     uint64_t* lmask = nullptr;     // [V]
@@ -56,6 +62,7 @@ struct rpq_graph {
     rpq::Csr out, in;
     bool has_in = false;
     uint8_t* vlabel = nullptr;          // [V] or null
+    rpq::Block vlabels;                 // its allocation
     uint64_t device_bytes = 0;
     int device = 0;
 };
