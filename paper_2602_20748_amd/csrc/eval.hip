@@ -375,9 +375,14 @@ __global__ __launch_bounds__(1024) void k_tally_sum(const unsigned long long* __
     constexpr int N = kTallies + 2;
     __shared__ uint64_t s_part[16][N];
     uint64_t t[N] = {};
+    // unrolled: one block's loads all in flight together
+#pragma unroll
     for (unsigned b = threadIdx.x; b < kMaxLevelBlocks; b += 1024)
+#pragma unroll
         for (int i = 0; i < kTallies; ++i) t[i] += tally[(uint64_t)b * kTallyStride + i];
+#pragma unroll
     for (unsigned b = threadIdx.x; b < kMaxExtractBlocks; b += 1024)
+#pragma unroll
         for (int i = 0; i < 2; ++i) t[kTallies + i] += xtally[2 * (uint64_t)b + i];
     for (int i = 0; i < N; ++i) {
         const uint64_t x = rpqd::wave_sum_u64(t[i]);
@@ -955,6 +960,171 @@ __global__ __launch_bounds__(kBlock) void k_seed(Args a, uint32_t G, uint32_t K)
 }
 
 // ------------------------------------------------------------------------------------------------
+// The whole search of a small graph.  Sources do not meet each other's bits, so a block takes 32 of them
+// from the seeds to the fixpoint by itself, with a word of visited and a word of Next bits per row in LDS,
+// and writes its half words of the visited bitmap once: no list, no launch and no wait of the host per
+// level.  A level is a chain of dependent LDS and cache accesses between two barriers, 3.2 us (4.1 with the
+// frontier gathered from LDS and only four edges of a row by its own lane; fewer sources a block, or the
+// adjacency in LDS too, gained nothing); three launches and a quarter of a wait take 27.  1,000 vertices,
+// 5,000 edges, all pairs with keys in 40 levels: 1.30 -> 0.25 ms a call.
+// A listed row's Next word holds its frontier bits (they are in Vis) and the bits found at this level
+// (they are not), so two words a row do.
+// ------------------------------------------------------------------------------------------------
+constexpr uint32_t kSmallRows = 16384;         // two words each: 128 of the 160 KB of LDS
+// items of a level, which one block visits alone.  4,000 vertices, 400,000 edges, 3 states (1.2 M items):
+// 64 sources 0.40 ms against 0.49 by levels, one source 0.23 against 0.30; the gap closes from there on
+constexpr uint64_t kSmallItems = 1ull << 20;
+constexpr int kSmallBlock = 1024;
+constexpr int kOwn = 4;   // edges in flight a lane
+constexpr int kSmallWaves = kSmallBlock / 64;
+
+__global__ __launch_bounds__(kSmallBlock) void k_small_search(Args a, uint64_t max_len) {
+    extern __shared__ uint32_t s_rows[];
+    __shared__ uint32_t s_delta[RPQ_MAX_STATES * RPQ_MAX_LABELS];
+    __shared__ uint64_t s_qlab[RPQ_MAX_STATES];
+    __shared__ uint32_t s_base[RPQ_MAX_STATES];
+    __shared__ uint16_t s_queue[kSmallWaves][128];   // a wave's frontier rows
+    __shared__ uint64_t s_part[kSmallWaves];
+    const uint32_t R = a.R, tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    uint32_t* const s_vis = s_rows;
+    uint32_t* const s_next = s_rows + R;
+    for (uint32_t i = tid; i < a.Q * a.L; i += kSmallBlock) s_delta[i] = a.nfa->delta[i];
+    if (tid < a.Q) {
+        s_qlab[tid] = a.nfa->qlab[tid];
+        s_base[tid] = a.nfa->base[tid];
+    }
+    for (uint32_t r = tid; r < 2 * R; r += kSmallBlock) s_rows[r] = 0;
+    __syncthreads();
+    const uint64_t gi = (uint64_t)blockIdx.x * 32 + tid;
+    if (tid < 32 && gi < a.n_srcs) {
+        const uint32_t v = a.srcs ? a.srcs[gi] : (uint32_t)gi;
+        for (uint32_t f = a.nfa->init; f; f &= f - 1) atomicOr(&s_next[s_base[__ffs(f) - 1] + v], 1u << tid);
+    }
+    __syncthreads();
+    uint16_t* const queue = s_queue[wave];
+    uint32_t top = 1;
+    while (2 * top < a.Q) top *= 2;
+    auto visit = [&](uint32_t w, uint32_t bits, uint32_t to) {
+        for (; to; to &= to - 1) {
+            const uint32_t t = s_base[__ffs(to) - 1] + w;
+            const uint32_t n = bits & ~s_vis[t];
+            if (n) atomicOr(&s_next[t], n);
+        }
+    };
+    uint64_t eprod = 0, level = 0;
+    // every level with a frontier sets a bit of Vis, so the loop ends
+    for (;; ++level) {
+        // bit i: the thread's i-th row is on the frontier
+        uint32_t hot = 0;
+        for (uint32_t i0 = 0; i0 * kSmallBlock < R; i0 += 4) {
+            uint32_t v[4], n[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) {
+                const uint32_t r = (i0 + u) * kSmallBlock + tid;
+                v[u] = r < R ? s_vis[r] : 0;
+                n[u] = r < R ? s_next[r] : 0;
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) {
+                const uint32_t r = (i0 + u) * kSmallBlock + tid;
+                n[u] &= ~v[u];
+                if (r < R) {
+                    s_next[r] = n[u];
+                    s_vis[r] = v[u] | n[u];
+                }
+                hot |= (uint32_t)(n[u] != 0) << (i0 + u);
+            }
+        }
+        if (!__syncthreads_or((int)hot)) break;
+        if (level >= max_len) {   // recorded, not expanded
+            ++level;
+            break;
+        }
+        uint32_t queued = 0;   // wave-uniform
+        for (uint32_t i = 0; i * kSmallBlock < R || queued; ++i) {
+            const bool on = i * kSmallBlock < R && ((hot >> i) & 1);
+            const uint64_t m = __ballot(on);
+            if (on) queue[queued + __popcll(m & rpqd::lanemask_lt())] = (uint16_t)(i * kSmallBlock + tid);
+            queued += (uint32_t)__popcll(m);
+            if (queued == 0 || (queued < 64 && (i + 1) * kSmallBlock < R)) continue;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const uint32_t take = min(queued, 64u);
+            uint2 row = make_uint2(0, 0);   // its number and its frontier bits
+            if ((uint32_t)lane < take) {
+                row.x = queue[lane];
+                row.y = __hip_atomic_load(&s_next[row.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & s_vis[row.x];
+            }
+            const uint16_t rest = queue[64 + lane];
+            queued -= take;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if ((uint32_t)lane < queued) queue[lane] = rest;
+            uint32_t q = 0;   // the last state whose rows begin at or before the row
+            for (uint32_t step = top; step >= 1; step >>= 1)
+                if (q + step < a.Q && s_base[q + step] <= row.x) q += step;
+            const uint64_t at = (uint64_t)(row.x - s_base[q]) * a.L;
+            uint64_t labels = row.y ? s_qlab[q] : 0;
+            while (__ballot(labels != 0)) {
+                uint32_t lo = 0, deg = 0, to = 0;
+                if (labels) {
+                    const int l = __ffsll((long long)labels) - 1;
+                    labels &= labels - 1;
+                    lo = a.row_ptr[at + l];
+                    deg = a.row_ptr[at + l + 1] - lo;
+                    to = s_delta[q * a.L + l];
+                    eprod += (uint64_t)__popc(row.y) * __popc(to) * deg;
+                }
+                // a row's first edges by its own lane, the others spread over the wave
+                uint32_t w[kOwn];
+                for (int turn = 0; turn < 2 && __ballot(deg != 0); ++turn) {
+#pragma unroll
+                    for (int u = 0; u < kOwn; ++u) w[u] = (uint32_t)u < deg ? a.dst[lo + u] : 0;
+#pragma unroll
+                    for (int u = 0; u < kOwn; ++u) visit(w[u], row.y, (uint32_t)u < deg ? to : 0);
+                    lo += kOwn;
+                    deg = deg > kOwn ? deg - kOwn : 0;
+                }
+                if (__ballot(deg != 0) == 0) continue;
+                const uint32_t incl = rpqd::wave_incl_scan_u32(deg), excl = incl - deg;
+                const uint32_t total = __shfl(incl, 63, 64);
+                for (uint32_t i0 = 0; i0 < total; i0 += 64 * kOwn) {
+                    uint32_t c[kOwn];
+#pragma unroll
+                    for (int u = 0; u < kOwn; ++u) {
+                        const uint32_t i = i0 + u * 64 + lane;
+                        c[u] = 0;   // the last lane whose edges begin at or before item i
+#pragma unroll
+                        for (int step = 32; step >= 1; step >>= 1)
+                            if ((uint32_t)__shfl(excl, c[u] + step, 64) <= i) c[u] += step;
+                        const uint32_t e = (uint32_t)__shfl(lo - excl, c[u], 64) + i;
+                        w[u] = i < total ? a.dst[e] : 0;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kOwn; ++u) {
+                        const uint32_t bits_of = __shfl(row.y, c[u], 64), to_of = __shfl(to, c[u], 64);
+                        visit(w[u], bits_of, i0 + u * 64 + lane < total ? to_of : 0);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // the half words of these sources, zero beyond the last
+    const uint32_t slot = blockIdx.x * 32 / a.W, half = blockIdx.x * 32 % a.W / 32, halves = a.W / 32;
+    uint32_t* const vis = reinterpret_cast<uint32_t*>(a.vis) + (uint64_t)slot * R * halves + half;
+    for (uint32_t r = tid; r < R; r += kSmallBlock) vis[(uint64_t)r * halves] = s_vis[r];
+    eprod = rpqd::wave_sum_u64(eprod);
+    if (lane == 0) s_part[wave] = eprod;
+    __syncthreads();
+    if (tid == 0) {
+        eprod = 0;
+        for (int w = 0; w < kSmallWaves; ++w) eprod += s_part[w];
+        a.tally[(uint64_t)blockIdx.x * kTallyStride + T_EPROD] += eprod;
+        atomicMax(&a.counters[C_LASTLEVEL], (unsigned long long)level);   // levels with a frontier
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
 // extraction
 // ------------------------------------------------------------------------------------------------
 // Answer words each lane loads per vertex: four adjacent words (two 16-byte loads) where K allows.
@@ -1526,10 +1696,12 @@ int make_layout(const rpq_graph* g, const Plan& p, uint64_t n_sources, uint64_t 
     }
     x.R = (uint32_t)R;
     x.desc_cap = G * desc_per_unit;
-    // answer vertices per extraction wave: 4096, fewer while that leaves the device idle
+    // answer vertices per extraction wave: 4096, fewer while that leaves the device idle, and down to one
+    // step of a wave on the smallest graphs (1,000 vertices, all pairs: tallies 40 us and keys 65 us at 256)
     const uint64_t ans = std::max<uint64_t>(1, p.ans_bound);
     x.chunk = 4096;
     while (x.chunk > 256 && G * ((x.K + 3) / 4) * ((ans + x.chunk - 1) / x.chunk) < 8192) x.chunk /= 2;
+    while (x.chunk > 64 && G * ((x.K + 3) / 4) * ((ans + x.chunk - 1) / x.chunk) < 1024) x.chunk /= 2;
     x.nchunks = (uint32_t)((ans + x.chunk - 1) / x.chunk);
     uint64_t off = 0;
     auto take = [&](uint64_t bytes) {
@@ -2073,6 +2245,18 @@ namespace {
 // pageable stack buffer instead of the thread's pinned staging buffer, extraction stays on the
 // caller's stream (the layout then holds a single visited bitmap), and no profiling events are
 // recorded.
+// Whether k_small_search takes the call: its rows fit in LDS, every state has all its rows, and one block can
+// visit all edges of a level.  A caller that sets a knob of the level kernels gets them.
+bool small_search(const Plan& p, const Layout& x, uint64_t n_bits, const rpq_eval_opts* o) {
+    if (o && (o->batch_width || o->concurrency || o->chunk_edges || o->sync_every || o->visit)) return false;
+    if (x.R > kSmallRows || p.desc_items > kSmallItems || n_bits == 0 || n_bits > (uint64_t)x.G * x.W ||
+        (uint64_t)x.G * (x.W / 32) > kMaxLevelBlocks)
+        return false;
+    for (uint32_t q = 0; q < p.dn.Q; ++q)
+        if (p.dn.kind[q] != ROW_ALL) return false;
+    return true;
+}
+
 int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64_t n_sources, uint32_t flags,
               const rpq_eval_opts* opts, const uint64_t* target, void* workspace, uint64_t workspace_bytes,
               rpq_result* res, hipStream_t stream, bool noalloc, const rpq_pair_stream* ps = nullptr) {
@@ -2209,7 +2393,8 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
     place_rows(plan, x.W, plan.dn.base);
     RPQ_HIP(hipMemcpyAsync(ws + x.off_nfa, &plan.dn, sizeof plan.dn, hipMemcpyHostToDevice, stream));
     a.target = target;
-    const bool order = x.order && n_bits > kOrderSources;
+    const bool small = small_search(plan, x, n_bits, opts);
+    const bool order = x.order && n_bits > kOrderSources && !small;
     OrderArgs oa;
     std::memset(&oa, 0, sizeof oa);
     oa.row_ptr = a.row_ptr;
@@ -2230,7 +2415,7 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
     a.bit_of = order ? oa.bit_of : nullptr;
     a.n_srcs = n_bits;
     const uint64_t bitmap_words = (uint64_t)x.R * x.K;   // of one unit
-    RPQ_TRY(rpq::fill_u64(a.touch, ((uint64_t)x.G * x.R + 63) / 64, 0, stream));
+    if (!small) RPQ_TRY(rpq::fill_u64(a.touch, ((uint64_t)x.G * x.R + 63) / 64, 0, stream));
     if (!x.seen_or) RPQ_TRY(rpq::fill_u64(a.next, x.G * bitmap_words, 0, stream));
 
     const uint64_t per_group = (uint64_t)x.G * x.W;
@@ -2280,59 +2465,65 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
             hipLaunchKernelGGL(k_order_place, og, dim3(kBlock), 0, stream, oa);
             RPQ_LAUNCH_CHECK();
         }
-        // the bitmap's previous group must be extracted before it is cleared for this one
-        if (side.stream && grp >= 2) RPQ_HIP(hipStreamWaitEvent(stream, side.extracted[buf], 0));
-        if (x.seen_or && G_eff == x.G) {   // Vis and Next lie side by side
-            const uint64_t* lo = std::min(a.vis, a.next);
-            const uint64_t span = (uint64_t)(std::max(a.vis, a.next) - lo) + x.G * bitmap_words;
-            RPQ_TRY(rpq::fill_u64(const_cast<uint64_t*>(lo), span, 0, stream));
+        if (small) {
+            hipLaunchKernelGGL(k_small_search, dim3(G_eff * (x.W / 32)), dim3(kSmallBlock), x.R * 8, stream, a,
+                               x.max_len);
+            RPQ_LAUNCH_CHECK();
         } else {
-            RPQ_TRY(rpq::fill_u64(a.vis, G_eff * bitmap_words, 0, stream));
-            if (x.seen_or) RPQ_TRY(rpq::fill_u64(a.next, G_eff * bitmap_words, 0, stream));
-        }
-        RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.full), (G_eff * (uint64_t)x.R + 7) / 8, 0, stream));
-        hipLaunchKernelGGL(k_seed, dim3((unsigned)(((uint64_t)G_eff * x.W + kBlock - 1) / kBlock)), dim3(kBlock), 0,
-                           stream, a, G_eff, x.K);
-        RPQ_LAUNCH_CHECK();
-        const uint64_t n_rows = (uint64_t)G_eff * x.R;
-        RPQ_DISPATCH_K(x.K, RPQ_TRY(launch_finalize<KK>(a, 0, n_rows, 0, x.max_len > 0, stream)));
-        uint64_t level = 1;
-        int p = 1;
-        // a first-reach distance in the product graph is below Q * V, so the
-        // fixpoint arrives within Q * V + 1 levels; more means a defect
-        const uint64_t level_bound = (uint64_t)x.Q * x.V + 2;
-        uint64_t launched = 0;
-        // level l expands depth l - 1 and finalizes depth l; a length bound k stops after level k
-        while (level <= x.max_len) {
-            uint32_t n_launch = 0;
-            for (; n_launch < x.sync_every && level <= x.max_len; ++n_launch) {
-                RPQ_DISPATCH_K(x.K, RPQ_TRY(launch_level<KK>(a, p, n_rows, (uint32_t)level, level < x.max_len,
-                                                              !noalloc, stream)));
-                p ^= 1;
-                ++level;
+            // the bitmap's previous group must be extracted before it is cleared for this one
+            if (side.stream && grp >= 2) RPQ_HIP(hipStreamWaitEvent(stream, side.extracted[buf], 0));
+            if (x.seen_or && G_eff == x.G) {   // Vis and Next lie side by side
+                const uint64_t* lo = std::min(a.vis, a.next);
+                const uint64_t span = (uint64_t)(std::max(a.vis, a.next) - lo) + x.G * bitmap_words;
+                RPQ_TRY(rpq::fill_u64(const_cast<uint64_t*>(lo), span, 0, stream));
+            } else {
+                RPQ_TRY(rpq::fill_u64(a.vis, G_eff * bitmap_words, 0, stream));
+                if (x.seen_or) RPQ_TRY(rpq::fill_u64(a.next, G_eff * bitmap_words, 0, stream));
             }
-            launched += n_launch;
-            RPQ_HIP(hipMemcpyAsync(stage, a.counters, C_NCOUNTERS * 8, hipMemcpyDeviceToHost, stream));
-            if (ps) RPQ_TRY(st.pump(false));   // the previous group's windows, while these levels run
-            RPQ_HIP(hipStreamSynchronize(stream));
-            if (!noalloc && profiler().on) profile_resolve();
-            if (stage[C_ERR] & (ERR_LIST | ERR_DESC)) {
-                rpq::set_error("internal capacity exceeded (flags 0x%llx)", (unsigned long long)stage[C_ERR]);
-                return RPQ_EDEVICE;
+            RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.full), (G_eff * (uint64_t)x.R + 7) / 8, 0, stream));
+            hipLaunchKernelGGL(k_seed, dim3((unsigned)(((uint64_t)G_eff * x.W + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+                               stream, a, G_eff, x.K);
+            RPQ_LAUNCH_CHECK();
+            const uint64_t n_rows = (uint64_t)G_eff * x.R;
+            RPQ_DISPATCH_K(x.K, RPQ_TRY(launch_finalize<KK>(a, 0, n_rows, 0, x.max_len > 0, stream)));
+            uint64_t level = 1;
+            int p = 1;
+            // a first-reach distance in the product graph is below Q * V, so the
+            // fixpoint arrives within Q * V + 1 levels; more means a defect
+            const uint64_t level_bound = (uint64_t)x.Q * x.V + 2;
+            uint64_t launched = 0;
+            // level l expands depth l - 1 and finalizes depth l; a length bound k stops after level k
+            while (level <= x.max_len) {
+                uint32_t n_launch = 0;
+                for (; n_launch < x.sync_every && level <= x.max_len; ++n_launch) {
+                    RPQ_DISPATCH_K(x.K, RPQ_TRY(launch_level<KK>(a, p, n_rows, (uint32_t)level, level < x.max_len,
+                                                                  !noalloc, stream)));
+                    p ^= 1;
+                    ++level;
+                }
+                launched += n_launch;
+                RPQ_HIP(hipMemcpyAsync(stage, a.counters, C_NCOUNTERS * 8, hipMemcpyDeviceToHost, stream));
+                if (ps) RPQ_TRY(st.pump(false));   // the previous group's windows, while these levels run
+                RPQ_HIP(hipStreamSynchronize(stream));
+                if (!noalloc && profiler().on) profile_resolve();
+                if (stage[C_ERR] & (ERR_LIST | ERR_DESC)) {
+                    rpq::set_error("internal capacity exceeded (flags 0x%llx)", (unsigned long long)stage[C_ERR]);
+                    return RPQ_EDEVICE;
+                }
+                if (stage[C_LIST + p] == 0) break;   // the last finalize produced no new entries
+                if (launched > level_bound) {
+                    rpq::set_error("no fixpoint after %llu levels", (unsigned long long)launched);
+                    return RPQ_EDEVICE;
+                }
             }
-            if (stage[C_LIST + p] == 0) break;   // the last finalize produced no new entries
-            if (launched > level_bound) {
-                rpq::set_error("no fixpoint after %llu levels", (unsigned long long)launched);
-                return RPQ_EDEVICE;
+            if (launched == 0) {   // a bound of 0: only the seeds' zero-length walks
+                RPQ_HIP(hipMemcpyAsync(stage, a.counters, C_NCOUNTERS * 8, hipMemcpyDeviceToHost, stream));
+                RPQ_HIP(hipStreamSynchronize(stream));
             }
+            const uint64_t lv = stage[C_LASTLEVEL];   // levels with a non-empty frontier, seeds included
+            levels_total += lv;
+            if (lv > 0 && lv - 1 > max_depth) max_depth = lv - 1;
         }
-        if (launched == 0) {   // a bound of 0: only the seeds' zero-length walks
-            RPQ_HIP(hipMemcpyAsync(stage, a.counters, C_NCOUNTERS * 8, hipMemcpyDeviceToHost, stream));
-            RPQ_HIP(hipStreamSynchronize(stream));
-        }
-        const uint64_t lv = stage[C_LASTLEVEL];   // levels with a non-empty frontier, seeds included
-        levels_total += lv;
-        if (lv > 0 && lv - 1 > max_depth) max_depth = lv - 1;
         if (side.stream) {
             RPQ_HIP(hipEventRecord(side.leveled, stream));
             RPQ_HIP(hipStreamWaitEvent(xs, side.leveled, 0));
@@ -2397,6 +2588,10 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
     RPQ_LAUNCH_CHECK();
     RPQ_HIP(hipMemcpyAsync(stage, a.counters, C_NCOUNTERS * 8, hipMemcpyDeviceToHost, stream));
     RPQ_HIP(hipStreamSynchronize(stream));
+    if (small) {
+        levels_total = stage[C_LASTLEVEL];
+        max_depth = levels_total ? levels_total - 1 : 0;
+    }
     const uint64_t* const tally = stage + C_TALLY;
     if (!noalloc) {
         Profiler& pr = profiler();
