@@ -130,8 +130,7 @@ struct BArgs {
     uint64_t* next;          // two reads: bits found at this level; seen_or: Vis as of the last finalize
     uint64_t* touch;
     uint64_t* ever;          // [G][slot_stride bits]: row touched at some level of the slot's unit
-    uint64_t* ans;
-    uint64_t* summ;          // [G][V/64 rounded up]: bit v set when Ans row v is non-empty
+    uint64_t* summ;          // [G][V/64 rounded up]: bit v set when a final state's row of v is non-empty
     uint32_t* ids0;
     uint32_t* ids1;
     uint64_t* rows0;
@@ -482,43 +481,105 @@ __device__ uint32_t phase_decide(const BArgs& a, uint32_t iter) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// retire: extraction over the non-empty Ans rows of each retiring slot
+// retire: extraction over the vertices that a retiring slot's summary lists
 // ------------------------------------------------------------------------------------------------
-template <int K, bool WRITE>
+// parts of a chunk where no chunk totals are kept: a part costs its per-source sums once per word of a row, a
+// whole chunk 64 dependent loads (256 single sources of R-MAT 18: 11.0 ms whole, 10.4 in quarters; 64 units of
+// R-MAT 20, 16 words a row: 60.0 whole, 58.0 in halves, 61.0 in quarters)
+template <int K>
+constexpr uint32_t drain_split() { return K <= 4 ? 4 : 2; }
+
+// SPLIT: parts of a chunk that waves take alone (the queries want no keys)
+template <int K, bool WRITE, uint32_t SPLIT>
 __device__ void phase_retire_extract(const BArgs& a, const uint32_t* list, uint32_t n_ret) {
     const int lane = threadIdx.x & 63;
-    const uint64_t total = (uint64_t)n_ret * K * a.nchunks;
+    constexpr uint32_t kPartV = kChunkV / SPLIT;
+    const uint32_t nchunks = a.nchunks * SPLIT;
+    const uint64_t total = (uint64_t)n_ret * K * nchunks;
+    // neighbouring waves take the words of the same rows
     for (uint64_t wv = gwave(a); wv < total; wv += gwaves(a)) {
-        const uint32_t chunk = (uint32_t)(wv % a.nchunks);
-        const uint32_t k = (uint32_t)((wv / a.nchunks) % K);
-        const uint32_t slot = ld32(&list[wv / ((uint64_t)a.nchunks * K)]);
+        const uint32_t k = (uint32_t)(wv % K);
+        const uint32_t chunk = (uint32_t)((wv / K) % nchunks);
+        const uint32_t slot = ld32(&list[wv / ((uint64_t)nchunks * K)]);
         const uint32_t u = ld32(&a.slots[slot].unit);
         const BUnit unit = a.units[u & a.unit_mask];
         const BQuery& Qy = a.queries[unit.query];
-        if (WRITE && !Qy.pairs) continue;
+        if ((WRITE && !Qy.pairs) || k * 64 >= unit.n) continue;
+        const bool tallies = Qy.per_source || Qy.pairs;   // counts and checksums per source
         const uint32_t j = k * 64 + lane;
         const bool valid = j < unit.n;
         const uint64_t sidx = unit.src_off + j;
         const uint64_t s = valid ? (Qy.sources ? Qy.sources[sidx] : sidx) : 0;
-        const uint32_t vbeg = chunk * kChunkV;
-        // the chunk's 64 summary words: bit set = Ans row non-empty
+        const uint32_t vbeg = chunk * kPartV;
+        if (vbeg >= a.V) continue;
+        const uint32_t finals = a.nfas[unit.query].final;
+        // the part's summary words (64 in a whole chunk): bit set = some source reaches the vertex
         const uint64_t sw_i = (uint64_t)slot * a.summ_words + vbeg / 64 + lane;
-        const uint64_t sw = (vbeg / 64 + lane < a.summ_words) ? xld(a.summ + sw_i) : 0;
+        const uint64_t sw = ((uint32_t)lane < kPartV / 64 && vbeg / 64 + lane < a.summ_words) ? xld(a.summ + sw_i) : 0;
         uint64_t cnt = 0, h = 0, cursor = 0;
         const rpqd::MixSource ms = rpqd::mix_source((uint32_t)s);
         const uint64_t pidx = ((uint64_t)slot * a.W + j) * a.nchunks + chunk;
         if (WRITE && valid) cursor = a.srcbase[(uint64_t)slot * a.W + j] + a.partial[pidx];
-        // per 64-vertex group with a non-empty summary word: one load per lane (lane = vertex),
-        // then the non-zero words in ascending vertex order
+        // per 64-vertex group with a non-empty summary word: one load per lane (lane = vertex), issued a
+        // group ahead; then, as in the plain form, the word block by rows (lane = source) or by columns
+        // (lane = vertex), whichever takes fewer steps.  One source of R-MAT 18 has 64 times fewer by
+        // columns: 256 of them 1.4 ms of the run by rows alone.
         uint64_t any = __ballot(sw != 0);
-        while (any) {
+        auto load = [&](uint32_t* vg) {   // the next group's words
             const int wl = __ffsll((long long)any) - 1;
             any &= any - 1;
             uint64_t bits = __shfl(sw, wl, 64);
-            const uint32_t vg = vbeg + (uint32_t)wl * 64;
-            if (Qy.target) bits &= Qy.target[vg >> 6];   // vg is a multiple of 64
-            const uint64_t mine = ((bits >> lane) & 1) ? xld(a.ans + ((uint64_t)slot * a.V + vg + lane) * K + k) : 0;
+            *vg = vbeg + (uint32_t)wl * 64;
+            if (Qy.target) bits &= Qy.target[*vg >> 6];   // vg is a multiple of 64
+            uint64_t x = 0;   // the OR of the vertex's rows of final states
+            if ((bits >> lane) & 1)
+                for (uint32_t f = finals; f; f &= f - 1)
+                    x |= xld(a.vis + ((uint64_t)slot * a.slot_stride + (uint64_t)(__ffs(f) - 1) * a.V + *vg + lane) * K + k);
+            return x;
+        };
+        uint32_t vg = 0, vg_next = 0;
+        bool more = any != 0;
+        uint64_t mine = 0, mine_next = more ? load(&vg_next) : 0;
+        while (more) {
+            mine = mine_next;
+            vg = vg_next;
+            more = any != 0;
+            if (more) mine_next = load(&vg_next);
             uint64_t nz = __ballot(mine != 0);
+            if (nz == 0) continue;
+            uint64_t cols = mine;
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) cols |= __shfl_xor(cols, o, 64);
+            const uint32_t nr = (uint32_t)__popcll(nz), nc = (uint32_t)__popcll(cols);
+            if (WRITE ? nc < 8 * nr : tallies ? 5 * nc < 2 * nr : 3 * nc < 2 * nr) {
+                while (cols) {
+                    const int c = __ffsll((long long)cols) - 1;
+                    cols &= cols - 1;
+                    const bool bit = (mine >> c) & 1;
+                    const uint32_t sc = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)s, c);
+                    const uint64_t key = ((uint64_t)sc << 32) | (vg + lane);
+                    const uint64_t m = __ballot(bit);
+                    if (WRITE) {
+                        const uint64_t cur = rpqd::readlane_u64(cursor, c);
+                        const uint64_t at = cur + __popcll(m & rpqd::lanemask_lt());
+                        if (bit && at < Qy.capacity) Qy.stage[at] = key;
+                        if (lane == c) cursor = cur + __popcll(m);
+                    } else {
+                        const uint64_t hv = bit ? rpqd::mix64(key) : 0;
+                        if (tallies) {
+                            const uint64_t hs = rpqd::wave_sum_u64(hv);
+                            if (lane == c) {
+                                cnt += __popcll(m);
+                                h += hs;
+                            }
+                        } else {
+                            cnt += bit;
+                            h += hv;
+                        }
+                    }
+                }
+                continue;
+            }
             while (nz) {
                 const int jj = __ffsll((long long)nz) - 1;
                 nz &= nz - 1;
@@ -607,10 +668,9 @@ __device__ void phase_retire_prefix(const BArgs& a, uint32_t n_ret) {
     }
 }
 
-// clear the rows a retiring unit visited, its Ans rows and summary; the slot becomes idle
+// clear the rows a retiring unit visited and its summary; the slot becomes idle
 template <int K>
 __device__ void phase_retire_clear(const BArgs& a, const uint32_t* list, uint32_t n_ret) {
-    const int lane = threadIdx.x & 63;
     // Vis rows from the per-slot log, and the slot's first-visit bits
     for (uint32_t r = 0; r < n_ret; ++r) {
         const uint32_t slot = ld32(&list[r]);
@@ -640,21 +700,10 @@ __device__ void phase_retire_clear(const BArgs& a, const uint32_t* list, uint32_
             }
         }
     }
-    // Ans rows flagged in the summary, then the summary itself
     for (uint32_t r = 0; r < n_ret; ++r) {
-        const uint32_t slot = ld32(&list[r]);
-        for (uint64_t w0 = gwave(a) * 64; w0 < a.summ_words; w0 += gwaves(a) * 64) {
-            const uint64_t wi = w0 + lane;
-            uint64_t sw = wi < a.summ_words ? xld(a.summ + (uint64_t)slot * a.summ_words + wi) : 0;
-            if (sw) a.summ[(uint64_t)slot * a.summ_words + wi] = 0;
-            while (sw) {
-                const int bb = __ffsll((long long)sw) - 1;
-                sw &= sw - 1;
-                uint64_t* an = a.ans + ((uint64_t)slot * a.V + wi * 64 + bb) * K;
-#pragma unroll
-                for (int k = 0; k < K; ++k) an[k] = 0;
-            }
-        }
+        uint64_t* summ = a.summ + (uint64_t)ld32(&list[r]) * a.summ_words;
+        for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < a.summ_words; i += (uint64_t)a.n_blocks * kBlock)
+            summ[i] = 0;
     }
     // The slot itself (log length, state) is reset in the next phase: other blocks may
     // still be reading log_n in this one.
@@ -782,7 +831,7 @@ __device__ void phase_seed(const BArgs& a, int p, uint32_t iter) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// finalize: list p^1 -> frontier rows, Vis, Ans (+ summary), slices of heavy entries.  First visits are
+// finalize: list p^1 -> frontier rows, Vis, summary, slices of heavy entries.  First visits are
 // logged earlier, by the compaction (and the seeding) that put the rows on the list.
 // Word phase: groups of K lanes per row; row phase: lane per row (as in the plain form).
 // ------------------------------------------------------------------------------------------------
@@ -807,7 +856,7 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
         uint32_t row32 = 0, slot = 0, lrow = 0, q = 0, v = 0, qid = 0;
         uint64_t eprod = 0, work = 0;
         const BNfa* nfa = a.nfas;
-        uint32_t my_ans = 0xFFFFFFFFu;   // Ans row of a final-state entry, else none
+        bool fin = false;   // entry of a final state
         // at the depth bound of a length-bounded query a row is recorded (Vis, Ans) but gets an
         // empty frontier row and no work: it is never expanded
         bool stop = false;
@@ -819,7 +868,7 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
             v = lrow - q * V;
             qid = ld32(&a.slots[slot].query);
             nfa = a.nfas + qid;
-            if ((nfa->final >> q) & 1) my_ans = slot * V + v;
+            fin = (nfa->final >> q) & 1;
             stop = iter - ld32(&a.slots[slot].start_iter) >= a.queries[qid].max_len;
         }
         const uint32_t n_here = (uint32_t)min<uint64_t>(fb, n - e0);
@@ -858,13 +907,12 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
         }
         uint32_t my_pc = 0;   // new source bits of this lane's row
         for (uint32_t j = 0; j < n_here; j += GS * kUnroll) {
-            uint32_t r[kUnroll], an[kUnroll], sp[kUnroll];
+            uint32_t r[kUnroll], sp[kUnroll];
             uint64_t nk[kUnroll], ov[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const uint32_t idx = j + u * GS + grp;
                 r[u] = __shfl(row32, idx & 63, 64);
-                an[u] = __shfl(my_ans, idx & 63, 64);
                 sp[u] = __shfl((uint32_t)stop, idx & 63, 64);
                 ov[u] = idx < n_here ? xld(a.next + (uint64_t)r[u] * K + k) : 0;
                 if (SEEN) nk[u] = idx < n_here ? xld(a.vis + (uint64_t)r[u] * K + k) : 0;
@@ -883,7 +931,6 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
                         if (!SEEN) a.vis[(uint64_t)r[u] * K + k] |= nk[u];
                         pc = (uint32_t)__popcll(nk[u]);
                         ++t_fwords;
-                        if (an[u] != 0xFFFFFFFFu) or_relaxed(a.ans + (uint64_t)an[u] * K + k, nk[u]);
                     }
                 }
 #pragma unroll
@@ -896,7 +943,7 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
         if (active) {
             const uint32_t pc = my_pc;
             ++t_frows;
-            if (my_ans != 0xFFFFFFFFu && pc)
+            if (fin && pc)
                 or_relaxed(&a.summ[(uint64_t)slot * a.summ_words + v / 64], 1ull << (v & 63));
             eprod = (uint64_t)pc * work;
         }
@@ -976,7 +1023,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_batch(BArgs a) {
         const uint32_t* drain = a.drain + (uint64_t)((iter - 1) & 1) * a.G;
         const uint32_t n_dr = (uint32_t)ld(&a.ctl->n_drain[(iter - 1) & 1]);
         phase_expand<K, SEEN>(a, p, t_items, t_descs, t_wread, t_wupd);
-        if (n_dr) phase_retire_extract<K, false>(a, drain, n_dr);
+        if (n_dr) phase_retire_extract<K, false, drain_split<K>()>(a, drain, n_dr);
         BAR(0);
         phase_compact(a, p, iter);
         if (n_dr) phase_retire_clear<K>(a, drain, n_dr);
@@ -987,12 +1034,12 @@ __global__ __launch_bounds__(kBlock, 4) void k_batch(BArgs a) {
         BAR(2);
         const uint32_t n_ret = (uint32_t)ld(&a.ctl->n_retiring);
         if (n_ret) {
-            phase_retire_extract<K, false>(a, a.retiring, n_ret);
+            phase_retire_extract<K, false, 1>(a, a.retiring, n_ret);
             BAR(3);
             if (ld(&a.ctl->n_pairs_retiring)) {
                 phase_retire_prefix(a, n_ret);
                 BAR(4);
-                phase_retire_extract<K, true>(a, a.retiring, n_ret);
+                phase_retire_extract<K, true, 1>(a, a.retiring, n_ret);
                 BAR(4);
             }
             phase_retire_clear<K>(a, a.retiring, n_ret);
@@ -1202,7 +1249,6 @@ __global__ __launch_bounds__(kBlock) void k_batch_clear(BArgs a, uint32_t K) {
     clear(a.next, G * a.slot_stride * K);
     clear(a.touch, G * a.slot_stride / 64);
     clear(a.ever, G * a.slot_stride / 64);
-    clear(a.ans, G * a.V * K);
     clear(a.summ, G * a.summ_words);
 }
 
@@ -1254,7 +1300,6 @@ struct Layout {
     uint64_t off_segs, off_srcs, off_pos, off_order;
     uint64_t slot_stride, summ_words, list_cap, desc_cap, log_cap, stage_keys;
     uint64_t off_ctl, off_nfas, off_queries, off_qout, off_units, off_slots, off_vis, off_next, off_touch, off_ever,
-        off_ans,
         off_summ, off_ids[2], off_rows[2], off_desc[2], off_logs, off_retiring, off_drain, off_partial, off_srcbase,
         off_stage,
         off_utotal, off_ustart, off_uprefix, off_scan_tmp, total;
@@ -1321,9 +1366,9 @@ void size_slots(const rpq_graph* g, uint32_t max_succ, bool auto_chunk, uint32_t
     *desc_per_slot = (2 * (uint64_t)x->Qmax * max_succ * g->E / x->H + 2) / share + 64;
     x->log_cap = std::max<uint64_t>(64, x->slot_stride / share);
     const uint64_t list_per_slot = x->slot_stride / share + 64;
-    // per slot: Vis + Next, touch and first-visit bits, Ans, summary, first-visit log, and its share
+    // per slot: Vis + Next, touch and first-visit bits, summary, first-visit log, and its share
     // of the two frontier lists (row id + K-word row per entry) and of the two slice buffers
-    *per_slot = x->slot_stride * x->K * 8 * 2 + x->slot_stride / 4 + (uint64_t)g->V * x->K * 8 + x->summ_words * 8 +
+    *per_slot = x->slot_stride * x->K * 8 * 2 + x->slot_stride / 4 + x->summ_words * 8 +
                 x->log_cap * 4 + 2 * list_per_slot * (4 + x->K * 8) + 2 * *desc_per_slot * sizeof(Desc);
 }
 
@@ -1347,7 +1392,6 @@ void place(const rpq_graph* g, uint32_t nq, uint64_t n_unit_entries, Layout* x) 
     x->off_next = take(G * x->slot_stride * x->K * 8);
     x->off_touch = take(G * x->slot_stride / 8);
     x->off_ever = take(G * x->slot_stride / 8);
-    x->off_ans = take(G * (uint64_t)g->V * x->K * 8);
     x->off_summ = take(G * x->summ_words * 8);
     for (int p = 0; p < 2; ++p) {
         x->off_ids[p] = take(x->list_cap * 4);
@@ -1489,7 +1533,6 @@ BArgs args_for(const rpq_graph* g, const Layout& x, char* ws, unsigned n_blocks,
     a.next = reinterpret_cast<uint64_t*>(ws + x.off_next);
     a.touch = reinterpret_cast<uint64_t*>(ws + x.off_touch);
     a.ever = reinterpret_cast<uint64_t*>(ws + x.off_ever);
-    a.ans = reinterpret_cast<uint64_t*>(ws + x.off_ans);
     a.summ = reinterpret_cast<uint64_t*>(ws + x.off_summ);
     a.ids0 = reinterpret_cast<uint32_t*>(ws + x.off_ids[0]);
     a.ids1 = reinterpret_cast<uint32_t*>(ws + x.off_ids[1]);
@@ -2232,7 +2275,6 @@ int resident_create(rpq_graph* g, uint32_t W, uint32_t G, uint32_t Qmax, uint32_
     RPQ_TRY(rpq::fill_u64(a.next, (uint64_t)x.G * x.slot_stride * x.K, 0, stream));
     RPQ_TRY(rpq::fill_u64(a.touch, (uint64_t)x.G * x.slot_stride / 64, 0, stream));
     RPQ_TRY(rpq::fill_u64(a.ever, (uint64_t)x.G * x.slot_stride / 64, 0, stream));
-    RPQ_TRY(rpq::fill_u64(a.ans, (uint64_t)x.G * g->V * x.K, 0, stream));
     RPQ_TRY(rpq::fill_u64(a.summ, (uint64_t)x.G * x.summ_words, 0, stream));
     RPQ_TRY(rpq::fill_u64(a.unit_total, kResRing, 0, stream));
     RPQ_HIP(hipStreamSynchronize(stream));
