@@ -46,6 +46,16 @@ __global__ void k_make_keys(const uint32_t* __restrict__ a, const uint8_t* __res
     }
 }
 
+// Keys (u, l, w) of one direction become (w, l, u) of the other.
+__global__ void k_turn_keys(uint64_t* __restrict__ keys, uint64_t n, uint32_t L) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        const uint64_t k = keys[i];
+        const uint32_t row = (uint32_t)(k >> 32), u = row / L, l = row - u * L;
+        keys[i] = ((uint64_t)((uint32_t)k * L + l) << 32) | u;
+    }
+}
+
 // Distinct keys: a block takes kTile sorted keys; a first pass counts those that differ from their
 // predecessor, a second writes them at the prefix of the counts and marks the start of each row.
 constexpr uint32_t kTile = 2048;
@@ -157,26 +167,27 @@ __global__ __launch_bounds__(1024) void k_row_after(uint32_t* __restrict__ mins,
     }
 }
 
-// In place: start becomes row_ptr[0 .. R].  Rows are v * L + l, so a row's label is its remainder.
-__global__ __launch_bounds__(kThreads) void k_row_fill(uint32_t* __restrict__ row_ptr, uint64_t R, uint32_t L,
+// In place: start becomes row_ptr[0 .. R].
+__global__ __launch_bounds__(kThreads) void k_row_fill(uint32_t* __restrict__ row_ptr, uint64_t R,
                                                        const uint32_t* __restrict__ after,
-                                                       const unsigned long long* __restrict__ n_edges,
-                                                       unsigned long long* __restrict__ per_label,
-                                                       unsigned long long* __restrict__ nonempty) {
+                                                       const unsigned long long* __restrict__ n_edges) {
     constexpr uint32_t kEach = kRows / kThreads;   // consecutive rows of a thread
+    static_assert(kEach == 8, "two 16-byte accesses");
     __shared__ uint32_t s_w[kThreads / 64];
-    __shared__ uint32_t s_lab[RPQ_MAX_LABELS];
-    __shared__ uint32_t s_rows;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (uint32_t i = threadIdx.x; i < L; i += kThreads) s_lab[i] = 0;
-    if (threadIdx.x == 0) s_rows = 0;
     const uint64_t r0 = (uint64_t)blockIdx.x * kRows + (uint64_t)threadIdx.x * kEach;
+    uint4* const p4 = reinterpret_cast<uint4*>(row_ptr + r0);   // the array is 256-byte aligned
+    const bool whole = r0 + kEach <= R;
     uint32_t x[kEach], lo = kNoRow;
+    if (whole) {
+        const uint4 u = p4[0], w = p4[1];
+        x[0] = u.x, x[1] = u.y, x[2] = u.z, x[3] = u.w, x[4] = w.x, x[5] = w.y, x[6] = w.z, x[7] = w.w;
+    } else {
 #pragma unroll
-    for (uint32_t j = 0; j < kEach; ++j) {
-        x[j] = r0 + j < R ? row_ptr[r0 + j] : kNoRow;
-        lo = min(lo, x[j]);
+        for (uint32_t j = 0; j < kEach; ++j) x[j] = r0 + j < R ? row_ptr[r0 + j] : kNoRow;
     }
+#pragma unroll
+    for (uint32_t j = 0; j < kEach; ++j) lo = min(lo, x[j]);
     // minimum over the threads after this one
     uint32_t incl = lo;
 #pragma unroll
@@ -190,43 +201,70 @@ __global__ __launch_bounds__(kThreads) void k_row_fill(uint32_t* __restrict__ ro
     for (int w = wv + 1; w < kThreads / 64; ++w) next = min(next, s_w[w]);
     const uint32_t later = __shfl_down(incl, 1, 64);
     if (lane < 63) next = min(next, later);
-    uint32_t rows = 0;
-    for (int j = kEach - 1; j >= 0; --j) {
-        if (r0 + j >= R) continue;
-        if (x[j] != kNoRow) {
-            atomicAdd(&s_lab[(uint32_t)((r0 + j) % L)], next - x[j]);
-            next = x[j];
-            ++rows;
-        }
-        row_ptr[r0 + j] = next;
+#pragma unroll
+    for (int j = kEach - 1; j >= 0; --j) x[j] = next = min(next, x[j]);   // starts ascend
+    if (whole) {
+        p4[0] = make_uint4(x[0], x[1], x[2], x[3]);
+        p4[1] = make_uint4(x[4], x[5], x[6], x[7]);
+    } else {
+        for (uint32_t j = 0; j < kEach; ++j)
+            if (r0 + j < R) row_ptr[r0 + j] = x[j];
     }
-    rows = (uint32_t)rpqd::wave_sum_u64(rows);
-    if (lane == 0 && rows) atomicAdd(&s_rows, rows);
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) row_ptr[R] = (uint32_t)*n_edges;
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < L; i += kThreads)
-        if (s_lab[i]) atomicAdd(&per_label[i], (unsigned long long)s_lab[i]);
-    if (threadIdx.x == 0 && s_rows) atomicAdd(nonempty, (unsigned long long)s_rows);
 }
 
-// Label masks: a wave takes 64 vertices, whose rows are one stretch of row pointers, and reads them 64 at a
-// time (a thread per vertex read them L apart: 207 us for a million vertices of 8 labels).
+// Label masks of the vertices; edges per label and rows with edges.  A wave's 64 vertices have 64 L rows, lane
+// + 64 t in step t, so a lane meets the same label in the same step of every wave and adds its edges into a
+// word of its own per step (one counter per label instead: 64 lanes on a few addresses, 112 us at 8M rows).
 __global__ __launch_bounds__(kThreads) void k_label_mask(const uint32_t* __restrict__ row_ptr, uint32_t V, uint32_t L,
-                                                         uint64_t* __restrict__ lmask) {
+                                                         uint64_t* __restrict__ lmask,
+                                                         unsigned long long* __restrict__ per_label,
+                                                         unsigned long long* __restrict__ nonempty) {
+    extern __shared__ uint32_t s_edges[];   // [L][64]
     __shared__ unsigned long long s_m[kThreads / 64][64];
+    __shared__ uint32_t s_lab[RPQ_MAX_LABELS];
+    __shared__ uint32_t s_rows;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (uint32_t i = threadIdx.x; i < 64 * L; i += kThreads) s_edges[i] = 0;
+    for (uint32_t i = threadIdx.x; i < L; i += kThreads) s_lab[i] = 0;
+    if (threadIdx.x == 0) s_rows = 0;
+    __syncthreads();
     const uint64_t stride = (uint64_t)gridDim.x * (kThreads / 64);
+    const uint32_t v_step = 64 / L, l_step = 64 % L, v_first = lane / L, l_first = lane % L;
+    uint32_t rows = 0;
     for (uint64_t w = (uint64_t)blockIdx.x * (kThreads / 64) + wv; w * 64 < V; w += stride) {
         s_m[wv][lane] = 0;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         const uint64_t r0 = w * 64 * L;
         const uint32_t n = (uint32_t)min((uint64_t)64, V - w * 64) * L;
-        for (uint32_t i = lane; i < n; i += 64)
-            if (row_ptr[r0 + i + 1] > row_ptr[r0 + i]) atomicOr(&s_m[wv][i / L], 1ull << (i % L));
+        uint32_t v = v_first, l = l_first;
+        for (uint32_t i = lane; i < n; i += 64) {
+            const uint32_t d = row_ptr[r0 + i + 1] - row_ptr[r0 + i];
+            if (d) {
+                atomicOr(&s_m[wv][v], 1ull << l);
+                atomicAdd(&s_edges[i], d);
+                ++rows;
+            }
+            v += v_step;
+            l += l_step;
+            if (l >= L) {
+                l -= L;
+                ++v;
+            }
+        }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         if (w * 64 + lane < V) lmask[w * 64 + lane] = s_m[wv][lane];
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
+    rows = (uint32_t)rpqd::wave_sum_u64(rows);
+    if (lane == 0 && rows) atomicAdd(&s_rows, rows);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < 64 * L; i += kThreads)
+        if (s_edges[i]) atomicAdd(&s_lab[i % L], s_edges[i]);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < L; i += kThreads)
+        if (s_lab[i]) atomicAdd(&per_label[i], (unsigned long long)s_lab[i]);
+    if (threadIdx.x == 0 && s_rows) atomicAdd(nonempty, (unsigned long long)s_rows);
 }
 
 // entered bits of a direction, from its keys (row << 32 | neighbour).  Hubs are entered by many edges: a
@@ -370,7 +408,7 @@ struct Scratch {
     }
     Scratch(const Scratch&) = delete;
     Scratch& operator=(const Scratch&) = delete;
-    uint64_t *keys, *alt, *counts, *scan;
+    uint64_t *keys, *alt, *sorted, *counts, *scan;   // sorted: the one of the two that holds the keys
     uint32_t* mins;
     void* sort;
     unsigned long long* ctr;   // [kCtr]
@@ -391,7 +429,7 @@ struct Scratch {
                        o_ctr = take(kCtr * 8);
         RPQ_TRY(blocks().take(off, &mem));
         char* b = reinterpret_cast<char*>(mem.p);
-        keys = reinterpret_cast<uint64_t*>(b + o_keys);
+        keys = sorted = reinterpret_cast<uint64_t*>(b + o_keys);
         alt = reinterpret_cast<uint64_t*>(b + o_alt);
         counts = reinterpret_cast<uint64_t*>(b + o_counts);
         scan = reinterpret_cast<uint64_t*>(b + o_scan);
@@ -424,14 +462,20 @@ int build_csr(const uint32_t* a, const uint8_t* lab, const uint32_t* b, uint64_t
     unsigned long long* ent = pl + RPQ_MAX_LABELS;   // [2][RPQ_MAX_LABELS]: entered counts, this and other
     RPQ_TRY(fill_u64(reinterpret_cast<uint64_t*>(c), Scratch::kCtr, 0, s));
     RPQ_TRY(fill_u32(out->row_ptr, R + 1, kNoRow, s));
-    uint64_t* sorted = sc.keys;
+    uint64_t* sorted = sc.sorted;
     if (n_edges) {
-        // an edge outside the graph becomes key 0 here and an error below
-        hipLaunchKernelGGL(k_make_keys, dim3(grid_for(n_edges)), dim3(kThreads), 0, s, a, lab, b, n_edges, V, L,
-                           sc.keys, c);
+        // The first direction's sorted keys are in the order of u, so the second's take a stable sort by row
+        // alone: three passes instead of six at 2^20 vertices and 8 labels (16M edges: 1.06 -> 0.63 ms).  In
+        // the first, an edge outside the graph becomes key 0 and an error below.
+        if (other)
+            hipLaunchKernelGGL(k_turn_keys, dim3(grid_for(n_edges)), dim3(kThreads), 0, s, sorted, n_edges, L);
+        else
+            hipLaunchKernelGGL(k_make_keys, dim3(grid_for(n_edges)), dim3(kThreads), 0, s, a, lab, b, n_edges, V, L,
+                               sorted, c);
         RPQ_LAUNCH_CHECK();
-        RPQ_TRY(radix_sort_u64(sc.keys, sc.alt, n_edges, bits_for(V ? V - 1 : 0), bits_for(R ? R - 1 : 0), sc.sort, s,
-                               &sorted));
+        RPQ_TRY(radix_sort_u64(sorted, sorted == sc.keys ? sc.alt : sc.keys, n_edges,
+                               other ? 0 : bits_for(V ? V - 1 : 0), bits_for(R ? R - 1 : 0), sc.sort, s, &sorted));
+        sc.sorted = sorted;
         const uint64_t tiles = (n_edges + kTile - 1) / kTile;
         hipLaunchKernelGGL(k_uniq_count, dim3((unsigned)tiles), dim3(kThreads), 0, s, sorted, n_edges, sc.counts);
         RPQ_LAUNCH_CHECK();
@@ -445,11 +489,10 @@ int build_csr(const uint32_t* a, const uint8_t* lab, const uint32_t* b, uint64_t
     RPQ_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_row_after, dim3(1), dim3(1024), 0, s, sc.mins, rblocks, c + 1);
     RPQ_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_row_fill, dim3((unsigned)rblocks), dim3(kThreads), 0, s, out->row_ptr, R, L, sc.mins, c + 1,
-                       pl, c + 2);
+    hipLaunchKernelGGL(k_row_fill, dim3((unsigned)rblocks), dim3(kThreads), 0, s, out->row_ptr, R, sc.mins, c + 1);
     RPQ_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_label_mask, dim3(grid_for(n_words * 64, 4096)), dim3(kThreads), 0, s, out->row_ptr, V, L,
-                       out->lmask);
+    hipLaunchKernelGGL(k_label_mask, dim3(grid_for(n_words * 64, 1024)), dim3(kThreads), L * 256, s, out->row_ptr, V,
+                       L, out->lmask, pl, c + 2);
     RPQ_LAUNCH_CHECK();
     // entered bits: for both directions from the other's masks once both are there, else from the edges
     const dim3 cgrid(grid_for(n_words, 32), L);
