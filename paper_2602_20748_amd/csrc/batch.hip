@@ -130,6 +130,7 @@ struct BArgs {
     uint64_t* next;          // two reads: bits found at this level; seen_or: Vis as of the last finalize
     uint64_t* touch;
     uint64_t* ever;          // [G][slot_stride bits]: row touched at some level of the slot's unit
+    uint64_t* fresh;         // the same shape: of the rows listed now, those touched for the first time
     uint64_t* summ;          // [G][V/64 rounded up]: bit v set when a final state's row of v is non-empty
     uint32_t* ids0;
     uint32_t* ids1;
@@ -386,7 +387,9 @@ __device__ void phase_compact(const BArgs& a, int p, uint32_t iter) {
             const uint64_t ev = xld(a.ever + wi);
             first = tw & ~ev;
             if (first) a.ever[wi] = ev | tw;
+            a.fresh[wi] = first;
         }
+        const uint64_t first0 = first;
         // first-visit log (the rows whose Vis the slot's retirement clears).  A wave's words
         // usually lie in one slot: then one counter update serves the wave
         const uint32_t fc = (uint32_t)__popcll(first);
@@ -429,6 +432,9 @@ __device__ void phase_compact(const BArgs& a, int p, uint32_t iter) {
             else left |= 1ull << bt;
             ++pos;
         }
+        // a fresh row that waits is not fresh when it is listed: its words of the second bitmap start here
+        for (uint64_t x = a.seen_or ? left & first0 : 0; x; x &= x - 1)
+            for (uint32_t i = 0, K = a.W / 64; i < K; ++i) a.next[(wi * 64 + __ffsll((long long)x) - 1) * K + i] = 0;
         if (tw0) {
             a.touch[wi] = left;
             // a row left for the next iteration reaches its level late: exact depths are lost, so a
@@ -681,12 +687,9 @@ __device__ void phase_retire_clear(const BArgs& a, const uint32_t* list, uint32_
         if (n > a.log_cap) {
             // the log overflowed: clear every row of the slot
             uint64_t* vs = a.vis + (uint64_t)slot * a.slot_stride * K;
-            uint64_t* os = a.next + (uint64_t)slot * a.slot_stride * K;
             const uint64_t words = a.slot_stride * K;
-            for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < words; i += (uint64_t)a.n_blocks * kBlock) {
+            for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < words; i += (uint64_t)a.n_blocks * kBlock)
                 vs[i] = 0;
-                if (a.seen_or) os[i] = 0;
-            }
             continue;
         }
         const uint32_t* log = a.logs + (uint64_t)slot * a.log_cap;
@@ -694,10 +697,6 @@ __device__ void phase_retire_clear(const BArgs& a, const uint32_t* list, uint32_
             const uint64_t at = ((uint64_t)slot * a.slot_stride + xld(log + i)) * K;
 #pragma unroll
             for (int k = 0; k < K; ++k) a.vis[at + k] = 0;
-            if (a.seen_or) {
-#pragma unroll
-                for (int k = 0; k < K; ++k) a.next[at + k] = 0;
-            }
         }
     }
     for (uint32_t r = 0; r < n_ret; ++r) {
@@ -805,6 +804,8 @@ __device__ void phase_seed(const BArgs& a, int p, uint32_t iter) {
                 row = (uint64_t)slot * a.slot_stride + (uint64_t)q * a.V + s;
                 or_relaxed(&(a.seen_or ? a.vis : a.next)[row * K + (j >> 6)], 1ull << (j & 63));
                 or_relaxed(&a.ever[row >> 6], 1ull << (row & 63));
+                if (a.seen_or)
+                    for (int i = 0; i < K; ++i) a.next[row * K + i] = 0;
             }
             const uint64_t m = __ballot(take);
             unsigned long long base = 0, lbase = 0;
@@ -860,6 +861,9 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
         // at the depth bound of a length-bounded query a row is recorded (Vis, Ans) but gets an
         // empty frontier row and no work: it is never expanded
         bool stop = false;
+        // seen OR: a row listed for the first time has nothing in the second bitmap yet, which is then
+        // written whole and not read: it need not be cleared before a unit or after it
+        bool fresh = false;
         if (active) {
             row32 = xld(ids + e);
             slot = row32 / stride;
@@ -870,6 +874,7 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
             nfa = a.nfas + qid;
             fin = (nfa->final >> q) & 1;
             stop = iter - ld32(&a.slots[slot].start_iter) >= a.queries[qid].max_len;
+            fresh = SEEN && ((xld(a.fresh + (row32 >> 6)) >> (row32 & 63)) & 1);
         }
         const uint32_t n_here = (uint32_t)min<uint64_t>(fb, n - e0);
         // the entry's work (its item count) and slices come first: a wave that finds no room for
@@ -898,7 +903,15 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
                 dd.len = 0;
                 dout[dbase + i] = dd;
             }
-            for (uint32_t idx = grp; idx < n_here; idx += GS) rows[(e0 + idx) * K + k] = 0;
+            for (uint32_t i0 = 0; i0 < n_here; i0 += GS) {
+                const uint32_t idx = i0 + grp;
+                const uint32_t ri = __shfl(row32, idx & 63, 64);
+                const bool fi = __shfl((int)fresh, idx & 63, 64);
+                if (idx < n_here) {
+                    rows[(e0 + idx) * K + k] = 0;
+                    if (fi) a.next[(uint64_t)ri * K + k] = 0;
+                }
+            }
             if (active) {
                 or_relaxed(&a.touch[row32 >> 6], 1ull << (row32 & 63));
                 if (a.queries[qid].max_len != 0xFFFFFFFFu) atomicOr(&a.ctl->err, 2ull);
@@ -907,14 +920,14 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
         }
         uint32_t my_pc = 0;   // new source bits of this lane's row
         for (uint32_t j = 0; j < n_here; j += GS * kUnroll) {
-            uint32_t r[kUnroll], sp[kUnroll];
+            uint32_t r[kUnroll], sp[kUnroll];   // sp: 1 = not expanded, 2 = fresh
             uint64_t nk[kUnroll], ov[kUnroll];
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const uint32_t idx = j + u * GS + grp;
                 r[u] = __shfl(row32, idx & 63, 64);
-                sp[u] = __shfl((uint32_t)stop, idx & 63, 64);
-                ov[u] = idx < n_here ? xld(a.next + (uint64_t)r[u] * K + k) : 0;
+                sp[u] = __shfl((uint32_t)stop | (uint32_t)fresh << 1, idx & 63, 64);
+                ov[u] = idx < n_here && !(sp[u] & 2) ? xld(a.next + (uint64_t)r[u] * K + k) : 0;
                 if (SEEN) nk[u] = idx < n_here ? xld(a.vis + (uint64_t)r[u] * K + k) : 0;
             }
 #pragma unroll
@@ -924,10 +937,10 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
                 const uint32_t idx = j + u * GS + grp;
                 uint32_t pc = 0;
                 if (idx < n_here) {
-                    rows[(e0 + idx) * K + k] = sp[u] ? 0 : nk[u];
+                    rows[(e0 + idx) * K + k] = sp[u] & 1 ? 0 : nk[u];
+                    // the row is on the list once and nothing else writes its words in this phase
+                    if (nk[u] || (sp[u] & 2)) a.next[(uint64_t)r[u] * K + k] = SEEN ? ov[u] | nk[u] : 0;
                     if (nk[u]) {
-                        // the row is on the list once and nothing else writes its words in this phase
-                        a.next[(uint64_t)r[u] * K + k] = SEEN ? ov[u] | nk[u] : 0;
                         if (!SEEN) a.vis[(uint64_t)r[u] * K + k] |= nk[u];
                         pc = (uint32_t)__popcll(nk[u]);
                         ++t_fwords;
@@ -1246,7 +1259,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_clear(BArgs a, uint32_t K) {
         if ((words & 1) && blockIdx.x == 0 && threadIdx.x == 0) p[words - 1] = 0;
     };
     clear(a.vis, G * a.slot_stride * K);
-    clear(a.next, G * a.slot_stride * K);
+    if (!a.seen_or) clear(a.next, G * a.slot_stride * K);
     clear(a.touch, G * a.slot_stride / 64);
     clear(a.ever, G * a.slot_stride / 64);
     clear(a.summ, G * a.summ_words);
@@ -1299,7 +1312,7 @@ struct Layout {
     uint64_t n_segs, n_srcs;   // closed form: source segments, sources of all queries
     uint64_t off_segs, off_srcs, off_pos, off_order;
     uint64_t slot_stride, summ_words, list_cap, desc_cap, log_cap, stage_keys;
-    uint64_t off_ctl, off_nfas, off_queries, off_qout, off_units, off_slots, off_vis, off_next, off_touch, off_ever,
+    uint64_t off_ctl, off_nfas, off_queries, off_qout, off_units, off_slots, off_vis, off_next, off_touch, off_ever, off_fresh,
         off_summ, off_ids[2], off_rows[2], off_desc[2], off_logs, off_retiring, off_drain, off_partial, off_srcbase,
         off_stage,
         off_utotal, off_ustart, off_uprefix, off_scan_tmp, total;
@@ -1368,7 +1381,7 @@ void size_slots(const rpq_graph* g, uint32_t max_succ, bool auto_chunk, uint32_t
     const uint64_t list_per_slot = x->slot_stride / share + 64;
     // per slot: Vis + Next, touch and first-visit bits, summary, first-visit log, and its share
     // of the two frontier lists (row id + K-word row per entry) and of the two slice buffers
-    *per_slot = x->slot_stride * x->K * 8 * 2 + x->slot_stride / 4 + x->summ_words * 8 +
+    *per_slot = x->slot_stride * x->K * 8 * 2 + x->slot_stride * 3 / 8 + x->summ_words * 8 +
                 x->log_cap * 4 + 2 * list_per_slot * (4 + x->K * 8) + 2 * *desc_per_slot * sizeof(Desc);
 }
 
@@ -1392,6 +1405,7 @@ void place(const rpq_graph* g, uint32_t nq, uint64_t n_unit_entries, Layout* x) 
     x->off_next = take(G * x->slot_stride * x->K * 8);
     x->off_touch = take(G * x->slot_stride / 8);
     x->off_ever = take(G * x->slot_stride / 8);
+    x->off_fresh = take(G * x->slot_stride / 8);
     x->off_summ = take(G * x->summ_words * 8);
     for (int p = 0; p < 2; ++p) {
         x->off_ids[p] = take(x->list_cap * 4);
@@ -1533,6 +1547,7 @@ BArgs args_for(const rpq_graph* g, const Layout& x, char* ws, unsigned n_blocks,
     a.next = reinterpret_cast<uint64_t*>(ws + x.off_next);
     a.touch = reinterpret_cast<uint64_t*>(ws + x.off_touch);
     a.ever = reinterpret_cast<uint64_t*>(ws + x.off_ever);
+    a.fresh = reinterpret_cast<uint64_t*>(ws + x.off_fresh);
     a.summ = reinterpret_cast<uint64_t*>(ws + x.off_summ);
     a.ids0 = reinterpret_cast<uint32_t*>(ws + x.off_ids[0]);
     a.ids1 = reinterpret_cast<uint32_t*>(ws + x.off_ids[1]);
