@@ -132,6 +132,8 @@ struct Args {
     uint64_t* vis;          // visited bits (with seen_or: also those found at the current level)
     uint64_t* next;         // two reads: bits found at this level; seen_or: Vis as of the last finalize
     uint64_t* touch;        // one bit per row: row has bits new at this level
+    uint64_t* ever;         // seen_or: at this level or before, in the group
+    uint64_t* fresh;        // seen_or: of the rows listed now, those listed for the first time
     uint8_t* full;          // per row: no source still searching can add to it
     uint64_t* active;       // [2][G][K] by list parity: sources with a bit in that frontier, or more
     uint64_t* rows0;
@@ -234,7 +236,7 @@ __device__ __forceinline__ void row_entry(const Args& a, const LdsNfa& s, uint32
 //              the two reads together.  The second bitmap holds the visited bits as of the last
 //              finalize, and finalize takes a listed row's new bits as Vis & ~that, then advances
 //              it.  One read and one OR per new word, the method's own accesses; finalize reads one
-//              more word per row word, and the second bitmap is cleared with Vis for every group.
+//              more word per row word after a row's first time, when it writes the row whole.
 //              Faster at both scales measured: R-MAT 23, 3.41 -> 2.91 s a step (expansion 2.11 ms
 //              a launch when each new word was also ORed into a Next bitmap, 1.53 ms now); R-MAT
 //              18, 603 -> 541 ms (expansion 1.43 -> 1.15 ms).
@@ -486,7 +488,14 @@ __global__ __launch_bounds__(kBlock) void k_compact(Args a, int p, uint64_t n_ro
     for (uint64_t w0 = wave * 64; w0 < n_words; w0 += n_waves * 64) {
         const uint64_t wi = w0 + lane;
         uint64_t tw = wi < n_words ? a.touch[wi] : 0;
-        if (tw) a.touch[wi] = 0;
+        if (tw) {
+            a.touch[wi] = 0;
+            if (a.seen_or) {
+                const uint64_t ev = a.ever[wi];
+                if (tw & ~ev) a.ever[wi] = ev | tw;
+                a.fresh[wi] = tw & ~ev;
+            }
+        }
         const uint32_t c = (uint32_t)__popcll(tw);
         const uint32_t incl = rpqd::wave_incl_scan_u32(c);
         const uint32_t tot = __shfl(incl, 63, 64);
@@ -570,6 +579,9 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
         const uint32_t my_row = active ? ids[e] : 0;
         uint32_t slot = 0, q = 0, v = 0;
         if (active) row_entry(a, s_nfa, my_row, &slot, &q, &v);
+        // seen OR: a row listed for the first time has nothing in the second bitmap yet, which is then
+        // written whole and not read: it is not cleared for a group
+        const uint64_t fresh = SEEN ? __ballot(active && ((a.fresh[my_row >> 6] >> (my_row & 63)) & 1)) : 0;
         const uint32_t n_here = (uint32_t)min<uint64_t>(fb, n - e0);
         t_rows += n_here * (lane == 0);
         const uint32_t slot0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot);
@@ -591,7 +603,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
                 nk[u] = ov[u] = 0;
                 if (idx < n_here) {
                     if constexpr (SEEN) {
-                        ov[u] = a.next[(uint64_t)r[u] * K + k];
+                        if (!((fresh >> idx) & 1)) ov[u] = a.next[(uint64_t)r[u] * K + k];
                         nk[u] = a.vis[(uint64_t)r[u] * K + k];
                     } else {
                         nk[u] = a.next[(uint64_t)r[u] * K + k];
@@ -616,9 +628,9 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
                 uint32_t pc = 0;
                 if (idx < n_here) {
                     rows[(e0 + idx) * K + k] = nk[u];
+                    // seen OR: the snapshot catches up with Vis.  Two reads: Next is cleared.
+                    if (nk[u] || ((fresh >> idx) & 1)) a.next[(uint64_t)r[u] * K + k] = SEEN ? (ov[u] | nk[u]) : 0;
                     if (nk[u]) {
-                        // seen OR: the snapshot catches up with Vis.  Two reads: Next is cleared.
-                        a.next[(uint64_t)r[u] * K + k] = SEEN ? (ov[u] | nk[u]) : 0;
                         // a row is on the list once, and nothing else writes its Vis word in this
                         // kernel: a plain read-modify-write (an atomic OR cost 0.82 vs 0.69 ms a
                         // launch).  With seen OR the expansion has already set these bits.
@@ -1492,7 +1504,7 @@ struct Layout {
     uint64_t off_counters, off_tally, off_xtally, off_src_bits, zero_words, off_nfa, off_tile_n, off_srcs, off_pos,
         off_srcs2, off_pos2, off_bit_of, off_hist, off_score, off_rank, off_verts, off_class_n, off_class_tile_n;
     // by the unit width and units in flight
-    uint64_t off_vis, off_next, off_vis2, off_touch, off_full, off_active, off_ids[2], off_rows[2], off_desc[2], off_acc, off_partial,
+    uint64_t off_vis, off_next, off_vis2, off_touch, off_ever, off_fresh, off_full, off_active, off_ids[2], off_rows[2], off_desc[2], off_acc, off_partial,
         off_srcbase, total;
 };
 
@@ -1763,12 +1775,13 @@ int make_layout(const rpq_graph* g, const Plan& p, uint64_t n_sources, uint64_t 
     x.off_class_n = take(p.n_classes * 4);
     x.off_class_tile_n = take(p.n_classes * ((p.n_words + 63) / 64) * 4);
     // With more than one group the visited bitmap is double-buffered: a group's answers are extracted
-    // from it on a second stream while the next group's levels fill the other one.  Vis, Next, Vis2 in
-    // this order: either Vis and Next are cleared with one fill.
+    // from it on a second stream while the next group's levels fill the other one.
     x.off_vis = take(G * bitmap_bytes);
     x.off_next = take(G * bitmap_bytes);
     x.off_vis2 = units > G && !noalloc ? take(G * bitmap_bytes) : x.off_vis;
     x.off_touch = take((G * R + 63) / 64 * 8);
+    x.off_ever = take(x.seen_or ? (G * R + 63) / 64 * 8 : 0);
+    x.off_fresh = take(x.seen_or ? (G * R + 63) / 64 * 8 : 0);
     x.off_full = take((G * R + 7) / 8 * 8);
     x.off_active = take(2 * G * x.K * 8);
     for (int i = 0; i < 2; ++i) {
@@ -1798,6 +1811,8 @@ Args make_args(const rpq_graph* g, const Plan& p, const Layout& x, char* ws) {
     a.vis = reinterpret_cast<uint64_t*>(ws + x.off_vis);
     a.next = reinterpret_cast<uint64_t*>(ws + x.off_next);
     a.touch = reinterpret_cast<uint64_t*>(ws + x.off_touch);
+    a.ever = reinterpret_cast<uint64_t*>(ws + x.off_ever);
+    a.fresh = reinterpret_cast<uint64_t*>(ws + x.off_fresh);
     a.full = reinterpret_cast<uint8_t*>(ws + x.off_full);
     a.active = reinterpret_cast<uint64_t*>(ws + x.off_active);
     a.n_active = (uint64_t)x.G * x.K;
@@ -2511,14 +2526,8 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
         } else {
             // the bitmap's previous group must be extracted before it is cleared for this one
             if (side.stream && grp >= 2) RPQ_HIP(hipStreamWaitEvent(stream, side.extracted[buf], 0));
-            if (x.seen_or && G_eff == x.G) {   // Vis and Next lie side by side
-                const uint64_t* lo = std::min(a.vis, a.next);
-                const uint64_t span = (uint64_t)(std::max(a.vis, a.next) - lo) + x.G * bitmap_words;
-                RPQ_TRY(rpq::fill_u64(const_cast<uint64_t*>(lo), span, 0, stream));
-            } else {
-                RPQ_TRY(rpq::fill_u64(a.vis, G_eff * bitmap_words, 0, stream));
-                if (x.seen_or) RPQ_TRY(rpq::fill_u64(a.next, G_eff * bitmap_words, 0, stream));
-            }
+            RPQ_TRY(rpq::fill_u64(a.vis, G_eff * bitmap_words, 0, stream));
+            if (x.seen_or) RPQ_TRY(rpq::fill_u64(a.ever, ((uint64_t)G_eff * x.R + 63) / 64, 0, stream));
             RPQ_TRY(rpq::fill_u64(reinterpret_cast<uint64_t*>(a.full), (G_eff * (uint64_t)x.R + 7) / 8, 0, stream));
             hipLaunchKernelGGL(k_seed, dim3((unsigned)(((uint64_t)G_eff * x.W + kBlock - 1) / kBlock)), dim3(kBlock), 0,
                                stream, a, G_eff, x.K);
