@@ -406,10 +406,11 @@ def other_rooflines(prof):
       compaction, read by finalize); per row word 16 B (Next or, with seen OR, the previous level's
       visited copy read, frontier write); per non-zero word 8 B more to clear Next or advance the
       copy; 8 B per finalize access to the visited bitmap (two reads: a read and a write of each
-      non-zero word; seen OR: a read of each row word); per non-zero word of a
-      final-state row 16 B for the answer word.  The touch bitmap compaction scans (one bit per row) is left out;
+      non-zero word; seen OR: a read of each row word, less the copy's words that rows listed for the
+      first time do not read); 16 B per word ORed into an answer bitmap (none: answers are read from
+      the final states' rows).  The touch bitmap compaction scans (one bit per row) is left out;
       the tallies include the seeding finalize of each group (one row per source), which is not timed.
-    extract (count passes, timed on the extraction stream): 8 B per answer word read."""
+    extract (count passes, timed on the extraction stream): 8 B per word of a final state's row."""
     out = {}
     fl = prof["finalize_launches"]
     if fl and prof["finalize_ms"] / fl > 1e-6:

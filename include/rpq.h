@@ -195,7 +195,9 @@ int rpq_nfa_reverse(const rpq_nfa* in, rpq_nfa* out);
                                  vertex) instead of per-unit bitmaps: workspace grows with what
                                  the sources reach, not with V * states * sources (for few
                                  sources on a large graph).  Same results; levels counts the
-                                 search's non-empty frontiers. */
+                                 search's non-empty frontiers.  Up to 512 sources, a search that
+                                 passes 2^16 triples goes to the bitmaps if the workspace holds
+                                 them. */
 #define RPQ_LENGTH_BOUND 32u  /* length-bounded RPQ (the extension named in the paper's conclusion,
                                  Section 10: a length constraint enforced by the traversal depth):
                                  only walks of at most opts->max_length edges count.  The search
@@ -208,8 +210,11 @@ int rpq_nfa_reverse(const rpq_nfa* in, rpq_nfa* out);
 /* Tuning knobs; zero fields take defaults (the autotuner's choice when one is cached). */
 typedef struct {
     uint32_t batch_width;    /* sources per unit: 64, 128, 256, 512, 1024, 2048 or 4096
-                                (0 = the widest up to 2048, or 4096 on graphs of 2^22 vertices
-                                or more, that n_sources / 8 fills) */
+                                (0 = as wide as the sources with a first edge need: from 128 up
+                                to 2048, or 4096 on graphs of 2^22 vertices or more).  A call
+                                that sets this, concurrency, sync_every, chunk_edges or visit
+                                runs the level kernels; one that leaves them 0 may run a search
+                                in LDS on a small graph.  Same results */
     uint32_t concurrency;    /* units advanced together (0 = ~64K sources in flight within
                                 64 GB of workspace, at least one unit) */
     uint32_t sync_every;     /* levels launched between host checks for the fixpoint (0 = 4) */
@@ -416,9 +421,8 @@ typedef struct {
                                for the next iteration, which changes no result (0 = 4, or 1 when a
                                query is length-bounded: such queries need exact depths and require 1) */
     uint32_t visit;         /* the expansion's visit scheme, RPQ_VISIT_TWO_READS or RPQ_VISIT_SEEN_OR
-                               (0 = seen OR on graphs of 2^22 vertices or more, two reads below).
-                               The batched kernel's seen OR ORs each new word into the visited word
-                               and into Next */
+                               (0 = seen OR; the resident engine: on graphs of 2^22 vertices or more,
+                               two reads below) */
 } rpq_batch_opts;
 
 typedef struct {
@@ -725,9 +729,11 @@ int rpq_serve_stop(rpq_server_t s);
  *   descriptors   work segments: light frontier entries taken whole from the list and 16-byte
  *                 slices of heavy ones
  *   row_words     8-byte frontier words read (K per segment)
- *   word_reads    8-byte visited words read, each with the 8-byte next-frontier word beside it
- *                 (frontier word != 0)
- *   word_updates  8-byte atomic ORs into the next-frontier bitmap (bits not yet there)
+ *   word_reads    8-byte visited words read (frontier word != 0); with two reads each with the
+ *                 8-byte next-frontier word beside it
+ *   word_updates  8-byte atomic ORs of new bits: into the visited bitmap (seen OR) or the
+ *                 next-frontier bitmap (two reads)
+ * Searches of small graphs in LDS launch no such kernels and count nothing here.
  * and of finalize (finalize_*) and of the extraction's count passes (extract_*).
  */
 typedef struct {
@@ -745,11 +751,12 @@ typedef struct {
     uint64_t finalize_words;     /* their non-zero 8-byte Next words (each cleared) */
     uint64_t finalize_vis_words; /* 8-byte accesses of finalize to Vis: with two reads a read and a
                                     write of each non-zero word; with seen OR a read of each row
-                                    word (its new bits are Vis minus the previous level's copy) */
-    uint64_t finalize_ans_words; /* those of final-state rows (each also ORed into Ans) */
+                                    word (its new bits are Vis minus the previous level's copy),
+                                    less the reads of that copy that first listings do without */
+    uint64_t finalize_ans_words; /* always 0: answers are read from the rows of the final states */
     uint64_t extract_launches;   /* extraction count passes, timed on the extraction stream */
     double extract_ms;
-    uint64_t extract_words;      /* 8-byte answer words those passes read */
+    uint64_t extract_words;      /* 8-byte words of final states' rows those passes read, at most */
     uint64_t expand_extra_words; /* 8-byte accesses of the expansion beyond the method's: the Next
                                     word read beside each visited word (two reads); none with
                                     seen OR */

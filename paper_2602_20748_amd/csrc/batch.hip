@@ -1,12 +1,13 @@
 // Batched evaluation: many RPQs (different automata, source sets, result
 // modes) advanced together by one persistent kernel, captured in a HIP graph.
 //
-// The queries are cut into units (a query's sources, at most W per unit; a
-// single-source query is one unit).  G slots each own a unit's bitmaps, sized
-// for the largest automaton of the batch: Vis/Next [Qmax][V][K] words, a
-// touch bitmap, a bitmap of the rows the unit has visited, Ans [V][K] and a
-// one-bit-per-vertex summary of non-empty Ans rows.  The persistent kernel
-// repeats
+// The queries are cut into units (the sources of a query that have a first
+// edge, at most W per unit; a single-source query is one unit).  G slots each
+// own a unit's bitmaps, sized for the largest automaton of the batch and the
+// widest unit: Vis/Next [Qmax][V][K] words, a touch bitmap, bitmaps of the
+// rows the unit has visited and of those listed for the first time now, and a
+// one-bit-per-vertex summary of the vertices reached in a final state.  The
+// persistent kernel repeats
 //
 //   expand -> compact -> decide -> (retire) -> refill/seed -> finalize
 //

@@ -74,7 +74,8 @@ constexpr int T_WREAD = 3;
 constexpr int T_WUPD = 4;
 constexpr int T_FROWS = 5;      // finalize (profiling): rows finalized,
 constexpr int T_FWORDS = 6;     //   and their non-zero Next words
-constexpr int kTallies = 7;
+constexpr int T_FFRESH = 7;     //   rows listed for the first time
+constexpr int kTallies = 8;
 constexpr int kTallyStride = 8;             // words per block
 constexpr unsigned kMaxLevelBlocks = 2048;  // upper bound of a level kernel's grid
 constexpr unsigned kMaxExtractBlocks = 4096;  // and of an extraction that keeps totals per block
@@ -548,7 +549,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
     Desc* dout = desc_of(a, np);
     unsigned long long* dcnt = &a.counters[C_DESC + np];
     const uint32_t H = a.H;
-    uint64_t eprod = 0, t_rows = 0, t_words = 0;
+    uint64_t eprod = 0, t_rows = 0, t_words = 0, t_fresh = 0;
     const uint64_t gmask = (K == 64) ? ~0ull : (((1ull << (K & 63)) - 1) << (grp * K));
     const uint64_t* was_active = a.active + p * a.n_active;
     unsigned long long* now_active = reinterpret_cast<unsigned long long*>(a.active + np * a.n_active);
@@ -584,6 +585,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
         const uint64_t fresh = SEEN ? __ballot(active && ((a.fresh[my_row >> 6] >> (my_row & 63)) & 1)) : 0;
         const uint32_t n_here = (uint32_t)min<uint64_t>(fb, n - e0);
         t_rows += n_here * (lane == 0);
+        t_fresh += __popcll(fresh) * (lane == 0);
         const uint32_t slot0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot);
         const bool one_slot = __ballot(active && slot != slot0) == 0;
         if (SEEN && track && (!one_slot || slot0 != acc_slot)) {
@@ -693,9 +695,9 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
         }
     }
     flush_active();
-    const uint64_t t_e[1] = {eprod}, t_f[2] = {t_rows, t_words};
+    const uint64_t t_e[1] = {eprod}, t_f[3] = {t_rows, t_words, t_fresh};
     add_tallies<1>(a, T_EPROD, t_e);
-    add_tallies<2>(a, T_FROWS, t_f);
+    add_tallies<3>(a, T_FROWS, t_f);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2650,8 +2652,9 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
             pr.acc.finalize_row_words += tally[T_FROWS] * x.K;
             pr.acc.finalize_words += tally[T_FWORDS];
             // 8-byte accesses of finalize to Vis: a read of every row word (seen OR), or a read and
-            // a write of every non-zero word (two reads)
-            pr.acc.finalize_vis_words += x.seen_or ? tally[T_FROWS] * x.K : 2 * tally[T_FWORDS];
+            // a write of every non-zero word (two reads); less the reads of the second bitmap that rows
+            // listed for the first time do without
+            pr.acc.finalize_vis_words += x.seen_or ? (tally[T_FROWS] - tally[T_FFRESH]) * x.K : 2 * tally[T_FWORDS];
             // beyond the method's bytes: the Next word read beside each visited word (two reads);
             // seen OR makes the method's accesses only
             pr.acc.expand_extra_words += x.seen_or ? 0 : tally[T_WREAD];
