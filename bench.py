@@ -717,7 +717,7 @@ def main():
                                                          "word_reads", "word_updates", "expand_extra_words",
                                                          "expand_ms", "finalize_ms")},
                           visit=(args.visit if args.visit != "auto"
-                                 else "seen-or" if el.n_vertices >= (1 << 22) else "two-reads")))
+                                 else "seen-or")))
 
     # ------------------------------------------------------------------ batched form
     g.release_workspace()

@@ -37,8 +37,9 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
-constexpr int kUnroll = 8;   // rows per lane group loaded before any is updated (64 units of 16-word rows on R-MAT 20: 61.3 ms
-                             // at 2, 55.2 at 4, 53.4 at 8, 84.5 at 16, where registers spill)
+// rows per lane group loaded before any is updated (64 units of 16-word rows on R-MAT 20: 61.3 ms at 2, 55.2
+// at 4, 53.4 at 8, 84.5 at 16, where registers spill)
+constexpr int kUnroll = 8;
 constexpr uint32_t kChunkV = 4096;          // vertices per extraction chunk (64 summary words)
 constexpr uint32_t kSeenOrFrom = 1u << 22;   // default visit scheme: seen OR from this many vertices
 

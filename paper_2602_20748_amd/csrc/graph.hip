@@ -343,6 +343,7 @@ public:
             e = hipMalloc(&out->p, bytes);
         }
         if (e != hipSuccess) {
+            (void)hipGetLastError();
             *out = rpq::Block();
             rpq::set_error("hipMalloc(%llu) failed: %s", (unsigned long long)bytes, hipGetErrorString(e));
             return e == hipErrorOutOfMemory ? RPQ_ENOMEM : RPQ_EDEVICE;
