@@ -2746,7 +2746,7 @@ int rpq_eval_noalloc(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources,
     uint64_t n = n_sources;
     if (g && (flags & RPQ_ALL_SOURCES) && n == 0) n = g->V;
     // the plan: the caller's knobs, with the unset ones narrowed until the workspace fits the
-    // scratch (fewer units in flight first, then narrower units)
+    // scratch (fewer units in flight first, then narrower units, then longer slices)
     rpq_eval_opts o{};
     if (opts) o = *opts;
     Plan plan;
@@ -2760,6 +2760,10 @@ int rpq_eval_noalloc(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources,
         } else if (!(opts && opts->batch_width) && lay.W > 64) {
             o.batch_width = lay.W / 2;
             o.concurrency = (opts && opts->concurrency) ? opts->concurrency : 0;
+        } else if (!(opts && opts->chunk_edges) && lay.H < 4096) {
+            o.batch_width = lay.W;
+            o.concurrency = lay.G;
+            o.chunk_edges = lay.H * 2;   // fewer slices
         } else {
             rpq::set_error("the evaluation needs %llu bytes of workspace; the static scratch holds %llu",
                            (unsigned long long)lay.total, (unsigned long long)kScratchBytes);
