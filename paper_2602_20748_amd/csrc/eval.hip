@@ -726,6 +726,11 @@ __device__ __forceinline__ bool has_bit(const SrcArgs& a, uint32_t s) {
     return s < a.V && (!a.compact || (a.lmask[s] & a.init_labels));
 }
 
+// the zero-length walk of s counts
+__device__ __forceinline__ bool self_result(const SrcArgs& a, uint32_t s) {
+    return a.eps && (!a.target || ((a.target[s >> 6] >> (s & 63)) & 1));
+}
+
 __global__ __launch_bounds__(kBlock) void k_src_count(SrcArgs a) {
     __shared__ uint64_t s_part[kWaves][3];
     const int lane = threadIdx.x & 63;
@@ -740,14 +745,9 @@ __global__ __launch_bounds__(kBlock) void k_src_count(SrcArgs a) {
                 atomicOr(&a.counters[C_ERR], (unsigned long long)ERR_SOURCES);
             alive = has_bit(a, s);
             if (!alive && s < a.V) {
-                const bool self = a.eps && (!a.target || ((a.target[s >> 6] >> (s & 63)) & 1));
-                const uint64_t h = self ? rpqd::mix64(((uint64_t)s << 32) | s) : 0;
+                const bool self = self_result(a, s);
                 dead += self;
-                hash += h;
-                if (a.per_source) {
-                    a.per_source[2 * i] = self;
-                    a.per_source[2 * i + 1] = h;
-                }
+                hash += self ? rpqd::mix64(((uint64_t)s << 32) | s) : 0;
             }
         }
         const uint64_t m = __ballot(alive);
@@ -796,6 +796,7 @@ __global__ __launch_bounds__(kBlock) void k_src_write(SrcArgs a) {
     __shared__ uint32_t s_n[kWaves];
     uint64_t at = block_sum_of(a.tile_n, blockIdx.x);
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) a.counters[C_ALIVE] = at + a.tile_n[blockIdx.x];
+    const bool valid = a.counters[C_ERR] == 0;   // an invalid call leaves its outputs as they are
     for (uint32_t r = 0; r < kSrcTile; r += kBlock) {
         const uint64_t i = (uint64_t)blockIdx.x * kSrcTile + r + threadIdx.x;
         uint32_t s = 0;
@@ -816,6 +817,10 @@ __global__ __launch_bounds__(kBlock) void k_src_write(SrcArgs a) {
             const uint64_t j = at + before + __popcll(m & rpqd::lanemask_lt());
             a.out_srcs[j] = s;
             a.out_pos[j] = (uint32_t)i;
+        } else if (valid && a.per_source && i < a.n) {
+            const bool self = self_result(a, s);
+            a.per_source[2 * i] = self;
+            a.per_source[2 * i + 1] = self ? rpqd::mix64(((uint64_t)s << 32) | s) : 0;
         }
         at += all;
         __syncthreads();

@@ -269,3 +269,37 @@ def test_ingest_tiles(rpq, m):
     for t in threads:
         t.join()
     assert outs == [[True] * 4, [True] * 4]
+
+
+@pytest.mark.parametrize("n_sources", [3, 64, 65, 600])
+@pytest.mark.parametrize("opts", [None, dict(sync_every=2)])
+def test_invalid_sources_leave_outputs_alone(rpq, n_sources, opts):
+    """Ids out of order, twice, or beyond the graph: refused, with the caller's arrays as they were, also those
+    of the sources without a first edge, whose results are written early; then a valid call."""
+    import torch
+    n = 6000
+    src, lab, dst = hub_graph(n, [600, 17], 9000, seed=12)
+    g = rpq.rpq_graph_create(src, lab, dst, n, 3, names=["a", "b", "c"])
+    og = oracle.OracleGraph(n, src, lab, dst, 3, ["a", "b", "c"])
+    good = np.unique(np.linspace(0, n - 1, n_sources).astype(np.uint32))
+    for rx in ("a.b*.c", "c*", "a"):
+        nfa = rpq.rpq_nfa_compile(rx, g.names)
+        want = oracle.rpq(og, rx, sources=good)
+        for how in ("order", "twice", "beyond"):
+            bad = good.copy()
+            if how == "order":
+                bad[[0, -1]] = bad[[-1, 0]]
+            elif how == "twice":
+                bad[-1] = bad[-2]
+            else:
+                bad[-1] = n
+            print("case: %d sources, %s, %s" % (len(good), rx, how), flush=True)
+            per = torch.full((len(good), 2), -7, dtype=torch.int64, device="cuda")
+            buf = torch.full((max(1, want.count),), -7, dtype=torch.int64, device="cuda")
+            for keys in (None, buf):
+                with pytest.raises(rpq.RpqError) as e:
+                    rpq.rpq_eval(g, nfa, bad, opts=opts, pairs=keys, per_source=per)
+                assert e.value.code == rpq.RPQ_EINVAL
+                assert bool((per == -7).all()) and bool((buf == -7).all())
+        same_as_oracle(evaluate(rpq, g, nfa, good, want, **(opts or {})), want)
+    g.close()
