@@ -196,8 +196,8 @@ int rpq_nfa_reverse(const rpq_nfa* in, rpq_nfa* out);
                                  the sources reach, not with V * states * sources (for few
                                  sources on a large graph).  Same results; levels counts the
                                  search's non-empty frontiers.  Up to 512 sources, a search that
-                                 passes 2^16 triples goes to the bitmaps if the workspace holds
-                                 them. */
+                                 passes 2^16 triples (2^15 in the smallest workspaces) goes to the
+                                 bitmaps if the workspace holds them. */
 #define RPQ_LENGTH_BOUND 32u  /* length-bounded RPQ (the extension named in the paper's conclusion,
                                  Section 10: a length constraint enforced by the traversal depth):
                                  only walks of at most opts->max_length edges count.  The search

@@ -1588,7 +1588,8 @@ int sparse_eval(rpq_graph_t g, const rpq_nfa* nfa_in, const uint32_t* sources, u
         const rpq::Csr& csr = reverse ? g->in : g->out;
         // room for the search and, after it, the sort of up to T/2 pairs (~12 bytes per slot)
         uint64_t T = sparse_start_slots(n_sources, nfa.n_states, dense_ok ? 0 : c.ar.free_bytes());
-        if (dense_ok) T = std::max(T, 2 * kFewFound);
+        // room for kFewFound triples, where the workspace has it: the size planned for the search is enough
+        if (dense_ok && 2 * kFewFound * 20 + (1ull << 16) <= c.ar.free_bytes()) T = std::max(T, 2 * kFewFound);
         uint64_t* keys = nullptr;
         uint64_t nk = 0, eprod = 0, levels = 0, found = 0;
         const uint64_t mark = c.ar.top;

@@ -1,0 +1,55 @@
+"""GPU tests of calls at the edges of the search forms' dispatch: exactly the planned workspace, searches that
+end or go on at the sizes where one form hands over to another, and the counts that describe a search.
+Expected values come from the oracle or follow from how the graph is built."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rpq():
+    import torch
+    import paper_2602_20748_amd as m
+    assert torch.cuda.is_available()
+    m.load_library()
+    return m
+
+
+def say(*a):
+    print("case:", *a, flush=True)
+
+
+def u64(t):
+    return t.cpu().numpy().view(np.uint64)
+
+
+def same_as_oracle(got, want, keys=True):
+    assert (got.count, got.hash, got.product_edges) == (want.count, want.hash, want.product_edges)
+    assert np.array_equal(u64(got.per_source), want.per_source)
+    if keys:
+        assert np.array_equal(u64(got.pairs), want.pairs)
+
+
+@pytest.mark.parametrize("n", [100, 1000, 3000])
+@pytest.mark.parametrize("n_sources", [1, 9])
+def test_sparse_runs_in_the_planned_workspace(rpq, n, n_sources):
+    """The size that rpq_eval_workspace_size gives holds 2^15 triples, and these searches find fewer: closures
+    where all triples together are fewer, chains of at most three edges elsewhere.  No call is refused."""
+    import torch
+    rng = np.random.default_rng(n)
+    src, dst = rng.integers(0, n, 3 * n).astype(np.uint32), rng.integers(0, n, 3 * n).astype(np.uint32)
+    lab = rng.integers(0, 2, 3 * n).astype(np.uint8)
+    g = rpq.rpq_graph_create(src, lab, dst, n, 2, names=["a", "b"])
+    og = oracle.OracleGraph(n, src, lab, dst, 2, ["a", "b"])
+    s = np.unique(np.linspace(0, n - 1, n_sources).astype(np.uint32))
+    for rx in ("a.b*", "a*.b?", "(a|b)*") if 3 * n * n_sources <= 1 << 15 else ("a.b", "a.b.a?", "a"):
+        say(n, n_sources, rx)
+        nfa = rpq.rpq_nfa_compile(rx, g.names)
+        want = oracle.rpq(og, rx, sources=s)
+        ws = torch.empty(rpq.rpq_eval_workspace_size(g, nfa, len(s), rpq.RPQ_SPARSE), dtype=torch.uint8, device="cuda")
+        buf = torch.zeros(max(1, want.count), dtype=torch.int64, device="cuda")
+        same_as_oracle(rpq.rpq_eval(g, nfa, s, flags=rpq.RPQ_SPARSE, pairs=buf, per_source=True, workspace=ws), want)
+    g.close()
