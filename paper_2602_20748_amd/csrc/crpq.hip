@@ -365,7 +365,7 @@ __global__ __launch_bounds__(kBlock) void k_edge_scan(const uint32_t* __restrict
 // Found triples go to one list in the order found; a level's frontier is a stretch [beg, end) of it.
 // Entries of more than kLight edges are cut into slices of kSlice edges, a wave each: a hub's edges
 // walked by one wave, and one counter update per 64 items, made a level of b.(a|c)* from one vertex of
-// R-MAT 22 5.7 ms and the search 78 ms; it takes 7.8 ms now, bound by the random accesses to the bitmap.
+// R-MAT 22 5.7 ms and the search 78 ms; 7.8 ms with both, bound by the random accesses to the bitmap.
 // ------------------------------------------------------------------------------------------------
 constexpr uint32_t kLight = 32;
 constexpr uint32_t kSlice = 256;
@@ -417,10 +417,10 @@ struct SArgs {
 // probing an overfull table.
 constexpr unsigned long long kFlagProbe = 1, kFlagFull = 2;
 
-__device__ __forceinline__ bool run_over(const SArgs& a) {
-    const unsigned long long f = __hip_atomic_load(&a.ctr[S_FLAGS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return __ballot(f != 0) != 0;
+__device__ __forceinline__ unsigned long long flags_of(const SArgs& a) {
+    return __hip_atomic_load(&a.ctr[S_FLAGS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ bool run_over(const SArgs& a) { return __ballot(flags_of(a) != 0) != 0; }
 
 // true if (source si, state q, vertex v) was not in the visited set (and is now)
 __device__ __forceinline__ bool set_insert(const SArgs& a, uint64_t si, uint32_t q, uint32_t Q, uint32_t v) {
@@ -441,15 +441,19 @@ __device__ __forceinline__ bool set_insert(const SArgs& a, uint64_t si, uint32_t
             if (prev == key) return false;
         }
         h = (h + 1) & a.mask;
+        // at the load limit chains are a few dozen slots; a longer one is the sign of an overfull table, which
+        // the waves that append will have seen (one level past the limit cost 3 to 9 ms of probing without this)
+        if ((p & 63) == 63 && flags_of(a)) return false;
     }
     atomicOr(&a.ctr[S_FLAGS], kFlagProbe);
     return false;
 }
 
-// Appends of found triples.  Stages hold back what the load limit of a hash set should see, so theirs
-// are short enough that all the waves of a launch together hold at most half the limit.
+// Appends of found triples.  Stages hold back what the limit should see.  A hash set's are short enough that
+// all the waves of a launch together hold at most half its limit; a bitmap cannot overflow, and its stages
+// only keep a wave from going on for long in a search that is over.
 __device__ __forceinline__ WaveStage found_stage(const SArgs& a, uint64_t (&stage)[kWaves][kStage]) {
-    const uint32_t most = a.bits ? kStage - 64 : (uint32_t)min<uint64_t>(kStage - 64, a.list_cap >> 14);
+    const uint32_t most = (uint32_t)min<uint64_t>(kStage - 64, a.list_cap >> (a.bits ? 11 : 14));
     return WaveStage{stage[threadIdx.x >> 6], 0, most};
 }
 
@@ -618,6 +622,7 @@ __global__ __launch_bounds__(kBlock) void k_sparse_slices(SArgs a, int parity) {
         const uint32_t q = lo / a.V, v = lo - q * a.V;
         const uint64_t m = a.lmask[v] & s_qlab[q];
         for (uint32_t base = 0; base < sl.len; base += 64) {
+            if (base && run_over(a)) break;
             uint32_t w = 0, succ = 0;
             if (base + lane < sl.len) edge_at(a, s_delta, L, q, v, m, (uint64_t)sl.beg + base + lane, &w, &succ);
             visit_edges(a, st, sl.key >> 32, w, succ, Q);
@@ -1482,6 +1487,10 @@ __global__ __launch_bounds__(kBlock) void k_key_tallies(const uint64_t* __restri
 }
 
 constexpr uint64_t kFewSources = 512, kFewFound = 1ull << 16;
+// A bitmap of up to this size takes the hash set's place in a search that may hand over: clearing and
+// reading 64 MB is about 30 us, and past the limit an insert still costs one access where an overfull hash
+// set is probed (64 sources of R-MAT 20, 25 MB: 1.47 ms a call with the hash set, 0.46 so).
+constexpr uint64_t kFewBitmap = 64ull << 20;
 
 // Starting hash-set size: 16 slots per (source, state), at least 2^16, and as large as the free
 // workspace allows up to 2^24 slots (filling 2^24 slots costs tens of microseconds, a restart
@@ -1589,19 +1598,25 @@ int sparse_eval(rpq_graph_t g, const rpq_nfa* nfa_in, const uint32_t* sources, u
         // room for the search and, after it, the sort of up to T/2 pairs (~12 bytes per slot)
         uint64_t T = sparse_start_slots(n_sources, nfa.n_states, dense_ok ? 0 : c.ar.free_bytes());
         // room for kFewFound triples, where the workspace has it: the size planned for the search is enough
-        if (dense_ok && 2 * kFewFound * 20 + (1ull << 16) <= c.ar.free_bytes()) T = std::max(T, 2 * kFewFound);
+        const uint64_t few_bits = bitmap_bytes(c, n_sources, nfa.n_states);
+        bool bitmap = dense_ok && few_bits <= kFewBitmap &&
+                      few_bits + few_bits / 8 + kFewFound * 12 + (1ull << 16) <= c.ar.free_bytes();
+        if (bitmap) T = 2 * kFewFound;
+        else if (dense_ok && 2 * kFewFound * 20 + (1ull << 16) <= c.ar.free_bytes()) T = std::max(T, 2 * kFewFound);
+        const bool few_bitmap = bitmap;
         uint64_t* keys = nullptr;
         uint64_t nk = 0, eprod = 0, levels = 0, found = 0;
         const uint64_t mark = c.ar.top;
         SArgs a;
-        bool bitmap = false;
         for (;;) {
-            if (T * 20 + (1ull << 16) > c.ar.free_bytes()) {
-                c.ar.need = std::max<uint64_t>(c.ar.need, c.ar.top + T * 20 + (1ull << 16) + (1ull << 20));
-                rpq::set_error("workspace exhausted (sparse search with %llu slots)", (unsigned long long)T);
-                return RPQ_ENOMEM;
+            if (!few_bitmap) {
+                if (T * 20 + (1ull << 16) > c.ar.free_bytes()) {
+                    c.ar.need = std::max<uint64_t>(c.ar.need, c.ar.top + T * 20 + (1ull << 16) + (1ull << 20));
+                    rpq::set_error("workspace exhausted (sparse search with %llu slots)", (unsigned long long)T);
+                    return RPQ_ENOMEM;
+                }
+                bitmap = use_bitmap(c, n_sources, nfa.n_states, T);
             }
-            bitmap = use_bitmap(c, n_sources, nfa.n_states, T);
             if (!bitmap) CRPQ_TAKE(keys, uint64_t, T / 2);
             const int rc =
                 sparse_run(c, nfa, csr, srcs, n_sources, nullptr, bitmap, T, &a, &found, &eprod, &levels, max_len);
