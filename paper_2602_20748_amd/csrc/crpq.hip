@@ -1553,17 +1553,22 @@ int sparse_eval(rpq_graph_t g, const rpq_nfa* nfa_in, const uint32_t* sources, u
         return RPQ_EDEVICE;
     }
     // Few sources may reach little of the graph or most of it.  The search starts with room for kFewFound
-    // triples; past them, if the workspace holds the bit-parallel search of the same sources in one unit
-    // (whose levels are then the same), that takes over: it is bound by far fewer random accesses per edge
-    // (b.(a|c)* from one vertex of R-MAT 22, 2.5 M triples: 9.4 ms in the hash set, 2.4 ms a call so).
+    // triples; past them, if the workspace holds the bit-parallel search of the same sources in one group of
+    // units (whose levels are then the same), that takes over: it is bound by far fewer random accesses per
+    // edge (b.(a|c)* from one vertex of R-MAT 22, 2.5 M triples: 9.4 ms in the hash set, 2.2 ms a call so).
+    // 512 sources are at most eight units: a plan that eight units in flight do not change has one group.
     rpq_eval_opts dense_opts;
     std::memset(&dense_opts, 0, sizeof dense_opts);
     if (flags & RPQ_LENGTH_BOUND) dense_opts.max_length = (uint32_t)max_len;
     const uint32_t dense_flags = flags & ~RPQ_SPARSE;
-    uint64_t dense_bytes = 0;
-    const bool dense_ok = n_sources <= kFewSources &&
-                          rpq_eval_workspace_size(g, nfa_in, n_sources, dense_flags, &dense_opts, &dense_bytes) == RPQ_OK &&
-                          dense_bytes <= workspace_bytes;
+    rpq_eval_opts one_group = dense_opts;
+    one_group.concurrency = kFewSources / 64;
+    uint64_t dense_bytes = 0, one_group_bytes = 0;
+    const bool dense_ok =
+        n_sources <= kFewSources &&
+        rpq_eval_workspace_size(g, nfa_in, n_sources, dense_flags, &dense_opts, &dense_bytes) == RPQ_OK &&
+        rpq_eval_workspace_size(g, nfa_in, n_sources, dense_flags, &one_group, &one_group_bytes) == RPQ_OK &&
+        dense_bytes == one_group_bytes && dense_bytes <= workspace_bytes;
     rpq::clear_error();
     bool take_over = false;
     auto nomem = [&](int rc) {

@@ -53,3 +53,36 @@ def test_sparse_runs_in_the_planned_workspace(rpq, n, n_sources):
         buf = torch.zeros(max(1, want.count), dtype=torch.int64, device="cuda")
         same_as_oracle(rpq.rpq_eval(g, nfa, s, flags=rpq.RPQ_SPARSE, pairs=buf, per_source=True, workspace=ws), want)
     g.close()
+
+
+def test_sparse_levels_where_the_bitmaps_take_two_groups(rpq):
+    """2^27 vertices and five states: the bitmaps of 300 sources take two units of 256, in flight one after the
+    other, and count a level for each; the hash-set search counts the five frontiers once.  All vertices lie on
+    a cycle, and vertex 0 also has edges to 70,000 others, so that the search passes 2^16 triples."""
+    import torch
+    n, hub = 1 << 27, 70_000
+    free, _ = torch.cuda.mem_get_info()
+    if free < 160 << 30:
+        pytest.skip("needs 160 GB of free device memory")
+    ring = torch.arange(n, dtype=torch.int32, device="cuda")
+    src = torch.cat([ring, torch.zeros(hub, dtype=torch.int32, device="cuda")])
+    dst = torch.cat([(ring + 1) % n, ring[1000:1000 + hub]])
+    del ring
+    lab = torch.zeros(src.numel(), dtype=torch.uint8, device="cuda")
+    g = rpq.rpq_graph_create(src, lab, dst, n, 1, names=["a"])
+    del src, dst, lab
+    nfa = rpq.rpq_nfa_compile("a.a.a.a", g.names)
+    s = np.arange(300, dtype=np.uint32) * 400_000
+    need = rpq.rpq_eval_workspace_size(g, nfa, len(s), 0)
+    say("workspace", need)
+    assert need < 120 << 30
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    dense = rpq.rpq_eval(g, nfa, s, per_source=True, workspace=ws)
+    got = rpq.rpq_eval(g, nfa, s, flags=rpq.RPQ_SPARSE, per_source=True, workspace=ws)
+    # three more steps from each of the hub's 70,001 neighbours end at as many vertices
+    assert (got.count, got.levels, got.max_depth) == (299 + 70_001, 5, 4)
+    assert (got.hash, got.product_edges) == (dense.hash, dense.product_edges) and dense.levels == 10
+    assert torch.equal(got.per_source, dense.per_source)
+    g.close()
+    del ws
+    torch.cuda.empty_cache()
