@@ -2493,8 +2493,8 @@ int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64
     uint64_t final_rows = 0;
     for (uint32_t q = 0; q < x.Q; ++q)
         if ((plan.dn.final >> q) & 1) final_rows += plan.rows[q];
-    // sources without a bit still have their zero-length level
-    uint64_t levels_total = n_bits ? 0 : 1, max_depth = 0;
+    // sources without a bit still have their zero-length level, if there is a state to start in
+    uint64_t levels_total = n_bits || !plan.dn.init ? 0 : 1, max_depth = 0;
     // Extraction of group g runs on a second stream (xs) while the levels of group g + 1 run on
     // `stream` into the other visited bitmap: the level kernels are bound by memory, extraction by its
     // instruction stream.  Events order each bitmap's reuse and the final join.

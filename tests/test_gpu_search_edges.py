@@ -86,3 +86,22 @@ def test_sparse_levels_where_the_bitmaps_take_two_groups(rpq):
     g.close()
     del ws
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n_sources", [1, 64, 65, 700])
+@pytest.mark.parametrize("form", ["bitmap", "levels", "sparse"])
+def test_levels_of_searches_that_go_nowhere(rpq, n_sources, form):
+    """One level where no source can leave (its frontier of zero-length walks), none where the automaton has no
+    state to start in: however many sources there are and whichever form runs."""
+    n = 9000
+    src, dst = np.arange(100, 200, dtype=np.uint32), np.arange(200, 300, dtype=np.uint32)
+    g = rpq.rpq_graph_create(src, np.zeros(100, dtype=np.uint8), dst, n, 1, names=["a"])
+    s = np.arange(1000, 1000 + n_sources, dtype=np.uint32)
+    kw = dict(flags=rpq.RPQ_SPARSE) if form == "sparse" else dict(opts=dict(sync_every=2)) if form == "levels" else {}
+    for init, levels in ((1, 1), (0, 0)):
+        nfa = rpq.rpq_nfa_compile("a.a", g.names)
+        nfa.initial_mask = init
+        say(n_sources, form, "initial states", init)
+        r = rpq.rpq_eval(g, nfa, s, **kw)
+        assert (r.count, r.levels, r.max_depth, r.product_edges) == (0, levels, 0, 0)
+    g.close()
