@@ -1580,6 +1580,7 @@ constexpr uint64_t kCompactBytes = 64ull << 20;
 // its launches.
 constexpr uint64_t kCompactSources = 64;
 constexpr uint64_t kOrderSources = 512;
+constexpr uint64_t kFillRows = 1ull << 18;
 
 uint32_t max_default_width(uint32_t V) { return V >= (1u << 22) ? 4096 : 2048; }
 
@@ -1688,13 +1689,27 @@ uint64_t place_rows(const Plan& p, uint32_t W, uint32_t* base) {
 // written (6.7 at 2048).  From 512 on, up to a quarter of a unit's sources rather go to a second unit.  A
 // row has at least two words: at one, ORs to neighbouring rows from different dies meet in one line more
 // often (R-MAT 18, about 30 sources: 0.57 ms at 64 and 0.56 at 128, 0.64 at 512).  On up to 2^13 vertices
-// a level is too short for wide units to fill the device (1,000 vertices, all pairs by levels: 1.05 ms at
-// 128, 1.29 at 1024).
+// wide units are few rows, and a level of few rows does not fill the device: units widen there only while
+// they have more than kFillRows rows together (by levels, all pairs of 2,000 vertices over a*: 0.67 ms at
+// 128, 2.06 at 2048; of 8,192 vertices over (a|b)*.a.b: 9.4 ms at 128, 3.9 at 2048).
 uint32_t default_width(const Plan& p, uint64_t n_bits, uint32_t V) {
     uint32_t W = 128;
-    while (V > (1u << 13) && W < max_default_width(V) && (W < 512 ? W < n_bits : (uint64_t)W * 4 < n_bits * 3)) W *= 2;
+    while (W < max_default_width(V) && (W < 512 ? W < n_bits : (uint64_t)W * 4 < n_bits * 3) &&
+           (V > (1u << 13) || (n_bits + W - 1) / W * place_rows(p, W, nullptr) > kFillRows))
+        W *= 2;
     while (W > 64 && unit_bytes(place_rows(p, W, nullptr), W) > kUnitBudget) W /= 2;
     return W;
+}
+
+// The part of k_small_search's conditions that the number of sources has no say in: its rows fit in LDS, every
+// state has all its rows, and one block can visit all edges of a level.  A caller that sets a knob of the
+// level kernels gets them.
+bool small_graph(const Plan& p, const rpq_eval_opts* o) {
+    if (o && (o->batch_width || o->concurrency || o->chunk_edges || o->sync_every || o->visit)) return false;
+    if (place_rows(p, 64, nullptr) > kSmallRows || p.desc_items > kSmallItems) return false;
+    for (uint32_t q = 0; q < p.dn.Q; ++q)
+        if (p.dn.kind[q] != ROW_ALL) return false;
+    return true;
 }
 
 // n_sources: the caller's; n_bits: those that get a bit (at most n_sources), which decides the shape.
@@ -1705,7 +1720,8 @@ int make_layout(const rpq_graph* g, const Plan& p, uint64_t n_sources, uint64_t 
     x.Q = p.dn.Q;
     x.L = g->L;
     x.V = g->V;
-    x.W = (o && o->batch_width) ? o->batch_width : default_width(p, n_bits, g->V);
+    // the search in LDS takes 32 sources a block whatever the width, and its answers are read in narrow rows
+    x.W = (o && o->batch_width) ? o->batch_width : small_graph(p, o) ? 128 : default_width(p, n_bits, g->V);
     if (x.W != 64 && x.W != 128 && x.W != 256 && x.W != 512 && x.W != 1024 && x.W != 2048 && x.W != 4096) {
         rpq::set_error("batch_width must be 64, 128, 256, 512, 1024, 2048 or 4096");
         return RPQ_EINVAL;
@@ -2302,22 +2318,16 @@ int rpq_eval(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64_
 
 namespace {
 
+// Whether k_small_search takes the call.
+bool small_search(const Plan& p, const Layout& x, uint64_t n_bits, const rpq_eval_opts* o) {
+    return small_graph(p, o) && n_bits != 0 && n_bits <= (uint64_t)x.G * x.W &&
+           (uint64_t)x.G * (x.W / 32) <= kMaxLevelBlocks;
+}
+
 // The plain evaluation.  With noalloc the call creates nothing: counters are read into a
 // pageable stack buffer instead of the thread's pinned staging buffer, extraction stays on the
 // caller's stream (the layout then holds a single visited bitmap), and no profiling events are
 // recorded.
-// Whether k_small_search takes the call: its rows fit in LDS, every state has all its rows, and one block can
-// visit all edges of a level.  A caller that sets a knob of the level kernels gets them.
-bool small_search(const Plan& p, const Layout& x, uint64_t n_bits, const rpq_eval_opts* o) {
-    if (o && (o->batch_width || o->concurrency || o->chunk_edges || o->sync_every || o->visit)) return false;
-    if (x.R > kSmallRows || p.desc_items > kSmallItems || n_bits == 0 || n_bits > (uint64_t)x.G * x.W ||
-        (uint64_t)x.G * (x.W / 32) > kMaxLevelBlocks)
-        return false;
-    for (uint32_t q = 0; q < p.dn.Q; ++q)
-        if (p.dn.kind[q] != ROW_ALL) return false;
-    return true;
-}
-
 int eval_core(rpq_graph_t g, const rpq_nfa* nfa, const uint32_t* sources, uint64_t n_sources, uint32_t flags,
               const rpq_eval_opts* opts, const uint64_t* target, void* workspace, uint64_t workspace_bytes,
               rpq_result* res, hipStream_t stream, bool noalloc, const rpq_pair_stream* ps = nullptr) {

@@ -105,3 +105,21 @@ def test_levels_of_searches_that_go_nowhere(rpq, n_sources, form):
         r = rpq.rpq_eval(g, nfa, s, **kw)
         assert (r.count, r.levels, r.max_depth, r.product_edges) == (0, levels, 0, 0)
     g.close()
+
+
+@pytest.mark.parametrize("n_sources", [600, 2500, 8192])
+def test_units_of_graphs_below_8192_vertices(rpq, n_sources):
+    """Five states on 8,192 vertices: too many rows for the search in LDS, units of 128 sources for 600 of them
+    and wider ones for more."""
+    n = 8192
+    rng = np.random.default_rng(14)
+    src, dst = rng.integers(0, n, 2 * n).astype(np.uint32), rng.integers(0, n, 2 * n).astype(np.uint32)
+    lab = rng.integers(0, 3, 2 * n).astype(np.uint8)
+    g = rpq.rpq_graph_create(src, lab, dst, n, 3, names=["a", "b", "c"])
+    og = oracle.OracleGraph(n, src, lab, dst, 3, ["a", "b", "c"])
+    s = np.unique(np.linspace(0, n - 1, n_sources).astype(np.uint32))
+    for rx in ("(a|b)*.a.b", "(a.b?)*.c.a"):
+        say(n_sources, rx)
+        nfa = rpq.rpq_nfa_compile(rx, g.names)
+        same_as_oracle(rpq.rpq_eval(g, nfa, s, per_source=True), oracle.rpq(og, rx, sources=s, pairs=False), keys=False)
+    g.close()
