@@ -96,7 +96,10 @@ typedef struct {
     uint64_t n_edges;                            /* distinct (src, label, dst) triples kept */
     uint64_t edges_per_label[RPQ_MAX_LABELS];
     uint64_t nonempty_rows;                      /* (vertex, label) pairs with >= 1 out-edge */
-    uint64_t device_bytes;                       /* device memory held by the graph */
+    uint64_t device_bytes;                       /* device memory held by the graph: its arrays, each
+                                                    direction's rounded up by at most a sixteenth,
+                                                    with room for repeated edges where they are at
+                                                    most a sixteenth of it */
     uint32_t has_in_csr;
     uint32_t has_vertex_labels;
 } rpq_graph_info;

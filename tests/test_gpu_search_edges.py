@@ -123,3 +123,38 @@ def test_units_of_graphs_below_8192_vertices(rpq, n_sources):
         nfa = rpq.rpq_nfa_compile(rx, g.names)
         same_as_oracle(rpq.rpq_eval(g, nfa, s, per_source=True), oracle.rpq(og, rx, sources=s, pairs=False), keys=False)
     g.close()
+
+
+@pytest.mark.parametrize("in_csr", [False, True])
+def test_graph_holds_what_it_reports(rpq, in_csr):
+    """2^25 edges of which 4,096 differ: the graph holds room for those alone, and device_bytes says so.  Three
+    builds of another size let go of the blocks that the large one left behind; the device hands out memory in
+    steps of up to 2 MiB."""
+    import torch
+    n, m = 4096, 1 << 25
+    small = [torch.zeros(8, dtype=t, device="cuda") for t in (torch.int32, torch.uint8, torch.int32)]
+
+    def settle():
+        for _ in range(3):
+            rpq.rpq_graph_create(*small, 8, 1).close()
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        return torch.cuda.mem_get_info()[0]
+
+    src = torch.arange(m, dtype=torch.int32, device="cuda") % n
+    dst, lab = (src * 7 + 1) % n, torch.zeros(m, dtype=torch.uint8, device="cuda")
+    before = settle()
+    g = rpq.rpq_graph_create(src, lab, dst, n, 1, flags=rpq.RPQ_BUILD_IN_CSR if in_csr else 0)
+    held, info = before - settle(), g.info()
+    say("in_csr", in_csr, "held", held, "reported", info["device_bytes"])
+    need = (1 + in_csr) * (4 * (n + 1) + 8 * n + 8 * n // 64 + 4 * n)
+    assert info["n_edges"] == n and need <= info["device_bytes"] <= need + need // 8 + 4096
+    assert held <= info["device_bytes"] + (4 << 20)
+    for reverse in (False, True) if in_csr else (False,):
+        ptr, nb = rpq.rpq_graph_export_csr(g, reverse)
+        assert torch.equal(ptr, torch.arange(n + 1, dtype=torch.int32, device="cuda"))
+        want = torch.empty(n, dtype=torch.int32, device="cuda")
+        u, w = (dst[:n], src[:n]) if reverse else (src[:n], dst[:n])
+        want[u.long()] = w
+        assert torch.equal(nb, want)
+    g.close()
