@@ -334,17 +334,17 @@ public:
         bytes = rounded(bytes);
         int dev = 0;
         (void)hipGetDevice(&dev);
-        std::lock_guard<std::mutex> lk(mu_);
-        for (int i = 0; i < n_; ++i)
-            if (kept_[i].b.device == dev && kept_[i].b.bytes == bytes) {
-                *out = kept_[i].b;
-                drop(i);
-                return RPQ_OK;
-            }
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            for (int i = 0; i < n_; ++i)
+                if (kept_[i].b.device == dev && kept_[i].b.bytes == bytes) {
+                    *out = drop(i);
+                    return RPQ_OK;
+                }
+        }
         hipError_t e = hipMalloc(&out->p, bytes);
-        if (e == hipErrorOutOfMemory && n_) {
+        if (e == hipErrorOutOfMemory && let_go([](const Kept&) { return true; })) {
             (void)hipGetLastError();
-            while (n_) release(0);
             e = hipMalloc(&out->p, bytes);
         }
         if (e != hipSuccess) {
@@ -362,21 +362,26 @@ public:
         if (!b->p) return;
         int dev = -1;
         (void)hipGetDevice(&dev);
-        std::lock_guard<std::mutex> lk(mu_);
+        rpq::Block gone[kSlots + 1];
+        int n_gone = 0;
         if (idle && b->device == dev && b->bytes <= kKept) {
-            while (n_ == kSlots || total_ + b->bytes > kKept) release(0);   // oldest first
+            std::lock_guard<std::mutex> lk(mu_);
+            while (n_ == kSlots || total_ + b->bytes > kKept) gone[n_gone++] = drop(0);   // oldest first
             kept_[n_++] = {*b, builds_};
             total_ += b->bytes;
         } else {
-            (void)hipFree(b->p);
+            gone[n_gone++] = *b;
         }
+        for (int i = 0; i < n_gone; ++i) (void)hipFree(gone[i].p);
         *b = rpq::Block();
     }
     void build_begins() {
-        std::lock_guard<std::mutex> lk(mu_);
-        ++builds_;
-        for (int i = n_; i-- > 0;)
-            if (builds_ - kept_[i].since > 2) release(i);
+        uint64_t now;
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            now = ++builds_;
+        }
+        let_go([now](const Kept& k) { return now > k.since + 2; });
     }
 
 private:
@@ -384,13 +389,25 @@ private:
         rpq::Block b;
         uint64_t since;   // builds begun when it came
     };
-    void drop(int i) {
-        total_ -= kept_[i].b.bytes;
+    rpq::Block drop(int i) {
+        const rpq::Block b = kept_[i].b;
+        total_ -= b.bytes;
         for (--n_; i < n_; ++i) kept_[i] = kept_[i + 1];
+        return b;
     }
-    void release(int i) {
-        (void)hipFree(kept_[i].b.p);
-        drop(i);
+    // The blocks that `which` names go back to the runtime, which may wait for the device: outside the lock, so
+    // that a build on another thread does not wait too.  Returns whether there were any.
+    template <class F>
+    bool let_go(F which) {
+        rpq::Block gone[kSlots];
+        int n_gone = 0;
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            for (int i = n_; i-- > 0;)
+                if (which(kept_[i])) gone[n_gone++] = drop(i);
+        }
+        for (int i = 0; i < n_gone; ++i) (void)hipFree(gone[i].p);
+        return n_gone > 0;
     }
     std::mutex mu_;
     Kept kept_[kSlots];
