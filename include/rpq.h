@@ -249,8 +249,9 @@ typedef struct {
  * Out fields: written (keys stored), count (= |R|), hash (sum over keys of
  *   SplitMix64-output(key) mod 2^64), product_edges (sum over reached
  *   (vertex, state) pairs of sum_l deg_l(v) * |delta(q, l)|, summed over
- *   sources), levels (expansion rounds run), max_depth (longest first-reach
- *   distance in the product graph).
+ *   sources), levels (expansion rounds run, summed over the groups of units: how
+ *   many depends on the width and on the units in flight), max_depth (longest
+ *   first-reach distance in the product graph).
  * If count > pair_offset + capacity and pairs != NULL the call returns
  * RPQ_EOVERFLOW after filling the buffer; calling again with pair_offset
  * advanced by capacity continues the same sorted sequence.
@@ -485,7 +486,8 @@ int rpq_batch_workspace_size(rpq_batch_t b, uint64_t* bytes);
  */
 int rpq_batch_run(rpq_batch_t b, void* workspace, uint64_t workspace_bytes, hipStream_t stream);
 
-/* Per-query results of the last run (host struct; counts, checksum, product edges, depth). */
+/* Per-query results of the last run (host struct; counts, checksum, product edges, depth).  levels is summed
+ * over the query's units and does not vary from run to run while no row waits (list_share 1). */
 int rpq_batch_result(rpq_batch_t b, uint32_t query_id, rpq_result* out);
 
 /* Plan and tallies of the batch (host struct). */

@@ -1208,9 +1208,30 @@ __global__ __launch_bounds__(kBlock) void k_batch_sources(BArgs a, const BSeg* _
             run += h4[j];
         }
         __syncthreads();
+        // Sources of a bucket stay in ascending order: where they fell differently from run to run, units held
+        // other sources and counted other levels.  One wave ranks them, 64 at a time, by matching the bits of
+        // their buckets; a source's bit takes its score's place.
+        if (wv == 0)
+            for (uint32_t i0 = 0; i0 < n; i0 += 64) {
+                const uint32_t i = i0 + lane;
+                const bool valid = i < n;
+                const uint32_t sc = valid ? s_score[i] : 0;
+                uint64_t peers = __ballot(valid);
+                for (uint32_t b = 1; b < kScores; b <<= 1) {
+                    const bool bit = (sc & b) != 0;
+                    const uint64_t m = __ballot(bit);
+                    peers &= bit ? m : ~m;
+                }
+                const uint32_t first = s_hist[sc], rank = (uint32_t)__popcll(peers & rpqd::lanemask_lt());
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if (valid) s_score[i] = (uint16_t)(first + rank);
+                if (valid && rank == 0) s_hist[sc] = first + (uint32_t)__popcll(peers);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            }
+        __syncthreads();
     }
     for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
-        const uint32_t bit = order ? atomicAdd(&s_hist[s_score[i]], 1u) : i;
+        const uint32_t bit = order ? s_score[i] : i;
         out_srcs[g.out + bit] = s_src[i];
         out_pos[g.out + bit] = (uint32_t)(g.off + s_at[i]);
     }

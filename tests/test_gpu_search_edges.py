@@ -158,3 +158,35 @@ def test_graph_holds_what_it_reports(rpq, in_csr):
         want[u.long()] = w
         assert torch.equal(nb, want)
     g.close()
+
+
+@pytest.mark.parametrize("width", [128, 512])
+def test_batch_levels_do_not_vary(rpq, width):
+    """16,384 sources that all meet the same hub first, each with a chain of its own length: a unit takes as many
+    levels as its longest chain, so the sum over the units tells which sources they hold.  Sources that meet the
+    same hub stay in ascending order."""
+    n_src, hub = 16384, 16384
+    rng = np.random.default_rng(18)
+    chain = rng.integers(1, 40, n_src)
+    # chain cells after the hub and its 100 neighbours
+    first = hub + 101 + np.concatenate([[0], np.cumsum(chain)[:-1]])
+    n = int(hub + 101 + chain.sum())
+    src = [np.arange(n_src), np.full(100, hub), np.arange(n_src)]
+    dst = [np.full(n_src, hub), np.arange(hub + 1, hub + 101), first]
+    cells = np.setdiff1d(np.arange(hub + 101, n), first + chain - 1)   # the last cell of a chain has no edge
+    src, dst = np.concatenate(src + [cells]).astype(np.uint32), np.concatenate(dst + [cells + 1]).astype(np.uint32)
+    g = rpq.rpq_graph_create(src, np.zeros(len(src), dtype=np.uint8), dst, n, 1, names=["a"])
+    nfa = rpq.rpq_nfa_compile("a*", g.names)
+    # depth of a source: its chain, or the two steps to a neighbour of the hub; a level for the seeds
+    depth = np.maximum(chain, 2)
+    want = int((depth.reshape(-1, width).max(axis=1) + 1).sum())
+    for turn in range(4):
+        b = rpq.rpq_batch_create(g, dict(batch_width=width, list_share=1))
+        rpq.rpq_batch_add(b, nfa, np.arange(n_src, dtype=np.uint32), per_source=True)
+        for run in range(3):
+            rpq.rpq_batch_run(b)
+            r = rpq.rpq_batch_result(b, 0)
+            say("width", width, "turn", turn, run, "levels", r.levels, "expected", want)
+            assert r.levels == want and r.count == n_src * 102 + int(chain.sum())
+        rpq.rpq_batch_destroy(b)
+    g.close()
