@@ -2076,11 +2076,17 @@ int rpq_batch_autotune(rpq_batch_t b, const rpq_batch_opts* candidates, uint32_t
         if (!b->opts.visit) b->opts.visit = saved.visit;   // the scheme is the batch's, not tuned
         b->frozen = false;
         if (plan(b) != RPQ_OK || b->lay.total > workspace_bytes) continue;
-        // time a bounded prefix of the unit queue: enough units for a few refills of every slot
+        // time a bounded prefix of the unit queue: enough units for a few refills of every slot, and whole
+        // segments, whose sources with a bit are packed into their first units: a prefix that ended inside one
+        // would run most of its work and count part of its sources
         const uint32_t prefix = std::max<uint32_t>(4 * b->lay.G, b->lay.n_units / 20);
-        b->unit_limit = std::min<uint32_t>(b->lay.n_units, prefix);
+        b->unit_limit = 0;
         uint64_t sources_run = 0;
-        for (uint32_t u = 0; u < b->unit_limit; ++u) sources_run += b->units[u].n;
+        for (const BSeg& sg : b->segs) {
+            if (b->unit_limit >= prefix) break;
+            b->unit_limit = sg.first_unit + sg.n_units;
+            sources_run += sg.n;
+        }
         if (b->exec) {
             (void)hipGraphExecDestroy(b->exec);
             b->exec = nullptr;

@@ -190,3 +190,22 @@ def test_batch_levels_do_not_vary(rpq, width):
             assert r.levels == want and r.count == n_src * 102 + int(chain.sum())
         rpq.rpq_batch_destroy(b)
     g.close()
+
+
+def test_autotune_times_whole_segments(rpq):
+    """One slot of 64 sources takes four units as its prefix of the queue, 256 of 8,192 sources.  The 4,096 that are
+    prepared together run together, and no others: a candidate is scored by the sources that it ran."""
+    n = 10_000
+    src = np.arange(n, dtype=np.uint32)
+    g = rpq.rpq_graph_create(src, np.zeros(n, dtype=np.uint8), (src * 7 + 3) % n, n, 1, names=["a"])
+    b = rpq.rpq_batch_create(g)
+    nfa = rpq.rpq_nfa_compile("a.a", g.names)
+    rpq.rpq_batch_add(b, nfa, np.arange(8192, dtype=np.uint32), per_source=True)
+    best = rpq.rpq_batch_autotune(b, [dict(batch_width=64, slots=1)])
+    ran = b.outputs[0][1][:, 0].cpu().numpy()
+    say("sources with a result", int((ran != 0).sum()))
+    assert best["batch_width"] == 64 and ran[:4096].all() and not ran[4096:].any()
+    rpq.rpq_batch_run(b)
+    assert rpq.rpq_batch_result(b, 0).count == 8192
+    rpq.rpq_batch_destroy(b)
+    g.close()
