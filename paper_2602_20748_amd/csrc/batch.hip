@@ -37,9 +37,13 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
-// rows per lane group loaded before any is updated (64 units of 16-word rows on R-MAT 20: 61.3 ms at 2, 55.2
-// at 4, 53.4 at 8, 84.5 at 16, where registers spill)
-constexpr int kUnroll = 8;
+// Rows per lane group loaded before any is updated.  The phases of k_batch share 128 registers, and more rows in
+// flight spill more of them: 24 at 4 and 95 at 8 rows of 8 words, 24 and 55 at 16 words (seen OR).  From 16 words
+// on 8 rows gain more than the spills cost (kernel time of full units on R-MAT 20, seen OR: 12.5 ms at 4 and 12.2
+// at 8 rows of 16 words, 11.7 and 11.3 of 32, 19.6 and 18.6 of 64; two reads 13.4 and 13.4, 12.8 and 12.6, 22.1
+// and 22.1), below they do not (8 words: 16.5 and 16.8, two reads 18.4 and 19.4; 1 to 4 words the same at both).
+template <int K>
+constexpr int unroll() { return K >= 16 ? 8 : 4; }
 constexpr uint32_t kChunkV = 4096;          // vertices per extraction chunk (64 summary words)
 constexpr uint32_t kSeenOrFrom = 1u << 22;   // default visit scheme: seen OR from this many vertices
 
@@ -224,7 +228,7 @@ __device__ __forceinline__ void expand_segments(const BArgs& a, const uint64_t* 
                                                 uint32_t slot, uint32_t q, uint32_t v, uint64_t m,
                                                 const uint32_t* delta, uint64_t beg, uint32_t len,
                                                 uint64_t& t_items, uint64_t& t_wread, uint64_t& t_wupd) {
-    constexpr int GS = 64 / K;
+    constexpr int GS = 64 / K, kUnroll = unroll<K>();
     const int lane = threadIdx.x & 63;
     const int grp = lane / K, k = lane % K;
     const uint64_t gmask = (K == 64) ? ~0ull : (((1ull << K) - 1) << (grp * K));
@@ -841,7 +845,7 @@ __device__ void phase_seed(const BArgs& a, int p, uint32_t iter) {
 // ------------------------------------------------------------------------------------------------
 template <int K, bool SEEN>
 __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t_frows, uint64_t& t_fwords) {
-    constexpr int GS = 64 / K;
+    constexpr int GS = 64 / K, kUnroll = unroll<K>();
     const int np = p ^ 1;
     const uint64_t n = min((uint64_t)ld(&a.ctl->list_cnt[np]), a.list_cap);
     if (n == 0) return;
