@@ -621,8 +621,8 @@ int crpq_eval(rpq_graph_t graph, const crpq_atom* atoms, uint32_t n_atoms, const
  * or the hash set of RPQ_SPARSE) and its traversal state.  Workspaces are carved from one device
  * pool that the caller hands over at start (first fit, 256-byte aligned); the server never
  * allocates device memory.  A request is admitted when its workspace fits in the free part of
- * the pool (a request may pass queued ones that do not fit yet, unless the oldest has waited
- * more than 50 ms), and runs at once on one of `workers` host threads, each with its own HIP
+ * the pool (a request may pass queued ones that do not fit yet, and while a dense RPQ runs the
+ * others pass the dense ones that wait, unless the oldest has waited more than 50 ms), and runs at once on one of `workers` host threads, each with its own HIP
  * stream, so the work of admitted requests overlaps on the device.  A dense RPQ larger than the
  * whole pool is split: fewer source units in flight (and narrower units), the same result.  A
  * request that asks for more workspace while running (RPQ_SPARSE, CRPQ) goes back to the front

@@ -209,3 +209,34 @@ def test_autotune_times_whole_segments(rpq):
     assert rpq.rpq_batch_result(b, 0).count == 8192
     rpq.rpq_batch_destroy(b)
     g.close()
+
+
+def test_served_conjunctive_queries_pass_waiting_slices(rpq):
+    """Two workers, eight slices of 4,096 sources and then a conjunctive query, with room for all of them at once:
+    the query takes the first worker that comes free while a slice runs on the other, not the last one.  Every
+    result is what it is alone."""
+    import synth
+    el = synth.workload_graph("rmat18_l8")
+    g = rpq.rpq_graph_create(el.src, el.label, el.dst, el.n_vertices, el.n_labels, flags=rpq.RPQ_BUILD_IN_CSR,
+                             names=el.names)
+    nfa = rpq.rpq_nfa_compile("(a.b)*", el.names)
+    slices = [np.arange(i * 4096, (i + 1) * 4096, dtype=np.uint32) for i in range(8)]
+    alone = [rpq.rpq_eval(g, nfa, s) for s in slices]
+    atoms, bind = [(0, "g.h?", 1), (1, "h", 2)], [int(el.src[np.argmax(el.label == 6)]), None, None]
+    want = rpq.crpq_eval(g, atoms, 3, binding=bind)
+    srv = rpq.Server(g, 24 << 30, workers=2)
+    warm = [srv.submit_rpq(nfa, slices[0]), srv.submit_crpq(atoms, 3, binding=bind)]
+    for t in warm:
+        srv.wait(t)
+    tickets = [srv.submit_rpq(nfa, s) for s in slices]
+    last = srv.submit_crpq(atoms, 3, binding=bind)
+    done = [srv.wait(t) for t in tickets]
+    x = srv.wait(last)
+    before = sum(d["start_ms"] < x["start_ms"] for d in done)
+    say("slices that began before the query", before, "wait", x["start_ms"] - x["arrival_ms"])
+    srv.stop()
+    assert (x["status"], x["count"], x["hash"]) == (0, want.count, want.hash)
+    for d, a in zip(done, alone):
+        assert (d["status"], d["count"], d["hash"], d["product_edges"]) == (0, a.count, a.hash, a.product_edges)
+    assert before <= 4
+    g.close()
