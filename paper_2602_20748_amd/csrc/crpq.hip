@@ -903,19 +903,20 @@ __global__ void k_write_tuples(OutArgs a, const uint32_t* __restrict__ perm, uin
 // ------------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------------
+// A stack; scratch of a step that leaves something behind comes from the far end (the step sets `end` back to 0:
+// what takes its place is written on the same stream).
 struct Arena {
     char* base = nullptr;
-    uint64_t size = 0, top = 0, need = 0;
+    uint64_t size = 0, top = 0, end = 0, need = 0;
     template <class T>
-    T* take(uint64_t count) {
-        const uint64_t bytes = align256(std::max<uint64_t>(1, count) * sizeof(T));
-        if (top + bytes > size) {
-            need = std::max(need, top + bytes);
+    T* take(uint64_t count, bool at_end = false) {
+        const uint64_t bytes = align256(std::max<uint64_t>(1, count) * sizeof(T)), room = size & ~255ull;
+        if (top + end + bytes > room) {
+            need = std::max(need, top + end + bytes);
             return nullptr;
         }
-        T* p = reinterpret_cast<T*>(base + top);
-        top += bytes;
-        return p;
+        (at_end ? end : top) += bytes;
+        return reinterpret_cast<T*>(base + (at_end ? room - end : top - bytes));
     }
     uint64_t free_bytes() const { return size > top ? size - top : 0; }
 };
@@ -936,9 +937,9 @@ struct Ctx {
     uint64_t n_words;
 };
 
-#define CRPQ_TAKE(ptr, T, n)                                                                  \
+#define CRPQ_TAKE(ptr, T, ...)                                                                \
     do {                                                                                      \
-        (ptr) = c.ar.take<T>(n);                                                              \
+        (ptr) = c.ar.take<T>(__VA_ARGS__);                                                    \
         if (!(ptr)) {                                                                         \
             rpq::set_error("workspace exhausted (%llu bytes needed so far)",                  \
                            (unsigned long long)c.ar.need);                                    \
@@ -1097,9 +1098,9 @@ void to_snfa(const rpq_nfa& n, uint32_t L, SNfa* d) {
 int eval_edge_scan(Ctx& c, const rpq::Csr& csr, uint64_t lang, const uint32_t* srcs, uint64_t n_src,
                    const uint64_t* target, uint64_t** keys, uint64_t* n, bool* sorted) {
     uint64_t* offs;
-    CRPQ_TAKE(offs, uint64_t, n_src + 1);
+    CRPQ_TAKE(offs, uint64_t, n_src + 1, true);
     uint64_t* stmp;
-    CRPQ_TAKE(stmp, uint64_t, rpq::scan_temp_elems(n_src));
+    CRPQ_TAKE(stmp, uint64_t, rpq::scan_temp_elems(n_src), true);
     hipLaunchKernelGGL(k_scan_degrees, dim3(grid_for(n_src, 16384)), dim3(kBlock), 0, c.s, csr.row_ptr, csr.lmask,
                        c.g->L, lang, srcs, n_src, offs);
     RPQ_LAUNCH_CHECK();
@@ -1110,12 +1111,15 @@ int eval_edge_scan(Ctx& c, const rpq::Csr& csr, uint64_t lang, const uint32_t* s
     // one label: (s, t) ascending and distinct, as the CSR holds them
     *sorted = (lang & (lang - 1)) == 0;
     *n = 0;
-    CRPQ_TAKE(*keys, uint64_t, 1);
-    if (!n_src || !total) return RPQ_OK;
+    if (!n_src || !total) {
+        c.ar.end = 0;
+        CRPQ_TAKE(*keys, uint64_t, 1);
+        return RPQ_OK;
+    }
     const uint64_t n_tiles = (total + kScanTile - 1) / kScanTile;
     uint64_t *tiles, *ttmp;
-    CRPQ_TAKE(tiles, uint64_t, n_tiles + 1);
-    CRPQ_TAKE(ttmp, uint64_t, rpq::scan_temp_elems(n_tiles));
+    CRPQ_TAKE(tiles, uint64_t, n_tiles + 1, true);
+    CRPQ_TAKE(ttmp, uint64_t, rpq::scan_temp_elems(n_tiles), true);
     const unsigned grid = grid_for(n_tiles * 64, 16384);
     hipLaunchKernelGGL(k_edge_scan<false>, dim3(grid), dim3(kBlock), 0, c.s, csr.row_ptr, csr.dst, csr.lmask, c.g->L,
                        lang, srcs, n_src, offs, total, target, tiles, nullptr);
@@ -1131,6 +1135,7 @@ int eval_edge_scan(Ctx& c, const rpq::Csr& csr, uint64_t lang, const uint32_t* s
         RPQ_LAUNCH_CHECK();
     }
     *n = m;
+    c.ar.end = 0;
     return RPQ_OK;
 }
 

@@ -240,3 +240,21 @@ def test_served_conjunctive_queries_pass_waiting_slices(rpq):
         assert (d["status"], d["count"], d["hash"], d["product_edges"]) == (0, a.count, a.hash, a.product_edges)
     assert before <= 4
     g.close()
+
+
+def test_edge_scan_leaves_only_its_pairs_in_the_workspace(rpq):
+    """All edges of one label as a query: the scan's offsets (8 bytes a source) do not stay beside the pairs, so
+    7.9 MB are enough where 7.7 are needed."""
+    import torch
+    n, m = 100_000, 800_000
+    rng = np.random.default_rng(n)
+    src, lab, dst = (rng.integers(0, n, m).astype(np.uint32), rng.integers(0, 4, m).astype(np.uint8),
+                     rng.integers(0, n, m).astype(np.uint32))
+    g = rpq.rpq_graph_create(src, lab, dst, n, 4, names=["a", "b", "c", "d"])
+    want = len(np.unique(src[lab == 0].astype(np.uint64) << np.uint64(32) | dst[lab == 0]))
+    ws = 7_900_000
+    r = rpq.crpq_eval(g, [(0, "a", 1)], 2, workspace_bytes=ws)
+    held = g.workspace(256).numel()   # the binding grows it when the library asks for more
+    say("workspace", held)
+    assert r.count == want and held == ws
+    g.close()
