@@ -258,3 +258,143 @@ def test_edge_scan_leaves_only_its_pairs_in_the_workspace(rpq):
     say("workspace", held)
     assert r.count == want and held == ws
     g.close()
+
+
+@pytest.fixture(scope="module")
+def ranked(rpq):
+    """300,000 vertices of which a label leads to a fifth at most: above 64 MB of bitmaps (9,000 sources) a state
+    has rows only for those."""
+    n, m = 300_000, 240_000
+    rng = np.random.default_rng(31)
+    src, dst = rng.integers(0, n, m).astype(np.uint32), rng.integers(0, n, m).astype(np.uint32)
+    lab = rng.choice(4, size=m, p=[0.3, 0.3, 0.3, 0.1]).astype(np.uint8)
+    dst[lab == 3] = dst[lab == 3] % 1000
+    names = ["a", "b", "c", "d"]
+    g = rpq.rpq_graph_create(src, lab, dst, n, 4, flags=rpq.RPQ_BUILD_IN_CSR, names=names)
+    yield (g, oracle.OracleGraph(n, src, lab, dst, 4, names), oracle.OracleGraph(n, dst, lab, src, 4, names),
+           np.unique(rng.integers(0, n, 9000)).astype(np.uint32), rng)
+    g.close()
+
+
+@pytest.mark.parametrize("reverse", [False, True])
+@pytest.mark.parametrize("rx,back", [("a.b*.c", "c.b*.a"), ("(a|d)?.c", "c.(a|d)?"), ("d?", "d?")])
+def test_ranked_rows_keys_streams_and_noalloc(rpq, ranked, rx, back, reverse):
+    g, og, ogt, s, _ = ranked
+    nfa = rpq.rpq_nfa_compile(rx, g.names)
+    want = oracle.rpq(ogt if reverse else og, back if reverse else rx, sources=s)
+    flags = rpq.RPQ_REVERSE if reverse else 0
+    say(rx, "reverse", reverse, "keys", want.count)
+    got = rpq.rpq_eval(g, nfa, s, flags=flags, pairs=True, per_source=True)
+    assert (got.count, got.hash) == (want.count, want.hash)
+    assert np.array_equal(u64(got.pairs), want.pairs) and np.array_equal(u64(got.per_source), want.per_source)
+    if not reverse:   # a reversed automaton counts its own product edges
+        assert got.product_edges == want.product_edges
+    chunks = []
+    st = rpq.rpq_eval_stream(g, nfa, lambda k: chunks.append(k.copy()) and None, s, flags=flags, chunk_keys=1000,
+                             per_source=True)
+    assert (st.count, st.hash, st.written) == (want.count, want.hash, want.count)
+    assert np.array_equal(np.concatenate(chunks), want.pairs) and np.array_equal(u64(st.per_source), want.per_source)
+    na = rpq.rpq_eval_noalloc(g, nfa, s, flags=flags)
+    assert (na.count, na.hash, na.product_edges) == (got.count, got.hash, got.product_edges)
+
+
+@pytest.mark.parametrize("rx", ["a.b*.c", "(a|d)?.c", "a.b"])
+def test_ranked_rows_with_a_destination_filter(rpq, ranked, rx):
+    """A bit-parallel atom from 9,000 sources whose destinations are limited to a tenth of the vertices."""
+    g, og, _, s, rng = ranked
+    keep = np.unique(rng.integers(0, og.n_vertices, og.n_vertices // 10)).astype(np.uint32)
+    keys = oracle.rpq(og, rx, sources=s).pairs
+    keys = keys[np.isin((keys & np.uint64(0xFFFFFFFF)).astype(np.uint32), keep)]
+    want = np.stack([(keys >> np.uint64(32)).astype(np.uint32), (keys & np.uint64(0xFFFFFFFF)).astype(np.uint32)], axis=1)
+    r = rpq.crpq_eval(g, [(0, rx, 1)], 2, domain=[s, keep], tuples=True,
+                      flags=rpq.CRPQ_FORCE_DENSE | rpq.CRPQ_NO_EDGE_SCAN | rpq.CRPQ_NO_REVERSE)
+    say(rx, "tuples", len(want))
+    assert len(want) > 10 and r.count == len(want) and r.atom_strategy[0] & 0xFF == 2
+    assert np.array_equal(r.tuples.cpu().numpy().view(np.uint32), want)
+
+
+@pytest.mark.parametrize("form", ["bitmap", "hash set"])
+@pytest.mark.parametrize("past", [0, 1])
+def test_sparse_search_at_its_limit(rpq, form, past):
+    """2^16 triples are found by the sparse search itself, one more by the bit-parallel one (whose level kernels the
+    profile counts).  A bitmap of one source is small; one of 512 sources and 600,000 vertices passes 64 MB."""
+    n = 70_000 if form == "bitmap" else 600_000
+    s = np.arange(1 if form == "bitmap" else 512, dtype=np.uint32)
+    leaves = (1 << 16) - len(s) + past   # a triple for every seed, one for every edge of vertex 0
+    src, dst = np.zeros(leaves, dtype=np.uint32), np.arange(1000, 1000 + leaves, dtype=np.uint32)
+    lab = np.zeros(leaves, dtype=np.uint8)
+    g = rpq.rpq_graph_create(src, lab, dst, n, 1, names=["a"])
+    want = oracle.rpq(oracle.OracleGraph(n, src, lab, dst, 1, ["a"]), "a", sources=s)
+    nfa = rpq.rpq_nfa_compile("a", g.names)
+    rpq.rpq_profile_enable(True)
+    rpq.rpq_profile_read(reset=True)
+    got = rpq.rpq_eval(g, nfa, s, flags=rpq.RPQ_SPARSE, pairs=True, per_source=True)
+    prof = rpq.rpq_profile_read(reset=True)
+    rpq.rpq_profile_enable(False)
+    say(form, leaves, "level launches", prof["expand_launches"])
+    same_as_oracle(got, want)
+    assert (prof["expand_launches"] > 0) == (past == 1) and (got.levels, got.max_depth) == (2, 1)
+    g.close()
+
+
+def test_sparse_workspace_asks_for_more(rpq):
+    """Where the bit-parallel search may not take over, because there are too many sources or its bitmaps do not
+    fit, a search that outgrows its workspace names a larger one; the binding's own grows until it ends."""
+    import torch
+    n = 8000
+    rng = np.random.default_rng(5)
+    src, dst = rng.integers(0, n, 2 * n).astype(np.uint32), rng.integers(0, n, 2 * n).astype(np.uint32)
+    lab = rng.integers(0, 2, 2 * n).astype(np.uint8)
+    g = rpq.rpq_graph_create(src, lab, dst, n, 2, names=["a", "b"])
+    og = oracle.OracleGraph(n, src, lab, dst, 2, ["a", "b"])
+    nfa = rpq.rpq_nfa_compile("(a|b)*", g.names)
+    s = np.unique(np.linspace(0, n - 1, 600).astype(np.uint32))
+    want = oracle.rpq(og, "(a|b)*", sources=s)
+    same_as_oracle(rpq.rpq_eval(g, nfa, s, flags=rpq.RPQ_SPARSE, pairs=True, per_source=True), want)
+    held = g.workspace(256).numel()
+    say("workspace", held, "for", want.count, "keys")
+    assert held > 64 << 20
+    g.close()
+    n = 200_000   # bitmaps of 25 MB and more: not in the 1.7 MB planned for the search
+    src, dst = rng.integers(0, n, 3 * n).astype(np.uint32), rng.integers(0, n, 3 * n).astype(np.uint32)
+    lab = np.zeros(3 * n, dtype=np.uint8)
+    g = rpq.rpq_graph_create(src, lab, dst, n, 1, names=["a"])
+    og = oracle.OracleGraph(n, src, lab, dst, 1, ["a"])
+    nfa = rpq.rpq_nfa_compile("a*", g.names)
+    s = np.arange(3, dtype=np.uint32)
+    want = oracle.rpq(og, "a*", sources=s)
+    buf = torch.zeros(want.count, dtype=torch.int64, device="cuda")
+    ws = torch.empty(rpq.rpq_eval_workspace_size(g, nfa, len(s), rpq.RPQ_SPARSE), dtype=torch.uint8, device="cuda")
+    with pytest.raises(rpq.RpqError) as e:
+        rpq.rpq_eval(g, nfa, s, flags=rpq.RPQ_SPARSE, pairs=buf, per_source=True, workspace=ws)
+    assert e.value.code == rpq.RPQ_ENOMEM
+    same_as_oracle(rpq.rpq_eval(g, nfa, s, flags=rpq.RPQ_SPARSE, pairs=buf, per_source=True), want)
+    g.close()
+
+
+@pytest.mark.parametrize("keys", [True, False])
+@pytest.mark.parametrize("width", [0, 64, 1024])
+def test_batch_segments_against_the_oracle(rpq, width, keys):
+    """Queries of 4,095 to 4,097 sources (a block prepares 4,096), of sources without a first edge alone, and with
+    the empty word."""
+    n = 5000
+    rng = np.random.default_rng(10)
+    hubs = [(0, 600), (1, 3000), (2, 17)]
+    src = np.concatenate([np.full(d, h) for h, d in hubs] + [rng.integers(0, 3500, 6000)]).astype(np.uint32)
+    dst, lab = rng.integers(0, n, len(src)).astype(np.uint32), rng.integers(0, 3, len(src)).astype(np.uint8)
+    g = rpq.rpq_graph_create(src, lab, dst, n, 3, names=["a", "b", "c"])
+    og = oracle.OracleGraph(n, src, lab, dst, 3, ["a", "b", "c"])
+    queries = [(rx, np.arange(k, dtype=np.uint32)) for k in (4095, 4096, 4097) for rx in ("a.b*.c", "(a.b)*")]
+    queries += [("c.a", np.arange(3500, 4200, dtype=np.uint32)), ("c?", np.arange(3400, 4300, dtype=np.uint32))]
+    b = rpq.rpq_batch_create(g, dict(batch_width=width) if width else None)
+    want = [oracle.rpq(og, rx, sources=s) for rx, s in queries]
+    for (rx, s), w in zip(queries, want):
+        rpq.rpq_batch_add(b, rpq.rpq_nfa_compile(rx, g.names), s, pairs_capacity=max(1, w.count) if keys else None,
+                          per_source=True)
+    for turn in range(2):
+        rpq.rpq_batch_run(b)
+        for i, w in enumerate(want):
+            say("width", width, "keys", keys, "run", turn, queries[i][0], len(queries[i][1]))
+            same_as_oracle(rpq.rpq_batch_result(b, i), w, keys)
+    rpq.rpq_batch_destroy(b)
+    g.close()
