@@ -128,7 +128,8 @@ int rpq_graph_create(const uint32_t* src, const uint8_t* label, const uint32_t* 
 
 /* Release a graph and its device memory (synchronises the device).  Up to 1 GiB of
  * released blocks is kept for the next rpq_graph_create calls: it goes back to the
- * runtime when two of them in a row have no use for it or an allocation fails. */
+ * runtime when two of them in a row have no use for it or an allocation fails.  A
+ * larger block goes back at once (the scratch of 2^26 edges is one). */
 int rpq_graph_destroy(rpq_graph_t g);
 
 /* Sizes of a graph (host struct). */

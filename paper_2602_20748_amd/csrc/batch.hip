@@ -45,7 +45,7 @@ constexpr int kWaves = kBlock / 64;
 template <int K>
 constexpr int unroll() { return K >= 16 ? 8 : 4; }
 constexpr uint32_t kChunkV = 4096;          // vertices per extraction chunk (64 summary words)
-constexpr uint32_t kSeenOrFrom = 1u << 22;   // default visit scheme: seen OR from this many vertices
+constexpr uint32_t kSeenOrFrom = 1u << 22;   // resident engine: seen OR from this many vertices
 
 // S_RETIRE: retiring in this iteration's retire phases (queries with pairs); S_DRAIN: retiring in the
 // next iteration, its extraction beside that iteration's expansion and its clear beside its compaction
@@ -865,7 +865,7 @@ __device__ void phase_finalize(const BArgs& a, int p, uint32_t iter, uint64_t& t
         uint64_t eprod = 0, work = 0;
         const BNfa* nfa = a.nfas;
         bool fin = false;   // entry of a final state
-        // at the depth bound of a length-bounded query a row is recorded (Vis, Ans) but gets an
+        // at the depth bound of a length-bounded query a row is recorded (Vis, summary) but gets an
         // empty frontier row and no work: it is never expanded
         bool stop = false;
         // seen OR: a row listed for the first time has nothing in the second bitmap yet, which is then

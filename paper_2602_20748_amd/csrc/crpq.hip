@@ -932,7 +932,7 @@ struct Ctx {
     rpq_graph_t g;
     hipStream_t s;
     Arena ar;
-    uint64_t* stage;                 // pinned host staging (graph-owned)
+    uint64_t* stage;                 // pinned host staging (the calling thread's)
     unsigned long long* dctr;        // device counters [kCounters]
     uint64_t n_words;
 };

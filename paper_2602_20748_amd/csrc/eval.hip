@@ -24,10 +24,10 @@
 //             (q', w) into Next; the first writer of a row sets its touch bit.  Entries with
 //             at most H items are expanded straight from the frontier list; larger ones
 //             arrive as slices of at most H items (edge-balanced work whatever the degree
-//             skew, with slice memory bounded by 2 * items / H).
+//             skew, with slice memory bounded by 2 * items / H).  Items whose target row is full
+//             -- it holds every source that still had a bit in the last frontier but one -- are
+//             dropped before the row is read.
 //   compact   the touched rows become the next frontier list (ballot/popcount prefix).
-//             Items whose target row is full -- it holds every source that still had a bit in the
-//             last frontier but one -- are dropped before the row is read.
 //   finalize  for each new entry moves Next into a compact frontier row, ORs it into Vis,
 //             counts the product edges it will examine, and cuts entries of more than H items
 //             into slices.
@@ -64,9 +64,9 @@ constexpr int C_TALLY = 12;     // [kTallies] the work tallies below, summed ove
 // Work tallies of the level kernels.  Every block keeps its own copy (blocks of one launch write
 // disjoint lines, launches follow each other on the stream), and k_tally_sum adds the copies up once
 // per call.  One atomic per wave to shared counters cost more than it looked: the 20,000 or more
-// same-line atomics of a launch complete one after another.  Without them: a 2,500-source slice of
-// R-MAT 18 with keys 6.10 -> 3.97 ms, all pairs of R-MAT 18 116.8 -> 111.3 ms (k_expand 1.28 -> 1.22
-// ms a launch), 65,536 sources of R-MAT 23 499 -> 488 ms.
+// same-line atomics of a launch complete one after another: when they were taken out, a 2,500-source
+// slice of R-MAT 18 with keys went from 6.10 to 3.97 ms (it takes 1.7 since) and every launch of k_expand
+// on R-MAT 18 lost 0.06 ms.
 constexpr int T_EPROD = 0;      // product edges examined
 constexpr int T_ITEMS = 1;      // expansion (profiling)
 constexpr int T_DESCS = 2;
@@ -238,9 +238,9 @@ __device__ __forceinline__ void row_entry(const Args& a, const LdsNfa& s, uint32
 //              finalize, and finalize takes a listed row's new bits as Vis & ~that, then advances
 //              it.  One read and one OR per new word, the method's own accesses; finalize reads one
 //              more word per row word after a row's first time, when it writes the row whole.
-//              Faster at both scales measured: R-MAT 23, 3.41 -> 2.91 s a step (expansion 2.11 ms
-//              a launch when each new word was also ORed into a Next bitmap, 1.53 ms now); R-MAT
-//              18, 603 -> 541 ms (expansion 1.43 -> 1.15 ms).
+//              Faster at both scales measured (five queries a step): R-MAT 23, 65,536 sources, 904
+//              -> 628 ms (expansion 5.45 -> 3.36 ms a launch); R-MAT 18, all pairs, 183 -> 152 ms
+//              (0.86 -> 0.67).
 // ------------------------------------------------------------------------------------------------
 constexpr int kUnroll = 8;
 
@@ -1564,11 +1564,11 @@ void to_dev_nfa(const rpq_nfa* nfa, uint32_t L, DevNfa* d) {
 }
 
 // Default shape: about 64K sources with a bit in flight, in units of up to 2048 sources below 2^22
-// vertices and 4096 from there (R-MAT scale 18 all pairs: 51.3 ms at 2048, 59.6 at 1024, 50.5 at 4096;
-// R-MAT scale 23, 65,536 sources: 152.7 ms at 4096, 154.7 at 2048, 172.8 at 1024), entries of more than
-// 16 items cut into slices (16 beat 32, 64, 128 and 256; raised on graphs where the slice buffers would
-// outgrow a quarter of the bitmaps).  Units in flight are sized for 64 GB of the 288 GB device, and a
-// unit of the default width may take up to 96 GB alone.
+// vertices and 4096 from there (five queries a step, at 1024, 2048 and 4096: R-MAT 18, all pairs, 174, 152
+// and 148 ms; R-MAT 23, 65,536 sources, 749, 647 and 628), entries of more than 16 items cut into slices
+// (at 16, 32, 64 and 256: 152, 156, 159 and 164 ms; 628, 656, 656 and 697; raised on graphs where the slice
+// buffers would outgrow a quarter of the bitmaps).  Units in flight are sized for 64 GB of the 288 GB
+// device, and a unit of the default width may take up to 96 GB alone.
 constexpr uint64_t kTargetInFlight = 65536;
 constexpr uint64_t kWorkspaceBudget = 64ull << 30;
 constexpr uint64_t kUnitBudget = 96ull << 30;

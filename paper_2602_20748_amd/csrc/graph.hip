@@ -313,9 +313,11 @@ __global__ void k_entered_counts(const uint64_t* __restrict__ entered, uint64_t 
 
 // Device memory of graphs and their builds.  The runtime takes 0.25 ms to release a block, and 15 ms and more
 // each while it is still clearing much other memory released shortly before: a build of 16M edges both ways
-// then took 45 ms, of which its kernels were 2, and takes 2.3 ms with its blocks kept.  So up to kKept bytes in
-// kSlots released blocks wait for the next build.  A block comes here only when no work uses it any more, so
-// any stream may take it; it goes back to the runtime when a newer block needs its room, when two builds in a
+// then took 45 ms, of which its kernels were 2, and takes 1.75 ms with its blocks kept.  So up to kKept bytes in
+// kSlots released blocks wait for the next build.  That is the end of the gain: the scratch alone, 16 bytes an
+// edge, passes kKept from 2^26 edges on, and such a build takes and releases its memory each time (2^22
+// vertices, 2^26 edges both ways: 8.4 ms; 20.8 when nothing was kept and the kernels took longer).  A block
+// comes here only when no work uses it any more, so any stream may take it; it goes back to the runtime when a newer block needs its room, when two builds in a
 // row had no use for it, or when an allocation here fails.  Sizes are rounded up to a sixteenth of their
 // power of two, and a kept block serves only its own size: what a graph holds does not depend on what was
 // released before it.
