@@ -42,6 +42,7 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -67,12 +68,12 @@ constexpr int C_TALLY = 12;     // [kTallies] the work tallies below, summed ove
 // same-line atomics of a launch complete one after another: when they were taken out, a 2,500-source
 // slice of R-MAT 18 with keys went from 6.10 to 3.97 ms (it takes 1.7 since) and every launch of k_expand
 // on R-MAT 18 lost 0.06 ms.
-constexpr int T_EPROD = 0;      // product edges examined
-constexpr int T_ITEMS = 1;      // expansion (profiling)
-constexpr int T_DESCS = 2;
-constexpr int T_WREAD = 3;
-constexpr int T_WUPD = 4;
-constexpr int T_FROWS = 5;      // finalize (profiling): rows finalized,
+constexpr int T_ITEMS = 0;      // expansion (profiling)
+constexpr int T_DESCS = 1;
+constexpr int T_WREAD = 2;
+constexpr int T_WUPD = 3;
+constexpr int T_EPROD = 4;      // finalize: product edges examined,
+constexpr int T_FROWS = 5;      //   (profiling) rows finalized,
 constexpr int T_FWORDS = 6;     //   and their non-zero Next words
 constexpr int T_FFRESH = 7;     //   rows listed for the first time
 constexpr int kTallies = 8;
@@ -254,7 +255,7 @@ __device__ __forceinline__ void keep_in_flight(uint64_t (&x)[N]) {
 }
 
 template <int K, bool SEEN>
-__device__ __forceinline__ void expand_segments(const Args& a, const LdsNfa& s, const uint64_t* rows,
+__device__ __forceinline__ void expand_segments(const Args& a, const LdsNfa& s, const uint64_t* rows, bool filter,
                                                 bool have, uint32_t ent, uint32_t slot, uint32_t q, uint32_t v,
                                                 uint64_t m, uint64_t beg, uint32_t len, uint64_t& t_items,
                                                 uint64_t& t_wread, uint64_t& t_wupd) {
@@ -290,7 +291,7 @@ __device__ __forceinline__ void expand_segments(const Args& a, const LdsNfa& s, 
             uint32_t w = 0, q2 = 0;
             rpqd::decode_item(a.row_ptr, a.dst, a.L, s.delta, c_v, c_q, c_m, c_beg + (item - c_ex), &w, &q2);
             my_row = c_slot * a.R + target_row(a, s, q2, w);
-            live = !SEEN || !a.full[my_row];
+            live = !SEEN || !filter || !a.full[my_row];
         }
         // live items to the front, so that the word phase sees no others
         const uint64_t lm = __ballot(live);
@@ -303,11 +304,12 @@ __device__ __forceinline__ void expand_segments(const Args& a, const LdsNfa& s, 
             my_ent = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)c_ent);
         }
         // word phase
-        for (uint32_t j = 0; j < n_here; j += GS * kUnroll) {
-            uint32_t r[kUnroll];
-            uint64_t f[kUnroll], nb[kUnroll];
+        auto words = [&](auto rows_each, uint32_t j) {
+            constexpr int U = decltype(rows_each)::value;
+            uint32_t r[U];
+            uint64_t f[U], nb[U];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const uint32_t idx = j + u * GS + grp;
                 r[u] = __shfl(my_row, idx & 63, 64);
                 const uint32_t e = __shfl(my_ent, idx & 63, 64);
@@ -316,12 +318,12 @@ __device__ __forceinline__ void expand_segments(const Args& a, const LdsNfa& s, 
             if constexpr (SEEN) {
                 // the visited word holds every bit of earlier levels (their ORs completed before
                 // this launch): bits not in it as read are new at this level
-                uint64_t sw[kUnroll];
+                uint64_t sw[U];
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) sw[u] = f[u] ? a.vis[(uint64_t)r[u] * K + k] : ~0ull;
-                keep_in_flight<kUnroll>(sw);
+                for (int u = 0; u < U; ++u) sw[u] = f[u] ? a.vis[(uint64_t)r[u] * K + k] : ~0ull;
+                keep_in_flight<U>(sw);
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
+                for (int u = 0; u < U; ++u) {
                     nb[u] = f[u] & ~sw[u];
                     if (nb[u]) {
                         or_relaxed(&a.vis[(uint64_t)r[u] * K + k], nb[u]);
@@ -331,31 +333,36 @@ __device__ __forceinline__ void expand_segments(const Args& a, const LdsNfa& s, 
                 // the visited word and the Next word together: bits already in Next need no OR, and
                 // the OR then finds its line in L2 (Next only gains bits during an expansion, so a
                 // stale copy can only let through an OR that is not needed)
-                uint64_t vw[kUnroll], nx[kUnroll];
+                uint64_t vw[U], nx[U];
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
+                for (int u = 0; u < U; ++u) {
                     vw[u] = f[u] ? a.vis[(uint64_t)r[u] * K + k] : ~0ull;
                     nx[u] = f[u] ? a.next[(uint64_t)r[u] * K + k] : ~0ull;
                 }
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
+                for (int u = 0; u < U; ++u) {
                     nb[u] = f[u] & ~vw[u] & ~nx[u];
                     if (nb[u]) or_relaxed(&a.next[(uint64_t)r[u] * K + k], nb[u]);
                 }
             }
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < U; ++u) {
                 t_wread += f[u] != 0;
                 t_wupd += nb[u] != 0;
                 const uint64_t hit = __ballot(nb[u] != 0) & gmask;
                 if (k == 0 && hit) or_relaxed(&a.touch[r[u] >> 6], 1ull << (r[u] & 63));
             }
-        }
+        };
+        // (a step of kUnroll rows costs its instructions whether the group has them or not)
+        if (SEEN && n_here <= (uint32_t)GS) words(std::integral_constant<int, SEEN ? 1 : kUnroll>(), 0);
+        else
+            for (uint32_t j = 0; j < n_here; j += GS * kUnroll) words(std::integral_constant<int, kUnroll>(), j);
     }
 }
 
 // Add each wave's N tallies to the block's copy, words [first, first + N).  Every thread of the block
-// calls it once, at the end of the kernel.
+// calls it once, at the end of the kernel.  The adds do not return: a short level waits for one access to
+// memory here, not for two.
 template <int N>
 __device__ __forceinline__ void add_tallies(const Args& a, int first, const uint64_t (&t)[N]) {
     __shared__ uint64_t s_part[kWaves][N];
@@ -368,7 +375,7 @@ __device__ __forceinline__ void add_tallies(const Args& a, int first, const uint
     if (threadIdx.x < N) {
         uint64_t x = 0;
         for (int w = 0; w < kWaves; ++w) x += s_part[w][threadIdx.x];
-        if (x) a.tally[(uint64_t)blockIdx.x * kTallyStride + first + threadIdx.x] += x;
+        if (x) atomicAdd(&a.tally[(uint64_t)blockIdx.x * kTallyStride + first + threadIdx.x], (unsigned long long)x);
     }
 }
 
@@ -409,6 +416,10 @@ __device__ __forceinline__ uint32_t batch_of(uint64_t n, uint64_t n_waves) {
     return b;
 }
 
+// A list of at most this many entries a wave is short: its levels are chains of dependent accesses, with few
+// full rows to gain from and one access more to see which are.  They are neither marked nor looked at there.
+constexpr uint32_t kShortBatch = 4;
+
 template <int K, bool SEEN>
 __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
     __shared__ LdsNfa s_nfa;
@@ -424,6 +435,7 @@ __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
     const uint64_t* rows = rows_of(a, p);
     const uint32_t* ids = ids_of(a, p);
     const uint32_t H = a.H;
+    const bool filter = lb > kShortBatch;
     uint64_t t_items = 0, t_segs = 0, t_wread = 0, t_wupd = 0;
     // light entries, straight from the frontier list
     for (uint64_t b = wave; b * lb < n_list; b += n_waves) {
@@ -439,7 +451,7 @@ __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
             len = have ? (uint32_t)work : 0;
         }
         t_segs += __popcll(__ballot(have)) * (lane == 0);
-        expand_segments<K, SEEN>(a, s_nfa, rows, have, (uint32_t)e, slot, q, v, m, 0, len, t_items, t_wread, t_wupd);
+        expand_segments<K, SEEN>(a, s_nfa, rows, filter, have, (uint32_t)e, slot, q, v, m, 0, len, t_items, t_wread, t_wupd);
     }
     // heavy entries, as slices
     const Desc* desc = desc_of(a, p);
@@ -458,7 +470,7 @@ __global__ __launch_bounds__(kBlock) void k_expand(Args a, int p) {
             have = true;
         }
         t_segs += __popcll(__ballot(have)) * (lane == 0);
-        expand_segments<K, SEEN>(a, s_nfa, rows, have, ent, slot, q, v, m, beg, len, t_items, t_wread, t_wupd);
+        expand_segments<K, SEEN>(a, s_nfa, rows, filter, have, ent, slot, q, v, m, beg, len, t_items, t_wread, t_wupd);
     }
     const uint64_t t[4] = {t_items, t_segs, t_wread, t_wupd};
     add_tallies<4>(a, T_ITEMS, t);
@@ -540,7 +552,17 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
     const uint64_t n = min((uint64_t)a.counters[C_LIST + np], a.list_cap);
     const uint64_t n_waves = (uint64_t)gridDim.x * kWaves, wave0 = (uint64_t)blockIdx.x * kWaves;
     const uint32_t fb = batch_of(n, n_waves);
+    const uint64_t* was_active = a.active + p * a.n_active;
+    unsigned long long* now_active = reinterpret_cast<unsigned long long*>(a.active + np * a.n_active);
+    // sources with a bit in the new frontier: word k of slot acc_slot, collected while the wave's rows
+    // share a slot.  A stale copy of the word only costs an OR that is not needed.  A short list keeps the
+    // previous frontier's sources, which hold its own: every wave's OR of a few words would be most of its
+    // time (one source of R-MAT 18: 14 us a launch).  The last block copies them, which has no entries then.
+    const bool track = SEEN && n * K >= kTrackWords;
+    if (SEEN && !track && blockIdx.x == gridDim.x - 1)
+        for (uint64_t i = threadIdx.x; i < a.n_active; i += kBlock) now_active[i] = was_active[i];
     if (wave0 * fb >= n) return;
+    const bool mark = fb > kShortBatch;
     load_nfa(a, s_nfa);
     const int lane = threadIdx.x & 63;
     const int grp = lane / K, k = lane % K;
@@ -551,15 +573,6 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
     const uint32_t H = a.H;
     uint64_t eprod = 0, t_rows = 0, t_words = 0, t_fresh = 0;
     const uint64_t gmask = (K == 64) ? ~0ull : (((1ull << (K & 63)) - 1) << (grp * K));
-    const uint64_t* was_active = a.active + p * a.n_active;
-    unsigned long long* now_active = reinterpret_cast<unsigned long long*>(a.active + np * a.n_active);
-    // sources with a bit in the new frontier: word k of slot acc_slot, collected while the wave's rows
-    // share a slot.  A stale copy of the word only costs an OR that is not needed.  A short list keeps the
-    // previous frontier's sources, which hold its own: every wave's OR of a few words would be most of its
-    // time (one source of R-MAT 18: 14 us a launch).
-    const bool track = SEEN && n * K >= kTrackWords;
-    if (SEEN && !track && blockIdx.x == 0)
-        for (uint64_t i = threadIdx.x; i < a.n_active; i += kBlock) now_active[i] = was_active[i];
     uint64_t acc_k = 0;
     uint32_t acc_slot = kNone;
     auto put_active = [&](uint32_t sl, uint64_t x) {
@@ -592,13 +605,22 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
             flush_active();
             acc_slot = one_slot ? slot0 : kNone;
         }
+        // a row's items (the product edges of each new source bit): its accesses beside the word phase's.  At
+        // the depth bound of a length-bounded query the entries are recorded but never expanded: no product
+        // edges, no slices.
+        uint64_t work = 0;
+        if (active && count_work) {
+            const uint64_t m = a.lmask[v] & s_nfa.qlab[q];
+            work = m ? rpqd::entry_work(a.row_ptr, a.L, s_nfa.delta, v, q, m) : 0;
+        }
         uint32_t my_pc = 0;
         // word phase
-        for (uint32_t j = 0; j < n_here; j += GS * kUnroll) {
-            uint32_t r[kUnroll], sl[kUnroll];
-            uint64_t nk[kUnroll], ov[kUnroll];
+        auto words = [&](auto rows_each, uint32_t j) {
+            constexpr int U = decltype(rows_each)::value;
+            uint32_t r[U], sl[U];
+            uint64_t nk[U], ov[U];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const uint32_t idx = j + u * GS + grp;
                 r[u] = __shfl(my_row, idx & 63, 64);
                 sl[u] = one_slot ? slot0 : __shfl(slot, idx & 63, 64);
@@ -614,18 +636,18 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
             }
             if constexpr (SEEN) {
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
+                for (int u = 0; u < U; ++u) {
                     const uint32_t idx = j + u * GS + grp;
-                    const bool ok = idx < n_here && (was_active[(uint64_t)sl[u] * K + k] & ~nk[u]) == 0;
+                    const bool ok = mark && idx < n_here && (was_active[(uint64_t)sl[u] * K + k] & ~nk[u]) == 0;
                     nk[u] &= ~ov[u];
                     if (one_slot) acc_k |= nk[u];
                     else if (track && idx < n_here && nk[u]) put_active(sl[u], nk[u]);
                     // the row is on the list once: nothing else writes its byte
-                    if ((__ballot(ok) & gmask) == gmask && k == 0) a.full[r[u]] = 1;
+                    if (mark && (__ballot(ok) & gmask) == gmask && k == 0) a.full[r[u]] = 1;
                 }
             }
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const uint32_t idx = j + u * GS + grp;
                 uint32_t pc = 0;
                 if (idx < n_here) {
@@ -648,16 +670,12 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
                 const uint32_t got = __shfl(pc, (rel % GS) * K, 64);
                 if (rel < (uint32_t)GS) my_pc = got;
             }
-        }
-        // row phase: product edges; entries of more than H items are cut into slices.  At the
-        // depth bound of a length-bounded query the entries are recorded but never expanded: no
-        // product edges, no slices.
-        uint64_t work = 0;
-        if (active && count_work) {
-            const uint64_t m = a.lmask[v] & s_nfa.qlab[q];
-            work = m ? rpqd::entry_work(a.row_ptr, a.L, s_nfa.delta, v, q, m) : 0;
-            eprod += (uint64_t)my_pc * work;
-        }
+        };
+        if (SEEN && n_here <= (uint32_t)GS) words(std::integral_constant<int, SEEN ? 1 : kUnroll>(), 0);
+        else
+            for (uint32_t j = 0; j < n_here; j += GS * kUnroll) words(std::integral_constant<int, kUnroll>(), j);
+        // row phase: product edges; entries of more than H items are cut into slices
+        eprod += (uint64_t)my_pc * work;
         const uint64_t ndesc = work > H ? (work + H - 1) / H : 0;
         const uint64_t dincl = rpqd::wave_incl_scan_u64(ndesc);
         const uint64_t dexcl = dincl - ndesc;
@@ -695,9 +713,8 @@ __global__ __launch_bounds__(kBlock) void k_finalize(Args a, int p, int count_wo
         }
     }
     flush_active();
-    const uint64_t t_e[1] = {eprod}, t_f[3] = {t_rows, t_words, t_fresh};
-    add_tallies<1>(a, T_EPROD, t_e);
-    add_tallies<3>(a, T_FROWS, t_f);
+    const uint64_t t[4] = {eprod, t_rows, t_words, t_fresh};
+    add_tallies<4>(a, T_EPROD, t);
 }
 
 // ------------------------------------------------------------------------------------------------
