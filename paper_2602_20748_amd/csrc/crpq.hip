@@ -30,6 +30,7 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <cstddef>
 #include <cstring>
 #include <vector>
 
@@ -1285,6 +1286,21 @@ bool use_bitmap(const Ctx& c, uint64_t n_src, uint32_t Q, uint64_t T) {
 // Levels between two looks of the host at the search.
 constexpr int kSparseLevels = 3;
 
+// Edges of the longest walk that the automaton allows; UINT64_MAX where a state can return to itself.  No level
+// is launched for what such walks cannot reach (a tiny search of a.b would end on empty launches).
+uint64_t longest_walk(const rpq_nfa& nfa) {
+    uint32_t next[RPQ_MAX_STATES] = {}, at = nfa.initial_mask;
+    for (uint32_t q = 0; q < nfa.n_states; ++q)
+        for (uint32_t l = 0; l < nfa.n_labels; ++l) next[q] |= nfa.delta[q * RPQ_MAX_LABELS + l];
+    for (uint64_t steps = 0; steps <= nfa.n_states; ++steps) {
+        uint32_t then = 0;
+        for (uint32_t m = at; m; m &= m - 1) then |= next[__builtin_ctz(m)];
+        if (!then) return steps;
+        at = then;
+    }
+    return ~0ull;
+}
+
 // One run of the sparse search: with a hash set of T slots (load at most 1/2), or with a bitmap and room
 // for T / 2 triples.  Everything stays in the arena above `mark`; returns RPQ_ENOMEM (without setting the
 // error) when T was too small.
@@ -1308,7 +1324,11 @@ int sparse_run(Ctx& c, const rpq_nfa& nfa, const rpq::Csr& csr, const uint32_t* 
     }
     a.slice_cap = cap / 8 + 64;
     CRPQ_TAKE(a.slices, SSlice, a.slice_cap);
-    RPQ_HIP(hipMemcpyAsync(dn, &h, sizeof h, hipMemcpyHostToDevice, c.s));
+    // from pinned memory where it fits (beyond the counters' place): the call does not wait for the copy
+    const size_t used = offsetof(SNfa, delta) + sizeof(uint32_t) * nfa.n_states * c.g->L;
+    const void* from = &h;
+    if (used <= 2048) from = std::memcpy(c.stage + 256, &h, used);
+    RPQ_HIP(hipMemcpyAsync(dn, from, used, hipMemcpyHostToDevice, c.s));
     RPQ_TRY(zero_counters(c));
     a.row_ptr = csr.row_ptr;
     a.dst = csr.dst;
@@ -1329,6 +1349,7 @@ int sparse_run(Ctx& c, const rpq_nfa& nfa, const rpq::Csr& csr, const uint32_t* 
     // a first-reach distance in the product graph is below Q * V
     const uint64_t level_bound = (uint64_t)nfa.n_states * c.g->V + 2;
     // level l expands depth l; a length bound k leaves depth k recorded but unexpanded
+    max_len = std::min(max_len, longest_walk(nfa));
     for (uint64_t level = 0;;) {
         for (int i = 0; i < kSparseLevels && level < max_len; ++i, ++level) {
             hipLaunchKernelGGL(k_sparse_level, dim3(2048), dim3(kBlock), 0, c.s, a, (int)(level & 1));
@@ -1644,15 +1665,21 @@ int sparse_eval(rpq_graph_t g, const rpq_nfa* nfa_in, const uint32_t* sources, u
         res->max_depth = levels ? levels - 1 : 0;
         if (flags & RPQ_PER_SOURCE) RPQ_TRY(rpq::fill_u64(res->per_source, 2 * n_sources, 0, c.s));
         if (bitmap) {
+            // no source left its vertex and none is its own answer: there is nothing to count
+            if (levels <= 1 && !(nfa.initial_mask & nfa.final_mask)) {
+                RPQ_HIP(hipStreamSynchronize(c.s));
+                return RPQ_OK;
+            }
             uint64_t *offs, n_tiles;
             RPQ_TRY(bitmap_count(c, a, &offs, &n_tiles, &nk));
             const bool write = (flags & RPQ_PAIRS) && res->pairs;
-            if (nk)
+            res->count = nk;
+            if (nk) {
                 RPQ_TRY(bitmap_keys(c, a, offs, n_tiles, res->pairs, res->pair_offset, write ? res->capacity : 0,
                                     (flags & RPQ_PER_SOURCE) ? res->per_source : nullptr, c.dctr + kCounters - 1));
-            RPQ_TRY(read_counters(c, kCounters));
-            res->count = nk;
-            res->hash = c.stage[kCounters - 1];
+                RPQ_TRY(read_counters(c, kCounters));
+                res->hash = c.stage[kCounters - 1];
+            }
             if (write) {
                 const uint64_t avail = nk > res->pair_offset ? nk - res->pair_offset : 0;
                 res->written = std::min<uint64_t>(avail, res->capacity);

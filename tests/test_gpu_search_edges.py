@@ -398,3 +398,24 @@ def test_batch_segments_against_the_oracle(rpq, width, keys):
             same_as_oracle(rpq.rpq_batch_result(b, i), w, keys)
     rpq.rpq_batch_destroy(b)
     g.close()
+
+
+@pytest.mark.parametrize("rx", ["a", "a.b", "a.b?.c", "(a|b).c.(a.b)?", "a?", "a*.b"])
+@pytest.mark.parametrize("bound", [None, 0, 1, 2])
+def test_sparse_search_of_finite_languages(rpq, rx, bound):
+    """The sparse search launches no level that the automaton's longest walk cannot reach: results, levels and product
+    edges as the oracle and the bit-parallel search have them, with bounds below and above that walk."""
+    n = 400
+    rng = np.random.default_rng(21)
+    src, dst, lab = (rng.integers(0, k, 1500) for k in (n, n, 3))
+    g = rpq.rpq_graph_create(src.astype(np.uint32), lab.astype(np.uint8), dst.astype(np.uint32), n, 3, names=["a", "b", "c"])
+    og = oracle.OracleGraph(n, src, lab, dst, 3, ["a", "b", "c"])
+    nfa = rpq.rpq_nfa_compile(rx, g.names)
+    for s in (np.arange(1, dtype=np.uint32), np.arange(0, n, 2, dtype=np.uint32)):
+        say(rx, "bound", bound, "sources", len(s))
+        want = oracle.rpq(og, rx, sources=s, max_length=bound)
+        level = rpq.rpq_eval(g, nfa, s, opts=dict(sync_every=1), max_length=bound)
+        got = rpq.rpq_eval(g, nfa, s, flags=rpq.RPQ_SPARSE, pairs=True, per_source=True, max_length=bound)
+        same_as_oracle(got, want)
+        assert (got.max_depth, got.levels) == (level.max_depth, level.max_depth + 1)
+    g.close()
