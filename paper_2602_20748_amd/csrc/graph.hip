@@ -317,10 +317,10 @@ __global__ void k_entered_counts(const uint64_t* __restrict__ entered, uint64_t 
 // kSlots released blocks wait for the next build.  That is the end of the gain: the scratch alone, 16 bytes an
 // edge, passes kKept from 2^26 edges on, and such a build takes and releases its memory each time (2^22
 // vertices, 2^26 edges both ways: 8.4 ms; 20.8 when nothing was kept and the kernels took longer).  A block
-// comes here only when no work uses it any more, so any stream may take it; it goes back to the runtime when a newer block needs its room, when two builds in a
-// row had no use for it, or when an allocation here fails.  Sizes are rounded up to a sixteenth of their
-// power of two, and a kept block serves only its own size: what a graph holds does not depend on what was
-// released before it.
+// comes here only when no work uses it any more, so any stream may take it; it goes back to the runtime when a
+// newer block needs its room, when two builds in a row had no use for it, or when an allocation here fails.
+// Sizes are rounded up to a sixteenth of their power of two, and a kept block serves only its own size: what a
+// graph holds does not depend on what was released before it.
 class Blocks {
 public:
     static constexpr uint64_t kKept = 1ull << 30;
